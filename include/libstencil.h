@@ -211,7 +211,7 @@ int stencil_stream_segment_rows(const stencil_t *st, int wavefronts_per_simd, in
  * (3 warm-ups + `reps` samples); the others keep their two-sample statistics.
  * STENCIL_OPT_NT_STORE (default 0): the kernels' 16-byte stores of output cells are issued as
  * non-temporal stores (the output is not read again by the launch that writes it); narrower
- * stores (unaligned rows, one cell per work-item, the threshold stencil) stay plain.  Same
+ * stores (a ragged row's last cells, one cell per work-item, the threshold stencil) stay plain.  Same
  * results, different cache behaviour: it pays on matrices beyond the caches and costs where
  * the next application would have found its input in a cache.
  * STENCIL_OPT_FAIL_LAUNCH (default 0 = off) is a testing aid for the handling of refused parameters

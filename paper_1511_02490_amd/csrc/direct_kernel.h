@@ -22,20 +22,20 @@ __device__ __forceinline__ void fetch_row(typename Op::V (&row)[W + CC + E], con
     if (gr >= 0 && fast_cols) {
         const T *p = in + (size_t)gr * cols + c0;
         T ctr[CC];
-        load_vec(ctr, p);
+        load_global(ctr, p);
 #pragma unroll
         for (int k = 0; k < CC; ++k) v[W + k] = ctr[k];
         if constexpr (W == 1) v[0] = p[-1];
         if constexpr (W > 1) {
             T side[CC];
-            load_vec(side, p - CC);
+            load_global(side, p - CC);
 #pragma unroll
             for (int k = 0; k < W; ++k) v[k] = side[CC - W + k];
         }
         if constexpr (E == 1) v[W + CC] = p[CC];
         if constexpr (E > 1) {
             T side[CC];
-            load_vec(side, p + CC);
+            load_global(side, p + CC);
 #pragma unroll
             for (int k = 0; k < E; ++k) v[W + CC + k] = side[k];
         }
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(MAXT) void direct_kernel(const TileArgs<Op, Halo> a
     const int c0 = (tile_c * (int)blockDim.x + (int)threadIdx.x) * CC;
     if (r0 >= rows || c0 >= cols) return;
 
-    const bool fast_cols = a.vec_ok && c0 >= (W > 0 ? CC : 0) && c0 + CC + (E > 0 ? CC : 0) <= cols;
+    const bool fast_cols = c0 >= (W > 0 ? CC : 0) && c0 + CC + (E > 0 ? CC : 0) <= cols;
 
     typename Op::State st[CR][CC];
 #pragma unroll
@@ -121,7 +121,7 @@ __global__ __launch_bounds__(MAXT) void direct_kernel(const TileArgs<Op, Halo> a
 #pragma unroll
         for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(st[cr][cc], a.scalar0);
         T *dst = a.out + (size_t)r * cols + c0;
-        if (a.vec_ok && c0 + CC <= cols) {
+        if (c0 + CC <= cols) {
             store_out_vec(dst, res, a.nt_store != 0);
         } else {
 #pragma unroll
@@ -167,7 +167,7 @@ __device__ __forceinline__ LifeRow life_fetch(const uint8_t *in, int gr_raw, int
     const int gr = resolve<B>(gr_raw, rows);
     const uint8_t *row = in + (size_t)(gr < 0 ? 0 : gr) * cols;
     if (gr >= 0 && fast_cols) {
-        const uint4 v = *reinterpret_cast<const uint4 *>(row + c0);
+        const any_word4 v = *reinterpret_cast<const any_word4 *>(row + c0);
         x.w[0] = v.x; x.w[1] = v.y; x.w[2] = v.z; x.w[3] = v.w;
     } else {
 #pragma unroll
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(MAXT) void life_direct_kernel(const TileArgs<OpLife
     const int r0 = (tile_r * (int)blockDim.y + (int)threadIdx.y) * CR;
     const int c0 = (tile_c * (int)blockDim.x + (int)threadIdx.x) * CC;
     if (r0 >= rows || c0 >= cols) return;
-    const bool fast_cols = a.vec_ok && c0 + CC <= cols;
+    const bool fast_cols = c0 + CC <= cols;
     // the columns just west and east of this work-item's cells, the same for every row
     const int gcw = resolve<B>(c0 - 1, cols), gce = resolve<B>(c0 + CC, cols);
 
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(MAXT) void life_direct_kernel(const TileArgs<OpLife
         uint32_t o[4];
         life_rule(o, win[cr], win[cr + 1], win[cr + 2]);
         uint8_t *dst = a.out + (size_t)r * cols + c0;
-        if (a.vec_ok && c0 + CC <= cols) {
+        if (c0 + CC <= cols) {
             store_word4(dst, make_uint4(o[0], o[1], o[2], o[3]), a.nt_store != 0);
         } else {
 #pragma unroll

@@ -22,13 +22,13 @@ __host__ __device__ constexpr int life_stream_cols(int depth, int words) {
 template <int WORDS>
 __device__ __forceinline__ void load_words(uint32_t (&v)[WORDS], const void *src) {
     if constexpr (WORDS == 1) {
-        v[0] = *reinterpret_cast<const uint32_t *>(src);
+        v[0] = *reinterpret_cast<const any_word *>(src);
     } else if constexpr (WORDS == 2) {
-        const uint2 t = *reinterpret_cast<const uint2 *>(src);
+        const any_word2 t = *reinterpret_cast<const any_word2 *>(src);
         v[0] = t.x, v[1] = t.y;
     } else {
         static_assert(WORDS == 4, "1, 2 or 4 words per lane");
-        const uint4 t = *reinterpret_cast<const uint4 *>(src);
+        const any_word4 t = *reinterpret_cast<const any_word4 *>(src);
         v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
     }
 }
@@ -36,15 +36,17 @@ __device__ __forceinline__ void load_words(uint32_t (&v)[WORDS], const void *src
 template <int WORDS>
 __device__ __forceinline__ void store_words(void *dst, const uint32_t (&v)[WORDS], bool nt) {
     if constexpr (WORDS == 1) {
-        *reinterpret_cast<uint32_t *>(dst) = v[0];
+        *reinterpret_cast<any_word *>(dst) = v[0];
     } else if constexpr (WORDS == 2) {
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(v[0], v[1]);
+        any_word2 t;
+        t.x = v[0], t.y = v[1];
+        *reinterpret_cast<any_word2 *>(dst) = t;
     } else {
         store_word4(dst, make_uint4(v[0], v[1], v[2], v[3]), nt);
     }
 }
 
-// FAST: rows are whole aligned 16-byte vectors, so a lane's cells lie either all inside the matrix
+// FAST: rows are whole lanes' widths (cols % CC == 0), so a lane's cells lie either all inside the matrix
 // or all outside it and a row is one load at a per-lane column plus a wavefront-uniform row
 // address, issued without a branch.  Otherwise cells are loaded and stored one by one.
 template <int B, int DEPTH, int WORDS, bool FAST>

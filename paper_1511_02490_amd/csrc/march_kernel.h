@@ -25,7 +25,7 @@ namespace sk {
 __host__ __device__ constexpr int march_rim(int h) { return (h + 3) / 4; }
 __host__ __device__ constexpr int march_vectors(int W, int E) { return 64 - march_rim(W) - march_rim(E); }
 
-// FAST: rows are whole aligned vectors (cols % 4 == 0, 16-byte aligned pointers).  A lane's four
+// FAST: rows are whole vectors (cols % 4 == 0).  A lane's four
 // columns then lie either all inside the matrix or all outside it, every row is one vector load
 // at a per-lane column plus a wavefront-uniform row address, and what the border mode asks for
 // beyond that is a per-lane fix-up of the loaded vector.  Otherwise elements are loaded one by one.
@@ -84,7 +84,7 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
         if (FAST) {
             // scalar row address + 32-bit lane offset; a padding row is fixed up later
             const char *rowp = reinterpret_cast<const char *>(a.in + (size_t)(gr < 0 ? 0 : gr) * cols);
-            load_vec(v, reinterpret_cast<const T *>(rowp + in_off));
+            load_global(v, reinterpret_cast<const T *>(rowp + in_off));
         } else {
 #pragma unroll
             for (int j = 0; j < CC; ++j)

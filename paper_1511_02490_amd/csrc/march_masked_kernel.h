@@ -115,7 +115,7 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
         const int gr = resolve<B>(r0 - n + tt, rows);
         if (FAST) {
             const char *rowp = reinterpret_cast<const char *>(a.in + (size_t)(gr < 0 ? 0 : gr) * cols);
-            load_vec(v, reinterpret_cast<const T *>(rowp + in_off));
+            load_global(v, reinterpret_cast<const T *>(rowp + in_off));
         } else {
 #pragma unroll
             for (int j = 0; j < CC; ++j)

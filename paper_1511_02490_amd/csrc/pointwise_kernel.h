@@ -13,7 +13,6 @@ struct ThresholdArgs {
     int rows, cols;
     int tiles_c, n_tiles;
     int xcd_chunk;   // > 0: tiles are dealt to the 8 XCDs in contiguous chunks of this many
-    int vec_ok;      // rows of `in` start 16-byte aligned, rows of `out` 4-byte aligned, cols % 4 == 0
     float level;
 };
 
@@ -36,10 +35,10 @@ __global__ __launch_bounds__(MAXT) void threshold_kernel(const ThresholdArgs a) 
         const float *src = a.in + (size_t)r * a.cols + c0;
         uint8_t *dst = a.out + (size_t)r * a.cols + c0;
         if constexpr (CC == 4) {
-            if (a.vec_ok && c0 + CC <= a.cols) {
+            if (c0 + CC <= a.cols) {
                 float v[4];
-                load_vec(v, src);
-                *reinterpret_cast<uint32_t *>(dst) = reaches(v[0], a.level) | (reaches(v[1], a.level) << 8) |
+                load_global(v, src);
+                *reinterpret_cast<any_word *>(dst) = reaches(v[0], a.level) | (reaches(v[1], a.level) << 8) |
                                                      (reaches(v[2], a.level) << 16) | (reaches(v[3], a.level) << 24);
                 continue;
             }

@@ -27,7 +27,7 @@ constexpr int kStreamMaxDepth = 8;
 __host__ __device__ constexpr int stream_rim(int depth) { return (depth + 3) / 4; }
 __host__ __device__ constexpr int stream_cols(int depth) { return (kStreamLanes - 2 * stream_rim(depth)) * 4; }
 
-// FAST: rows are whole aligned vectors (cols % 4 == 0, 16-byte aligned pointers).  A lane's four
+// FAST: rows are whole vectors (cols % 4 == 0).  A lane's four
 // columns then lie either all inside the matrix or all outside it, every input row is one vector
 // load at a per-lane column plus a wavefront-uniform row address, issued without a branch three
 // steps ahead, and the time loop is straight-line code.  Otherwise elements are loaded one by one.
@@ -80,7 +80,7 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
         const int gr = resolve<B>(r0 - DEPTH + tt, rows);      // the same for the whole wavefront
         if (FAST) {
             const char *rowp = reinterpret_cast<const char *>(a.in + (size_t)(gr < 0 ? 0 : gr) * cols);
-            load_vec(v, reinterpret_cast<const T *>(rowp + in_off));
+            load_global(v, reinterpret_cast<const T *>(rowp + in_off));
         } else {
 #pragma unroll
             for (int j = 0; j < CC; ++j)

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(MAXT) void temporal_kernel(const TileArgs<Op, HaloC
     const int ER = min(th, rows - r0) + 2 * depth;   // staged rows in use
 
     stage_tile<Op, B, CC>(src, a.plane, pitch, a.in, rows, cols, row_first, col_first, ER, cols + HC, a.pad,
-                          a.vec_ok, a.stage_magic, tid, nthreads);
+                          a.stage_magic, tid, nthreads);
     __syncthreads();
 
     // does the staged tile reach outside the matrix?  (same answer for the whole workgroup)
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(MAXT) void temporal_kernel(const TileArgs<Op, HaloC
             T res[CC];
             temporal_quad<Op>(res, up, mid, dn, a.w, a.scalar0);
             T *out = a.out + (size_t)r * cols + c;
-            if (a.vec_ok && c + CC <= cols) {
+            if (c + CC <= cols) {
                 store_out_vec(out, res, a.nt_store != 0);
             } else {
 #pragma unroll
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLi
     const int ER = min(th, rows - r0) + 2 * depth;
 
     stage_tile<OpLife, B, CC>(src, a.plane, pitch, a.in, rows, cols, row_first, col_first, ER, cols + HC, a.pad,
-                              a.vec_ok, a.stage_magic, tid, nthreads);
+                              a.stage_magic, tid, nthreads);
     __syncthreads();
 
     const bool at_border = row_first < 0 || row_first + ER > rows || col_first < 0 || col_first + pitch > cols;
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLi
             uint32_t o[4];
             life_rule(o, up, mid, dn);
             uint8_t *out = a.out + (size_t)r * cols + c;
-            if (a.vec_ok && c + CC <= cols) {
+            if (c + CC <= cols) {
                 store_word4(out, make_uint4(o[0], o[1], o[2], o[3]), a.nt_store != 0);
             } else {
 #pragma unroll

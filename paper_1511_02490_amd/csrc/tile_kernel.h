@@ -40,7 +40,6 @@ struct TileArgs {
     int pitch;       // LDS tile pitch, in staged elements
     int plane;       // elements per LDS plane (tile rows x pitch)
     unsigned stage_magic;   // ceil(2^32 / items per staged row): tid / items by one multiply
-    int vec_ok;      // rows of `in` / `out` start at multiples of a work-item's load / store width and cols % CC == 0
     int nt_store;    // vector stores of output cells are non-temporal
     typename Op::T pad;
     float scalar0;
@@ -51,21 +50,15 @@ struct TileArgs {
 __host__ __device__ constexpr int round_up(int x, int m) { return (x + m - 1) / m * m; }
 __host__ __device__ constexpr int round_down(int x, int m) { return x / m * m; }
 
-// 16-byte moves between global memory / LDS and register arrays (a load may also be one 4-byte
-// word: four byte cells that are widened to floats afterwards).
+// 16-byte moves between LDS and register arrays (16-byte aligned on the LDS side).
 template <class E, int CNT>
 __device__ __forceinline__ void load_vec(E (&dst)[CNT], const E *src) {
-    if constexpr (sizeof(E) * CNT == 4) {
-        const uint32_t tmp = *reinterpret_cast<const uint32_t *>(src);
-        __builtin_memcpy(dst, &tmp, 4);
-    } else {
-        static_assert(sizeof(E) * CNT % 16 == 0, "vector moves are whole 16-byte words");
-        constexpr int NV = sizeof(E) * CNT / 16;
-        uint4 tmp[NV];
+    static_assert(sizeof(E) * CNT % 16 == 0, "vector moves are whole 16-byte words");
+    constexpr int NV = sizeof(E) * CNT / 16;
+    uint4 tmp[NV];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) tmp[k] = reinterpret_cast<const uint4 *>(src)[k];
-        __builtin_memcpy(dst, tmp, sizeof(tmp));
-    }
+    for (int k = 0; k < NV; ++k) tmp[k] = reinterpret_cast<const uint4 *>(src)[k];
+    __builtin_memcpy(dst, tmp, sizeof(tmp));
 }
 template <class E, int CNT>
 __device__ __forceinline__ void store_vec(E *dst, const E (&src)[CNT]) {
@@ -76,18 +69,40 @@ __device__ __forceinline__ void store_vec(E *dst, const E (&src)[CNT]) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) reinterpret_cast<uint4 *>(dst)[k] = tmp[k];
 }
-// The same to global memory, optionally as non-temporal stores: output cells are not read again
-// by the launch that writes them, and on matrices beyond the caches keeping them out of the way
-// of the input pays (measured on a plain copy: +20 % on 256 MiB, nothing on 64 MiB).
-typedef unsigned int nt_word4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void store_word4(void *dst, uint4 v, bool nt) {
-    if (nt) {
-        nt_word4 t;
-        t.x = v.x, t.y = v.y, t.z = v.z, t.w = v.w;
-        __builtin_nontemporal_store(t, reinterpret_cast<nt_word4 *>(dst));
+// The same between global memory and registers, from and to any element's address: gfx950 moves a
+// vector of 4, 8 or 16 bytes that starts at any byte (the types say so, or the compiler would assume
+// natural alignment), so a row of any length is moved in vectors and only its last, partial one
+// element by element.  (Rows that do not start at multiples of 16 bytes were moved one element at a
+// time before: a 7x7 sum on 3001 x 4099 floats 43.8 -> 38.5 us, four Life generations per launch on
+// 1001 x 1503 bytes 34.3 -> 31.4 us, a 36-tap int32 sum on 2500 x 3003 35.0 -> 32.7 us.)
+typedef uint32_t any_word __attribute__((aligned(1), may_alias));
+typedef uint32_t any_word2 __attribute__((ext_vector_type(2), aligned(1), may_alias));
+typedef uint32_t any_word4 __attribute__((ext_vector_type(4), aligned(1), may_alias));
+template <class E, int CNT>
+__device__ __forceinline__ void load_global(E (&dst)[CNT], const E *src) {
+    if constexpr (sizeof(E) * CNT == 4) {       // four byte cells that are widened to floats afterwards
+        const uint32_t tmp = *reinterpret_cast<const any_word *>(src);
+        __builtin_memcpy(dst, &tmp, 4);
     } else {
-        *reinterpret_cast<uint4 *>(dst) = v;
+        static_assert(sizeof(E) * CNT % 16 == 0, "vector moves are whole 16-byte words");
+        constexpr int NV = sizeof(E) * CNT / 16;
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const any_word4 tmp = reinterpret_cast<const any_word4 *>(src)[k];
+            __builtin_memcpy(reinterpret_cast<char *>(dst) + 16 * k, &tmp, 16);
+        }
     }
+}
+// Stores of output cells are optionally non-temporal: they are not read again by the launch that
+// writes them, and on matrices beyond the caches keeping them out of the way of the input pays
+// (measured on a plain copy: +20 % on 256 MiB, nothing on 64 MiB).
+__device__ __forceinline__ void store_word4(void *dst, uint4 v, bool nt) {
+    any_word4 t;
+    t.x = v.x, t.y = v.y, t.z = v.z, t.w = v.w;
+    if (nt)
+        __builtin_nontemporal_store(t, reinterpret_cast<any_word4 *>(dst));
+    else
+        *reinterpret_cast<any_word4 *>(dst) = t;
 }
 template <class E, int CNT>
 __device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT], bool nt) {
@@ -96,7 +111,7 @@ __device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT], bool 
     uint4 tmp[NV];
     __builtin_memcpy(tmp, src, sizeof(tmp));
 #pragma unroll
-    for (int k = 0; k < NV; ++k) store_word4(reinterpret_cast<uint4 *>(dst) + k, tmp[k], nt);
+    for (int k = 0; k < NV; ++k) store_word4(reinterpret_cast<unsigned char *>(dst) + 16 * k, tmp[k], nt);
 }
 
 // What a cell keeps while one row of its region goes by (operators that fold a row at a time).
@@ -121,6 +136,49 @@ __device__ __forceinline__ uint32_t from_lane_above(uint32_t v) {
 template <int CC>
 __host__ __device__ constexpr int staged_halo(int h) { return CC == 1 ? h : round_up(h, CC); }
 
+// stage_tile for a tile that needs no border resolution: `src` is the matrix cell under the tile's first one.
+// Staging is bound by the latency of its loads and by the instructions that find their addresses, and the
+// latter were a third of a light stencil's: the general walk resolves a row and four columns per vector and
+// multiplies out both addresses; here an item is two adds, a compare and two selects.  (7x7 sum on 3001 x 4099
+// floats 38.5 -> 36.3 us, 5x5 sum on 4096^2 doubles 59.5 -> 56.9 us.)
+template <class Op, int CC>
+__device__ __forceinline__ void stage_inside(typename Op::L *tile, int plane, int n_items, const typename Op::T *src, int cols,
+                                             int total, unsigned magic, int tid, int nthreads) {
+    using T = typename Op::T;
+    using L = typename Op::L;
+    constexpr int NP = Op::kPlanes;
+    constexpr int kBatch = 4;
+    const unsigned i0 = __umulhi((unsigned)tid, magic), di = __umulhi((unsigned)nthreads, magic);
+    unsigned q = tid - i0 * n_items;
+    const unsigned dq = nthreads - di * n_items;
+    const unsigned row_bytes = (unsigned)cols * (unsigned)sizeof(T);
+    unsigned off = i0 * row_bytes + q * (unsigned)(CC * sizeof(T));
+    const unsigned step = di * row_bytes + dq * (unsigned)(CC * sizeof(T));       // one more pass of the workgroup, same row of items
+    const unsigned carry = row_bytes - (unsigned)n_items * (unsigned)(CC * sizeof(T));   // ... and into the next row
+    const char *base = reinterpret_cast<const char *>(src);
+    for (int at = tid; at < total; at += kBatch * nthreads) {
+        T v[kBatch][CC];
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            if (at + b * nthreads < total) load_global(v[b], reinterpret_cast<const T *>(base + off));
+            off += step;
+            q += dq;
+            if (q >= (unsigned)n_items) {
+                q -= n_items;
+                off += carry;
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) {
+            if (at + b * nthreads >= total) continue;
+            L sv[NP][CC];
+            Op::template stage_vec<CC>(v[b], sv);
+#pragma unroll
+            for (int p = 0; p < NP; ++p) store_vec(tile + p * plane + (at + b * nthreads) * CC, sv[p]);
+        }
+    }
+}
+
 // Stages `n_rows` rows of a tile into LDS with border resolution (Section 2).  Tile row i is
 // matrix row row_first + i, tile column j is matrix column col_first + j; each plane of the
 // staged values has `pitch` elements per row.  The rows are walked as one linear sequence of
@@ -131,12 +189,24 @@ __host__ __device__ constexpr int staged_halo(int h) { return CC == 1 ? h : roun
 template <class Op, int B, int CC>
 __device__ __forceinline__ void stage_tile(typename Op::L *tile, int plane, int pitch, const typename Op::T *in,
                                            int rows, int cols, int row_first, int col_first, int n_rows,
-                                           int col_end, typename Op::T pad, int vec_ok, unsigned magic, int tid,
+                                           int col_end, typename Op::T pad, unsigned magic, int tid,
                                            int nthreads) {
     using T = typename Op::T;
     using L = typename Op::L;
     constexpr int NP = Op::kPlanes;
     const int n_items = pitch / CC;   // per staged row
+    // A tile that lies inside the matrix with its border region (nearly all of them on a large matrix) has nothing
+    // to resolve: the items of the linear walk are loaded from a running 32-bit offset and, the tile being rows of
+    // n_items vectors, land in LDS at their own index.
+    const bool inside = CC > 1 && row_first >= 0 && row_first + n_rows <= rows && col_first >= 0 && col_first + pitch <= cols &&
+                        (uint64_t)n_rows * cols * sizeof(T) < (1ull << 32);
+    if constexpr (CC > 1) {
+        if (inside) {
+            stage_inside<Op, CC>(tile, plane, n_items, in + (size_t)row_first * cols + col_first, cols, n_rows * n_items, magic,
+                                 tid, nthreads);
+            return;
+        }
+    }
     int i = (int)__umulhi((unsigned)tid, magic);
     int q = tid - i * n_items;
     const int di = (int)__umulhi((unsigned)nthreads, magic), dq = nthreads - di * n_items;
@@ -162,8 +232,8 @@ __device__ __forceinline__ void stage_tile(typename Op::L *tile, int plane, int 
                     const int gc0 = col_first + q * CC;
                     have[b] = gc0 < col_end;
                     if (have[b]) {
-                        if (gr >= 0 && vec_ok && gc0 >= 0 && gc0 + CC <= cols) {
-                            load_vec(v[b], in + (size_t)gr * cols + gc0);
+                        if (gr >= 0 && gc0 >= 0 && gc0 + CC <= cols) {
+                            load_global(v[b], in + (size_t)gr * cols + gc0);
                         } else {
 #pragma unroll
                             for (int k = 0; k < CC; ++k) {
@@ -227,7 +297,7 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
     const int TH = th + hn + hs;
 
     stage_tile<Op, B, CC>(tile, a.plane, pitch, a.in, rows, cols, r0 - hn, c0 - hwa, TH, cols + he, a.pad,
-                          a.vec_ok, a.stage_magic, ty * wc + tx, wr * wc);
+                          a.stage_magic, ty * wc + tx, wr * wc);
     __syncthreads();
 
     // ---- fold the customising function over the border region ----------------------------
@@ -382,7 +452,7 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
         for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(st[cr][cc], a.scalar0);
         O *dst = a.out + (size_t)r * cols + c0 + lc0;
         if constexpr (CC > 1) {
-            if (a.vec_ok && c0 + lc0 + CC <= cols) {
+            if (c0 + lc0 + CC <= cols) {
                 store_out_vec(dst, res, a.nt_store != 0);
                 continue;
             }

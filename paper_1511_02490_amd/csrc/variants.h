@@ -101,12 +101,6 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
         const unsigned items = std::max(1u, (unsigned)(g.pitch / CC));
         a.stage_magic = (unsigned)((0x100000000ull + items - 1) / items);
     }
-    // a work-item moves CC cells at a time: rows of both matrices must start at multiples of that
-    // (16 bytes, except 4 where four byte cells are loaded)
-    using O = typename sk::out_type_of<Op>::type;
-    constexpr size_t in_vec = CC * sizeof(T), out_vec = CC * sizeof(O);
-    a.vec_ok = (CC > 1 && ((size_t)s->cols * sizeof(T)) % in_vec == 0 && (uintptr_t)in % in_vec == 0 &&
-                ((size_t)s->cols * sizeof(O)) % out_vec == 0 && (uintptr_t)out % out_vec == 0) ? 1 : 0;
     a.nt_store = s->nt_store;
     a.pad = (T)s->pad;
     a.scalar0 = s->scalar0;
@@ -180,8 +174,9 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
     const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
     blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
     const dim3 grid(blocks), block(wc, wr);
+    const bool whole = s->cols % 4 == 0;      // rows of whole vectors, or the element-by-element body
 #define STREAM_LAUNCH(D)                                                                                       \
-    if (a.vec_ok)                                                                                              \
+    if (whole)                                                                                                 \
         hipLaunchKernelGGL((sk::stream_kernel<Op, B, D, true, kMaxT>), grid, block, 0, stream, a, CR);         \
     else                                                                                                       \
         hipLaunchKernelGGL((sk::stream_kernel<Op, B, D, false, kMaxT>), grid, block, 0, stream, a, CR);        \
@@ -219,8 +214,9 @@ hipError_t launch_life_stream(const stencil *s, const void *in, void *out, int w
     const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
     blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
     const dim3 grid(blocks), block(wc, wr);
+    const bool whole = s->cols % (4 * WORDS) == 0;      // rows of whole vectors, or the cell-by-cell body
 #define LIFE_STREAM_LAUNCH(D)                                                                                  \
-    if (a.vec_ok)                                                                                              \
+    if (whole)                                                                                                 \
         hipLaunchKernelGGL((sk::life_stream_kernel<B, D, WORDS, true, kMaxT>), grid, block, 0, stream, a, CR); \
     else                                                                                                       \
         hipLaunchKernelGGL((sk::life_stream_kernel<B, D, WORDS, false, kMaxT>), grid, block, 0, stream, a, CR);\
@@ -251,7 +247,6 @@ hipError_t launch_threshold(const stencil *s, const void *in, void *out, int wr,
     const int th = wr * CR, tw = wc * CC;
     a.tiles_c = (a.cols + tw - 1) / tw;
     a.n_tiles = ((a.rows + th - 1) / th) * a.tiles_c;
-    a.vec_ok = (CC == 4 && s->cols % 4 == 0 && (uintptr_t)in % 16 == 0 && (uintptr_t)out % 4 == 0) ? 1 : 0;
     a.level = s->scalar0;
     unsigned blocks = (unsigned)a.n_tiles;
     a.xcd_chunk = 0;
@@ -278,8 +273,7 @@ hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int
         a.xcd_chunk = (int)((blocks + 7) / 8);
         blocks = (unsigned)a.xcd_chunk * 8u;
     }
-    // whole aligned vectors per row, or the element-by-element body
-    if (a.vec_ok)
+    if (s->cols % 4 == 0)      // rows of whole vectors, or the element-by-element body
         hipLaunchKernelGGL((sk::march_kernel<Op, B, Halo, true, kMaxT>), dim3(blocks), dim3(wc, wr), 0, stream, a,
                            s->cr);
     else
@@ -308,7 +302,7 @@ hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int 
             a.xcd_chunk = (int)((blocks + 7) / 8);
             blocks = (unsigned)a.xcd_chunk * 8u;
         }
-        if (a.vec_ok)
+        if (s->cols % 4 == 0)
             hipLaunchKernelGGL((sk::march_masked_kernel<Op, B, Halo, WC, true, kMaxT>), dim3(blocks), dim3(wc, wr), 0,
                                stream, a, s->cr);
         else
@@ -366,7 +360,7 @@ hipError_t launch_life_direct(const stencil *s, const void *in, void *out, int w
 }
 
 
-// The kernel behind each launcher (the variant with whole aligned vectors where there are two).
+// The kernel behind each launcher (the variant for rows of whole vectors where there are two).
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 const void *kernel_tile(const stencil *) { return reinterpret_cast<const void *>(&sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>); }
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>

@@ -225,6 +225,35 @@ def test_heat_conserves_total_and_long_run(ls):
     assert got.min() >= g.min() and got.max() <= g.max()
 
 
+@pytest.mark.parametrize("cols", [160, 161, 162, 163, 175])
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+def test_vectors_at_any_address(ls, border, cols):
+    """Rows of every length modulo a vector, matrices that start at any element: tiles inside the matrix (staged
+    without border resolution) and at its edges (the last vector of a row is partial)."""
+    rng = np.random.default_rng(cols)
+    for offset in (0, 1, 3):
+        for halo in [(2, 2, 2, 2), (3, 1, 0, 4)]:
+            w = custom(wl.WEIGHTED_SUM, 70, cols, halo, border, pad=0.5, seed=cols)
+            for blocking, wg in [((2, 4), (4, 8)), ((1, 4), (8, 16)), ((4, 4), (2, 5))]:
+                check(ls, w, wg, blocking=blocking, offset=offset)
+            wf = rng.random((halo[0] + halo[1] + 1, halo[2] + halo[3] + 1), dtype=np.float32)
+            wd = wl.Workload("f64", 70, cols, "f64", halo, border, 0.5, wl.WEIGHTED_SUM, 1, 5, "pow2", weights=wf)
+            check(ls, wd, (4, 8), blocking=(2, 2), offset=offset)
+            wi = wl.Workload("i32", 70, cols, "i32", halo, border, 3.0, wl.WEIGHTED_SUM, 1, 6, "pow2",
+                             weights=np.rint(wf * 9).astype(np.float32))
+            check(ls, wi, (4, 8), blocking=(2, 4), offset=offset)
+            wu = wl.Workload("u8", 70, cols, "u8", halo, border, 9.0, wl.WEIGHTED_SUM, 1, 7, "pow2", weights=wf)
+            check(ls, wu, (4, 8), blocking=(2, 4), offset=offset)
+        life = wl.config(2, rows=70, cols=cols, iters=5)
+        life.border = border
+        heat = wl.config(3, rows=70, cols=cols, iters=5)
+        heat.border, heat.pad = border, 50.0
+        for w, cc in ((life, 16), (heat, 4)):
+            check(ls, w, (4, 2), blocking=(2, cc), offset=offset)
+            check(ls, w, (4, 2), blocking=("direct", 2, cc), offset=offset)
+            check(ls, w, (4, 2), blocking=("temporal", 2, cc, 3), offset=offset)
+
+
 # ---- the other element types of the paper's template (Section 3.3) ---------------------------
 
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
