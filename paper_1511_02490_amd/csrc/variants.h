@@ -14,6 +14,7 @@
 #include "direct_kernel.h"
 #include "stream_kernel.h"
 #include "temporal_kernel.h"
+#include "life_bits.h"
 #include "tile_kernel.h"
 #include "march_kernel.h"
 #include "march_masked_kernel.h"
@@ -148,11 +149,12 @@ hipError_t launch_temporal(const stencil *s, const void *in, void *out, int wr, 
     unsigned blocks;
     size_t lds;
     const auto a = make_args<Op, Halo, CR, 4>(s, STENCIL_STAGING_TEMPORAL, in, out, wr, wc, &blocks, &lds);
-    static thread_local int raised_on = -1;
-    hipError_t e = allow_large_tiles(reinterpret_cast<const void *>(&sk::temporal_kernel<Op, B, CR, MAXT>), lds,
-                                     &raised_on);
+    const bool whole_waves = wr * wc % 64 == 0;
+    const auto kernel = whole_waves ? &sk::temporal_kernel<Op, B, true, MAXT> : &sk::temporal_kernel<Op, B, false, MAXT>;
+    static thread_local int raised_on[2] = {-1, -1};
+    hipError_t e = allow_large_tiles(reinterpret_cast<const void *>(kernel), lds, &raised_on[whole_waves]);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sk::temporal_kernel<Op, B, CR, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a, depth);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(wc, wr), lds, stream, a, depth, wr * CR);
     return hipGetLastError();
 }
 
@@ -317,12 +319,15 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
                                 hipStream_t stream) {
     unsigned blocks;
     size_t lds;
-    const auto a = make_args<sk::OpLife, sk::HaloC<1, 1, 1, 1>, CR, 16>(s, STENCIL_STAGING_TEMPORAL, in, out, wr, wc,
-                                                                        &blocks, &lds);
-    static thread_local int raised_on = -1;
-    hipError_t e = allow_large_tiles(reinterpret_cast<const void *>(&sk::life_temporal_kernel<B, CR, MAXT>), lds,
-                                     &raised_on);
-    if (e != hipSuccess) return e;
+    auto a = make_args<sk::OpLife, sk::HaloC<1, 1, 1, 1>, CR, 16>(s, STENCIL_STAGING_TEMPORAL, in, out, wr, wc,
+                                                                  &blocks, &lds);
+    // The kernel keeps the tile as bits, rows of whole words.  (Which sizes are legal still follows from
+    // the tile counted in bytes: tile_geom.)
+    const unsigned words = (unsigned)(a.pitch + 31) / 32;
+    a.pitch = (int)words;
+    a.plane = (wr * CR + 2 * s->temporal_depth) * a.pitch;
+    a.stage_magic = (unsigned)((0x100000000ull + words - 1) / words);
+    lds = 4 * (2 * (size_t)a.plane + 2);         // + one spare word at each end
     hipLaunchKernelGGL((sk::life_temporal_kernel<B, CR, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a, depth);
     return hipGetLastError();
 }
@@ -367,8 +372,8 @@ template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 const void *kernel_direct(const stencil *) { return reinterpret_cast<const void *>(&sk::direct_kernel<Op, B, Halo, CR, CC, MAXT>); }
 template <int B, int CR, int MAXT>
 const void *kernel_life_direct(const stencil *) { return reinterpret_cast<const void *>(&sk::life_direct_kernel<B, CR, MAXT>); }
-template <class Op, int B, int CR, int MAXT>
-const void *kernel_temporal(const stencil *) { return reinterpret_cast<const void *>(&sk::temporal_kernel<Op, B, CR, MAXT>); }
+template <class Op, int B, int MAXT>
+const void *kernel_temporal(const stencil *) { return reinterpret_cast<const void *>(&sk::temporal_kernel<Op, B, true, MAXT>); }
 template <int B, int CR, int MAXT>
 const void *kernel_life_temporal(const stencil *) { return reinterpret_cast<const void *>(&sk::life_temporal_kernel<B, CR, MAXT>); }
 template <int CR, int CC>
@@ -487,7 +492,7 @@ void reg_temporal_one(std::vector<Variant> &r) {
     v.staged_bytes = 4;
     v.fuses = true;
     v.launch = &launch_temporal<Op, B, CR, STENCIL_MAX_WG_SIZE>;
-    v.kernel_of = &kernel_temporal<Op, B, CR, STENCIL_MAX_WG_SIZE>;
+    v.kernel_of = &kernel_temporal<Op, B, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);
 }
 

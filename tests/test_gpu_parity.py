@@ -440,6 +440,28 @@ def test_temporal_blocking_life_bit_exact(ls, border):
         check(ls, wt, (2, 4), blocking=("temporal", 2, 16, 4))
 
 
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("cols", [2, 15, 16, 17, 31, 33, 47, 49, 129])
+def test_life_on_bits_at_word_and_tile_edges(ls, border, cols):
+    """Rows that end anywhere in a word or a 16-cell vector, tiles of an odd number of vectors, workgroups of fewer
+    work-items than a row has words, and a last tile of a single row."""
+    for rows, wg, cr in [(1, (1, 1), 1), (33, (16, 2), 2), (65, (8, 3), 8)]:
+        w = custom(wl.LIFE, rows, cols, (1, 1, 1, 1), border, pad=1.0, seed=rows + cols, iters=7)
+        check(ls, w, wg, blocking=("temporal", cr, 16, 4), offset=cols % 3)
+
+
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("wg", [(1, 1), (1, 64), (2, 64), (1, 256), (5, 13), (16, 64)])
+def test_temporal_items_of_whole_and_ragged_workgroups(ls, border, wg):
+    """Overlapping wavefronts, more than one pass over a row of vectors, and workgroups that are no whole wavefronts."""
+    for rows, cols in [(wg[0] * 2 + 1, wg[1] * 4 - 1), (67, 2 * wg[1] * 4 + 2)]:
+        w = custom(wl.WEIGHTED_SUM, rows, cols, (1, 1, 1, 1), border, pad=0.25, seed=7, iters=5)
+        check(ls, w, wg, blocking=("temporal", 2, 4, 4))
+        h = wl.config(3, rows=rows, cols=cols, iters=5)
+        h.border, h.pad = border, 30.0
+        check(ls, h, wg, blocking=("temporal", 2, 4, 4))
+
+
 @pytest.mark.parametrize("border", ["wrap", "constant"])
 def test_register_streaming_temporal_kernel_bit_exact(ls, border):
     """Time levels kept in registers, row neighbours from adjacent lanes; every wavefront owns a
