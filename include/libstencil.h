@@ -169,6 +169,10 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            rows, which hands row neighbours through local memory (a few KiB per workgroup,
  *            never a reason for refusal).  Larger regions: not available (the local-memory
  *            tile is as fast there: its fold is bound by arithmetic).
+ *            LIFE, WRAP and CONSTANT borders: one bit per cell, cells_cols in {4,8,16}; up to
+ *            STENCIL_MAX_STREAM_DEPTH generations per launch, and between the launches of a run
+ *            the matrix stays in bits.  The library cuts the tile from the matrix, the depth and
+ *            the workgroup's number of wavefronts; cells_rows and cells_cols do not change it.
  *            The workgroup only groups wavefronts: w_r*w_c must be a multiple of 64 (other
  *            sizes are refused) and at most 256.  Not available for a matrix whose rows are 4 GiB
  *            or longer (cells within a row are addressed by 32-bit byte offsets).

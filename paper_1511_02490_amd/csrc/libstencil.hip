@@ -67,6 +67,7 @@ void query_device_limits() {
 }  // namespace
 
 int64_t stencil_local_memory_limit() { return g_limits.local_memory; }
+int stencil_compute_units() { return g_limits.compute_units; }
 
 namespace {
 
@@ -285,16 +286,25 @@ int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *p
     // matrix so that the last one lands in `out`
     const int per = v->fuses ? s->temporal_depth : 1;
     const int launches = launches_of(s, v, iters);
+    // (or, where the kernel can hand on packed bits, between two such matrices, which the scratch matrix
+    // holds both of unless its rows are shorter than two words are in bytes)
+    const size_t packed_bytes = (size_t)s->rows * (size_t)life_words(s) * 4;
+    const bool packed = v->launch_packed && launches > 1 && 2 * packed_bytes <= s->bytes();
+    void *const halves[2] = {pingpong, static_cast<char *>(pingpong) + (packed ? packed_bytes : 0)};
     const void *src = in;
-    void *dst = (launches % 2 == 1) ? out : pingpong;
+    void *dst = packed ? halves[0] : (launches % 2 == 1) ? out : pingpong;
     for (int done = 0; done < iters;) {
         const int now = std::min(per, iters - done);
+        const bool last = done + now == iters;
+        if (packed && last) dst = out;
         const bool injected = s->fail_rows == -1 || (s->fail_rows == wr && s->fail_cols == wc);
-        hipError_t e = injected ? hipErrorLaunchOutOfResources : v->launch(s, src, dst, wr, wc, now, stream);
+        hipError_t e = injected ? hipErrorLaunchOutOfResources
+                       : packed ? v->launch_packed(s, src, src != in, dst, !last, wr, wc, now, stream)
+                                : v->launch(s, src, dst, wr, wc, now, stream);
         if (e != hipSuccess) return launch_failure(e, wr, wc);
         done += now;
         src = dst;
-        dst = (dst == out) ? pingpong : out;
+        dst = packed ? halves[dst == halves[0]] : (dst == out) ? pingpong : out;
     }
     return STENCIL_OK;
 }

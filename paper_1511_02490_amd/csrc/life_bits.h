@@ -27,8 +27,16 @@ __device__ __forceinline__ uint4 unpack_cells16(uint32_t bits) {
 __device__ __forceinline__ uint32_t west_of(uint32_t x, uint32_t before) { return __builtin_amdgcn_alignbit(x, before, 31); }
 __device__ __forceinline__ uint32_t east_of(uint32_t x, uint32_t after) { return __builtin_amdgcn_alignbit(after, x, 1); }
 
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return a ^ b ^ c; }
-__device__ __forceinline__ uint32_t majority(uint32_t a, uint32_t b, uint32_t c) { return (a & b) | (c & (a | b)); }
+// Three-input functions by their truth tables: TABLE is the function of a = 0xf0, b = 0xcc, c = 0xaa.  (Written as
+// ordinary logic the compiler makes two operations of a three-way xor, and 27 of a row's 14.)
+template <uint32_t TABLE>
+__device__ __forceinline__ uint32_t logic3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, TABLE);
+}
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return logic3<0xf0 ^ 0xcc ^ 0xaa>(a, b, c); }
+__device__ __forceinline__ uint32_t majority(uint32_t a, uint32_t b, uint32_t c) {
+    return logic3<(0xf0 & 0xcc) | (0xaa & (0xf0 | 0xcc))>(a, b, c);
+}
 
 // One row as its neighbours above and below see it: the cells, and the sum of each cell and its west
 // and east neighbours as a two-bit number.
@@ -43,8 +51,10 @@ __device__ __forceinline__ LifeBits life_bits(uint32_t x, uint32_t west, uint32_
 __device__ __forceinline__ uint32_t life_next(const LifeBits &up, const LifeBits &mid, const LifeBits &dn) {
     const uint32_t ones = xor3(up.h0, mid.h0, dn.h0), carry = majority(up.h0, mid.h0, dn.h0);
     const uint32_t h = xor3(up.h1, mid.h1, dn.h1);
-    const uint32_t twos = carry ^ h, fours = majority(up.h1, mid.h1, dn.h1) ^ (carry & h);
-    return ~(ones ^ twos) & (ones ^ fours) & (ones | mid.x);
+    const uint32_t twos = carry ^ h;
+    const uint32_t fours = logic3<0xf0 ^ (0xcc & 0xaa)>(majority(up.h1, mid.h1, dn.h1), carry, h);
+    const uint32_t three_or_four = logic3<~(0xf0 ^ 0xcc) & (0xf0 ^ 0xaa) & 0xff>(ones, twos, fours);
+    return logic3<0xf0 & (0xcc | 0xaa)>(three_or_four, ones, mid.x);
 }
 
 // The bits of a word whose first cell is matrix column `col` that are matrix cells.

@@ -1,204 +1,168 @@
-// Game of Life, several generations per launch, with every time level in registers: the packed-
-// byte arithmetic of the direct Life kernel on the marching order of the streaming fp32 kernel.
+// Game of Life, several generations per launch, on bits in registers (the arithmetic: life_bits.h).
 //
-// A lane holds WORDS 32-bit words (4 * WORDS cells) of a row; a wavefront's 64 lanes make a strip
-// and walk down H + 2 * DEPTH rows.  For each generation k the last three rows of generation
-// k - 1 are kept; their byte-wise column sums need only one byte from each neighbouring lane
-// (one cross-lane move per side and generation), and the 3x3 block sums, the neighbour counts and
-// the rule follow as in the direct kernel.  What a generation computes within k cells of a
-// strip's edge is stale after k generations: the outermost ceil(DEPTH / (4 * WORDS)) lanes of
-// each side are rim lanes and are not written.  WRAP and CONSTANT borders, as for the fp32 kernel.
+// A work-item holds RPT rows of one word (32 cells) of the matrix.  16, 32 or 64 adjacent lanes hold adjacent
+// words, the lanes' groups rows below each other, and the workgroup so holds a tile.  Per generation a row's
+// west and east neighbours come from the adjacent lanes by cross-lane moves, and only the first and the last
+// row of every work-item pass through local memory, behind one barrier (two buffers in turn).  What a generation
+// computes within k rows or cells of the tile's rim is stale after k generations: `depth` rows above and below
+// and a word left and right are not written.  WRAP and CONSTANT borders: a periodic copy evolves like its
+// original, a padded cell is set back after every generation.
+//
+// Between the launches of a run the matrix is kept as bits, rows of whole words: the first launch turns bytes
+// into bits, the last one bits into bytes, and the launches between them move an eighth of the bytes.  They are
+// bound by the generations' serial chain (a row's sums, the barrier, the rule), not by memory: the tile is cut
+// so that the device's wavefronts are filled evenly and its rim repeats as little as possible (life_tile in
+// variants.h).
+// (100 generations of 4096 x 4096, WRAP, 8 per launch: 282 -> 121 us, before by marching packed bytes down the
+// matrix; a generation is 0.55 us of a launch of 9.8, of which 5.7 are the launch, its loads and its stores.)
 #pragma once
-#include "tile_kernel.h"
+#include "life_bits.h"
 
 namespace sk {
 
-constexpr int kLifeStreamMaxDepth = 8;
-__host__ __device__ constexpr int life_stream_rim(int depth, int words) { return (depth + 4 * words - 1) / (4 * words); }
-__host__ __device__ constexpr int life_stream_cols(int depth, int words) {
-    return (64 - 2 * life_stream_rim(depth, words)) * 4 * words;
-}
+constexpr int kLifeStreamMaxDepth = 8;      // (the rim of 32 cells would allow more)
+constexpr int kLifeStreamMaxThreads = 256;
 
-template <int WORDS>
-__device__ __forceinline__ void load_words(uint32_t (&v)[WORDS], const void *src) {
-    if constexpr (WORDS == 1) {
-        v[0] = *reinterpret_cast<const any_word *>(src);
-    } else if constexpr (WORDS == 2) {
-        const any_word2 t = *reinterpret_cast<const any_word2 *>(src);
-        v[0] = t.x, v[1] = t.y;
-    } else {
-        static_assert(WORDS == 4, "1, 2 or 4 words per lane");
-        const any_word4 t = *reinterpret_cast<const any_word4 *>(src);
-        v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
-    }
-}
-// (the 16-byte stores can be non-temporal, as in the other kernels; the narrower ones are plain)
-template <int WORDS>
-__device__ __forceinline__ void store_words(void *dst, const uint32_t (&v)[WORDS], bool nt) {
-    if constexpr (WORDS == 1) {
-        *reinterpret_cast<any_word *>(dst) = v[0];
-    } else if constexpr (WORDS == 2) {
-        any_word2 t;
-        t.x = v[0], t.y = v[1];
-        *reinterpret_cast<any_word2 *>(dst) = t;
-    } else {
-        store_word4(dst, make_uint4(v[0], v[1], v[2], v[3]), nt);
-    }
-}
+struct LifeStreamArgs {
+    const void *in;
+    void *out;
+    int rows, cols, words;       // words per row of a matrix of bits
+    int tiles_c, n_tiles;
+    int group_shift;             // log2 of the lanes that hold a row of the tile
+    int pad;                     // 0 or 1
+    int nt_store;
+};
 
-// FAST: rows are whole lanes' widths (cols % CC == 0), so a lane's cells lie either all inside the matrix
-// or all outside it and a row is one load at a per-lane column plus a wavefront-uniform row
-// address, issued without a branch.  Otherwise cells are loaded and stored one by one.
-template <int B, int DEPTH, int WORDS, bool FAST>
-__device__ __forceinline__ void life_stream_body(const TileArgs<OpLife, HaloC<1, 1, 1, 1>> &a, const int H) {
+template <int B, int RPT, bool IN_BITS, bool OUT_BITS>
+__global__ __launch_bounds__(kLifeStreamMaxThreads) void life_stream_kernel(const LifeStreamArgs a, const int depth) {
     static_assert(B == kWrap || B == kConstant, "wrap and constant borders only");
-    static_assert(DEPTH >= 1 && DEPTH <= kLifeStreamMaxDepth, "generations per launch");
-    constexpr int CC = 4 * WORDS;                   // cells per lane
-    constexpr int R = 3;                            // rows of a generation kept
-    constexpr int PF = 6;                           // input rows in flight = steps per round (a multiple of R)
-    constexpr int kRim = life_stream_rim(DEPTH, WORDS);
-    constexpr int kCols = life_stream_cols(DEPTH, WORDS);
-
-    const int tid = (int)threadIdx.y * (int)blockDim.x + (int)threadIdx.x;
-    const int lane = tid & 63;
-    const int waves_per_block = ((int)blockDim.x * (int)blockDim.y) >> 6;
-    // a wavefront's index is the same in all its lanes: keep it, and all that follows from it, scalar
-    const int wave = __builtin_amdgcn_readfirstlane((int)blockIdx.x * waves_per_block + (tid >> 6));
-    if (wave >= a.n_tiles) return;
-    const int seg = wave / a.tiles_c, strip = wave - seg * a.tiles_c;
+    const int tid = (int)threadIdx.y * (int)blockDim.x + (int)threadIdx.x, nthreads = (int)(blockDim.x * blockDim.y);
+    const int G = 1 << a.group_shift, groups = nthreads >> a.group_shift;
     const int rows = a.rows, cols = a.cols;
-    const int r0 = seg * H;
-    const int gc0 = strip * kCols - kRim * CC + lane * CC;     // first of this lane's cells
-    const bool writes = lane >= kRim && lane < 64 - kRim && gc0 < cols;
-    const uint32_t pad_word = (uint32_t)a.pad * 0x01010101u;
+    const int tile_r = (int)blockIdx.x / a.tiles_c, tile_c = (int)blockIdx.x - tile_r * a.tiles_c;
+    const int word = tile_c * (G - 2) - 1 + (tid & (G - 1)), col = word * 32;
+    const int tile_rows = groups * RPT - 2 * depth;                    // the rows it writes
+    const int row0 = tile_r * tile_rows - depth + (tid >> a.group_shift) * RPT;
+    const uint32_t pad = a.pad ? ~0u : 0u;
+    const uint32_t inside = inside_bits(col, cols);
 
-    // FAST: the column the lane's load starts at (wrapped, or any valid one for padding)
-    const bool outside = (unsigned)gc0 >= (unsigned)cols;
-    const int vcol = !outside ? gc0 : (B == kWrap ? resolve<B>(gc0, cols) : 0);
-    const bool edge_wave = __any(outside) != 0;     // the same for the whole wavefront
-    // otherwise: per cell, the column after border resolution, and which bytes are matrix cells
-    uint32_t inside_mask[WORDS];
+    // the matrix rows it loads: under WRAP row0's and, going round, those after it; under CONSTANT any where there is none
+    int gr[RPT];
+    gr[0] = B == kWrap ? resolve<kWrap>(row0, rows) : max(0, min(row0, rows - 1));
 #pragma unroll
-    for (int w = 0; w < WORDS; ++w) {
-        inside_mask[w] = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            if ((unsigned)(gc0 + 4 * w + b) < (unsigned)cols) inside_mask[w] |= 0xffu << (8 * b);
+    for (int i = 1; i < RPT; ++i) {
+        if (B == kWrap)
+            gr[i] = gr[i - 1] + 1 == rows ? 0 : gr[i - 1] + 1;
+        else
+            gr[i] = max(0, min(row0 + i, rows - 1));
     }
-
-    const int kSteps = H + 2 * DEPTH;               // input rows a segment consumes
-    const int kRounds = (kSteps + PF - 1) / PF;     // whole rounds; steps past kSteps store nothing
-
-    // issue the loads of input row r0 - DEPTH + t
-    auto load_row = [&](int t, uint32_t (&v)[WORDS]) {
-        const int tt = t < kSteps ? t : kSteps - 1;
-        const int gr = resolve<B>(r0 - DEPTH + tt, rows);      // the same for the whole wavefront
-        if (FAST) {
-            load_words<WORDS>(v, a.in + (size_t)(gr < 0 ? 0 : gr) * cols + (unsigned)vcol);
+    uint32_t x[RPT];
+    if constexpr (IN_BITS) {
+        const uint32_t *in = static_cast<const uint32_t *>(a.in);
+        const int there = max(0, min(word, a.words - 1));
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) x[i] = in[(unsigned)(gr[i] * a.words + there)];
+        if (B == kWrap && inside != ~0u) {
+            // a word that is not simply there: 32 cells from column `col` round the end of the row
+            const int at = resolve<B>(col, cols);
+            if (cols >= 32) {
+                const int w = at >> 5, after = min(w + 1, a.words - 1), have = cols - at;
+                const uint32_t keep = have >= 32 ? ~0u : (1u << have) - 1u;
+#pragma unroll
+                for (int i = 0; i < RPT; ++i) {
+                    const uint32_t *row = in + (unsigned)(gr[i] * a.words);
+                    x[i] = (__builtin_amdgcn_alignbit(row[after], row[w], at & 31) & keep) | (have >= 32 ? 0u : row[0] << (have & 31));
+                }
+            } else {        // the row is one word
+                uint32_t y[RPT] = {};
+                int from = at;
+#pragma unroll 1
+                for (int k = 0; k < 32; ++k) {
+#pragma unroll
+                    for (int i = 0; i < RPT; ++i) y[i] |= ((x[i] >> from) & 1u) << k;
+                    from = from + 1 == cols ? 0 : from + 1;
+                }
+#pragma unroll
+                for (int i = 0; i < RPT; ++i) x[i] = y[i];
+            }
+        }
+    } else {
+        const uint8_t *in = static_cast<const uint8_t *>(a.in);
+        if (cols >= 16) {
+            LifeLoad v[RPT][2];
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                v[i][0] = life_load16<B>(in, gr[i], col, cols);
+                v[i][1] = life_load16<B>(in, gr[i], col + 16, cols);
+            }
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) {
+                x[i] = life_bits16<B>(v[i][0], in, gr[i], cols, 0) | (life_bits16<B>(v[i][1], in, gr[i], cols, 0) << 16);
+            }
         } else {
 #pragma unroll
-            for (int w = 0; w < WORDS; ++w) {
-                uint32_t word = 0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int gc = resolve<B>(gc0 + 4 * w + b, cols);
-                    const uint32_t cell = (gr < 0 || gc < 0) ? a.pad : a.in[(size_t)gr * cols + gc];
-                    word |= cell << (8 * b);
-                }
-                v[w] = word;
+            for (int i = 0; i < RPT; ++i) {
+                x[i] = life_bits16_narrow<B>(in, gr[i], col, cols, 0) | (life_bits16_narrow<B>(in, gr[i], col + 16, cols, 0) << 16);
             }
         }
-    };
-    // CONSTANT: cells of matrix row gr (any generation) that are not matrix cells hold the padding
-    auto pad_outside = [&](int gr, uint32_t (&v)[WORDS]) {
-        if (B != kConstant) return;
-        const bool outside_r = (unsigned)gr >= (unsigned)rows;
-        if (FAST) {
-            if (outside_r || edge_wave) {
+    }
+    // CONSTANT: cells that are not matrix cells hold the padding
+    const bool at_border = B == kConstant && (tile_r * tile_rows < depth || tile_r * tile_rows + tile_rows + depth > rows ||
+                                              tile_c == 0 || (tile_c + 1) * (G - 2) * 32 + 32 > cols);
+    auto pad_outside = [&] {
+        if (!at_border) return;
 #pragma unroll
-                for (int w = 0; w < WORDS; ++w) v[w] = (outside_r || outside) ? pad_word : v[w];
-            }
+        for (int i = 0; i < RPT; ++i) {
+            const uint32_t keep = (unsigned)(row0 + i) < (unsigned)rows ? inside : 0u;
+            x[i] = (x[i] & keep) | (pad & ~keep);
+        }
+    };
+    pad_outside();
+
+    // a row with its neighbours from the adjacent lanes; what the two ends of a group of lanes get is no
+    // neighbour, and stays in the rim
+    auto sums = [](uint32_t v) { return life_bits(v, west_of(v, from_lane_below(v)), east_of(v, from_lane_above(v))); };
+    __shared__ uint32_t first_rows[2][kLifeStreamMaxThreads], last_rows[2][kLifeStreamMaxThreads];
+    const int above_at = max(0, tid - G), below_at = min(tid + G, nthreads - 1);
+    for (int k = 0; k < depth; ++k) {
+        first_rows[k & 1][tid] = x[0];
+        last_rows[k & 1][tid] = x[RPT - 1];
+        LifeBits h[RPT];
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) h[i] = sums(x[i]);
+        __syncthreads();
+        const uint32_t above = last_rows[k & 1][above_at], below = first_rows[k & 1][below_at];
+#pragma unroll
+        for (int i = 1; i < RPT - 1; ++i) x[i] = life_next(h[i - 1], h[i], h[i + 1]);
+        x[0] = life_next(sums(above), h[0], h[1]);
+        x[RPT - 1] = life_next(h[RPT - 2], h[RPT - 1], sums(below));
+        pad_outside();
+    }
+
+    const int lane = tid & (G - 1), end = min(rows, tile_r * tile_rows + tile_rows);
+    if (lane == 0 || lane == G - 1 || word >= a.words) return;
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        const int r = row0 + i;
+        if (r < tile_r * tile_rows || r >= end) continue;
+        if constexpr (OUT_BITS) {
+            static_cast<uint32_t *>(a.out)[(unsigned)(r * a.words + word)] = x[i];
         } else {
+            uint8_t *out = static_cast<uint8_t *>(a.out) + (unsigned)(r * cols + col);
 #pragma unroll
-            for (int w = 0; w < WORDS; ++w) {
-                const uint32_t keep = outside_r ? 0u : inside_mask[w];
-                v[w] = (v[w] & keep) | (pad_word & ~keep);
-            }
-        }
-    };
-
-    // lv[k][s]: generation k's row that was produced at a time step with t % 3 == s (0 = input)
-    uint32_t lv[DEPTH][R][WORDS];
+            for (int half = 0; half < 2; ++half) {
+                const uint4 o = unpack_cells16(x[i] >> (16 * half));
+                if (col + 16 * half + 16 <= cols) {
+                    store_word4(out + 16 * half, o, a.nt_store != 0);
+                } else {
+                    const uint32_t w[4] = {o.x, o.y, o.z, o.w};
 #pragma unroll
-    for (int k = 0; k < DEPTH; ++k)
-#pragma unroll
-        for (int s = 0; s < R; ++s)
-#pragma unroll
-            for (int w = 0; w < WORDS; ++w) lv[k][s][w] = 0;
-    uint32_t pf[PF][WORDS];   // rows on their way from memory, PF time steps ahead
-#pragma unroll
-    for (int s = 0; s < PF; ++s) {
-        load_row(s, pf[s]);
-        // in the order the march consumes them: were the scheduler to issue the first-needed row
-        // last, every round of the loop would begin by waiting for all loads in flight
-        __builtin_amdgcn_sched_barrier(0);
-    }
-
-    for (int round = 0; round < kRounds; ++round) {
-#pragma unroll
-        for (int p = 0; p < PF; ++p) {
-            const int t = round * PF + p;
-            const int u = p % R;                    // = t % R
-#pragma unroll
-            for (int w = 0; w < WORDS; ++w) lv[0][u][w] = pf[p][w];
-            pad_outside(r0 - DEPTH + t, lv[0][u]);
-            load_row(t + PF, pf[p]);
-#pragma unroll
-            for (int k = 1; k <= DEPTH; ++k) {
-                // generation k's first row that anything depends on is due at step 2k
-                if (t < 2 * k) continue;
-                // generation k's row r0 - DEPTH + t - k from generation k-1's three newest rows
-                const uint32_t(&up)[WORDS] = lv[k - 1][(u + 1) % R];
-                const uint32_t(&mid)[WORDS] = lv[k - 1][(u + 2) % R];
-                const uint32_t(&dn)[WORDS] = lv[k - 1][u];
-                uint32_t v[WORDS];                  // byte-wise column sums, <= 3
-#pragma unroll
-                for (int w = 0; w < WORDS; ++w) v[w] = up[w] + mid[w] + dn[w];
-                const uint32_t from_w = from_lane_below(v[WORDS - 1]);   // its top byte: the column west of ours
-                const uint32_t from_e = from_lane_above(v[0]);           // its low byte: the column east of ours
-                uint32_t res[WORDS];
-#pragma unroll
-                for (int w = 0; w < WORDS; ++w) {
-                    const uint32_t prev = w == 0 ? from_w : v[w - 1], next = w == WORDS - 1 ? from_e : v[w + 1];
-                    const uint32_t west = (v[w] << 8) | (prev >> 24);
-                    const uint32_t east = (v[w] >> 8) | (next << 24);
-                    const uint32_t s = v[w] + west + east;         // 3x3 block sums, <= 9 per byte
-                    const uint32_t n = s - mid[w];                 // neighbours only
-                    res[w] = zero_bytes((n | mid[w]) ^ 0x03030303u);   // zero byte <=> alive next (B3/S23)
-                }
-                const int gr = r0 - DEPTH + t - k;      // the matrix row just produced
-                if (k < DEPTH) {
-                    pad_outside(gr, res);
-#pragma unroll
-                    for (int w = 0; w < WORDS; ++w) lv[k][u][w] = res[w];
-                } else if (t >= 2 * DEPTH && t < kSteps && gr < rows && writes) {
-                    uint8_t *dst = a.out + (size_t)gr * cols + (unsigned)gc0;
-                    if (FAST) {
-                        store_words<WORDS>(dst, res, a.nt_store != 0);
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < CC; ++c)
-                            if (gc0 + c < cols) dst[c] = (uint8_t)(res[c >> 2] >> (8 * (c & 3)));
-                    }
+                    for (int b = 0; b < 16; ++b)
+                        if (col + 16 * half + b < cols) out[16 * half + b] = (uint8_t)(w[b >> 2] >> (8 * (b & 3)));
                 }
             }
         }
     }
-}
-
-template <int B, int DEPTH, int WORDS, bool FAST, int MAXT>
-__global__ __launch_bounds__(MAXT) void life_stream_kernel(const TileArgs<OpLife, HaloC<1, 1, 1, 1>> a, const int H) {
-    life_stream_body<B, DEPTH, WORDS, FAST>(a, H);
 }
 
 }  // namespace sk

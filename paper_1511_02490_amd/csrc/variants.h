@@ -26,6 +26,7 @@
 // Local memory a workgroup may allocate: the device's own figure once a GPU has been used, the
 // header's constant before that (defined in libstencil.hip).
 int64_t stencil_local_memory_limit();
+int stencil_compute_units();
 
 namespace {
 
@@ -36,6 +37,12 @@ int variant_kernel(const stencil *s) {
     if (s->kernel == STENCIL_WEIGHTED_SUM && s->dtype == STENCIL_U8) return STENCIL_WEIGHTED_SUM_U8;
     return s->kernel;
 }
+
+// Words per row of a Life matrix kept as bits.
+int64_t life_words(const stencil *s) { return (s->cols + 31) / 32; }
+// What the segment heights of stencil_stream_segment_rows are counted in for LIFE: 64 lanes of `cells` cells
+// less a rim that covers `depth` generations.
+int life_strip_cols(int depth, int cells) { return (64 - 2 * ((depth + cells - 1) / cells)) * cells; }
 
 struct TileGeom {
     int th, tw;        // elements covered by one workgroup
@@ -61,7 +68,7 @@ TileGeom tile_geom(const stencil *s, const Variant &v, int wr, int wc) {
         // one wavefront per tile: s->cr rows of a strip of 62..64 vectors; no local memory
         g.th = s->cr;
         g.tw = !v.fuses ? sk::march_vectors(s->hw, s->he) * 4
-               : s->kernel == STENCIL_LIFE ? sk::life_stream_cols(s->temporal_depth, v.cc / 4)
+               : s->kernel == STENCIL_LIFE ? life_strip_cols(s->temporal_depth, v.cc)
                                            : sk::stream_cols(s->temporal_depth);
         g.pitch = 4;
         g.plane = 0;
@@ -198,44 +205,79 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
     return hipGetLastError();
 }
 
-// Game of Life, `depth` generations per launch in registers (life_stream_kernel.h).
-template <int B, int WORDS>
-hipError_t launch_life_stream(const stencil *s, const void *in, void *out, int wr, int wc, int depth,
-                              hipStream_t stream) {
-    using Halo = sk::HaloC<1, 1, 1, 1>;
-    constexpr int kMaxT = 256;
-    if (depth < 1 || depth > sk::kLifeStreamMaxDepth) return hipErrorInvalidValue;
-    const int CR = s->cr;   // rows per segment
-    unsigned blocks;
-    size_t lds;
-    auto a = make_args<sk::OpLife, Halo, 0, 16>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
-    const int strip_cols = sk::life_stream_cols(depth, WORDS);
-    a.tiles_c = (int)((s->cols + strip_cols - 1) / strip_cols);
-    a.n_tiles = (int)((s->rows + CR - 1) / CR) * a.tiles_c;
-    a.xcd_chunk = 0;
-    const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
-    blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
-    const dim3 grid(blocks), block(wc, wr);
-    const bool whole = s->cols % (4 * WORDS) == 0;      // rows of whole vectors, or the cell-by-cell body
-#define LIFE_STREAM_LAUNCH(D)                                                                                  \
-    if (whole)                                                                                                 \
-        hipLaunchKernelGGL((sk::life_stream_kernel<B, D, WORDS, true, kMaxT>), grid, block, 0, stream, a, CR); \
-    else                                                                                                       \
-        hipLaunchKernelGGL((sk::life_stream_kernel<B, D, WORDS, false, kMaxT>), grid, block, 0, stream, a, CR);\
-    break
-    switch (depth) {
-    case 1: LIFE_STREAM_LAUNCH(1);
-    case 2: LIFE_STREAM_LAUNCH(2);
-    case 3: LIFE_STREAM_LAUNCH(3);
-    case 4: LIFE_STREAM_LAUNCH(4);
-    case 5: LIFE_STREAM_LAUNCH(5);
-    case 6: LIFE_STREAM_LAUNCH(6);
-    case 7: LIFE_STREAM_LAUNCH(7);
-    case 8: LIFE_STREAM_LAUNCH(8);
-    default: return hipErrorInvalidValue;
+// The tile of a Life launch (life_stream_kernel.h): rows per work-item and lanes per row.  A generation takes as
+// long as the wavefronts of a SIMD take for their rows and for what a generation costs whatever their number (about
+// kOverheadRows rows' worth), one wavefront's time at least; narrow tiles also load and store shorter pieces of
+// rows, which costs a launch up to a quarter.  (us per launch of 8 generations with 256 work-items, rows per item x
+// lanes: 4096 x 4096 4x16 9.8, 8x16 10.3, 8x32 9.8, 8x64 11.2, 16x16 11.0, 16x32 10.4, 16x64 11.1; 256 x 256 4x16
+// 4.6, 4x32 4.8, 8x32 6.2, 16x32 8.2.  12 rows per item cost more than 16 on either.)  A launch that reads bytes
+// has 32 registers per row under way: 16 rows leave room for two wavefronts per SIMD, too few to keep the memory
+// busy (8192 x 8192, one generation: 8x32 23.3, 16x32 27.0).
+struct LifeTile {
+    int rows_per_item = 0, group_shift = 0;
+    int tile_rows = 0;       // rows a tile writes
+};
+LifeTile life_tile(int64_t rows, int64_t words, int threads, int depth, bool from_bytes) {
+    constexpr int kOverheadRows = 2;
+    const double simds = 4.0 * stencil_compute_units();
+    LifeTile best;
+    double best_cost = 0.0;
+    for (int shift = 4; shift <= 6; ++shift)
+        for (int rpt = 4; rpt <= 16; rpt *= 2) {
+            const int tile_rows = (threads >> shift) * rpt - 2 * depth;
+            if (tile_rows <= 0) continue;
+            const int64_t strips = (words + (1 << shift) - 3) / ((1 << shift) - 2);
+            const double waves = (double)strips * (double)((rows + tile_rows - 1) / tile_rows) * (threads / 64);
+            const double cost = std::max(1.0, waves / simds) * (rpt + kOverheadRows) *
+                                (shift == 4 ? 1.25 : shift == 5 ? 1.05 : 1.0) * (from_bytes && rpt == 16 ? 1.3 : 1.0);
+            if (best.tile_rows == 0 || cost < best_cost) {
+                best.rows_per_item = rpt;
+                best.group_shift = shift;
+                best.tile_rows = tile_rows;
+                best_cost = cost;
+            }
+        }
+    return best;
+}
+
+// Game of Life, `depth` generations per launch in registers, from and to a matrix of bytes or of bits.
+template <int B, bool IN_BITS, bool OUT_BITS>
+hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *out, int wr, int wc, int depth,
+                                      hipStream_t stream) {
+    sk::LifeStreamArgs a;
+    a.in = in;
+    a.out = out;
+    a.rows = (int)s->rows;
+    a.cols = (int)s->cols;
+    a.words = (int)life_words(s);
+    const LifeTile t = life_tile(s->rows, a.words, wr * wc, depth, !IN_BITS);
+    if (t.tile_rows == 0) return hipErrorInvalidValue;
+    a.group_shift = t.group_shift;
+    a.tiles_c = (a.words + (1 << t.group_shift) - 3) / ((1 << t.group_shift) - 2);
+    a.n_tiles = a.tiles_c * (int)((s->rows + t.tile_rows - 1) / t.tile_rows);
+    a.pad = s->pad != 0.0;
+    a.nt_store = s->nt_store;
+    const dim3 grid((unsigned)a.n_tiles), block(wc, wr);
+    switch (t.rows_per_item) {
+    case 4: hipLaunchKernelGGL((sk::life_stream_kernel<B, 4, IN_BITS, OUT_BITS>), grid, block, 0, stream, a, depth); break;
+    case 8: hipLaunchKernelGGL((sk::life_stream_kernel<B, 8, IN_BITS, OUT_BITS>), grid, block, 0, stream, a, depth); break;
+    default: hipLaunchKernelGGL((sk::life_stream_kernel<B, 16, IN_BITS, OUT_BITS>), grid, block, 0, stream, a, depth); break;
     }
-#undef LIFE_STREAM_LAUNCH
     return hipGetLastError();
+}
+template <int B>
+hipError_t launch_life_stream(const stencil *s, const void *in, void *out, int wr, int wc, int depth, hipStream_t stream) {
+    if (depth < 1 || depth > sk::kLifeStreamMaxDepth) return hipErrorInvalidValue;
+    return launch_life_stream_formats<B, false, false>(s, in, out, wr, wc, depth, stream);
+}
+template <int B>
+hipError_t launch_life_stream_packed(const stencil *s, const void *in, bool in_bits, void *out, bool out_bits, int wr, int wc,
+                                     int depth, hipStream_t stream) {
+    if (depth < 1 || depth > sk::kLifeStreamMaxDepth) return hipErrorInvalidValue;
+    if (in_bits && out_bits) return launch_life_stream_formats<B, true, true>(s, in, out, wr, wc, depth, stream);
+    if (in_bits) return launch_life_stream_formats<B, true, false>(s, in, out, wr, wc, depth, stream);
+    if (out_bits) return launch_life_stream_formats<B, false, true>(s, in, out, wr, wc, depth, stream);
+    return launch_life_stream_formats<B, false, false>(s, in, out, wr, wc, depth, stream);
 }
 
 // The threshold stencil: float in, bytes out, no border region (pointwise_kernel.h).
@@ -403,20 +445,8 @@ const void *kernel_stream(const stencil *s) {
     default: return nullptr;
     }
 }
-template <int B, int WORDS>
-const void *kernel_life_stream(const stencil *s) {
-    switch (s->temporal_depth) {
-    case 1: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 1, WORDS, true, 256>);
-    case 2: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 2, WORDS, true, 256>);
-    case 3: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 3, WORDS, true, 256>);
-    case 4: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 4, WORDS, true, 256>);
-    case 5: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 5, WORDS, true, 256>);
-    case 6: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 6, WORDS, true, 256>);
-    case 7: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 7, WORDS, true, 256>);
-    case 8: return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 8, WORDS, true, 256>);
-    default: return nullptr;
-    }
-}
+template <int B>
+const void *kernel_life_stream(const stencil *) { return reinterpret_cast<const void *>(&sk::life_stream_kernel<B, 16, false, false>); }
 
 // Per-kernel workgroup-size limit (Section 3.1: the registers a kernel needs bound its
 // maximum workgroup size).  The heavily blocked variants are compiled for 256 work-items so
@@ -526,27 +556,27 @@ void reg_stream(std::vector<Variant> &r) {
     reg_stream_one<Op, KID, sk::kConstant>(r);
 }
 
-template <int B, int WORDS>
-void reg_life_stream_one(std::vector<Variant> &r) {
+template <int B>
+void reg_life_stream_one(std::vector<Variant> &r, int cells) {
     Variant v;
     v.staging = STENCIL_STAGING_STREAM;
     v.kernel = STENCIL_LIFE;
     v.border = B;
     v.hn = v.hs = v.he = v.hw = 1;
     v.cr = 0;
-    v.cc = 4 * WORDS;
-    v.max_threads = 256;
+    v.cc = cells;
+    v.max_threads = sk::kLifeStreamMaxThreads;
     v.staged_bytes = 0;
     v.fuses = true;
-    v.launch = &launch_life_stream<B, WORDS>;
-    v.kernel_of = &kernel_life_stream<B, WORDS>;
+    v.launch = &launch_life_stream<B>;
+    v.launch_packed = &launch_life_stream_packed<B>;
+    v.kernel_of = &kernel_life_stream<B>;
     r.push_back(v);
 }
 
-template <int WORDS>
-void reg_life_stream(std::vector<Variant> &r) {
-    reg_life_stream_one<sk::kWrap, WORDS>(r);
-    reg_life_stream_one<sk::kConstant, WORDS>(r);
+inline void reg_life_stream(std::vector<Variant> &r, int cells) {
+    reg_life_stream_one<sk::kWrap>(r, cells);
+    reg_life_stream_one<sk::kConstant>(r, cells);
 }
 
 template <int B, int CR, int CC>

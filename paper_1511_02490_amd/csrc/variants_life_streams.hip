@@ -2,7 +2,7 @@
 #include "variants.h"
 
 void register_life_streams(std::vector<Variant> &r) {
-    reg_life_stream<1>(r);
-    reg_life_stream<2>(r);
-    reg_life_stream<4>(r);
+    reg_life_stream(r, 4);
+    reg_life_stream(r, 8);
+    reg_life_stream(r, 16);
 }

@@ -41,8 +41,8 @@ _COMMON = ["stencil_ops.h", "tile_kernel.h", "variants.h"]
 FAMILY_SOURCES = {
     "tile": _COMMON,
     "direct": _COMMON + ["direct_kernel.h"],
-    "temporal": _COMMON + ["temporal_kernel.h"],
-    "stream": _COMMON + ["stream_kernel.h", "life_stream_kernel.h"],
+    "temporal": _COMMON + ["temporal_kernel.h", "life_bits.h"],
+    "stream": _COMMON + ["stream_kernel.h", "life_stream_kernel.h", "life_bits.h"],
     "march": _COMMON + ["march_kernel.h", "march_masked_kernel.h"],
 }
 

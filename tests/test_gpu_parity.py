@@ -573,6 +573,17 @@ def test_register_marching_single_application_kernels(ls, border):
 
 
 @pytest.mark.parametrize("border", ["wrap", "constant"])
+@pytest.mark.parametrize("cols", [7, 8, 17, 31, 32, 33, 63, 64, 65, 447, 449])
+def test_life_between_launches_in_bits(ls, border, cols):
+    """Runs of one, two and several launches: rows too short for packed matrices, rows that end anywhere in a word
+    (where a wrapped word is put together from three), tiles of one strip and of two, a last tile of a few rows."""
+    for rows, wg in [(1, (1, 64)), (49, (4, 64)), (130, (2, 64))]:
+        for depth, iters in [(8, 5), (8, 19), (3, 6)]:
+            w = custom(wl.LIFE, rows, cols, (1, 1, 1, 1), border, pad=1.0, seed=rows * cols, iters=iters)
+            check(ls, w, wg, blocking=("stream", 16, 8, depth), offset=cols % 3)
+
+
+@pytest.mark.parametrize("border", ["wrap", "constant"])
 def test_register_streaming_life_bit_exact(ls, border):
     """Generations kept in registers, 4 / 8 / 16 cells per lane: matrices wider than one strip, ragged
     ones (cell-by-cell loads), ones smaller than a strip, live padding, unaligned rows."""
