@@ -85,18 +85,25 @@ __global__ __launch_bounds__(256) void copy_kernel(const uint4 *__restrict__ in,
 
 // A weight table travels to the device inside kernel arguments, 512 floats per launch: ordered on
 // the caller's stream like the stencil launches that read it, no staging buffer, no allocation.
-struct TableChunk { float v[512]; };
-__global__ __launch_bounds__(512) void table_upload_kernel(float *dst, const TableChunk c, int offset, int n) {
+// Its entries are 32-bit words: the weights, for an I32 matrix as integers.
+struct TableChunk { uint32_t v[512]; };
+__global__ __launch_bounds__(512) void table_upload_kernel(uint32_t *dst, const TableChunk c, int offset, int n) {
     const int i = (int)threadIdx.x;
     if (i < n) dst[offset + i] = c.v[i];
 }
 
-hipError_t upload_table(float *dst, const std::vector<float> &w, hipStream_t stream) {
+hipError_t upload_table(void *dst, const stencil *s, hipStream_t stream) {
+    const std::vector<float> &w = s->weights;
     for (size_t at = 0; at < w.size(); at += 512) {
         TableChunk c;
         const int n = (int)std::min<size_t>(512, w.size() - at);
-        std::memcpy(c.v, w.data() + at, (size_t)n * sizeof(float));
-        hipLaunchKernelGGL(table_upload_kernel, dim3(1), dim3(512), 0, stream, dst, c, (int)at, n);
+        for (int k = 0; k < n; ++k) {
+            if (s->dtype == STENCIL_I32)
+                c.v[k] = (uint32_t)(int32_t)w[at + k];
+            else
+                std::memcpy(&c.v[k], &w[at + k], 4);
+        }
+        hipLaunchKernelGGL(table_upload_kernel, dim3(1), dim3(512), 0, stream, static_cast<uint32_t *>(dst), c, (int)at, n);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -230,10 +237,10 @@ int ensure_device_state(stencil *s, const Variant *v, bool need_scratch, hipStre
         // run's stream: earlier launches (on any stream) keep reading the table they were given.
         const int slot = s->d_weights == s->d_tables[0] && s->d_tables[0] ? 1 : 0;
         if (!s->d_tables[slot]) {
-            hipError_t e = hipMalloc((void **)&s->d_tables[slot], kStaticTableBytes);
+            hipError_t e = hipMalloc(&s->d_tables[slot], kStaticTableBytes);
             if (e != hipSuccess) return fail(STENCIL_E_RESOURCES, "hipMalloc(weights): %s", hipGetErrorString(e));
         }
-        hipError_t e = upload_table(s->d_tables[slot], s->weights, stream);
+        hipError_t e = upload_table(s->d_tables[slot], s, stream);
         if (e != hipSuccess) return fail_hip(e, "weight table upload");
         s->d_weights = s->d_tables[slot];
         s->weights_uploaded = true;
@@ -475,7 +482,7 @@ void stencil_destroy(stencil_t *s) {
     if (!s) return;
     for (hipEvent_t e : s->events) (void)hipEventDestroy(e);
     if (s->scratch) (void)hipFree(s->scratch);
-    for (float *t : s->d_tables)
+    for (void *t : s->d_tables)
         if (t) (void)hipFree(t);
     delete s;
 }
@@ -716,12 +723,12 @@ int stencil_run_static(stencil_t *s, const void *in, void *out, int iters, int w
     rc = static_scratch(&buf);
     if (rc != STENCIL_OK) return rc;
     hipStream_t stream = (hipStream_t)stream_;
-    float *table = reinterpret_cast<float *>(buf);
+    void *table = buf;
     void *matrix = buf + kStaticTableBytes;
     if (needs_table) {
         // the buffer keeps whatever the last call (of any handle) left: this run's table goes in
         // first, ordered on the stream before the launches that read it
-        hipError_t e = upload_table(table, s->weights, stream);
+        hipError_t e = upload_table(table, s, stream);
         if (e != hipSuccess) return fail_hip(e, "weight table upload");
     }
     // every launch writes its whole destination matrix before the next reads it: nothing to clear

@@ -58,9 +58,9 @@ struct stencil {
     int predictor_handler = 0;
     // device-side state, created on first use
     void *scratch = nullptr;
-    float *d_tables[2] = {nullptr, nullptr};   // weight tables of a run-time region; a replaced table goes into the other one
-    float *d_weights = nullptr;                // the current one of the two
-    const float *table_in_use = nullptr;       // what the launchers hand to the kernels
+    void *d_tables[2] = {nullptr, nullptr};    // weight tables of a run-time region; a replaced table goes into the other one
+    void *d_weights = nullptr;                 // the current one of the two
+    const void *table_in_use = nullptr;        // what the launchers hand to the kernels
     bool weights_uploaded = false;
     std::vector<hipEvent_t> events;
     // matrix pairs the sweeps' applications go round (stencil_set_sweep_rotation); empty: the caller's pair

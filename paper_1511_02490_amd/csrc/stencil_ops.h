@@ -42,8 +42,10 @@ struct HaloC {
     __host__ __device__ constexpr int e() const { return E_; }
     __host__ __device__ constexpr int w() const { return W_; }
 };
-// ... or one only known at launch.
+// ... or one only known at launch: of up to kCompiledColumns columns ...
+constexpr int kCompiledColumns = 9;
 struct HaloD {
+    static constexpr bool kWide = false;
     static constexpr bool kStatic = false;
     static constexpr bool kMasked = false;
     static constexpr int N = 0, S = 0, E = 0, W = 0;
@@ -52,6 +54,11 @@ struct HaloD {
     __host__ __device__ int s() const { return s_; }
     __host__ __device__ int e() const { return e_; }
     __host__ __device__ int w() const { return w_; }
+};
+
+// ... or of more (a kernel of its own, or the registers of either fold would limit the wavefronts of both).
+struct HaloWide : HaloD {
+    static constexpr bool kWide = true;
 };
 
 // ---- weighted sum ("gaussian" of Table 2): fp32 fma chain ---------------------------------
@@ -103,6 +110,8 @@ struct OpWeightedSumF64 {
     __device__ static __forceinline__ T finish(const State &s, float) { return s.acc; }
 };
 
+// (The products stay 32 bits wide: on gfx950 a 24-bit multiply-add takes the vector unit as long as a 32-bit
+// product, so that two of them on a cell's halves cost more than one product and its sum.)
 struct OpWeightedSumI32 {
     static constexpr bool kRowFold = false;
     using T = int32_t;
@@ -110,6 +119,7 @@ struct OpWeightedSumI32 {
     using V = int32_t;
     static constexpr int kPlanes = 1;
     static constexpr bool kWeights = true;
+    using Wt = int32_t;
     struct State { uint32_t acc; };
     __device__ static __forceinline__ void stage(T v, L (&out)[1]) { out[0] = v; }
     __device__ static __forceinline__ V combine(const L (&p)[1]) { return p[0]; }
@@ -119,8 +129,8 @@ struct OpWeightedSumI32 {
         for (int k = 0; k < CC; ++k) out[0][k] = v[k];
     }
     __device__ static __forceinline__ void init(State &s) { s.acc = 0u; }
-    __device__ static __forceinline__ void visit(State &s, int, int, float w, V v) {
-        s.acc += (uint32_t)(int32_t)w * (uint32_t)v;      // modulo 2^32
+    __device__ static __forceinline__ void visit(State &s, int, int, int32_t w, V v) {
+        s.acc += (uint32_t)w * (uint32_t)v;      // modulo 2^32
     }
     __device__ static __forceinline__ T finish(const State &s, float) { return (T)s.acc; }
 };
@@ -155,7 +165,8 @@ struct OpWeightedSumU8 {
 
 // The type in which a compile-time weight table travels in the kernel arguments: Op::Wt where the
 // function names one (doubles for the fp64 sum: a scalar register pair is an operand of the fp64
-// fma, a float would first have to be converted into a pair of vector registers), else float.
+// fma, a float would first have to be converted into a pair of vector registers; integers for the
+// int32 sum), else float.  A run-time region's table is one of 32-bit words: that type, or floats.
 template <class Op, class = void>
 struct weight_type_of { using type = float; };
 template <class Op>

@@ -10,6 +10,8 @@
 #pragma once
 #include "stencil_ops.h"
 
+#include <type_traits>
+
 namespace sk {
 
 template <class Op, class Halo, bool Static = Halo::kStatic>
@@ -25,8 +27,27 @@ struct WeightStore<Op, Halo, true> {
 // Run-time region: table in device memory (uniform index -> scalar loads).
 template <class Op, class Halo>
 struct WeightStore<Op, Halo, false> {
-    const float *v;
-    __device__ __forceinline__ float operator[](int k) const { return Op::kWeights ? v[k] : 0.0f; }
+    using Wt = typename weight_type_of<Op>::type;
+    using W = typename std::conditional<sizeof(Wt) == 4, Wt, float>::type;
+    const W *v;
+    __device__ __forceinline__ W operator[](int k) const { return Op::kWeights ? v[k] : W(0); }
+    // Entries k .. k + CNT - 1, k the same in all lanes, as scalar loads of up to four.  (Nothing writes a table while a
+    // kernel reads it, which the constant address space says; scalar loads want no more than 4-byte alignment.)
+    template <int CNT>
+    __device__ __forceinline__ void load(W (&dst)[CNT], unsigned k) const {
+        typedef W four __attribute__((ext_vector_type(4), aligned(4)));
+        const __attribute__((address_space(4))) W *p = (const __attribute__((address_space(4))) W *)(v + k);
+#pragma unroll
+        for (int i = 0; i < CNT; i += 4) {
+            if (i + 4 <= CNT) {
+                const four t = *(const __attribute__((address_space(4))) four *)(p + i);
+                dst[i] = t.x, dst[i + 1] = t.y, dst[i + 2] = t.z, dst[i + 3] = t.w;
+            } else {
+#pragma unroll
+                for (int j = i; j < CNT; ++j) dst[j] = p[j];
+            }
+        }
+    }
 };
 
 template <class Op, class Halo>
@@ -269,6 +290,247 @@ __device__ __forceinline__ void stage_tile(typename Op::L *tile, int plane, int 
     }
 }
 
+// ---- the fold over a run-time region ------------------------------------------------------------------
+// A window row is read from local memory once, for all the cell rows of a work-item that it touches: window row wi
+// is region row wi - cr of cell row cr.  What a row (or a chunk of one) needs is requested while the one before it is
+// folded, and waited for before the next requests go out: scalar loads return out of order, so a wait for a vector
+// from local memory waits for every weight under way as well, and one that was requested in between would be waited
+// for at once.
+__device__ __forceinline__ void wait_for_lds_and_scalars() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);          // lgkmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Regions of WC columns, compiled: a row is straight-line code, WC weights per region row in scalar registers.
+// (Bound by arithmetic and by what of staging and storing it does not cover.  Before, every tap was a branch and waited
+// for its own weight, and every cell row read its own window: 9 columns x 7 rows on 7135 x 456 floats 22.6 -> 13.1 us,
+// 6 x 6 int32 on 2500 x 3003 32.0 -> 22.5 us, sin/cos over 7 x 4 on 3344 x 6704 152 -> 81 us.)
+template <class Op, class Halo, int CR, int CC, int WC>
+__device__ __forceinline__ void fold_columns(typename Op::State (&st)[CR][CC], const TileArgs<Op, Halo> &a,
+                                             const typename Op::L *window, int hn, int hw, int wrows) {
+    using L = typename Op::L;
+    using Wt = typename WeightStore<Op, Halo>::W;
+    constexpr int NP = Op::kPlanes;
+    constexpr int kColumns = round_up(WC - 1 + CC, CC);              // window columns read, whole vectors
+    constexpr bool kAhead = NP == 1;         // two planes of two rows do not fit the registers
+    // weights of the last CR region rows kept, as far as scalar registers go and the moves from row to row pay
+    constexpr bool kRing = CR * WC <= 40 && !(CR == 4 && WC <= 4);
+    const int window_rows = CR - 1 + wrows;
+    struct Row {
+        L v[NP][kColumns];
+        Wt w[WC];                            // of region row wi, the first cell row's
+    };
+    auto load_row = [&](Row &r, int wi) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) load_vec(r.v[p], window + p * a.plane + wi * a.pitch);
+        if constexpr (kRing) a.w.load(r.w, (unsigned)(min(wi, wrows - 1) * WC));
+    };
+    Wt older[CR][WC];                        // ... of region row wi - cr, the cr-th's
+    auto step = [&](Row &cur, Row &ahead, int wi) {
+        if constexpr (kAhead) {
+            wait_for_lds_and_scalars();
+            if (wi + 1 < window_rows) load_row(ahead, wi + 1);
+        } else {
+            load_row(cur, wi);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int cr = 0; cr < CR; ++cr) {
+            const int k = wi - cr;
+            if ((unsigned)k >= (unsigned)wrows) continue;
+            [[maybe_unused]] typename row_state_of<Op>::type rs[CC] = {};
+            Wt own[WC];
+            if constexpr (!kRing) a.w.load(own, (unsigned)(k * WC));
+#pragma unroll
+            for (int kk = 0; kk < WC; ++kk) {
+                const Wt w = !kRing ? own[kk] : cr == 0 ? cur.w[kk] : older[cr][kk];
+#pragma unroll
+                for (int cc = 0; cc < CC; ++cc) {
+                    L parts[NP];
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) parts[p] = cur.v[p][kk + cc];
+                    if constexpr (Op::kRowFold)
+                        Op::row_visit(st[cr][cc], rs[cc], kk, w, Op::combine(parts));
+                    else
+                        Op::visit(st[cr][cc], k - hn, kk - hw, w, Op::combine(parts));
+                }
+            }
+            if constexpr (Op::kRowFold) {
+#pragma unroll
+                for (int cc = 0; cc < CC; ++cc) Op::row_end(st[cr][cc], rs[cc], WC, k, wrows);
+            }
+        }
+        if constexpr (kRing) {
+#pragma unroll
+            for (int cr = CR - 1; cr > 0; --cr)
+#pragma unroll
+                for (int kk = 0; kk < WC; ++kk) older[cr][kk] = cr == 1 ? cur.w[kk] : older[cr - 1][kk];
+        }
+    };
+    Row even, odd;
+    if constexpr (kAhead) load_row(even, 0);
+#pragma unroll
+    for (int cr = 0; cr < CR; ++cr)
+#pragma unroll
+        for (int kk = 0; kk < WC; ++kk) older[cr][kk] = Wt(0);
+    for (int wi = 0; wi < window_rows; wi += kAhead ? 2 : 1) {
+        step(even, odd, wi);
+        if constexpr (kAhead)
+            if (wi + 1 < window_rows) step(odd, even, wi + 1);
+    }
+}
+
+// Any number of columns (compiling each up to the largest, 65, would not pay), BW at a time: the same for a block of
+// columns of a row, the last of which may have fewer.
+template <class Op, class Halo, int CR, int CC>
+__device__ __forceinline__ void fold_blocks(typename Op::State (&st)[CR][CC], const TileArgs<Op, Halo> &a,
+                                            const typename Op::L *window, int hn, int hw, int wrows, int wcols) {
+    using L = typename Op::L;
+    using Wt = typename WeightStore<Op, Halo>::W;
+    constexpr int NP = Op::kPlanes;
+    constexpr int BW = 8, VL = 16 / (int)sizeof(L);
+    constexpr int kColumns = round_up(BW - 1 + CC, VL);
+    constexpr bool kAhead = NP == 1;         // (two planes: see fold_columns)
+    const int window_rows = CR - 1 + wrows;
+    struct Block {
+        L v[NP][kColumns];
+        Wt w[CR][BW];                        // of region row wi - cr (of any row where there is none)
+    };
+    // (The weights beyond a row's last column are read, where the table has room, and not used; the cells beyond the
+    // last one needed are not read.)
+    auto load_block = [&](Block &r, int wi, int kk) {
+        const int need = min(BW, wcols - kk) - 1 + CC;
+#pragma unroll
+        for (int i = 0; i < kColumns; i += VL) {
+            if (i >= need) break;
+#pragma unroll
+            for (int p = 0; p < NP; ++p) {
+                L part[VL];
+                load_vec(part, window + p * a.plane + wi * a.pitch + kk + i);
+#pragma unroll
+                for (int k = 0; k < VL; ++k) r.v[p][i + k] = part[k];
+            }
+        }
+        if constexpr (kAhead) {
+#pragma unroll
+            for (int cr = 0; cr < CR; ++cr) a.w.load(r.w[cr], (unsigned)(max(0, min(wi - cr, wrows - 1)) * wcols + kk));
+        }
+    };
+    [[maybe_unused]] typename row_state_of<Op>::type rs[CR][CC] = {};
+    int wi = 0, kk0 = 0;                     // the block at hand: window row, first column
+    auto step = [&](Block &cur, Block &ahead) {
+        const bool in_row = kk0 + BW < wcols;
+        const int wi1 = in_row ? wi : wi + 1, kk1 = in_row ? kk0 + BW : 0;
+        if constexpr (kAhead) {
+            wait_for_lds_and_scalars();
+            if (wi1 < window_rows) load_block(ahead, wi1, kk1);
+        } else {
+            load_block(cur, wi, kk0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int cr = 0; cr < CR; ++cr) {
+            const int k = wi - cr;
+            if ((unsigned)k >= (unsigned)wrows) continue;
+            Wt own[BW];
+            if constexpr (!kAhead) a.w.load(own, (unsigned)(k * wcols + kk0));
+            auto taps = [&](int n_taps) {
+#pragma unroll
+                for (int t = 0; t < BW; ++t) {
+                    if (t >= n_taps) break;
+                    const Wt w = kAhead ? cur.w[cr][t] : own[t];
+#pragma unroll
+                    for (int cc = 0; cc < CC; ++cc) {
+                        L parts[NP];
+#pragma unroll
+                        for (int p = 0; p < NP; ++p) parts[p] = cur.v[p][t + cc];
+                        if constexpr (Op::kRowFold)
+                            Op::row_visit(st[cr][cc], rs[cr][cc], kk0 + t, w, Op::combine(parts));
+                        else
+                            Op::visit(st[cr][cc], k - hn, kk0 + t - hw, w, Op::combine(parts));
+                    }
+                }
+            };
+            if (kk0 + BW <= wcols)
+                taps(BW);
+            else
+                taps(wcols - kk0);
+            if constexpr (Op::kRowFold) {
+                if (!in_row) {
+#pragma unroll
+                    for (int cc = 0; cc < CC; ++cc) Op::row_end(st[cr][cc], rs[cr][cc], wcols, k, wrows);
+                }
+            }
+        }
+        wi = wi1;
+        kk0 = kk1;
+    };
+    Block even, odd;
+    if constexpr (kAhead) load_block(even, 0, 0);
+    while (wi < window_rows) {
+        step(even, odd);
+        if constexpr (kAhead) {
+            if (wi >= window_rows) break;
+            step(odd, even);
+        }
+    }
+}
+
+// The same tap by tap, every cell row with its own window: the cells of a row need window columns kk .. kk + CC - 1 for
+// tap kk, i.e. two aligned vectors per chunk of CC taps, of which one is the previous chunk's.  Work-items of four and more
+// rows have the arithmetic between two weights to cover the wait for the next, and no registers for more
+// (17 x 17 on 2500 x 3000 floats, four rows: 91 us, 8 columns at a time 105; eight rows: 99 and 132).
+template <class Op, class Halo, int CR, int CC>
+__device__ __forceinline__ void fold_taps(typename Op::State (&st)[CR][CC], const TileArgs<Op, Halo> &a,
+                                          const typename Op::L *window, int hn, int hw, int wrows, int wcols) {
+    using L = typename Op::L;
+    constexpr int NP = Op::kPlanes;
+    for (int i = 0; i < wrows; ++i) {
+        [[maybe_unused]] typename row_state_of<Op>::type rs[CR][CC] = {};
+        L va[CR][NP][CC], vb[CR][NP][CC];
+        auto load_chunk = [&](L (&v)[CR][NP][CC], int j) {
+#pragma unroll
+            for (int cr = 0; cr < CR; ++cr)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) load_vec(v[cr][p], window + p * a.plane + (i + cr) * a.pitch + CC * j);
+        };
+        // taps CC * j .. CC * j + CC - 1: `lo` holds window columns CC * j .., `hi` the next CC
+        auto chunk = [&](const L (&lo)[CR][NP][CC], L (&hi)[CR][NP][CC], int j) {
+            if (CC * j + 1 < wcols) load_chunk(hi, j + 1);
+#pragma unroll
+            for (int t = 0; t < CC; ++t) {
+                const int kk = CC * j + t;
+                if (kk >= wcols) continue;
+                const auto w = a.w[i * wcols + kk];
+#pragma unroll
+                for (int cr = 0; cr < CR; ++cr)
+#pragma unroll
+                    for (int cc = 0; cc < CC; ++cc) {
+                        L parts[NP];
+#pragma unroll
+                        for (int p = 0; p < NP; ++p)
+                            parts[p] = t + cc < CC ? lo[cr][p][(t + cc) % CC] : hi[cr][p][(t + cc) % CC];
+                        if constexpr (Op::kRowFold)
+                            Op::row_visit(st[cr][cc], rs[cr][cc], kk, w, Op::combine(parts));
+                        else
+                            Op::visit(st[cr][cc], i - hn, kk - hw, w, Op::combine(parts));
+                    }
+            }
+        };
+        load_chunk(va, 0);
+        for (int j = 0; CC * j < wcols; j += 2) {
+            chunk(va, vb, j);
+            if (CC * (j + 1) < wcols) chunk(vb, va, j + 1);
+        }
+        if constexpr (Op::kRowFold) {
+#pragma unroll
+            for (int cr = 0; cr < CR; ++cr)
+#pragma unroll
+                for (int cc = 0; cc < CC; ++cc) Op::row_end(st[cr][cc], rs[cr][cc], wcols, i, wrows);
+        }
+    }
+}
+
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) {
     using O = typename out_type_of<Op>::type;
@@ -289,7 +551,9 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
     const int hn = h.n(), hs = h.s(), he = h.e(), hw = h.w();
     const int th = wr * CR, tw = wc * CC;
     const int r0 = tile_r * th, c0 = tile_c * tw;
-    const int hwa = staged_halo<CC>(hw);
+    // columns staged west of the tile: under a run-time region exactly the region's (the fold wants the region's
+    // west edge at a vector's start), else whole vectors
+    const int hwa = Halo::kStatic ? staged_halo<CC>(hw) : hw;
     const int pitch = a.pitch;
     const int rows = a.rows, cols = a.cols;
     // the whole tile height is staged, also where the last tile hangs over the matrix edge (those
@@ -354,60 +618,33 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
         // tap's weight (a uniform, scalar load) is fetched once for all of them; every cell still
         // sees its taps in row-major order.
         const int wcols = he + hw + 1, wrows = hn + hs + 1;
-        constexpr bool kVec = CC > 1 && (sizeof(L) * CC) % 16 == 0;
-        if constexpr (kVec) {
-            // Columns are counted from the staged tile's aligned west edge (column kk of the window
-            // of cell (cr, 0) is dc = kk - hwa) and taken CC at a time: the cells of a row need
-            // window columns kk .. kk + CC - 1 for tap kk, i.e. two aligned vectors per chunk, of
-            // which one is the previous chunk's.  Taps outside [k_lo, k_hi] are not in the region.
-            const int k_lo = hwa - hw, k_hi = hwa + he;
-            const L *west[CR];
-#pragma unroll
-            for (int cr = 0; cr < CR; ++cr) west[cr] = tile + (lr0 + cr) * pitch + lc0;
-            for (int i = 0; i < wrows; ++i) {
-                const int dr = i - hn;
-                [[maybe_unused]] typename row_state_of<Op>::type rs[CR][CC] = {};
-                L va[CR][NP][CC], vb[CR][NP][CC];
-                auto load_chunk = [&](L (&v)[CR][NP][CC], int j) {
-#pragma unroll
-                    for (int cr = 0; cr < CR; ++cr)
-#pragma unroll
-                        for (int p = 0; p < NP; ++p) load_vec(v[cr][p], west[cr] + p * a.plane + i * pitch + CC * j);
-                };
-                // taps CC * j .. CC * j + CC - 1: `lo` holds window columns CC * j .., `hi` the next CC
-                auto chunk = [&](const L (&lo)[CR][NP][CC], L (&hi)[CR][NP][CC], int j) {
-                    if (CC * j + 1 <= k_hi) load_chunk(hi, j + 1);
-#pragma unroll
-                    for (int t = 0; t < CC; ++t) {
-                        const int kk = CC * j + t;
-                        if (kk < k_lo || kk > k_hi) continue;
-                        const auto w = a.w[i * wcols + kk - k_lo];
-#pragma unroll
-                        for (int cr = 0; cr < CR; ++cr)
-#pragma unroll
-                            for (int cc = 0; cc < CC; ++cc) {
-                                L parts[NP];
-#pragma unroll
-                                for (int p = 0; p < NP; ++p)
-                                    parts[p] = t + cc < CC ? lo[cr][p][(t + cc) % CC] : hi[cr][p][(t + cc) % CC];
-                                if constexpr (Op::kRowFold)
-                                    Op::row_visit(st[cr][cc], rs[cr][cc], kk - k_lo, w, Op::combine(parts));
-                                else
-                                    Op::visit(st[cr][cc], dr, kk - hwa, w, Op::combine(parts));
-                            }
-                    }
-                };
-                int j = k_lo / CC;
-                load_chunk(va, j);
-                for (; CC * j <= k_hi; j += 2) {
-                    chunk(va, vb, j);
-                    if (CC * (j + 1) <= k_hi) chunk(vb, va, j + 1);
-                }
-                if constexpr (Op::kRowFold) {
-#pragma unroll
-                    for (int cr = 0; cr < CR; ++cr)
-#pragma unroll
-                        for (int cc = 0; cc < CC; ++cc) Op::row_end(st[cr][cc], rs[cr][cc], wcols, i, wrows);
+        if constexpr (CC > 1) {
+            // The tile is staged from the region's west edge: tap kk of cell cc is window column kk + cc, and a
+            // work-item's window starts at a vector.
+            const L *const window = tile + lr0 * pitch + lc0;
+            // Up to the Gaussian of radius 4 the fold is compiled for the region's number of columns: straight-line rows
+            // against blocks of 8 columns with a shorter last one (2500 x 3000 floats, 2 x 4 cells: 7 x 8 taps 20.8 us
+            // compiled, 5 x 13 taps 31.1 in blocks, where the former took 38 either way).
+            if constexpr (Halo::kWide) {
+                if constexpr (CR >= (NP == 1 ? 4 : 8))
+                    fold_taps<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
+                else
+                    fold_blocks<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
+            } else {
+                static_assert(kCompiledColumns == 9, "a case each");
+                switch (wcols) {
+#define FOLD_COLUMNS(WC)                                                                                       \
+                case WC: fold_columns<Op, Halo, CR, CC, WC>(st, a, window, hn, hw, wrows); break
+                FOLD_COLUMNS(1);
+                FOLD_COLUMNS(2);
+                FOLD_COLUMNS(3);
+                FOLD_COLUMNS(4);
+                FOLD_COLUMNS(5);
+                FOLD_COLUMNS(6);
+                FOLD_COLUMNS(7);
+                FOLD_COLUMNS(8);
+                FOLD_COLUMNS(9);
+#undef FOLD_COLUMNS
                 }
             }
         } else {

@@ -104,9 +104,14 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
     a.n_tiles = g.tiles_r * g.tiles_c;
     a.pitch = g.pitch;
     a.plane = g.plane;
+    if (!Halo::kStatic && !Halo::kMasked) {
+        // the tile kernel stages a run-time region from its west edge (never more than the geometry allows for)
+        a.pitch = sk::round_up(s->hw + g.tw + s->he, CC);
+        a.plane = (g.th + s->hn + s->hs) * a.pitch;
+    }
     {
         // vectors (elements when CC = 1) per staged row; kernels that stage nothing have none
-        const unsigned items = std::max(1u, (unsigned)(g.pitch / CC));
+        const unsigned items = std::max(1u, (unsigned)(a.pitch / CC));
         a.stage_magic = (unsigned)((0x100000000ull + items - 1) / items);
     }
     a.nt_store = s->nt_store;
@@ -114,7 +119,7 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
     a.scalar0 = s->scalar0;
     if constexpr (Halo::kStatic) {
         if constexpr (Op::kWeights)
-            for (int k = 0; k < (int)(sizeof(a.w.v) / sizeof(a.w.v[0])); ++k) a.w.v[k] = s->weights[k];
+            for (int k = 0; k < (int)(sizeof(a.w.v) / sizeof(a.w.v[0])); ++k) a.w.v[k] = (typename decltype(a.w)::W)s->weights[k];
         else
             a.w.v[0] = 0.0f;
     } else {
@@ -122,7 +127,7 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
         a.halo.s_ = s->hs;
         a.halo.e_ = s->he;
         a.halo.w_ = s->hw;
-        a.w.v = s->table_in_use;
+        a.w.v = static_cast<decltype(a.w.v)>(s->table_in_use);
     }
     *blocks = (unsigned)a.n_tiles;
     a.xcd_chunk = 0;
@@ -376,6 +381,9 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
 
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
+    if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1)
+        if (s->he + s->hw + 1 > sk::kCompiledColumns)
+            return launch_tile<Op, B, sk::HaloWide, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
     unsigned blocks;
     size_t lds;
     const auto a = make_args<Op, Halo, CR, CC>(s, STENCIL_STAGING_LOCAL, in, out, wr, wc, &blocks, &lds);
@@ -409,7 +417,11 @@ hipError_t launch_life_direct(const stencil *s, const void *in, void *out, int w
 
 // The kernel behind each launcher (the variant for rows of whole vectors where there are two).
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
-const void *kernel_tile(const stencil *) { return reinterpret_cast<const void *>(&sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>); }
+const void *kernel_tile(const stencil *s) {
+    if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1)
+        if (s->he + s->hw + 1 > sk::kCompiledColumns) return kernel_tile<Op, B, sk::HaloWide, CR, CC, MAXT>(s);
+    return reinterpret_cast<const void *>(&sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>);
+}
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 const void *kernel_direct(const stencil *) { return reinterpret_cast<const void *>(&sk::direct_kernel<Op, B, Halo, CR, CC, MAXT>); }
 template <int B, int CR, int MAXT>

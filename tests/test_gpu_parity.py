@@ -397,6 +397,32 @@ def test_canny_chain_stage_by_stage(ls):
     assert x[25, 58:62].max() == 1 and x[25, 20:40].max() == 0
 
 
+@pytest.mark.parametrize("wcols", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 13, 17])
+def test_run_time_regions_by_number_of_columns(ls, wcols):
+    """The fold compiled for its number of columns and the one in chunks, under every blocking of the tile: regions all
+    east, all west and between, of one row and of several, and an infinite cell that only its neighbours may see."""
+    kernels = [wl.WEIGHTED_SUM, wl.SINCOS]
+    for k, (n, s, west) in enumerate([(0, 0, 0), (2, 3, wcols - 1), (3, 1, wcols // 2)]):
+        halo = (n, s, wcols - 1 - west, west)
+        for kernel in kernels:
+            w = custom(kernel, 37, 61, halo, ("clamp", "wrap", "constant")[k], pad=0.3, seed=wcols + k)
+            g = w.grid()
+            one = gpu_apply(ls, w, g, (4, 8), blocking=(1, 1))
+            # absolute error (a sum of sines and cosines passes near zero): each sine and cosine is within 2e-7, and
+            # each of 2 taps additions rounds a partial sum of at most 2 taps
+            taps = w.weights.size
+            ref = oracle.apply(g, w.kernel, w.halo, w.border, w.pad, w.weights, w.scalars, 1)
+            assert np.max(np.abs(one.astype(np.float64) - ref)) <= 4e-7 * taps + 2 * taps * 2.0 ** -24 * 2 * taps
+            for cr, wg in [(1, (4, 8)), (2, (8, 4)), (4, (3, 5)), (8, (2, 16))]:
+                np.testing.assert_array_equal(gpu_apply(ls, w, g, wg, blocking=(cr, 4), offset=cr % 2), one)
+        w = custom(wl.WEIGHTED_SUM, 37, 61, halo, "clamp", seed=wcols)
+        g = w.grid()
+        g[11, 23] = np.inf
+        ref = oracle.apply(g, w.kernel, w.halo, w.border, w.pad, w.weights, w.scalars, 1)
+        for cr in (2, 8):
+            np.testing.assert_array_equal(np.isinf(gpu_apply(ls, w, g, (4, 8), blocking=(cr, 4))), np.isinf(ref))
+
+
 # ---- temporal blocking: several applications per launch ------------------------------------
 
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
