@@ -60,13 +60,17 @@ struct TileArgs {
     int xcd_chunk;   // > 0: tiles are dealt to the 8 XCDs in contiguous chunks of this many
     int pitch;       // LDS tile pitch, in staged elements
     int plane;       // elements per LDS plane (tile rows x pitch)
-    unsigned stage_magic;   // ceil(2^32 / items per staged row): tid / items by one multiply
+    unsigned stage_magic;   // ceil(2^32 / items per staged row), modulo 2^32: see row_of_item
     int nt_store;    // vector stores of output cells are non-temporal
     typename Op::T pad;
     float scalar0;
     Halo halo;
     WeightStore<Op, Halo> w;
 };
+
+// item / items per row by one multiply.  A row of a single item (a workgroup one work-item wide, a region of one
+// column) has 2^32 for its multiplier, which arrives as 0: there every item is a row of its own.
+__device__ __forceinline__ unsigned row_of_item(unsigned item, unsigned magic) { return magic ? __umulhi(item, magic) : item; }
 
 __host__ __device__ constexpr int round_up(int x, int m) { return (x + m - 1) / m * m; }
 __host__ __device__ constexpr int round_down(int x, int m) { return x / m * m; }
@@ -175,7 +179,7 @@ __device__ __forceinline__ void stage_inside(typename Op::L *tile, int plane, in
     using L = typename Op::L;
     constexpr int NP = Op::kPlanes;
     constexpr int kBatch = 4;
-    const unsigned i0 = __umulhi((unsigned)tid, magic), di = __umulhi((unsigned)nthreads, magic);
+    const unsigned i0 = row_of_item(tid, magic), di = row_of_item(nthreads, magic);
     unsigned q = tid - i0 * n_items;
     const unsigned dq = nthreads - di * n_items;
     const unsigned row_bytes = (unsigned)cols * (unsigned)sizeof(T);
@@ -212,7 +216,7 @@ __device__ __forceinline__ void stage_inside(typename Op::L *tile, int plane, in
 // 16-byte vectors (single elements when CC = 1), work-item k taking items k, k + n, k + 2n, ...
 // so that the halo columns cost a fraction of a pass rather than a whole extra pass with most
 // lanes idle.  Vectors starting at or beyond matrix column `col_end` are not needed and skipped.
-// `magic` = ceil(2^32 / (pitch / CC)) turns the one division into a multiply.
+// `magic` belongs to pitch / CC items per row (row_of_item).
 template <class Op, int B, int CC>
 __device__ __forceinline__ void stage_tile(typename Op::L *tile, int plane, int pitch, const typename Op::T *in,
                                            int rows, int cols, int row_first, int col_first, int n_rows,
@@ -234,9 +238,9 @@ __device__ __forceinline__ void stage_tile(typename Op::L *tile, int plane, int 
             return;
         }
     }
-    int i = (int)__umulhi((unsigned)tid, magic);
+    int i = (int)row_of_item(tid, magic);
     int q = tid - i * n_items;
-    const int di = (int)__umulhi((unsigned)nthreads, magic), dq = nthreads - di * n_items;
+    const int di = (int)row_of_item(nthreads, magic), dq = nthreads - di * n_items;
     // Vectors are taken kBatch at a time: the loads of a batch are all issued before the first of
     // them is waited for and written to LDS, so a work-item with several items pays one memory
     // round trip per batch, not one per item.  (Single elements gain nothing from it.)

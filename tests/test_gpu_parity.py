@@ -254,6 +254,26 @@ def test_vectors_at_any_address(ls, border, cols):
             check(ls, w, (4, 2), blocking=("temporal", 2, cc, 3), offset=offset)
 
 
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("halo", [(2, 3, 0, 0), (0, 0, 0, 0), (1, 0, 0, 0)])
+def test_staged_rows_of_a_single_item(ls, border, halo):
+    """Workgroups one work-item wide under regions of one column: a staged row is one vector (or one cell), in tiles
+    at the matrix's edge and inside it."""
+    for cols in (1, 3, 24, 29):
+        w = custom(wl.WEIGHTED_SUM, 157, cols, halo, border, pad=0.5, seed=cols)
+        wd = wl.Workload("f64", 157, cols, "f64", halo, border, 0.5, wl.WEIGHTED_SUM, 1, 5, "pow2", weights=w.weights)
+        wi = wl.Workload("i32", 157, cols, "i32", halo, border, 3.0, wl.WEIGHTED_SUM, 1, 6, "pow2",
+                         weights=np.rint(w.weights * 99).astype(np.float32))
+        for wg in [(1, 1), (3, 1), (8, 1), (64, 1)]:
+            for blocking in [(1, 1), (8, 1), (1, 4), (2, 4), (8, 4)]:
+                check(ls, w, wg, blocking=blocking)
+            check(ls, wd, wg, blocking=(2, 2))
+            check(ls, wi, wg, blocking=(2, 4))
+        ws = custom(wl.SINCOS, 157, cols, halo, border, pad=0.5, seed=cols)
+        one = gpu_apply(ls, ws, ws.grid(), (4, 4), blocking=(1, 1))
+        np.testing.assert_array_equal(gpu_apply(ls, ws, ws.grid(), (8, 1), blocking=(2, 4)), one)
+
+
 # ---- the other element types of the paper's template (Section 3.3) ---------------------------
 
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
