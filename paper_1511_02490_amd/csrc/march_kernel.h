@@ -29,7 +29,8 @@ __host__ __device__ constexpr int march_vectors(int W, int E) { return 64 - marc
 // columns then lie either all inside the matrix or all outside it, every row is one vector load
 // at a per-lane column plus a wavefront-uniform row address, and what the border mode asks for
 // beyond that is a per-lane fix-up of the loaded vector.  Otherwise elements are loaded one by one.
-template <class Op, int B, class Halo, bool FAST>
+// NT: output vectors are stored non-temporally (element-by-element stores are plain either way).
+template <class Op, int B, class Halo, bool FAST, bool NT>
 __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const int H) {
     using T = typename Op::T;
     using L = typename Op::L;
@@ -217,7 +218,7 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
                             for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(st[slot][cc], a.scalar0);
                             if (FAST) {
                                 char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
-                                store_out_vec(reinterpret_cast<T *>(rowp + out_off), res, a.nt_store != 0);
+                                store_out_vec<NT>(reinterpret_cast<T *>(rowp + out_off), res);
                             } else {
                                 T *out = a.out + (size_t)gr * cols + gc0;
 #pragma unroll
@@ -232,9 +233,9 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
     }
 }
 
-template <class Op, int B, class Halo, bool FAST, int MAXT>
+template <class Op, int B, class Halo, bool FAST, bool NT, int MAXT>
 __global__ __launch_bounds__(MAXT) void march_kernel(const TileArgs<Op, Halo> a, const int H) {
-    march_body<Op, B, Halo, FAST>(a, H);
+    march_body<Op, B, Halo, FAST, NT>(a, H);
 }
 
 }  // namespace sk

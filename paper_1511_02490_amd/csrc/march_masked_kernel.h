@@ -36,7 +36,7 @@ struct HaloM {
     __host__ __device__ int w() const { return w_; }
 };
 
-template <class Op, int B, class Halo, int WC, bool FAST, int MAXT>
+template <class Op, int B, class Halo, int WC, bool FAST, bool NT, int MAXT>
 __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, const int H) {
     using T = typename Op::T;
     using L = typename Op::L;
@@ -226,7 +226,7 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
                         for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(sum[cc], a.scalar0);
                         if (FAST) {
                             char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
-                            store_out_vec(reinterpret_cast<T *>(rowp + out_off), res, a.nt_store != 0);
+                            store_out_vec<NT>(reinterpret_cast<T *>(rowp + out_off), res);
                         } else {
                             T *out = a.out + (size_t)gr * cols + gc0;
 #pragma unroll
@@ -240,9 +240,9 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
     }
 }
 
-template <class Op, int B, class Halo, int WC, bool FAST, int MAXT>
+template <class Op, int B, class Halo, int WC, bool FAST, bool NT, int MAXT>
 __global__ __launch_bounds__(MAXT) void march_masked_kernel(const TileArgs<Op, Halo> a, const int H) {
-    march_masked_body<Op, B, Halo, WC, FAST, MAXT>(a, H);
+    march_masked_body<Op, B, Halo, WC, FAST, NT, MAXT>(a, H);
 }
 
 }  // namespace sk

@@ -121,28 +121,45 @@ __device__ __forceinline__ void load_global(E (&dst)[CNT], const E *src) {
 // Stores of output cells are optionally non-temporal: they are not read again by the launch that
 // writes them, and on matrices beyond the caches keeping them out of the way of the input pays
 // (measured on a plain copy: +20 % on 256 MiB, nothing on 64 MiB).
-// (The compiler makes one store of two that differ in nothing else, and a plain one: the empty statements keep
-// the two branches apart.  28 taps on 8192^2 floats, a pass on matrices not used before: 165 us with one plain store,
-// 115 us with non-temporal ones.)
-__device__ __forceinline__ void store_word4(void *dst, uint4 v, bool nt) {
+template <bool NT>
+__device__ __forceinline__ void store_word4(void *dst, uint4 v) {
     any_word4 t;
     t.x = v.x, t.y = v.y, t.z = v.z, t.w = v.w;
+    if constexpr (NT)
+        __builtin_nontemporal_store(t, reinterpret_cast<any_word4 *>(dst));
+    else
+        *reinterpret_cast<any_word4 *>(dst) = t;
+}
+// The same, chosen at run time, for kernels that store at one place, once per cell row.  (The compiler makes one store of
+// two that differ in nothing else, and a plain one: the empty statements keep the two branches apart.  28 taps on 8192^2
+// floats, a pass on matrices not used before: 165 us with one plain store, 115 us with non-temporal ones.  In a march of
+// many unrolled steps the statements cost registers and cross-lane moves that would be part of an addition: the marching
+// kernels are compiled for either kind.)
+__device__ __forceinline__ void store_word4(void *dst, uint4 v, bool nt) {
     if (nt) {
         asm volatile("");
-        __builtin_nontemporal_store(t, reinterpret_cast<any_word4 *>(dst));
+        store_word4<true>(dst, v);
         asm volatile("");
     } else {
-        *reinterpret_cast<any_word4 *>(dst) = t;
+        store_word4<false>(dst, v);
     }
 }
-template <class E, int CNT>
-__device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT], bool nt) {
+template <class E, int CNT, class Store>
+__device__ __forceinline__ void store_words_of(E *dst, const E (&src)[CNT], Store store) {
     static_assert(sizeof(E) * CNT % 16 == 0, "vector moves are whole 16-byte words");
     constexpr int NV = sizeof(E) * CNT / 16;
     uint4 tmp[NV];
     __builtin_memcpy(tmp, src, sizeof(tmp));
 #pragma unroll
-    for (int k = 0; k < NV; ++k) store_word4(reinterpret_cast<unsigned char *>(dst) + 16 * k, tmp[k], nt);
+    for (int k = 0; k < NV; ++k) store(reinterpret_cast<unsigned char *>(dst) + 16 * k, tmp[k]);
+}
+template <class E, int CNT>
+__device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT], bool nt) {
+    store_words_of(dst, src, [&](void *p, uint4 v) { store_word4(p, v, nt); });
+}
+template <bool NT, class E, int CNT>
+__device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT]) {
+    store_words_of(dst, src, [](void *p, uint4 v) { store_word4<NT>(p, v); });
 }
 
 // What a cell keeps while one row of its region goes by (operators that fold a row at a time).

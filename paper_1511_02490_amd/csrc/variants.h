@@ -190,10 +190,10 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
     const dim3 grid(blocks), block(wc, wr);
     const bool whole = s->cols % 4 == 0;      // rows of whole vectors, or the element-by-element body
 #define STREAM_LAUNCH(D)                                                                                       \
-    if (whole)                                                                                                 \
-        hipLaunchKernelGGL((sk::stream_kernel<Op, B, D, true, kMaxT>), grid, block, 0, stream, a, CR);         \
-    else                                                                                                       \
-        hipLaunchKernelGGL((sk::stream_kernel<Op, B, D, false, kMaxT>), grid, block, 0, stream, a, CR);        \
+    hipLaunchKernelGGL(!whole        ? (&sk::stream_kernel<Op, B, D, false, false, kMaxT>)                     \
+                       : s->nt_store ? (&sk::stream_kernel<Op, B, D, true, true, kMaxT>)                       \
+                                     : (&sk::stream_kernel<Op, B, D, true, false, kMaxT>),                     \
+                       grid, block, 0, stream, a, CR);                                                         \
     break
     switch (depth) {
     case 1: STREAM_LAUNCH(1);
@@ -322,12 +322,11 @@ hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int
         a.xcd_chunk = (int)((blocks + 7) / 8);
         blocks = (unsigned)a.xcd_chunk * 8u;
     }
-    if (s->cols % 4 == 0)      // rows of whole vectors, or the element-by-element body
-        hipLaunchKernelGGL((sk::march_kernel<Op, B, Halo, true, kMaxT>), dim3(blocks), dim3(wc, wr), 0, stream, a,
-                           s->cr);
-    else
-        hipLaunchKernelGGL((sk::march_kernel<Op, B, Halo, false, kMaxT>), dim3(blocks), dim3(wc, wr), 0, stream, a,
-                           s->cr);
+    // rows of whole vectors, with either kind of store, or the element-by-element body
+    hipLaunchKernelGGL(s->cols % 4 != 0 ? (&sk::march_kernel<Op, B, Halo, false, false, kMaxT>)
+                       : s->nt_store    ? (&sk::march_kernel<Op, B, Halo, true, true, kMaxT>)
+                                        : (&sk::march_kernel<Op, B, Halo, true, false, kMaxT>),
+                       dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
     return hipGetLastError();
 }
 
@@ -351,12 +350,10 @@ hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int 
             a.xcd_chunk = (int)((blocks + 7) / 8);
             blocks = (unsigned)a.xcd_chunk * 8u;
         }
-        if (s->cols % 4 == 0)
-            hipLaunchKernelGGL((sk::march_masked_kernel<Op, B, Halo, WC, true, kMaxT>), dim3(blocks), dim3(wc, wr), 0,
-                               stream, a, s->cr);
-        else
-            hipLaunchKernelGGL((sk::march_masked_kernel<Op, B, Halo, WC, false, kMaxT>), dim3(blocks), dim3(wc, wr), 0,
-                               stream, a, s->cr);
+        hipLaunchKernelGGL(s->cols % 4 != 0 ? (&sk::march_masked_kernel<Op, B, Halo, WC, false, false, kMaxT>)
+                           : s->nt_store    ? (&sk::march_masked_kernel<Op, B, Halo, WC, true, true, kMaxT>)
+                                            : (&sk::march_masked_kernel<Op, B, Halo, WC, true, false, kMaxT>),
+                           dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
         return hipGetLastError();
     }
 }
@@ -415,7 +412,7 @@ hipError_t launch_life_direct(const stencil *s, const void *in, void *out, int w
 }
 
 
-// The kernel behind each launcher (the variant for rows of whole vectors where there are two).
+// The kernel behind each launcher (the variant for rows of whole vectors and plain stores where there are several).
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 const void *kernel_tile(const stencil *s) {
     if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1)
@@ -433,7 +430,7 @@ const void *kernel_life_temporal(const stencil *) { return reinterpret_cast<cons
 template <int CR, int CC>
 const void *kernel_threshold(const stencil *) { return reinterpret_cast<const void *>(&sk::threshold_kernel<CR, CC, STENCIL_MAX_WG_SIZE>); }
 template <class Op, int B, class Halo>
-const void *kernel_march(const stencil *) { return reinterpret_cast<const void *>(&sk::march_kernel<Op, B, Halo, true, 256>); }
+const void *kernel_march(const stencil *) { return reinterpret_cast<const void *>(&sk::march_kernel<Op, B, Halo, true, false, 256>); }
 template <class Op, int B, class Halo, int WC = 1>
 const void *kernel_march_masked(const stencil *s) {
     if constexpr (WC > Halo::E + Halo::W + 1)
@@ -441,19 +438,19 @@ const void *kernel_march_masked(const stencil *s) {
     else if (s->he + s->hw + 1 != WC)
         return kernel_march_masked<Op, B, Halo, WC + 1>(s);
     else
-        return reinterpret_cast<const void *>(&sk::march_masked_kernel<Op, B, Halo, WC, true, 256>);
+        return reinterpret_cast<const void *>(&sk::march_masked_kernel<Op, B, Halo, WC, true, false, 256>);
 }
 template <class Op, int B>
 const void *kernel_stream(const stencil *s) {
     switch (s->temporal_depth) {
-    case 1: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 1, true, 256>);
-    case 2: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 2, true, 256>);
-    case 3: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 3, true, 256>);
-    case 4: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 4, true, 256>);
-    case 5: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 5, true, 256>);
-    case 6: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 6, true, 256>);
-    case 7: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 7, true, 256>);
-    case 8: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 8, true, 256>);
+    case 1: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 1, true, false, 256>);
+    case 2: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 2, true, false, 256>);
+    case 3: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 3, true, false, 256>);
+    case 4: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 4, true, false, 256>);
+    case 5: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 5, true, false, 256>);
+    case 6: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 6, true, false, 256>);
+    case 7: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 7, true, false, 256>);
+    case 8: return reinterpret_cast<const void *>(&sk::stream_kernel<Op, B, 8, true, false, 256>);
     default: return nullptr;
     }
 }

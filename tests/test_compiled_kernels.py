@@ -1,0 +1,97 @@
+"""What the compiler made of the kernels: properties that the source asks for, that results do not show and that an
+optimiser may undo without a sign.  Reads the gfx950 code of the library as it was built (no GPU)."""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+from paper_1511_02490_amd import build, libstencil  # noqa: F401  (loads, and so builds, the library)
+
+LLVM = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")))), "llvm", "bin")
+
+
+class Kernels:
+    """The library's kernels: demangled name -> (code object, symbol, vector registers)."""
+
+    def __init__(self, path, folder):
+        data = open(path, "rb").read()
+        self.found = {}
+        magic = b"__CLANG_OFFLOAD_BUNDLE__"
+        at = data.find(magic)
+        while at >= 0:
+            pos = at + len(magic) + 8
+            for _ in range(struct.unpack_from("<Q", data, at + len(magic))[0]):
+                off, size, n = struct.unpack_from("<QQQ", data, pos)
+                if b"gfx950" in data[pos + 24:pos + 24 + n]:
+                    self._add(os.path.join(folder, "%d.elf" % at), data[at + off:at + off + size])
+                pos += 24 + n
+            at = data.find(magic, at + 1)
+
+    def _add(self, path, code):
+        with open(path, "wb") as fh:
+            fh.write(code)
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], capture_output=True, text=True, check=True).stdout
+        kernels = re.findall(r"\.name:\s+(_Z\S+)\n(?:.*\n)*?.*\.vgpr_count:\s+(\d+)", notes)
+        names = subprocess.run(["c++filt"], input="\n".join(k for k, _ in kernels), capture_output=True, text=True, check=True).stdout
+        for (symbol, vgprs), name in zip(kernels, names.splitlines()):
+            self.found[name.split("(")[0].replace("void ", "").replace("sk::", "")] = (path, symbol, int(vgprs))
+
+    def matching(self, pattern):
+        return {name: k for name, k in self.found.items() if re.search(pattern, name)}
+
+    def instructions(self, pattern):
+        """name -> list of instructions (mnemonic and operands) of every kernel whose name matches."""
+        by_file, out = {}, {}
+        for name, (path, symbol, _) in self.matching(pattern).items():
+            by_file.setdefault(path, {})[symbol] = name
+        for path, symbols in by_file.items():
+            text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn",
+                                   "--disassemble-symbols=" + ",".join(symbols), path], capture_output=True, text=True, check=True).stdout
+            for block in re.split(r"\n(?=[0-9a-f]+ <)", text)[1:]:
+                lines = block.splitlines()
+                out[symbols[re.search(r"<(.+)>:", lines[0]).group(1)]] = [re.sub(r"\s*//.*", "", l).strip() for l in lines[1:]]
+        return out
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    return Kernels(build.LIB_PATH, str(tmp_path_factory.mktemp("code")))
+
+
+def vector_stores(instructions):
+    """(plain, non-temporal) 16-byte stores to global memory."""
+    stores = [i for i in instructions if i.startswith("global_store_dwordx4")]
+    nt = sum(1 for i in stores if i.endswith(" nt"))
+    return len(stores) - nt, nt
+
+
+def test_marching_kernels_store_as_they_were_compiled_to(kernels):
+    """The marches over rows of whole vectors exist once for plain and once for non-temporal stores."""
+    code = kernels.instructions(r"^(stream_kernel|march_kernel|march_masked_kernel)<.*, true, (true|false), 256>$")
+    assert len(code) >= 2 * (2 * 2 * 8 + 3 * 5 + 3 * 2 * 9)
+    for name, instructions in code.items():
+        plain, nt = vector_stores(instructions)
+        assert (plain, nt > 0) == (0, True) if ", true, true, 256>" in name else (plain > 0, nt) == (True, 0), (name, plain, nt)
+
+
+def test_kernels_that_choose_at_run_time_keep_both_kinds_of_store(kernels):
+    """A plain and a non-temporal store differ in nothing else, and a compiler that merges them leaves plain ones."""
+    code = kernels.instructions(r"^(tile_kernel<OpWeightedSum, |tile_kernel<OpSinCos, |direct_kernel<OpHeat, |temporal_kernel<OpHeat, |"
+                                r"life_temporal_kernel<|life_direct_kernel<|life_stream_kernel<.*, false>)")
+    checked = 0
+    for name, instructions in code.items():
+        if re.match(r"tile_kernel<.*, \d+, 1, \d+>$", name):
+            continue                               # one cell per work-item and row: no vectors
+        plain, nt = vector_stores(instructions)
+        assert plain > 0 and nt > 0, (name, plain, nt)
+        checked += 1
+    assert checked > 60
+
+
+def test_heat_marches_keep_their_wavefronts(kernels):
+    """A SIMD's 512 vector registers hold this many wavefronts of a heat march of so many steps per launch."""
+    for border, depth, waves in [(1, 5, 5), (1, 7, 4), (2, 5, 5), (2, 7, 4), (1, 8, 3), (2, 8, 4)]:
+        for name, (_, _, vgprs) in kernels.matching(r"^stream_kernel<OpHeat, %d, %d, true, " % (border, depth)).items():
+            assert 512 // ((vgprs + 7) // 8 * 8) >= waves, (name, vgprs)
