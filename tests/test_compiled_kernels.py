@@ -95,3 +95,14 @@ def test_heat_marches_keep_their_wavefronts(kernels):
     for border, depth, waves in [(1, 5, 5), (1, 7, 4), (2, 5, 5), (2, 7, 4), (1, 8, 3), (2, 8, 4)]:
         for name, (_, _, vgprs) in kernels.matching(r"^stream_kernel<OpHeat, %d, %d, true, " % (border, depth)).items():
             assert 512 // ((vgprs + 7) // 8 * 8) >= waves, (name, vgprs)
+
+
+def test_window_rows_are_read_in_vectors(kernels):
+    """Tiles of bytes and of two planes: what a work-item reads of a window row are 16-byte vectors (12 of their bytes
+    where the last cell is not needed) and, of bytes, the cells beside them."""
+    for pattern, pieces in [(r"^tile_kernel<OpLife, ., .*, 16, \d+>$", {"ds_read_b128", "ds_read_u8"}),
+                            (r"^tile_kernel<OpSinCos, ., HaloC<.*, 4, \d+>$", {"ds_read_b128", "ds_read_b96"})]:
+        code = kernels.instructions(pattern)
+        assert len(code) == 12
+        for name, instructions in code.items():
+            assert {i.split()[0] for i in instructions if i.startswith("ds_read")} <= pieces, name
