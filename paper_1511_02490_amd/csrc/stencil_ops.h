@@ -42,10 +42,12 @@ struct HaloC {
     __host__ __device__ constexpr int e() const { return E_; }
     __host__ __device__ constexpr int w() const { return W_; }
 };
-// ... or one only known at launch: of up to kCompiledColumns columns ...
+// ... or one only known at launch, folded (tile_kernel.h) by rows compiled for their number of columns, which is at most
+// kCompiledColumns ...
+enum class Fold { columns, blocks, taps };
 constexpr int kCompiledColumns = 9;
 struct HaloD {
-    static constexpr bool kWide = false;
+    static constexpr Fold kFold = Fold::columns;
     static constexpr bool kStatic = false;
     static constexpr bool kMasked = false;
     static constexpr int N = 0, S = 0, E = 0, W = 0;
@@ -56,9 +58,13 @@ struct HaloD {
     __host__ __device__ int w() const { return w_; }
 };
 
-// ... or of more (a kernel of its own, or the registers of either fold would limit the wavefronts of both).
-struct HaloWide : HaloD {
-    static constexpr bool kWide = true;
+// ... by blocks of columns, or tap by tap (kernels of their own, or the registers of one fold would limit the wavefronts
+// of the others).
+struct HaloBlocks : HaloD {
+    static constexpr Fold kFold = Fold::blocks;
+};
+struct HaloTaps : HaloD {
+    static constexpr Fold kFold = Fold::taps;
 };
 
 // ---- weighted sum ("gaussian" of Table 2): fp32 fma chain ---------------------------------

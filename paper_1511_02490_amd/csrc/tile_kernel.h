@@ -234,7 +234,7 @@ __device__ __forceinline__ void stage_inside(typename Op::L *tile, int plane, in
 // so that the halo columns cost a fraction of a pass rather than a whole extra pass with most
 // lanes idle.  Vectors starting at or beyond matrix column `col_end` are not needed and skipped.
 // `magic` belongs to pitch / CC items per row (row_of_item).
-template <class Op, int B, int CC>
+template <class Op, int B, int CC, bool INSIDE = true>
 __device__ __forceinline__ void stage_tile(typename Op::L *tile, int plane, int pitch, const typename Op::T *in,
                                            int rows, int cols, int row_first, int col_first, int n_rows,
                                            int col_end, typename Op::T pad, unsigned magic, int tid,
@@ -245,10 +245,10 @@ __device__ __forceinline__ void stage_tile(typename Op::L *tile, int plane, int 
     const int n_items = pitch / CC;   // per staged row
     // A tile that lies inside the matrix with its border region (nearly all of them on a large matrix) has nothing
     // to resolve: the items of the linear walk are loaded from a running 32-bit offset and, the tile being rows of
-    // n_items vectors, land in LDS at their own index.
-    const bool inside = CC > 1 && row_first >= 0 && row_first + n_rows <= rows && col_first >= 0 && col_first + pitch <= cols &&
+    // n_items vectors, land in LDS at their own index.  (INSIDE: whether the kernel has that walk.)
+    const bool inside = INSIDE && CC > 1 && row_first >= 0 && row_first + n_rows <= rows && col_first >= 0 && col_first + pitch <= cols &&
                         (uint64_t)n_rows * cols * sizeof(T) < (1ull << 32);
-    if constexpr (CC > 1) {
+    if constexpr (INSIDE && CC > 1) {
         if (inside) {
             stage_inside<Op, CC>(tile, plane, n_items, in + (size_t)row_first * cols + col_first, cols, n_rows * n_items, magic,
                                  tid, nthreads);
@@ -506,7 +506,8 @@ __device__ __forceinline__ void fold_blocks(typename Op::State (&st)[CR][CC], co
 // The same tap by tap, every cell row with its own window: the cells of a row need window columns kk .. kk + CC - 1 for
 // tap kk, i.e. two aligned vectors per chunk of CC taps, of which one is the previous chunk's.  Work-items of four and more
 // rows have the arithmetic between two weights to cover the wait for the next, and no registers for more
-// (17 x 17 on 2500 x 3000 floats, four rows: 91 us, 8 columns at a time 105; eight rows: 99 and 132).
+// (17 x 17 on 2500 x 3000 floats, four rows: 91 us, 8 columns at a time 105; eight rows: 99 and 132).  And where a region
+// has few taps, the windows of all cell rows are requested at once, where the other folds wait for one after the other.
 template <class Op, class Halo, int CR, int CC>
 __device__ __forceinline__ void fold_taps(typename Op::State (&st)[CR][CC], const TileArgs<Op, Halo> &a,
                                           const typename Op::L *window, int hn, int hw, int wrows, int wcols) {
@@ -587,8 +588,11 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
     // rows resolve like any other out-of-matrix row): no window row ever needs a range check
     const int TH = th + hn + hs;
 
-    stage_tile<Op, B, CC>(tile, a.plane, pitch, a.in, rows, cols, r0 - hn, c0 - hwa, TH, cols + he, a.pad,
-                          a.stage_magic, ty * wc + tx, wr * wc);
+    // Under a run-time region, eight rows of cells per work-item: nine items and more per work-item, and no gain from
+    // finding their addresses sooner (2048 x 4096 floats, 1 x 7 taps, resolved / not: 16.2 / 17.7 us; 7 x 4 taps 21.2 / 22.4).
+    constexpr bool kInside = Halo::kStatic || CR < 8 || NP > 1;
+    stage_tile<Op, B, CC, kInside>(tile, a.plane, pitch, a.in, rows, cols, r0 - hn, c0 - hwa, TH, cols + he, a.pad,
+                                   a.stage_magic, ty * wc + tx, wr * wc);
     __syncthreads();
 
     // ---- fold the customising function over the border region ----------------------------
@@ -649,14 +653,11 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
             // The tile is staged from the region's west edge: tap kk of cell cc is window column kk + cc, and a
             // work-item's window starts at a vector.
             const L *const window = tile + lr0 * pitch + lc0;
-            // Up to the Gaussian of radius 4 the fold is compiled for the region's number of columns: straight-line rows
-            // against blocks of 8 columns with a shorter last one (2500 x 3000 floats, 2 x 4 cells: 7 x 8 taps 20.8 us
-            // compiled, 5 x 13 taps 31.1 in blocks, where the former took 38 either way).
-            if constexpr (Halo::kWide) {
-                if constexpr (CR >= (NP == 1 ? 4 : 8))
-                    fold_taps<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
-                else
-                    fold_blocks<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
+            // (which of the three serves a region: region_fold in variants.h)
+            if constexpr (Halo::kFold == Fold::taps) {
+                fold_taps<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
+            } else if constexpr (Halo::kFold == Fold::blocks) {
+                fold_blocks<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
             } else {
                 static_assert(kCompiledColumns == 9, "a case each");
                 switch (wcols) {

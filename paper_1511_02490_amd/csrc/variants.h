@@ -376,11 +376,37 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
     return hipGetLastError();
 }
 
+// Which fold of the tile kernel serves a run-time region (work-items of several columns of cells).
+// - Up to the Gaussian of radius 4 it is compiled for the region's number of columns: straight-line rows against blocks
+//   of 8 columns with a shorter last one (2500 x 3000 floats, 2 x 4 cells: 7 x 8 taps 20.8 us compiled, 5 x 13 taps 31.1 in
+//   blocks, where tap by tap took 38 either way).
+// - Beyond, in blocks; tap by tap where work-items have four rows and more (fold_taps), and for a single row of taps under
+//   two rows of cells, where a block's weights are loaded twice (300 x 500 floats, 1 x 41 taps: 6.5 us, 7.3 in blocks).
+// - Four rows of cells and more under a region of few taps: tap by tap.  The compiled fold takes the window rows one after
+//   the other, and up to 1.5 times the registers (2048 x 4096, tap by tap / compiled: floats, 4 x 4 cells, 1 x 5 taps
+//   14.5 / 16.7 us, 3 x 9 taps 20.1 / 18.6; 8 x 4 cells, 1 x 5 taps 16.2 / 18.8, 8 x 5 taps 28.6 / 24.6; doubles on
+//   2048^2, 4 x 2 cells, 3 x 5 taps 16.7 / 17.4, 7 x 4 taps 23.6 / 21.0).  Integers spend longer on each tap, bytes longer
+//   on staging: there it pays up to a row of the widest regions (int32, 4 x 4 cells, 1 x 5 taps 16.5 / 17.4 us, 3 x 5 taps 21.3 / 20.6).
+template <class Op, int CR>
+sk::Fold region_fold(const stencil *s) {
+    const int rows = s->hn + s->hs + 1, cols = s->he + s->hw + 1;
+    constexpr bool kOnePlane = Op::kPlanes == 1;
+    if (cols > sk::kCompiledColumns)
+        return CR >= (kOnePlane ? 4 : 8) || (kOnePlane && CR == 2 && rows == 1) ? sk::Fold::taps : sk::Fold::blocks;
+    constexpr int kFewTaps = !kOnePlane || CR < 4                             ? 0
+                             : !std::is_floating_point<typename Op::T>::value ? 9
+                             : CR >= 8                                        ? 27
+                                                                              : 18;
+    return rows * cols <= kFewTaps ? sk::Fold::taps : sk::Fold::columns;
+}
+
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
-    if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1)
-        if (s->he + s->hw + 1 > sk::kCompiledColumns)
-            return launch_tile<Op, B, sk::HaloWide, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
+    if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1) {
+        const sk::Fold fold = region_fold<Op, CR>(s);
+        if (fold == sk::Fold::blocks) return launch_tile<Op, B, sk::HaloBlocks, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
+        if (fold == sk::Fold::taps) return launch_tile<Op, B, sk::HaloTaps, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
+    }
     unsigned blocks;
     size_t lds;
     const auto a = make_args<Op, Halo, CR, CC>(s, STENCIL_STAGING_LOCAL, in, out, wr, wc, &blocks, &lds);
@@ -415,8 +441,11 @@ hipError_t launch_life_direct(const stencil *s, const void *in, void *out, int w
 // The kernel behind each launcher (the variant for rows of whole vectors and plain stores where there are several).
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 const void *kernel_tile(const stencil *s) {
-    if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1)
-        if (s->he + s->hw + 1 > sk::kCompiledColumns) return kernel_tile<Op, B, sk::HaloWide, CR, CC, MAXT>(s);
+    if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1) {
+        const sk::Fold fold = region_fold<Op, CR>(s);
+        if (fold == sk::Fold::blocks) return kernel_tile<Op, B, sk::HaloBlocks, CR, CC, MAXT>(s);
+        if (fold == sk::Fold::taps) return kernel_tile<Op, B, sk::HaloTaps, CR, CC, MAXT>(s);
+    }
     return reinterpret_cast<const void *>(&sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>);
 }
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>

@@ -106,3 +106,13 @@ def test_window_rows_are_read_in_vectors(kernels):
         assert len(code) == 12
         for name, instructions in code.items():
             assert {i.split()[0] for i in instructions if i.startswith("ds_read")} <= pieces, name
+
+
+def test_folds_of_few_taps_keep_their_wavefronts(kernels):
+    """The tap-by-tap tiles with four rows of cells are kernels of their own: 8 wavefronts per SIMD (int32: 6)."""
+    for pattern, limit in [("OpWeightedSum, ., HaloTaps, 4, 4,", 64), ("OpWeightedSumF64, ., HaloTaps, 4, 2,", 64),
+                           ("OpWeightedSumU8, ., HaloTaps, 4, 4,", 64), ("OpWeightedSumI32, ., HaloTaps, 4, 4,", 80)]:
+        found = kernels.matching("^tile_kernel<" + pattern)
+        assert len(found) == 3
+        for name, (_, _, vgprs) in found.items():
+            assert vgprs <= limit, (name, vgprs)

@@ -443,6 +443,25 @@ def test_run_time_regions_by_number_of_columns(ls, wcols):
             np.testing.assert_array_equal(np.isinf(gpu_apply(ls, w, g, (4, 8), blocking=(cr, 4))), np.isinf(ref))
 
 
+@pytest.mark.parametrize("shape", [(1, 1), (1, 9), (9, 1), (3, 3), (2, 5), (6, 3), (3, 6), (4, 5), (3, 9), (4, 7), (1, 10), (2, 10)])
+def test_run_time_regions_at_the_line_between_two_folds(ls, shape):
+    """Regions of as many taps as go tap by tap under four and eight rows of cells (9, 18, 27), of one more, and single rows
+    beyond the compiled widths, for every element type: bit for bit the one-cell mapping's sums."""
+    rows, cols = shape
+    for k, border in enumerate(("clamp", "wrap", "constant")):
+        halo = (rows // 2, rows - 1 - rows // 2, cols - 1 - (cols * k) // 3, (cols * k) // 3)
+        wf = custom(wl.WEIGHTED_SUM, 75, 141, halo, border, pad=0.5, seed=rows * cols + k)
+        others = {dtype: wl.Workload(dtype, 75, 141, dtype, halo, border, 2.0, wl.WEIGHTED_SUM, 1, 3, "pow2",
+                                     weights=np.rint(wf.weights * 99).astype(np.float32)) for dtype in ("f64", "i32", "u8")}
+        for w, blockings in [(wf, [(2, 4), (4, 4), (8, 4)]), (others["f64"], [(2, 2), (4, 2)]), (others["i32"], [(2, 4), (4, 4)]),
+                             (others["u8"], [(2, 4), (4, 4)])]:
+            g = w.grid()
+            one = check(ls, w, (4, 8), grid=g)
+            for blocking in blockings:
+                for wg in [(2, 8), (8, 16)]:
+                    np.testing.assert_array_equal(gpu_apply(ls, w, g, wg, blocking=blocking), one)
+
+
 # ---- temporal blocking: several applications per launch ------------------------------------
 
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
