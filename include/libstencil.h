@@ -72,7 +72,8 @@ enum stencil_border { STENCIL_CLAMP = 0, STENCIL_WRAP = 1, STENCIL_CONSTANT = 2 
  *                 application per stencil_run / sweep sample; local-memory tile only, cells
  *                 per work-item (1,1), (4,1), (1,4), (2,4), (4,4), (1,16) or (2,16).
  *   LIFE (u8):    Conway B3/S23 on cells 0/1, region 1/1/1/1 - "gol".  Precondition: every cell
- *                 is 0 or 1 (the kernels add packed bytes); a padding value above 1 is rejected.
+ *                 is 0 or 1 (kernels pack cells into bits, or add packed bytes); a padding value
+ *                 above 1 is rejected.
  *   HEAT (f32):   u + alpha * (((n + s) + (e + w)) - 4u), region 1/1/1/1, every operation
  *                 rounded to fp32 in this order - "he".  scalars[0] = alpha.
  *   SINCOS (f32): sum over the region of w * sin(V) + cos(V) - a compute-intensive
@@ -172,7 +173,8 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            LIFE, WRAP and CONSTANT borders: one bit per cell, cells_cols in {4,8,16}; up to
  *            STENCIL_MAX_STREAM_DEPTH generations per launch, and between the launches of a run
  *            the matrix stays in bits.  The library cuts the tile from the matrix, the depth and
- *            the workgroup's number of wavefronts; cells_rows and cells_cols do not change it.
+ *            the workgroup's number of wavefronts (STENCIL_OPT_LIFE_TILE overrules it); cells_rows
+ *            and cells_cols do not change it.
  *            The workgroup only groups wavefronts: w_r*w_c must be a multiple of 64 (other
  *            sizes are refused) and at most 256.  Not available for a matrix whose rows are 4 GiB
  *            or longer (cells within a row are addressed by 32-bit byte offsets).
@@ -222,11 +224,14 @@ int stencil_stream_segment_rows(const stencil_t *st, int wavefronts_per_simd, in
  * that only show when a launch fails (Section 3.1): with value (w_r << 16) | w_c every launch with
  * that workgroup size - with -1 every launch - is not made and reports the runtime's
  * out-of-resources error instead, which stencil_run returns as STENCIL_E_REFUSED and the sweeps
- * record as a refused size. */
+ * record as a refused size.
+ * STENCIL_OPT_LIFE_TILE (default 0: the library chooses) is the tile of LIFE under
+ * STENCIL_STAGING_STREAM: (rows of a work-item << 16) | lanes that hold a row of the tile, of 4, 8 or
+ * 16 rows and 16, 32 or 64 lanes.  A launch whose tile has no rows left beside its rim is refused. */
 #define STENCIL_MAX_TEMPORAL_DEPTH 4   /* STENCIL_STAGING_TEMPORAL */
 #define STENCIL_MAX_STREAM_DEPTH 8     /* STENCIL_STAGING_STREAM */
 enum stencil_option { STENCIL_OPT_XCD_REMAP = 0, STENCIL_OPT_TEMPORAL_DEPTH = 1, STENCIL_OPT_SWEEP_CUTOFF = 2,
-                      STENCIL_OPT_NT_STORE = 3, STENCIL_OPT_FAIL_LAUNCH = 4 };
+                      STENCIL_OPT_NT_STORE = 3, STENCIL_OPT_FAIL_LAUNCH = 4, STENCIL_OPT_LIFE_TILE = 5 };
 int stencil_set_option(stencil_t *st, int option, int value);
 
 /* ---- legality (Section 3.1) ---------------------------------------------------------- */

@@ -508,8 +508,8 @@ int stencil_set_kernel(stencil_t *s, int kernel_id, const float *weights, int n_
     case STENCIL_LIFE:
         if (s->dtype != STENCIL_U8) return fail(STENCIL_E_INVALID, "LIFE needs a U8 matrix");
         if (!unit_region) return fail(STENCIL_E_INVALID, "LIFE needs border region 1/1/1/1");
-        // the packed-byte kernels add cells without carries between bytes: every cell, the padding
-        // value included, must be 0 or 1
+        // the kernels pack cells into bits, or add packed bytes without carries between them: every cell,
+        // the padding value included, must be 0 or 1
         if (s->pad != 0.0 && s->pad != 1.0)
             return fail(STENCIL_E_INVALID, "LIFE needs a padding value of 0 or 1 (it is %g)", s->pad);
         s->weights.clear();
@@ -639,6 +639,14 @@ int stencil_set_option(stencil_t *s, int option, int value) {
             s->fail_cols = value & 0xffff;
         }
         return STENCIL_OK;
+    case STENCIL_OPT_LIFE_TILE: {
+        const int rows = value >> 16, lanes = value & 0xffff;
+        if (value != 0 && ((rows != 4 && rows != 8 && rows != 16) || (lanes != 16 && lanes != 32 && lanes != 64)))
+            return fail(STENCIL_E_INVALID, "STENCIL_OPT_LIFE_TILE takes (4, 8 or 16 rows << 16) | 16, 32 or 64 lanes, or 0");
+        s->life_rows = rows;
+        s->life_lanes = lanes;
+        return STENCIL_OK;
+    }
     default:
         return fail(STENCIL_E_INVALID, "unknown option %d", option);
     }

@@ -50,6 +50,7 @@ struct stencil {
     int xcd_remap = 1;
     int nt_store = 0;         // output vectors are written with non-temporal stores
     int temporal_depth = 2;   // applications per launch under STENCIL_STAGING_TEMPORAL
+    int life_rows = 0, life_lanes = 0;   // the tile of the Life streams (0: chosen for each launch)
     int sweep_cutoff_pct = 0; // > 0: sizes slower than this percentage of the best so far are cut short
     int best_rows = 0, best_cols = 0;
     int fail_rows = 0, fail_cols = 0;   // testing aid: launches of this workgroup size fail (-1: every launch)

@@ -222,15 +222,16 @@ struct LifeTile {
     int rows_per_item = 0, group_shift = 0;
     int tile_rows = 0;       // rows a tile writes
 };
-LifeTile life_tile(int64_t rows, int64_t words, int threads, int depth, bool from_bytes) {
+LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
     constexpr int kOverheadRows = 2;
     const double simds = 4.0 * stencil_compute_units();
+    const int64_t rows = s->rows, words = life_words(s);
     LifeTile best;
     double best_cost = 0.0;
     for (int shift = 4; shift <= 6; ++shift)
         for (int rpt = 4; rpt <= 16; rpt *= 2) {
             const int tile_rows = (threads >> shift) * rpt - 2 * depth;
-            if (tile_rows <= 0) continue;
+            if (tile_rows <= 0 || (s->life_rows && (rpt != s->life_rows || 1 << shift != s->life_lanes))) continue;
             const int64_t strips = (words + (1 << shift) - 3) / ((1 << shift) - 2);
             const double waves = (double)strips * (double)((rows + tile_rows - 1) / tile_rows) * (threads / 64);
             const double cost = std::max(1.0, waves / simds) * (rpt + kOverheadRows) *
@@ -255,7 +256,7 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     a.rows = (int)s->rows;
     a.cols = (int)s->cols;
     a.words = (int)life_words(s);
-    const LifeTile t = life_tile(s->rows, a.words, wr * wc, depth, !IN_BITS);
+    const LifeTile t = life_tile(s, wr * wc, depth, !IN_BITS);
     if (t.tile_rows == 0) return hipErrorInvalidValue;
     a.group_shift = t.group_shift;
     a.tiles_c = (a.words + (1 << t.group_shift) - 3) / ((1 << t.group_shift) - 2);

@@ -649,6 +649,33 @@ def test_life_between_launches_in_bits(ls, border, cols):
 
 
 @pytest.mark.parametrize("border", ["wrap", "constant"])
+@pytest.mark.parametrize("rows_per_item", [4, 8, 16])
+@pytest.mark.parametrize("lanes", [16, 32, 64])
+def test_every_tile_of_the_life_streams(ls, border, rows_per_item, lanes):
+    """Every kernel of the Life streams - rows per work-item, lanes per row, bytes or bits in and out (a single launch, the
+    first, one between and the last of a run) - on ragged boards of several tiles each way with live padding."""
+    for wg, depth in [((4, 64), 8), ((2, 64), 3), ((1, 64), 1)]:
+        tile_rows = wg[0] * wg[1] // lanes * rows_per_item - 2 * depth
+        rows, cols = 2 * max(tile_rows, 1) + 5, 2 * (lanes - 2) * 32 + 45
+        for iters in (depth, 2 * depth + 1, 3 * depth):
+            w = custom(wl.LIFE, rows, cols, (1, 1, 1, 1), border, pad=1.0, seed=rows + lanes, iters=iters)
+            st = ls.Stencil.from_workload(w)
+            st.set_mapping("stream", 16, 8)
+            st.set_option(ls.OPT_TEMPORAL_DEPTH, depth)
+            st.set_option(ls.OPT_LIFE_TILE, (rows_per_item << 16) | lanes)
+            g = w.grid()
+            tin = torch.from_numpy(g).cuda()
+            tout = torch.full_like(tin, 9)
+            if tile_rows <= 0:
+                with pytest.raises(ls.StencilError):
+                    st.run(tin, tout, iters, wg)
+            else:
+                st.run(tin, tout, iters, wg)
+                np.testing.assert_array_equal(tout.cpu().numpy(), oracle.apply_workload(w, g))
+            st.close()
+
+
+@pytest.mark.parametrize("border", ["wrap", "constant"])
 def test_register_streaming_life_bit_exact(ls, border):
     """Generations kept in registers, 4 / 8 / 16 cells per lane: matrices wider than one strip, ragged
     ones (cell-by-cell loads), ones smaller than a strip, live padding, unaligned rows."""

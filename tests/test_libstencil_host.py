@@ -365,6 +365,16 @@ def test_sweep_records_launch_failures_as_refused_and_finishes():
     st.close()
 
 
+def test_life_tile_option_takes_what_the_kernels_have():
+    st = ls.Stencil(64, 64, "u8", (1, 1, 1, 1), "wrap")
+    for tile in (1, (4 << 16) | 8, (5 << 16) | 32, -1):
+        with pytest.raises(ls.StencilError):
+            st.set_option(ls.OPT_LIFE_TILE, tile)
+    for tile in ((4 << 16) | 16, (16 << 16) | 64, 0):
+        st.set_option(ls.OPT_LIFE_TILE, tile)
+    st.close()
+
+
 def test_predictor_from_a_text_file_and_inside_the_librarys_own_choice(tmp_path):
     """stencil_predictor_load reads (f(s), size) pairs from text; an attached classifier decides
     what stencil_run(0, 0) launches when the handle has no sweep to go by (Section 2: choosing the
