@@ -217,7 +217,8 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
 // lanes: 4096 x 4096 4x16 9.8, 8x16 10.3, 8x32 9.8, 8x64 11.2, 16x16 11.0, 16x32 10.4, 16x64 11.1; 256 x 256 4x16
 // 4.6, 4x32 4.8, 8x32 6.2, 16x32 8.2.  12 rows per item cost more than 16 on either.)  A launch that reads bytes
 // has 32 registers per row under way: 16 rows leave room for two wavefronts per SIMD, too few to keep the memory
-// busy (8192 x 8192, one generation: 8x32 23.3, 16x32 27.0).
+// busy (8192 x 8192, one generation: 4x32 25.5, 8x32 23.5, 16x32 27.6).  And a single generation on a matrix that is up to three
+// wavefronts of four-row items per SIMD (the rim aside) is over before eight rows' loads are in (4096 x 4096: 8.0, 9.3, 10.7).
 struct LifeTile {
     int rows_per_item = 0, group_shift = 0;
     int tile_rows = 0;       // rows a tile writes
@@ -226,6 +227,7 @@ LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
     constexpr int kOverheadRows = 2;
     const double simds = 4.0 * stencil_compute_units();
     const int64_t rows = s->rows, words = life_words(s);
+    const double four_row_waves = (double)rows * (double)words / (4 * 64);
     LifeTile best;
     double best_cost = 0.0;
     for (int shift = 4; shift <= 6; ++shift)
@@ -234,6 +236,7 @@ LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
             if (tile_rows <= 0 || (s->life_rows && (rpt != s->life_rows || 1 << shift != s->life_lanes))) continue;
             const int64_t strips = (words + (1 << shift) - 3) / ((1 << shift) - 2);
             const double waves = (double)strips * (double)((rows + tile_rows - 1) / tile_rows) * (threads / 64);
+            if (s->life_rows == 0 && from_bytes && depth == 1 && rpt > 4 && best.tile_rows > 0 && four_row_waves <= 3.0 * simds) continue;
             const double cost = std::max(1.0, waves / simds) * (rpt + kOverheadRows) *
                                 (shift == 4 ? 1.25 : shift == 5 ? 1.05 : 1.0) * (from_bytes && rpt == 16 ? 1.3 : 1.0);
             if (best.tile_rows == 0 || cost < best_cost) {
