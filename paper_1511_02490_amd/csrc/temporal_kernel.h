@@ -65,7 +65,6 @@ struct TemporalTile {
     int row_first, col_first;       // the matrix cell under the staged tile's first one
     int staged_rows;                // ER
     int first_row, last_row;        // the staged rows that an application may read or compute
-    int wc;                         // vectors of the tile itself
     int depth;
     int R;                          // rows of an item
 };
@@ -75,7 +74,7 @@ struct TemporalItem {
     int group_row;                  // first of its rows, counted from the first the application computes
     int group_off;                  // ... and where its cells lie in local memory
     int first_off, last_off;        // where the first and the last row lie that may be read
-    bool stores, in_tile;
+    bool stores;
 };
 
 // Application k of a launch: tile rows [k, ER - k), everything that can still be right; the LAST one, on the
@@ -87,7 +86,8 @@ struct TemporalItem {
 // one step ahead, and takes the cells west and east of its own from the adjacent lanes: wavefronts overlap by
 // two lanes, whose values are not stored, so that no lane has to look elsewhere.  (Vectors at the two ends of
 // a staged row get whatever the lanes beside them hold - values that only ever reach rim cells that are
-// stale.)  In a workgroup that is not WHOLE wavefronts the two cells are read from local memory instead.
+// stale.)  In a workgroup that is not WHOLE wavefronts the two cells are read from local memory instead, and so
+// they are in the last application, whose items are not the others'.
 template <class Op, int B, bool WHOLE, bool EDGE, bool LAST>
 __device__ __forceinline__ void temporal_application(const TileArgs<Op, HaloC<1, 1, 1, 1>> &a, const TemporalTile &s,
                                                      const TemporalItem &it, int k, const float *src, float *dst) {
@@ -119,10 +119,11 @@ __device__ __forceinline__ void temporal_application(const TileArgs<Op, HaloC<1,
     neighbours(row[1], off[1]);
     int gr = s.row_first + k_begin + it.group_row;
     [[maybe_unused]] T *out = a.out + (ptrdiff_t)gr * cols + it.gc;
-    for (int rr = 0; rr < s.R; rr += 4) {
+    const int R = min(s.R, k_end - k_begin);   // (a single group holds fewer rows from application to application)
+    for (int rr = 0; rr < R; rr += 4) {
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            if (rr + p >= s.R) break;              // (the same for the whole workgroup)
+            if (rr + p >= R) break;                // (the same for the whole workgroup)
             QuadRow &up = row[p], &mid = row[(p + 1) % 4], &dn = row[(p + 2) % 4], &ahead = row[(p + 3) % 4];
             off[(p + 3) % 4] = min(at + 2 * pitch, it.last_off);
             load_vec(ahead.v, src + off[(p + 3) % 4]);
@@ -134,7 +135,7 @@ __device__ __forceinline__ void temporal_application(const TileArgs<Op, HaloC<1,
                 for (int cc = 0; cc < CC; ++cc)
                     if ((unsigned)gr >= (unsigned)rows || (unsigned)(it.gc + cc) >= (unsigned)cols) res[cc] = a.pad;
             }
-            if (it.stores && at < end_off && (!LAST || it.in_tile)) {
+            if (it.stores && at < end_off) {
                 if (!LAST) {
                     store_vec(dst + at, res);
                 } else if (!EDGE || it.gc + CC <= cols) {
@@ -152,9 +153,14 @@ __device__ __forceinline__ void temporal_application(const TileArgs<Op, HaloC<1,
     }
 }
 
+// All applications of a launch.  The last one computes the tile's own cells, one for one those of the work-items: each its
+// own `cells_rows` rows of its own vector, all lanes at work, the two cells beside the vector from local memory.  (Walked in
+// the groups of the others it kept a third of the lanes idle and went on for as many rows as the first application has:
+// four heat steps per launch on 4096^2, WRAP, us per launch before / now: 4x4 cells, 1x256 work-items 287 / 261, 2x5 214 / 191;
+// 2x4 cells, 4x64 work-items 52.3 / 50.4.)
 template <class Op, int B, bool WHOLE, bool EDGE>
-__device__ __forceinline__ void temporal_applications(const TileArgs<Op, HaloC<1, 1, 1, 1>> &a, TemporalTile &s, int tid,
-                                                      int nthreads, float *src, float *dst) {
+__device__ __forceinline__ void temporal_applications(const TileArgs<Op, HaloC<1, 1, 1, 1>> &a, TemporalTile &s, int cells_rows,
+                                                      int tid, int nthreads, float *src, float *dst) {
     const int lane = tid & 63;
     // as many groups of rows as one pass of the workgroup has lanes for: one pass, except where the workgroup
     // holds less than a row of vectors
@@ -171,7 +177,6 @@ __device__ __forceinline__ void temporal_applications(const TileArgs<Op, HaloC<1
         it.first_off = s.first_row * s.pitch + q * 4;
         it.last_off = s.last_row * s.pitch + q * 4;
         it.stores = (!WHOLE || (lane > 0 && lane < 63)) && index < items;
-        it.in_tile = q >= 1 && q <= s.wc && it.gc < a.cols;
         return it;
     };
     const TemporalItem first = item_of(0);
@@ -184,14 +189,20 @@ __device__ __forceinline__ void temporal_applications(const TileArgs<Op, HaloC<1
         src = dst;
         dst = tmp;
     }
-    temporal_application<Op, B, WHOLE, EDGE, true>(a, s, first, s.depth, src, dst);
-    for (int base = per_pass; base < items; base += per_pass)
-        temporal_application<Op, B, WHOLE, EDGE, true>(a, s, item_of(base), s.depth, src, dst);
+    TemporalItem own;
+    own.gc = s.col_first + (1 + (int)threadIdx.x) * 4;
+    own.group_row = (int)threadIdx.y * cells_rows;
+    own.group_off = own.group_row * s.pitch + (1 + (int)threadIdx.x) * 4;
+    own.first_off = s.first_row * s.pitch + (1 + (int)threadIdx.x) * 4;
+    own.last_off = s.last_row * s.pitch + (1 + (int)threadIdx.x) * 4;
+    own.stores = own.gc < a.cols;
+    s.R = cells_rows;
+    temporal_application<Op, B, false, EDGE, true>(a, s, own, s.depth, src, dst);
 }
 
 template <class Op, int B, bool WHOLE, int MAXT>
 __global__ __launch_bounds__(MAXT) void temporal_kernel(const TileArgs<Op, HaloC<1, 1, 1, 1>> a, const int depth,
-                                                        const int tile_rows) {
+                                                        const int cells_rows) {
     static_assert(Op::kPlanes == 1 && sizeof(typename Op::T) == 4 && sizeof(typename Op::L) == 4, "fp32, one plane");
     constexpr int CC = 4, HC = 4;   // cells per vector; staged columns each side of the tile
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -208,7 +219,7 @@ __global__ __launch_bounds__(MAXT) void temporal_kernel(const TileArgs<Op, HaloC
     if (t >= a.n_tiles) return;
     const int tile_r = t / a.tiles_c, tile_c = t - tile_r * a.tiles_c;
     const int rows = a.rows, cols = a.cols, pitch = a.pitch;
-    const int r0 = tile_r * tile_rows, c0 = tile_c * wc * CC;
+    const int tile_rows = wr * cells_rows, r0 = tile_r * tile_rows, c0 = tile_c * wc * CC;
     TemporalTile s;
     s.pitch = pitch;
     s.nq = pitch / CC;
@@ -216,7 +227,6 @@ __global__ __launch_bounds__(MAXT) void temporal_kernel(const TileArgs<Op, HaloC
     s.col_first = c0 - HC;
     const int ER = min(tile_rows, rows - r0) + 2 * depth;   // staged rows in use
     s.staged_rows = ER;
-    s.wc = wc;
     s.depth = depth;
 
     stage_tile<Op, B, CC>(src, a.plane, pitch, a.in, rows, cols, s.row_first, s.col_first, ER, cols + HC, a.pad,
@@ -228,9 +238,9 @@ __global__ __launch_bounds__(MAXT) void temporal_kernel(const TileArgs<Op, HaloC
     s.last_row = B == kClamp ? min(ER, rows - s.row_first) - 1 : ER - 1;
     // does the staged tile reach outside the matrix?  (same answer for the whole workgroup)
     if (s.row_first < 0 || s.row_first + ER > rows || s.col_first < 0 || s.col_first + pitch > cols)
-        temporal_applications<Op, B, WHOLE, true>(a, s, tid, nthreads, src, dst);
+        temporal_applications<Op, B, WHOLE, true>(a, s, cells_rows, tid, nthreads, src, dst);
     else
-        temporal_applications<Op, B, WHOLE, false>(a, s, tid, nthreads, src, dst);
+        temporal_applications<Op, B, WHOLE, false>(a, s, cells_rows, tid, nthreads, src, dst);
 }
 
 }  // namespace sk

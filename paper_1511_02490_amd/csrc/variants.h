@@ -166,7 +166,7 @@ hipError_t launch_temporal(const stencil *s, const void *in, void *out, int wr, 
     static thread_local int raised_on[2] = {-1, -1};
     hipError_t e = allow_large_tiles(reinterpret_cast<const void *>(kernel), lds, &raised_on[whole_waves]);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(wc, wr), lds, stream, a, depth, wr * CR);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(wc, wr), lds, stream, a, depth, CR);
     return hipGetLastError();
 }
 
