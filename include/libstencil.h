@@ -201,8 +201,9 @@ int stencil_get_mapping(const stencil_t *st, int *staging, int *cells_rows, int 
  * *cells_rows the smallest height at which strips x segments <= 4 x compute units x
  * wavefronts_per_simd (the compute units: the device's, 256 until a GPU has been used); taller
  * segments repeat fewer run-in rows, shorter ones hide more latency - 2 to 6 per SIMD are the
- * values to sweep (stencil_sweep_configs).  STENCIL_E_INVALID on another mapping,
- * STENCIL_E_REFUSED if the height would exceed the kernels' 4096. */
+ * values to sweep (stencil_sweep_configs).  LIFE has no segments (its height changes nothing): there
+ * strips are counted as 64 lanes of cells_cols cells less a rim of the depth's.  STENCIL_E_INVALID on
+ * another mapping, STENCIL_E_REFUSED if the height would exceed the kernels' 4096. */
 int stencil_stream_segment_rows(const stencil_t *st, int wavefronts_per_simd, int *cells_rows);
 
 /* Launch options.  STENCIL_OPT_XCD_REMAP (default 1): workgroups are numbered so that each of
@@ -240,7 +241,9 @@ int stencil_set_option(stencil_t *st, int option, int value);
 int stencil_max_wg_size(const stencil_t *st);
 
 /* Bytes of local memory the tile of Section 2 (workgroup plus perimeter border region)
- * needs for this scenario and workgroup size, as laid out by the kernels. */
+ * needs for this scenario and workgroup size, as Eq. 1 counts it: in the staged elements.  (The
+ * kernels lay it out so, except two that take less: LIFE under STENCIL_STAGING_TEMPORAL keeps one bit
+ * per cell, and a region given at run time is staged without widening it to whole vectors.) */
 int64_t stencil_tile_bytes(const stencil_t *st, int wg_rows, int wg_cols);
 
 /* Eq. 1: 1 if (wg_rows, wg_cols) is legal for this scenario (w_r*w_c <= W_max(s) and not a

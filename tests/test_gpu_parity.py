@@ -541,7 +541,9 @@ def test_register_streaming_temporal_kernel_bit_exact(ls, border):
                 check(ls, w, wg, blocking=("stream", h, 4, depth))
     w = custom(wl.WEIGHTED_SUM, 90, 300, (1, 1, 1, 1), border, pad=0.4, seed=22, iters=7)
     check(ls, w, (1, 64), blocking=("stream", 32, 4, 4))
-    check(ls, w, (2, 64), blocking=("stream", 16, 4, 3), offset=1)          # unaligned rows: element loads
+    check(ls, w, (2, 64), blocking=("stream", 16, 4, 3), offset=1)          # rows of whole vectors, at no multiple of 16 bytes
+    w = custom(wl.WEIGHTED_SUM, 90, 301, (1, 1, 1, 1), border, pad=0.4, seed=23, iters=7)
+    check(ls, w, (2, 64), blocking=("stream", 16, 4, 3), offset=1)          # ragged rows: element by element
     st = ls.Stencil.from_workload(wl.config(3, rows=64, cols=64))
     st.set_mapping("stream", 32, 4)
     assert st.max_wg_size() == 256 and st.tile_bytes(1, 64) == 0
@@ -616,7 +618,9 @@ def test_register_marching_single_application_kernels(ls, border):
                     ref = gpu_apply(ls, w, w.grid(), (8, 8), blocking=(2, 4))
                 np.testing.assert_array_equal(got, ref)
         w = custom(kernel, 50, 300, halo, border, pad=0.3, seed=77)
-        check(ls, w, (1, 64), blocking=("stream", 16, 4), offset=1)            # unaligned rows: element loads
+        check(ls, w, (1, 64), blocking=("stream", 16, 4), offset=1)            # rows of whole vectors, at no multiple of 16 bytes
+        check(ls, custom(kernel, 50, 301, halo, border, pad=0.3, seed=78), (1, 64), blocking=("stream", 16, 4),
+              offset=1)                                                          # ragged rows: element by element
         big = w.grid() * np.float32(300.0)                                       # beyond the small-argument range
         big[3, 5], big[20, 299] = 1.0e6, -3.0e7
         # sums of sines and cosines of large arguments pass near zero: absolute error here
@@ -677,8 +681,9 @@ def test_every_tile_of_the_life_streams(ls, border, rows_per_item, lanes):
 
 @pytest.mark.parametrize("border", ["wrap", "constant"])
 def test_register_streaming_life_bit_exact(ls, border):
-    """Generations kept in registers, 4 / 8 / 16 cells per lane: matrices wider than one strip, ragged
-    ones (cell-by-cell loads), ones smaller than a strip, live padding, unaligned rows."""
+    """Generations kept in registers: matrices wider than one tile, ragged ones, ones smaller than a
+    tile, live padding, unaligned rows, and every segment height and number of cells the mapping
+    accepts (neither changes the kernel: test_every_tile_of_the_life_streams goes through those)."""
     for rows, cols, iters in [(70, 1200, 9), (37, 256, 5), (130, 83, 6), (64, 512, 8), (5, 3, 7), (1, 1, 4),
                               (40, 976, 17), (33, 2064, 11)]:
         w = wl.config(2, rows=rows, cols=cols, iters=iters)
