@@ -15,7 +15,8 @@ bandwidth figure is then an HBM figure (the figure on one pair is reported besid
 workloads, and four heat steps on 8192^2 and 16384^2 matrices, follow as sub-records with the
 same fields.
 
-Prints ONE JSON line.  `value` = Gcells/s (cell updates per second) of the timed steps;
+Prints ONE JSON line, short enough for a reader that keeps a few thousand characters: of the other
+workloads and the sweeps it holds the outcome only (--record FILE writes the complete record).  `value` = Gcells/s (cell updates per second) of the timed steps;
 `roofline` prices the stencil kernel's algorithmic bytes (one read + one write per cell
 update) over its HIP-event-measured launch time against the 8 TB/s HBM peak, with the
 arithmetic views beside it; `cpu_baseline` is the CPU oracle timed on a bounded sample of the
@@ -102,6 +103,7 @@ def parse_args():
     ap.add_argument("--nt-store", default=None, choices=["0", "1"],
                     help="force plain (0) or non-temporal (1) output stores instead of timing both")
     ap.add_argument("--xcd-remap", default=None, choices=["0", "1"], help="workgroup numbering to go with --wg")
+    ap.add_argument("--record", default="", metavar="FILE", help="write the complete record (the printed line is its summary)")
     ap.add_argument("--copy-only", action="store_true",
                     help="launch only the plain copy kernel on the workload's matrix (counter calibration)")
     return ap.parse_args()
@@ -609,6 +611,31 @@ def leave_one_out_prediction(ls, wl, torch, index, mapping_of, reps):
     return pred, table
 
 
+def rounded(x):
+    """The record with its floats to six significant digits."""
+    if isinstance(x, float):
+        return float("%.6g" % x) if math.isfinite(x) else None
+    if isinstance(x, dict):
+        return {k: rounded(v) for k, v in x.items()}
+    if isinstance(x, (list, tuple)):
+        return [rounded(v) for v in x]
+    return x
+
+
+def summary(out):
+    """What goes to stdout of the complete record: the same fields, the sweeps and the other workloads by their outcome."""
+    pick = lambda d, *keys: {k: d[k] for k in keys if d and d.get(k) is not None}
+    short = dict(out)
+    short["sweep"] = {"seconds": out["sweep"]["seconds"],
+                      "best_by_mapping": {name: [s["best_wg"], s["best_gcells_s"]] for name, s in out["sweep"]["by_blocking"].items()}}
+    short["predictor"] = {tag: pick(p, "mapping", "predicted_wg", "oracle_wg", "performance") for tag, p in out["predictor"].items()}
+    short["other_workloads"] = {
+        name: dict(pick(r, "value", "ms_per_step"), **pick(r["config"], "mapping", "wg", "nt_store"),
+                   **{"one_per_launch": pick(r.get("roofline"), "kernel_ms", "achieved", "frac")})
+        for name, r in out["other_workloads"].items() if r}
+    return rounded({k: v for k, v in short.items() if v not in (None, {}) or k in ("vs_baseline", "roofline", "config")})
+
+
 def main():
     args = parse_args()
     if args.gpus != 1:
@@ -817,7 +844,10 @@ def main():
     }
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w, args.cpu_seconds)
-    print(json.dumps(out))
+    if args.record:
+        with open(args.record, "w") as fh:
+            json.dump(rounded(out), fh, indent=1)
+    print(json.dumps(summary(out)))
 
 
 if __name__ == "__main__":

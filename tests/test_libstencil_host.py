@@ -629,3 +629,28 @@ def test_bench_refuses_more_than_one_gpu():
     out = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], cwd=root, capture_output=True,
                          text=True, timeout=120)
     assert out.returncode != 0 and "one GPU" in out.stderr and out.stdout.strip() == ""
+
+
+def test_bench_line_is_short_and_keeps_the_contracts_fields():
+    """The printed summary of a record with every workload's sub-record stays within a few thousand characters."""
+    import json
+    import bench
+    roof = {"bound": "hbm", "achieved": 4613.790162653119, "peak": 8000.0, "unit": "GB/s", "frac": 0.5767237703316399,
+            "traffic": None, "kernel": "k" * 80, "kernel_ms": 0.11636222998301188}
+    sub = {"workload": "w" * 40, "metric": "Gcells/s", "value": 712.345678901234, "unit": "Gcells/s", "ms_per_step": 0.0123456789,
+           "steps": 10, "config": {"mapping": "stream 134x4 depth 8", "wg": [4, 64], "nt_store": 1, "iters": 1},
+           "roofline": roof, "cpu_baseline": {"value": 1.0 / 3, "sample": "s" * 80}}
+    swept = {"sizes": 590, "refused": 0, "best_wg": [8, 32], "best_gcells_s": 193.711123456789, "worst_ms": float("nan")}
+    out = {"metric": "Gcells/s", "value": 570.2891234567, "unit": "Gcells/s", "n_gpus": 1, "steps": 20, "warmup": 5, "ms_per_step": 0.1,
+           "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32", "data": "synthetic",
+           "config": {"workload": "C5"}, "roofline": roof, "roofline_timed_kernel": None, "best_vs_fixed": None,
+           "sweep": {"seconds": 1.0, "confirmation_pass": [swept] * 20, "by_blocking": {"mapping %d" % k: swept for k in range(16)}},
+           "predictor": {"fast": {"mapping": "local 2x4", "predicted_wg": [8, 8], "trained_on": [swept] * 20}},
+           "other_workloads": {name: sub for name in bench.WORKLOADS}, "cpu_baseline": {"value": 0.05, "kind": "oracle"}}
+    line = json.dumps(bench.summary(out))
+    assert len(line) < 6000 and "NaN" not in line
+    rec = json.loads(line)
+    for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+                "vs_baseline", "dtype", "data", "config", "roofline", "cpu_baseline"):
+        assert key in rec, key
+    assert set(rec["other_workloads"]) == set(bench.WORKLOADS) and rec["other_workloads"]["W8192"]["value"] == 712.346
