@@ -165,11 +165,11 @@ __device__ __forceinline__ void temporal_applications(const TileArgs<Op, HaloC<1
     // as many groups of rows as one pass of the workgroup has lanes for: one pass, except where the workgroup
     // holds less than a row of vectors
     const int per_pass = WHOLE ? nthreads / 64 * 62 : nthreads;
-    const int groups = max(1, (int)__umulhi((unsigned)per_pass, a.stage_magic)), items = groups * s.nq;
+    const int groups = max(1, (int)row_of_item(per_pass, a.stage_magic)), items = groups * s.nq;
     s.R = (s.staged_rows - 2 + groups - 1) / groups;
     auto item_of = [&](int base) {
         const int index = base + (WHOLE ? (tid >> 6) * 62 + lane - 1 : tid), item = max(0, min(index, items - 1));
-        const int g = (int)__umulhi((unsigned)item, a.stage_magic), q = item - g * s.nq;
+        const int g = (int)row_of_item(item, a.stage_magic), q = item - g * s.nq;
         TemporalItem it;
         it.gc = s.col_first + q * 4;
         it.group_row = g * s.R;

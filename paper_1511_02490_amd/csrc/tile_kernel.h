@@ -60,7 +60,7 @@ struct TileArgs {
     int xcd_chunk;   // > 0: tiles are dealt to the 8 XCDs in contiguous chunks of this many
     int pitch;       // LDS tile pitch, in staged elements
     int plane;       // elements per LDS plane (tile rows x pitch)
-    unsigned stage_magic;   // ceil(2^32 / items per staged row), modulo 2^32: see row_of_item
+    unsigned stage_magic;   // for the division by the items of a staged row: see row_of_item
     int nt_store;    // vector stores of output cells are non-temporal
     typename Op::T pad;
     float scalar0;
@@ -68,9 +68,11 @@ struct TileArgs {
     WeightStore<Op, Halo> w;
 };
 
-// item / items per row by one multiply.  A row of a single item (a workgroup one work-item wide, a region of one
-// column) has 2^32 for its multiplier, which arrives as 0: there every item is a row of its own.
-__device__ __forceinline__ unsigned row_of_item(unsigned item, unsigned magic) { return magic ? __umulhi(item, magic) : item; }
+// item / d, the items of a staged row, by a multiply: floor((item + 1) floor((2^32 - 1) / d) / 2^32), exact where
+// (item + 1) d <= 2^32.  (The usual ceil(2^32 / d) needs no addition and 33 bits for d = 1: a workgroup one work-item wide
+// under a region of one column.)
+constexpr unsigned row_magic(unsigned d) { return 0xffffffffu / d; }
+__device__ __forceinline__ unsigned row_of_item(unsigned item, unsigned magic) { return __umulhi(item + 1u, magic); }
 
 __host__ __device__ constexpr int round_up(int x, int m) { return (x + m - 1) / m * m; }
 __host__ __device__ constexpr int round_down(int x, int m) { return x / m * m; }

@@ -112,7 +112,7 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
     {
         // vectors (elements when CC = 1) per staged row; kernels that stage nothing have none
         const unsigned items = std::max(1u, (unsigned)(a.pitch / CC));
-        a.stage_magic = (unsigned)((0x100000000ull + items - 1) / items);
+        a.stage_magic = sk::row_magic(items);
     }
     a.nt_store = s->nt_store;
     a.pad = (T)s->pad;
@@ -374,7 +374,7 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
     const unsigned words = (unsigned)(a.pitch + 31) / 32;
     a.pitch = (int)words;
     a.plane = (wr * CR + 2 * s->temporal_depth) * a.pitch;
-    a.stage_magic = (unsigned)((0x100000000ull + words - 1) / words);
+    a.stage_magic = sk::row_magic(words);
     lds = 4 * (2 * (size_t)a.plane + 2);         // + one spare word at each end
     hipLaunchKernelGGL((sk::life_temporal_kernel<B, CR, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a, depth);
     return hipGetLastError();
