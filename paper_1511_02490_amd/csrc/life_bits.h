@@ -111,7 +111,8 @@ __device__ __forceinline__ uint32_t life_bits16_narrow(const uint8_t *in, int gr
 // The scheme of temporal_kernel on bits: a workgroup stages its tile with `depth` more rows above and
 // below and 16 more cells left and right (the tile starts at bit 16 of a row's first word), and
 // ping-pongs between two buffers; what a generation computes within k cells of the rim is stale
-// after k generations, and exactly the tile is written.  a.pitch and a.stage_magic count words.
+// after k generations, and exactly the tile is written.  a.pitch counts words, and a.stage_magic is
+// ceil(2^32 / words of a row).
 //
 // Out-of-matrix cells: WRAP copies evolve like their originals, CONSTANT ones are set back after every
 // generation, CLAMP ones are not kept - the rows' sums take the edge cell itself there.
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLi
 #pragma unroll
             for (int b = 0; b < kBatch; ++b) {
                 const int item = min(at + b * nthreads, ER * nw - 1);      // (beyond the last: the last again)
-                const int i = (int)row_of_item(item, a.stage_magic);
+                const int i = (int)__umulhi((unsigned)item, a.stage_magic);
                 const int col = col_first + (item - i * nw) * 32;
                 gr[b] = resolve<B>(row_first + i, rows);
                 v[b][0] = life_load16<B>(a.in, gr[b], col, cols);
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLi
         }
     } else {
         for (int at = tid; at < ER * nw; at += nthreads) {
-            const int i = (int)row_of_item(at, a.stage_magic);
+            const int i = (int)__umulhi((unsigned)at, a.stage_magic);
             const int col = col_first + (at - i * nw) * 32, gr = resolve<B>(row_first + i, rows);
             src[at] = life_bits16_narrow<B>(a.in, gr, col, cols, a.pad) |
                       (life_bits16_narrow<B>(a.in, gr, col + 16, cols, a.pad) << 16);
@@ -187,11 +188,11 @@ __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLi
     };
     // Items of a generation: a word column x a group of R rows, as many groups as one pass of the workgroup has
     // work-items for.
-    const int groups = max(1, (int)row_of_item(nthreads, a.stage_magic));
+    const int groups = max(1, (int)__umulhi((unsigned)nthreads, a.stage_magic));
     const int R = (ER - 2 + groups - 1) / groups;
     for (int k = 1; k < depth; ++k) {
         for (int item = tid; item < groups * nw; item += nthreads) {
-            const int g = (int)row_of_item(item, a.stage_magic);
+            const int g = (int)__umulhi((unsigned)item, a.stage_magic);
             const int q = item - g * nw, col = col_first + q * 32;
             int i = k + g * R;
             const int end = min(i + R, ER - k);

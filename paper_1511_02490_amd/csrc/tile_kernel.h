@@ -70,7 +70,7 @@ struct TileArgs {
 
 // item / d, the items of a staged row, by a multiply: floor((item + 1) floor((2^32 - 1) / d) / 2^32), exact where
 // (item + 1) d <= 2^32.  (The usual ceil(2^32 / d) needs no addition and 33 bits for d = 1: a workgroup one work-item wide
-// under a region of one column.)
+// under a region of one column.  The temporal Life kernel, whose rows have two words and more, uses that.)
 constexpr unsigned row_magic(unsigned d) { return 0xffffffffu / d; }
 __device__ __forceinline__ unsigned row_of_item(unsigned item, unsigned magic) { return __umulhi(item + 1u, magic); }
 

@@ -374,7 +374,7 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
     const unsigned words = (unsigned)(a.pitch + 31) / 32;
     a.pitch = (int)words;
     a.plane = (wr * CR + 2 * s->temporal_depth) * a.pitch;
-    a.stage_magic = sk::row_magic(words);
+    a.stage_magic = (unsigned)((0x100000000ull + words - 1) / words);     // (never one word: a vector of cells and the rim)
     lds = 4 * (2 * (size_t)a.plane + 2);         // + one spare word at each end
     hipLaunchKernelGGL((sk::life_temporal_kernel<B, CR, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a, depth);
     return hipGetLastError();
