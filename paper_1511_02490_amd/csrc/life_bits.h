@@ -117,8 +117,8 @@ __device__ __forceinline__ uint32_t life_bits16_narrow(const uint8_t *in, int gr
 // Out-of-matrix cells: WRAP copies evolve like their originals, CONSTANT ones are set back after every
 // generation, CLAMP ones are not kept - the rows' sums take the edge cell itself there.
 // What bounds a launch of four generations is the launch itself, its loads and its stores; a generation of
-// a 128 x 128 tile is one pass of 512 work-items and 0.7 us.  (1001 x 1503 cells, tiles of 128 x 128, CLAMP:
-// 30.5 us with packed bytes and a search for clamped cells after every generation, now 6.9 us.)
+// a 128 x 128 tile is one pass of 512 work-items and 0.65 us.  (1001 x 1503 cells, tiles of 128 x 128, CLAMP:
+// 30.5 us with packed bytes and a search for clamped cells after every generation, now 6.5 us.)
 template <int B, int CR, int MAXT>
 __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLife, HaloC<1, 1, 1, 1>> a,
                                                              const int depth) {

@@ -12,7 +12,7 @@
 // inside read themselves in their place, and a cell at the west or east edge takes its own value for
 // the neighbour it lacks.  (They used to be copied from the nearest cell's new value after every
 // application, a search over the whole tile behind a second barrier that the launch waited for:
-// four heat steps on 1025 x 1999, tiles of 64 x 128, 23.2 -> 13.1 us, and 11.3 us with the walk below.)
+// four heat steps on 1025 x 1999, tiles of 64 x 128, 23.2 -> 13.1 us, and 11.1 us with the walk below.)
 // The per-cell arithmetic is the same fold as in the single-application kernels, so results
 // are bit-identical to `depth` separate launches.
 #pragma once

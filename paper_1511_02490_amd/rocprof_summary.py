@@ -63,6 +63,7 @@ def kernel_source_hash(family: str) -> str:
             h.update(name.encode() + b"\0" + fh.read())
     from paper_1511_02490_amd import build
     h.update(" ".join(build.HIPCC_FLAGS).encode())
+    h.update(repr(sorted(build.UNIT_FLAGS.items())).encode())
     return h.hexdigest()[:16]
 
 
