@@ -1,6 +1,6 @@
 """Condenses rocprofv3 output of a bench.py run into a short text summary and a counter record.
 
-    python -m paper_1511_02490_amd.rocprof_summary --prefix c5march --dir gpurun_out/prof \
+    python -m paper_1511_02490_amd.rocprof_summary --prefix c5march --dir prof_out \
         --kernel march_kernel --title "..." --command "<bench.py arguments>" --record > profiles/<name>.md
 
 expects, each produced with --output-format csv by the commands the summary prints:
@@ -145,7 +145,7 @@ def main():
     out = []
     out.append("# %s" % (a.title or k))
     out.append("")
-    out.append("Commands (from the repository root on the GPU box, after `python -c \"import __graft_entry__ as g; "
+    out.append("Commands (from the repository root on the machine with the GPU, after `python -c \"import __graft_entry__ as g; "
                "g.build()\"`; `cd /tmp && export TMPDIR=/tmp` first, paths then relative to the repository):")
     out.append("")
     runs = [("--kernel-trace --stats", "trace"), ("--pmc FETCH_SIZE", "fetch"), ("--pmc WRITE_SIZE", "write")]
