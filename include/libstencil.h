@@ -145,7 +145,8 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            STENCIL_STAGING_TEMPORAL - temporal blocking for iterated runs: one launch stages
  *            the tile plus a border region STENCIL_OPT_TEMPORAL_DEPTH cells deep in local
  *            memory and advances it by that many applications before writing it back, so a
- *            stencil_run of `iters` applications takes ceil(iters / depth) launches.
+ *            stencil_run of `iters` applications takes at most ceil(iters / depth) launches
+ *            (a run of more than one may be made by a kernel that fuses more: see LIFE below).
  *            Available for HEAT and WEIGHTED_SUM with region 1/1/1/1 (cells_cols = 4) and
  *            for LIFE (cells_cols = 16); cells_rows in {1,2,4,8}.
  *   cells_rows x cells_cols: block of adjacent cells one work-item computes (register
@@ -172,9 +173,12 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            tile is as fast there: its fold is bound by arithmetic).
  *            LIFE, WRAP and CONSTANT borders: one bit per cell, cells_cols in {4,8,16}; up to
  *            STENCIL_MAX_STREAM_DEPTH generations per launch, and between the launches of a run
- *            the matrix stays in bits.  The library cuts the tile from the matrix, the depth and
- *            the workgroup's number of wavefronts (STENCIL_OPT_LIFE_TILE overrules it); cells_rows
- *            and cells_cols do not change it.
+ *            the matrix stays in bits.  A run of more generations than one launch makes is dealt to
+ *            fewer launches where that is faster (up to 32 generations in one, unless the depth is 1 or
+ *            the tile is prescribed); under STENCIL_STAGING_TEMPORAL, where the workgroup is whole
+ *            wavefronts, such a run is made by the same kernel.  The library cuts the tile from the
+ *            matrix, the depth and the workgroup's number of wavefronts (STENCIL_OPT_LIFE_TILE
+ *            overrules it); cells_rows and cells_cols do not change it.
  *            The workgroup only groups wavefronts: w_r*w_c must be a multiple of 64 (other
  *            sizes are refused) and at most 256.  Not available for a matrix whose rows are 4 GiB
  *            or longer (cells within a row are addressed by 32-bit byte offsets).
@@ -208,7 +212,7 @@ int stencil_stream_segment_rows(const stencil_t *st, int wavefronts_per_simd, in
 
 /* Launch options.  STENCIL_OPT_XCD_REMAP (default 1): workgroups are numbered so that each of
  * the eight XCDs (each with its own L2) works on one contiguous band of tiles.
- * STENCIL_OPT_TEMPORAL_DEPTH (default 2): applications fused into one launch, 1..
+ * STENCIL_OPT_TEMPORAL_DEPTH (default 2): applications fused into one launch (at least), 1..
  * STENCIL_MAX_TEMPORAL_DEPTH under STENCIL_STAGING_TEMPORAL, 1..STENCIL_MAX_STREAM_DEPTH under
  * STENCIL_STAGING_STREAM (a depth above 4 makes every size illegal under the former).
  * STENCIL_OPT_SWEEP_CUTOFF (default 0 = off; otherwise a percentage >= 100): adaptive sampling
@@ -227,7 +231,7 @@ int stencil_stream_segment_rows(const stencil_t *st, int wavefronts_per_simd, in
  * out-of-resources error instead, which stencil_run returns as STENCIL_E_REFUSED and the sweeps
  * record as a refused size.
  * STENCIL_OPT_LIFE_TILE (default 0: the library chooses) is the tile of LIFE under
- * STENCIL_STAGING_STREAM: (rows of a work-item << 16) | lanes that hold a row of the tile, of 4, 8 or
+ * STENCIL_STAGING_STREAM (and, if it has rows left, of runs of several launches under STENCIL_STAGING_TEMPORAL): (rows of a work-item << 16) | lanes that hold a row of the tile, of 4, 8 or
  * 16 rows and 16, 32 or 64 lanes.  A launch whose tile has no rows left beside its rim is refused. */
 #define STENCIL_MAX_TEMPORAL_DEPTH 4   /* STENCIL_STAGING_TEMPORAL */
 #define STENCIL_MAX_STREAM_DEPTH 8     /* STENCIL_STAGING_STREAM */

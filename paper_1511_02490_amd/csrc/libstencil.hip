@@ -291,12 +291,14 @@ int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *p
     }
     // `per` applications per launch; the launches alternate between `out` and the scratch
     // matrix so that the last one lands in `out`
-    const int per = v->fuses ? s->temporal_depth : 1;
-    const int launches = launches_of(s, v, iters);
-    // (or, where the kernel can hand on packed bits, between two such matrices, which the scratch matrix
-    // holds both of unless its rows are shorter than two words are in bytes)
+    int per = v->fuses ? s->temporal_depth : 1;
+    const int run_per = v->per_launch && iters > per ? v->per_launch(s, iters, wr, wc) : 0;
+    if (run_per > 0) per = run_per;
+    const int launches = (iters + per - 1) / per;
+    // (or, of Life, between two matrices of packed bits, which the scratch matrix holds both of unless its rows are
+    // shorter than two words are in bytes)
     const size_t packed_bytes = (size_t)s->rows * (size_t)life_words(s) * 4;
-    const bool packed = v->launch_packed && launches > 1 && 2 * packed_bytes <= s->bytes();
+    const bool packed = run_per > 0 && s->kernel == STENCIL_LIFE && launches > 1 && 2 * packed_bytes <= s->bytes();
     void *const halves[2] = {pingpong, static_cast<char *>(pingpong) + (packed ? packed_bytes : 0)};
     const void *src = in;
     void *dst = packed ? halves[0] : (launches % 2 == 1) ? out : pingpong;
@@ -306,8 +308,8 @@ int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *p
         if (packed && last) dst = out;
         const bool injected = s->fail_rows == -1 || (s->fail_rows == wr && s->fail_cols == wc);
         hipError_t e = injected ? hipErrorLaunchOutOfResources
-                       : packed ? v->launch_packed(s, src, src != in, dst, !last, wr, wc, now, stream)
-                                : v->launch(s, src, dst, wr, wc, now, stream);
+                       : run_per > 0 ? v->launch_run(s, src, packed && src != in, dst, packed && !last, wr, wc, now, stream)
+                                     : v->launch(s, src, dst, wr, wc, now, stream);
         if (e != hipSuccess) return launch_failure(e, wr, wc);
         done += now;
         src = dst;

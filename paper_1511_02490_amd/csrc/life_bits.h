@@ -23,6 +23,31 @@ __device__ __forceinline__ uint4 unpack_cells16(uint32_t bits) {
     return make_uint4(unpack_cells(bits, 0), unpack_cells(bits, 1), unpack_cells(bits, 2), unpack_cells(bits, 3));
 }
 
+// The first n < 16 of 16 cells in bytes, a row's last ones: in pieces of 8, 4, 2 and 1.  (One by one they were a
+// third of a launch: eight generations of 300 x 300, of which a row ends with 12 cells, 13.0 us, now 8.1.)
+__device__ __forceinline__ void store_first_cells(uint8_t *out, uint4 cells, int n) {
+    typedef uint16_t any_half __attribute__((aligned(1), may_alias));
+    uint32_t lo = cells.x, hi = cells.y, next = cells.z, last = cells.w;
+    if (n & 8) {
+        any_word2 v;
+        v.x = lo, v.y = hi;
+        *reinterpret_cast<any_word2 *>(out) = v;
+        out += 8;
+        lo = next, hi = last;
+    }
+    if (n & 4) {
+        *reinterpret_cast<any_word *>(out) = lo;
+        out += 4;
+        lo = hi;
+    }
+    if (n & 2) {
+        *reinterpret_cast<any_half *>(out) = (uint16_t)lo;
+        out += 2;
+        lo >>= 16;
+    }
+    if (n & 1) *out = (uint8_t)lo;
+}
+
 // Every cell's west (east) neighbour, given the word before (after).
 __device__ __forceinline__ uint32_t west_of(uint32_t x, uint32_t before) { return __builtin_amdgcn_alignbit(x, before, 31); }
 __device__ __forceinline__ uint32_t east_of(uint32_t x, uint32_t after) { return __builtin_amdgcn_alignbit(after, x, 1); }
@@ -118,7 +143,8 @@ __device__ __forceinline__ uint32_t life_bits16_narrow(const uint8_t *in, int gr
 // generation, CLAMP ones are not kept - the rows' sums take the edge cell itself there.
 // What bounds a launch of four generations is the launch itself, its loads and its stores; a generation of
 // a 128 x 128 tile is one pass of 512 work-items and 0.65 us.  (1001 x 1503 cells, tiles of 128 x 128, CLAMP:
-// 30.5 us with packed bytes and a search for clamped cells after every generation, now 6.5 us.)
+// 30.5 us with packed bytes and a search for clamped cells after every generation, now 6.5 us.  Runs of several launches of
+// workgroups of whole wavefronts are made by life_stream_kernel, which may fuse more.)
 template <int B, int CR, int MAXT>
 __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLife, HaloC<1, 1, 1, 1>> a,
                                                              const int depth) {
@@ -236,10 +262,7 @@ __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLi
         if (c + CC <= cols) {
             store_word4(out, o, a.nt_store != 0);
         } else {
-            const uint32_t w[4] = {o.x, o.y, o.z, o.w};
-#pragma unroll
-            for (int b = 0; b < CC; ++b)
-                if (c + b < cols) out[b] = (uint8_t)(w[b >> 2] >> (8 * (b & 3)));
+            store_first_cells(out, o, cols - c);
         }
         up = mid;
         mid = dn;

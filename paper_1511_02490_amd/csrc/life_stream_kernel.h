@@ -5,24 +5,30 @@
 // west and east neighbours come from the adjacent lanes by cross-lane moves, and only the first and the last
 // row of every work-item pass through local memory, behind one barrier (two buffers in turn).  What a generation
 // computes within k rows or cells of the tile's rim is stale after k generations: `depth` rows above and below
-// and a word left and right are not written.  WRAP and CONSTANT borders: a periodic copy evolves like its
-// original, a padded cell is set back after every generation.
+// and a word left and right are not written.
+//
+// Borders.  WRAP: a periodic copy evolves like its original.  CLAMP and CONSTANT: the first tile of a column of
+// tiles begins with the matrix's first row and the last one ends with its last, so that what a row lacks above or
+// below is found once per work-item and generation (itself, or the padding) and not looked for at every row; at
+// the west and east edge a cell takes itself for the neighbour it lacks, or the cells outside are set back.
 //
 // Between the launches of a run the matrix is kept as bits, rows of whole words: the first launch turns bytes
 // into bits, the last one bits into bytes, and the launches between them move an eighth of the bytes.  They are
-// bound by the generations' serial chain (a row's sums, the barrier, the rule), not by memory: the tile is cut
-// so that the device's wavefronts are filled evenly and its rim repeats as little as possible (life_tile in
-// variants.h).
-// (100 generations of 4096 x 4096, WRAP, 8 per launch: 282 -> 121 us, before by marching packed bytes down the
-// matrix; between two launches in bits one of 8 generations takes 9.3 us, 0.53 each and 5.1 for the launch, its loads and its
-// stores.)
+// bound by the generations' serial chain (a row's sums, the barrier, the rule), not by memory, and by what a launch,
+// its loads and its stores cost whatever it computes: the tile is cut, and the generations of a run are dealt to
+// launches, so that both are small together (life_tile and life_per_launch in variants.h).
+// (100 generations of 4096 x 4096, WRAP: 282 us by marching packed bytes down the matrix, 121 on bits with 8 to a
+// launch, 77 with 20 or 25.  50 generations of 1001 x 1503, CLAMP: 83 us by life_temporal_kernel, 4 to a launch from
+// bytes to bytes, 24 here with 17.)
 #pragma once
 #include "life_bits.h"
 
 namespace sk {
 
-constexpr int kLifeStreamMaxDepth = 8;      // (the rim of 32 cells would allow more)
-constexpr int kLifeStreamMaxThreads = 256;
+constexpr int kLifeStreamMaxDepth = 32;     // generations that the rim, a word of cells a side, is right for
+// Workgroups: of 16 rows per work-item (the registers of a launch that reads bytes) up to 256 work-items.
+constexpr int life_stream_max_threads(int rows_per_item) { return rows_per_item == 16 ? 256 : 1024; }
+constexpr unsigned life_stream_lds(int threads) { return 4 * (unsigned)threads * (unsigned)sizeof(uint32_t); }
 
 struct LifeStreamArgs {
     const void *in;
@@ -35,27 +41,37 @@ struct LifeStreamArgs {
 };
 
 template <int B, int RPT, bool IN_BITS, bool OUT_BITS>
-__global__ __launch_bounds__(kLifeStreamMaxThreads) void life_stream_kernel(const LifeStreamArgs a, const int depth) {
-    static_assert(B == kWrap || B == kConstant, "wrap and constant borders only");
+__global__ __launch_bounds__(life_stream_max_threads(RPT)) void life_stream_kernel(const LifeStreamArgs a, const int depth) {
     const int tid = (int)threadIdx.y * (int)blockDim.x + (int)threadIdx.x, nthreads = (int)(blockDim.x * blockDim.y);
     const int G = 1 << a.group_shift, groups = nthreads >> a.group_shift;
     const int rows = a.rows, cols = a.cols;
     const int tile_r = (int)blockIdx.x / a.tiles_c, tile_c = (int)blockIdx.x - tile_r * a.tiles_c;
     const int word = tile_c * (G - 2) - 1 + (tid & (G - 1)), col = word * 32;
-    const int tile_rows = groups * RPT - 2 * depth;                    // the rows it writes
-    const int row0 = tile_r * tile_rows - depth + (tid >> a.group_shift) * RPT;
+    const int held = groups * RPT, step = held - 2 * depth;            // rows of the tile; the rows from one tile to the next
+    // the first row it holds, and the rows it writes
+    int top, begin, end;
+    if (B == kWrap) {
+        top = tile_r * step - depth;
+        begin = tile_r * step;
+        end = min(rows, begin + step);
+    } else {
+        top = max(0, min(tile_r * step, rows - held));
+        begin = tile_r == 0 ? 0 : tile_r * step + depth;
+        end = tile_r * step + held >= rows ? rows : (tile_r + 1) * step + depth;
+    }
+    const int row0 = top + (tid >> a.group_shift) * RPT;
     const uint32_t pad = a.pad ? ~0u : 0u;
     const uint32_t inside = inside_bits(col, cols);
 
-    // the matrix rows it loads: under WRAP row0's and, going round, those after it; under CONSTANT any where there is none
+    // the matrix rows it loads: under WRAP row0's and, going round, those after it; else any where there is none
     int gr[RPT];
-    gr[0] = B == kWrap ? resolve<kWrap>(row0, rows) : max(0, min(row0, rows - 1));
+    gr[0] = B == kWrap ? resolve<kWrap>(row0, rows) : min(row0, rows - 1);
 #pragma unroll
     for (int i = 1; i < RPT; ++i) {
         if (B == kWrap)
             gr[i] = gr[i - 1] + 1 == rows ? 0 : gr[i - 1] + 1;
         else
-            gr[i] = max(0, min(row0 + i, rows - 1));
+            gr[i] = min(row0 + i, rows - 1);
     }
     uint32_t x[RPT];
     if constexpr (IN_BITS) {
@@ -107,45 +123,84 @@ __global__ __launch_bounds__(kLifeStreamMaxThreads) void life_stream_kernel(cons
             }
         }
     }
+    // does the tile reach outside the matrix, east or west, and below (a matrix lower than a tile)?  The same for the
+    // whole workgroup.
+    const bool at_sides = tile_c == 0 || (tile_c + 1) * (G - 2) * 32 + 32 > cols, below_matrix = held > rows;
     // CONSTANT: cells that are not matrix cells hold the padding
-    const bool at_border = B == kConstant && (tile_r * tile_rows < depth || tile_r * tile_rows + tile_rows + depth > rows ||
-                                              tile_c == 0 || (tile_c + 1) * (G - 2) * 32 + 32 > cols);
     auto pad_outside = [&] {
-        if (!at_border) return;
+        int below = rows - row0;
+        asm volatile("" : "+v"(below));         // (or the rows' masks are kept in registers from generation to generation)
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-            const uint32_t keep = (unsigned)(row0 + i) < (unsigned)rows ? inside : 0u;
+            const uint32_t keep = i < below ? inside : 0u;
             x[i] = (x[i] & keep) | (pad & ~keep);
         }
     };
-    pad_outside();
+    if (B == kConstant && (at_sides || below_matrix)) pad_outside();
 
-    // a row with its neighbours from the adjacent lanes; what the two ends of a group of lanes get is no
-    // neighbour, and stays in the rim
-    auto sums = [](uint32_t v) { return life_bits(v, west_of(v, from_lane_below(v)), east_of(v, from_lane_above(v))); };
-    __shared__ uint32_t first_rows[2][kLifeStreamMaxThreads], last_rows[2][kLifeStreamMaxThreads];
+    // CLAMP: the columns outside are not kept; a cell at the matrix's edge takes itself for the neighbour it lacks
+    const uint32_t first = column_bit(col, 0), last = column_bit(col, cols - 1);
+    extern __shared__ __align__(16) unsigned char lds_raw[];      // two buffers of the work-items' first and last rows
+    uint32_t *first_rows = reinterpret_cast<uint32_t *>(lds_raw), *last_rows = first_rows + nthreads;
     const int above_at = max(0, tid - G), below_at = min(tid + G, nthreads - 1);
-    for (int k = 0; k < depth; ++k) {
-        first_rows[k & 1][tid] = x[0];
-        last_rows[k & 1][tid] = x[RPT - 1];
-        LifeBits h[RPT];
+    const bool no_above = row0 == 0, no_below = row0 + RPT == rows;
+    // EDGE, BELOW: the tile has an edge of the matrix (and may reach outside it east or west); below_matrix
+    auto generations = [&](auto EDGE, auto BELOW) {
+        constexpr bool kEdge = decltype(EDGE)::value, kBelow = decltype(BELOW)::value;
+        // a row with its neighbours from the adjacent lanes; what the two ends of a group of lanes get is no
+        // neighbour, and stays in the rim
+        auto sums = [&](uint32_t v) {
+            uint32_t w = west_of(v, from_lane_below(v)), e = east_of(v, from_lane_above(v));
+            if (B == kClamp && kEdge) {
+                w = (w & ~first) | (v & first);
+                e = (e & ~last) | (v & last);
+            }
+            return life_bits(v, w, e);
+        };
+        auto next = [&](const LifeBits &up, const LifeBits &mid, const LifeBits &dn, int i) {
+            return life_next(up, mid, B == kClamp && kBelow && row0 + i == rows - 1 ? mid : dn);
+        };
+        for (int k = 0; k < depth; ++k) {
+            const int buffer = (k & 1) * 2 * nthreads;
+            first_rows[buffer + tid] = x[0];
+            last_rows[buffer + tid] = x[RPT - 1];
+            LifeBits h[RPT];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) h[i] = sums(x[i]);
-        __syncthreads();
-        const uint32_t above = last_rows[k & 1][above_at], below = first_rows[k & 1][below_at];
+            for (int i = 0; i < RPT; ++i) h[i] = sums(x[i]);
+            const uint32_t x_first = x[0], x_last = x[RPT - 1];
 #pragma unroll
-        for (int i = 1; i < RPT - 1; ++i) x[i] = life_next(h[i - 1], h[i], h[i + 1]);
-        x[0] = life_next(sums(above), h[0], h[1]);
-        x[RPT - 1] = life_next(h[RPT - 2], h[RPT - 1], sums(below));
-        pad_outside();
-    }
+            for (int i = 1; i < RPT - 1; ++i) x[i] = next(h[i - 1], h[i], h[i + 1], i);
+            __syncthreads();
+            uint32_t above = last_rows[buffer + above_at], below = first_rows[buffer + below_at];
+            if (kEdge) {
+                above = no_above ? (B == kClamp ? x_first : pad) : above;
+                below = no_below ? (B == kClamp ? x_last : pad) : below;
+            }
+            x[0] = next(sums(above), h[0], h[1], 0);
+            x[RPT - 1] = next(h[RPT - 2], h[RPT - 1], sums(below), RPT - 1);
+            if (B == kConstant) {
+                if (kBelow) {
+                    pad_outside();
+                } else if (kEdge) {
+#pragma unroll
+                    for (int i = 0; i < RPT; ++i) x[i] = (x[i] & inside) | (pad & ~inside);
+                }
+            }
+        }
+    };
+    if (B != kWrap && below_matrix)
+        generations(std::true_type{}, std::true_type{});
+    else if (B != kWrap && (at_sides || top == 0 || top + held == rows))
+        generations(std::true_type{}, std::false_type{});
+    else
+        generations(std::false_type{}, std::false_type{});
 
-    const int lane = tid & (G - 1), end = min(rows, tile_r * tile_rows + tile_rows);
+    const int lane = tid & (G - 1);
     if (lane == 0 || lane == G - 1 || word >= a.words) return;
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
         const int r = row0 + i;
-        if (r < tile_r * tile_rows || r >= end) continue;
+        if (r < begin || r >= end) continue;
         if constexpr (OUT_BITS) {
             static_cast<uint32_t *>(a.out)[(unsigned)(r * a.words + word)] = x[i];
         } else {
@@ -155,11 +210,8 @@ __global__ __launch_bounds__(kLifeStreamMaxThreads) void life_stream_kernel(cons
                 const uint4 o = unpack_cells16(x[i] >> (16 * half));
                 if (col + 16 * half + 16 <= cols) {
                     store_word4(out + 16 * half, o, a.nt_store != 0);
-                } else {
-                    const uint32_t w[4] = {o.x, o.y, o.z, o.w};
-#pragma unroll
-                    for (int b = 0; b < 16; ++b)
-                        if (col + 16 * half + b < cols) out[16 * half + b] = (uint8_t)(w[b >> 2] >> (8 * (b & 3)));
+                } else if (col + 16 * half < cols) {
+                    store_first_cells(out + 16 * half, o, cols - (col + 16 * half));
                 }
             }
         }

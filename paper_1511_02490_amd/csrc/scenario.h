@@ -14,10 +14,11 @@
 // (scenario, in, out, wg_rows, wg_cols, applications fused into this launch, stream)
 using LaunchFn = hipError_t (*)(const stencil *, const void *, void *, int, int, int, hipStream_t);
 
-// The same between matrices of cells and of packed bits (Life: one bit per cell, rows of whole 32-bit words), the
-// form in which the launches of one run may hand each other the matrix.
-using PackedLaunchFn = hipError_t (*)(const stencil *, const void *in, bool in_bits, void *out, bool out_bits, int wg_rows,
-                                      int wg_cols, int fused, hipStream_t);
+// A launch of a run of several, which may fuse more applications than the handle's depth (Variant::per_launch), between
+// matrices of cells and (Life) of packed bits - one bit per cell, rows of whole 32-bit words - the form in which the
+// launches of one run may hand each other the matrix.
+using RunLaunchFn = hipError_t (*)(const stencil *, const void *in, bool in_bits, void *out, bool out_bits, int wg_rows,
+                                   int wg_cols, int fused, hipStream_t);
 
 struct Variant {
     int staging;          // STENCIL_STAGING_LOCAL, _DIRECT, _TEMPORAL or _STREAM
@@ -29,7 +30,10 @@ struct Variant {
     int staged_bytes;     // bytes per staged element in LDS
     bool fuses = false;   // a launch makes `temporal_depth` applications instead of one
     LaunchFn launch;
-    PackedLaunchFn launch_packed = nullptr;
+    // where runs of several launches have a kernel of their own: the applications it makes per launch of a run of so many
+    // (0: the run is made by `launch`), and its launcher
+    int (*per_launch)(const stencil *, int iters, int wg_rows, int wg_cols) = nullptr;
+    RunLaunchFn launch_run = nullptr;
     // the compiled kernel a launch of this scenario would start (what hipFuncGetAttributes is asked about)
     const void *(*kernel_of)(const stencil *) = nullptr;
 };

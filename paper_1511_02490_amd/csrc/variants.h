@@ -210,43 +210,86 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
     return hipGetLastError();
 }
 
-// The tile of a Life launch (life_stream_kernel.h): rows per work-item and lanes per row.  A generation takes as
-// long as the wavefronts of a SIMD take for their rows and for what a generation costs whatever their number (about
-// kOverheadRows rows' worth), one wavefront's time at least; narrow tiles also load and store shorter pieces of
-// rows, which costs a launch up to a quarter.  (us per launch of 8 generations with 256 work-items, rows per item x
-// lanes: 4096 x 4096 4x16 9.8, 8x16 10.3, 8x32 9.8, 8x64 11.2, 16x16 11.0, 16x32 10.4, 16x64 11.1; 256 x 256 4x16
-// 4.6, 4x32 4.8, 8x32 6.2, 16x32 8.2.  12 rows per item cost more than 16 on either.)  A launch that reads bytes
-// has 32 registers per row under way: 16 rows leave room for two wavefronts per SIMD, too few to keep the memory
-// busy (8192 x 8192, one generation: 4x32 25.5, 8x32 23.5, 16x32 27.6).  And a single generation on a matrix that is up to three
-// wavefronts of four-row items per SIMD (the rim aside) is over before eight rows' loads are in (4096 x 4096: 8.0, 9.3, 10.7).
+// The tile of a Life launch (life_stream_kernel.h): rows per work-item and lanes per row.  A generation takes as long
+// as the wavefronts of a SIMD take for their rows and for what a generation costs whatever their number (some rows' worth);
+// narrow tiles also load and store shorter pieces of rows.  Two rules:
+// - A launch of as many generations as the handle asks for, or fewer, is as much loading and storing as computing, and its
+//   tiles come and go: wavefronts are counted over the whole device, one at least, and narrow tiles cost up to a quarter.
+//   (us per launch of 8 generations with 256 work-items, rows per item x lanes: 4096 x 4096 4x16 9.8, 8x16 10.3, 8x32 9.8,
+//   8x64 11.2, 16x16 11.0, 16x32 10.4, 16x64 11.1; 256 x 256 4x16 4.6, 4x32 4.8, 8x32 6.2, 16x32 8.2.)  A launch that reads
+//   bytes has 32 registers per row under way: 16 rows leave room for two wavefronts per SIMD, too few to keep the memory busy
+//   (8192 x 8192, one generation: 4x32 25.5, 8x32 23.5, 16x32 27.6).  And a single generation on a matrix that is up to three
+//   wavefronts of four-row items per SIMD (the rim aside) is over before eight rows' loads are in (4096 x 4096: 8.0, 9.3, 10.7).
+// - A launch of more is a long stay of few tiles: its generations take what the SIMDs of the fullest compute unit take.
+//   (us per generation / rows by this rule, rows per item x lanes, workgroup, generations per launch: 4096 x 4096, WRAP, 8x16,
+//   256, 20 0.55 / 20; 8x16, 512, 25 0.54 / 20; 4x16, 1024, 25 0.55 / 20; 16x16, 256, 25 0.66 / 20; 1001 x 1503, CLAMP, 2x16,
+//   512, 17 0.21 / 8.  By the first rule runs of 400 generations on 2048 x 2048 take 211 us, 170 by this.)
 struct LifeTile {
     int rows_per_item = 0, group_shift = 0;
-    int tile_rows = 0;       // rows a tile writes
+    int tiles_r = 0, tiles_c = 0;
+    double rows_worth = 0.0;         // of a generation, in rows of a SIMD
 };
+constexpr double kLifeRowUs = 0.028, kLifeLaunchUs = 4.5;
 LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
-    constexpr int kOverheadRows = 2;
-    const double simds = 4.0 * stencil_compute_units();
-    const int64_t rows = s->rows, words = life_words(s);
-    const double four_row_waves = (double)rows * (double)words / (4 * 64);
+    const bool as_asked = depth <= s->temporal_depth;
+    const int units = stencil_compute_units(), rows = (int)s->rows, words = (int)life_words(s), wave_count = threads / 64;
+    const double simds = 4.0 * units;
+    const bool few_rows = from_bytes && depth == 1 && (double)rows * words / (4 * 64) <= 3.0 * simds;
     LifeTile best;
-    double best_cost = 0.0;
-    for (int shift = 4; shift <= 6; ++shift)
-        for (int rpt = 4; rpt <= 16; rpt *= 2) {
-            const int tile_rows = (threads >> shift) * rpt - 2 * depth;
-            if (tile_rows <= 0 || (s->life_rows && (rpt != s->life_rows || 1 << shift != s->life_lanes))) continue;
-            const int64_t strips = (words + (1 << shift) - 3) / ((1 << shift) - 2);
-            const double waves = (double)strips * (double)((rows + tile_rows - 1) / tile_rows) * (threads / 64);
-            if (s->life_rows == 0 && from_bytes && depth == 1 && rpt > 4 && best.tile_rows > 0 && four_row_waves <= 3.0 * simds) continue;
-            const double cost = std::max(1.0, waves / simds) * (rpt + kOverheadRows) *
-                                (shift == 4 ? 1.25 : shift == 5 ? 1.05 : 1.0) * (from_bytes && rpt == 16 ? 1.3 : 1.0);
-            if (best.tile_rows == 0 || cost < best_cost) {
+    for (int shift = 4; shift <= 6; ++shift) {
+        const int strips = words / ((1 << shift) - 2) + (words % ((1 << shift) - 2) != 0);
+        for (int rpt = as_asked ? 4 : 2; rpt <= 16; rpt *= 2) {
+            const int held = (threads >> shift) * rpt, step = held - 2 * depth;
+            if (step <= 0 || threads > sk::life_stream_max_threads(rpt)) continue;
+            if (s->life_rows ? rpt != s->life_rows || 1 << shift != s->life_lanes : few_rows && rpt > 4 && best.tiles_r > 0) continue;
+            const int steps = (rows - 1) / step + 1;
+            const int tiles = s->border == STENCIL_WRAP ? steps : rows <= held ? 1 : (rows - held - 1) / step + 2;
+            double cost;
+            if (as_asked) {
+                cost = std::max(1.0, (double)strips * steps * wave_count / simds) * (rpt + 2) *
+                       (shift == 4 ? 1.25 : shift == 5 ? 1.05 : 1.0) * (from_bytes && rpt == 16 ? 1.3 : 1.0);
+            } else {
+                const int64_t fullest = ((int64_t)strips * tiles + units - 1) / units * wave_count;      // wavefronts
+                cost = ((double)((fullest + 3) / 4) * rpt + 4) * (shift == 4 ? 1.05 : shift == 5 ? 1.02 : 1.0) *
+                       (rpt == 16 ? 1.12 : 1.0);
+            }
+            if (best.tiles_r == 0 || cost < best.rows_worth) {
                 best.rows_per_item = rpt;
                 best.group_shift = shift;
-                best.tile_rows = tile_rows;
-                best_cost = cost;
+                best.tiles_r = tiles;
+                best.tiles_c = strips;
+                best.rows_worth = cost;
             }
         }
+    }
     return best;
+}
+
+// Generations per launch of a run that takes several launches: a launch costs as much as some ten generations do
+// (kLifeLaunchUs), but every generation fused repeats two more rows of every tile.  At least the number asked for, as far as
+// it divides the run into the same launches, and exactly that where the tile is prescribed or nothing is to be fused.  0: the workgroup is no
+// whole wavefronts, or too small for a tile.
+int life_per_launch(const stencil *s, int iters, int wr, int wc) {
+    const int threads = wr * wc;
+    if (threads % 64 != 0) return 0;
+    if (s->life_rows != 0 || s->temporal_depth == 1)
+        return s->staging == STENCIL_STAGING_STREAM || life_tile(s, threads, s->temporal_depth, false).tiles_r > 0 ? s->temporal_depth : 0;
+    int best = s->temporal_depth, launches_before = 0;
+    double best_us = 0.0;
+    for (int d = s->temporal_depth; d <= sk::kLifeStreamMaxDepth; ++d) {
+        const int launches = (iters + d - 1) / d;
+        if (launches == launches_before) continue;
+        launches_before = launches;
+        const int per = (iters + launches - 1) / launches;
+        const LifeTile t = life_tile(s, threads, per, false);
+        if (t.tiles_r == 0) break;
+        const double us = launches * (kLifeLaunchUs + per * t.rows_worth * kLifeRowUs);
+        if (best_us == 0.0 || us < best_us) {
+            best_us = us;
+            best = per;
+        }
+    }
+    return best_us == 0.0 ? 0 : best;
 }
 
 // Game of Life, `depth` generations per launch in registers, from and to a matrix of bytes or of bits.
@@ -260,28 +303,31 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     a.cols = (int)s->cols;
     a.words = (int)life_words(s);
     const LifeTile t = life_tile(s, wr * wc, depth, !IN_BITS);
-    if (t.tile_rows == 0) return hipErrorInvalidValue;
+    if (t.tiles_r == 0) return hipErrorInvalidValue;
     a.group_shift = t.group_shift;
-    a.tiles_c = (a.words + (1 << t.group_shift) - 3) / ((1 << t.group_shift) - 2);
-    a.n_tiles = a.tiles_c * (int)((s->rows + t.tile_rows - 1) / t.tile_rows);
+    a.tiles_c = t.tiles_c;
+    a.n_tiles = t.tiles_r * t.tiles_c;
     a.pad = s->pad != 0.0;
     a.nt_store = s->nt_store;
     const dim3 grid((unsigned)a.n_tiles), block(wc, wr);
+    const unsigned lds = sk::life_stream_lds(wr * wc);
     switch (t.rows_per_item) {
-    case 4: hipLaunchKernelGGL((sk::life_stream_kernel<B, 4, IN_BITS, OUT_BITS>), grid, block, 0, stream, a, depth); break;
-    case 8: hipLaunchKernelGGL((sk::life_stream_kernel<B, 8, IN_BITS, OUT_BITS>), grid, block, 0, stream, a, depth); break;
-    default: hipLaunchKernelGGL((sk::life_stream_kernel<B, 16, IN_BITS, OUT_BITS>), grid, block, 0, stream, a, depth); break;
+    case 2: hipLaunchKernelGGL((sk::life_stream_kernel<B, 2, IN_BITS, OUT_BITS>), grid, block, lds, stream, a, depth); break;
+    case 4: hipLaunchKernelGGL((sk::life_stream_kernel<B, 4, IN_BITS, OUT_BITS>), grid, block, lds, stream, a, depth); break;
+    case 8: hipLaunchKernelGGL((sk::life_stream_kernel<B, 8, IN_BITS, OUT_BITS>), grid, block, lds, stream, a, depth); break;
+    default: hipLaunchKernelGGL((sk::life_stream_kernel<B, 16, IN_BITS, OUT_BITS>), grid, block, lds, stream, a, depth); break;
     }
     return hipGetLastError();
 }
 template <int B>
 hipError_t launch_life_stream(const stencil *s, const void *in, void *out, int wr, int wc, int depth, hipStream_t stream) {
-    if (depth < 1 || depth > sk::kLifeStreamMaxDepth) return hipErrorInvalidValue;
+    if (depth < 1 || depth > STENCIL_MAX_STREAM_DEPTH) return hipErrorInvalidValue;
     return launch_life_stream_formats<B, false, false>(s, in, out, wr, wc, depth, stream);
 }
+// ... a launch of a run of several, also where the mapping is the local-memory temporal one.
 template <int B>
-hipError_t launch_life_stream_packed(const stencil *s, const void *in, bool in_bits, void *out, bool out_bits, int wr, int wc,
-                                     int depth, hipStream_t stream) {
+hipError_t launch_life_stream_run(const stencil *s, const void *in, bool in_bits, void *out, bool out_bits, int wr, int wc,
+                                  int depth, hipStream_t stream) {
     if (depth < 1 || depth > sk::kLifeStreamMaxDepth) return hipErrorInvalidValue;
     if (in_bits && out_bits) return launch_life_stream_formats<B, true, true>(s, in, out, wr, wc, depth, stream);
     if (in_bits) return launch_life_stream_formats<B, true, false>(s, in, out, wr, wc, depth, stream);
@@ -598,27 +644,29 @@ void reg_stream(std::vector<Variant> &r) {
     reg_stream_one<Op, KID, sk::kConstant>(r);
 }
 
-template <int B>
-void reg_life_stream_one(std::vector<Variant> &r, int cells) {
+template <int B, int CELLS>
+void reg_life_stream_one(std::vector<Variant> &r) {
     Variant v;
     v.staging = STENCIL_STAGING_STREAM;
     v.kernel = STENCIL_LIFE;
     v.border = B;
     v.hn = v.hs = v.he = v.hw = 1;
     v.cr = 0;
-    v.cc = cells;
-    v.max_threads = sk::kLifeStreamMaxThreads;
+    v.cc = CELLS;
+    v.max_threads = sk::life_stream_max_threads(16);
     v.staged_bytes = 0;
     v.fuses = true;
     v.launch = &launch_life_stream<B>;
-    v.launch_packed = &launch_life_stream_packed<B>;
+    v.per_launch = &life_per_launch;
+    v.launch_run = &launch_life_stream_run<B>;
     v.kernel_of = &kernel_life_stream<B>;
     r.push_back(v);
 }
 
-inline void reg_life_stream(std::vector<Variant> &r, int cells) {
-    reg_life_stream_one<sk::kWrap>(r, cells);
-    reg_life_stream_one<sk::kConstant>(r, cells);
+template <int CELLS>
+void reg_life_stream(std::vector<Variant> &r) {
+    reg_life_stream_one<sk::kWrap, CELLS>(r);
+    reg_life_stream_one<sk::kConstant, CELLS>(r);
 }
 
 template <int B, int CR, int CC>
@@ -712,6 +760,8 @@ void reg_life_temporal_one(std::vector<Variant> &r) {
     v.staged_bytes = 1;
     v.fuses = true;
     v.launch = &launch_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;
+    v.per_launch = &life_per_launch;
+    v.launch_run = &launch_life_stream_run<B>;
     v.kernel_of = &kernel_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);
 }

@@ -1,4 +1,4 @@
-// Variants: the direct kernels and the local-memory temporal kernels.
+// Variants: the direct kernels and the local-memory temporal kernels of floats.
 #include "variants.h"
 
 void register_direct_and_temporal(std::vector<Variant> &r) {
@@ -15,10 +15,6 @@ void register_direct_and_temporal(std::vector<Variant> &r) {
     reg_temporal<sk::OpWeightedSum, STENCIL_WEIGHTED_SUM, 8>(r);
     reg_direct<sk::OpSobel, STENCIL_SOBEL, sk::HaloC<1, 1, 1, 1>, 4>(r);
     reg_direct<sk::OpNms, STENCIL_NMS, sk::HaloC<1, 1, 1, 1>, 4>(r);
-    reg_life_temporal<1>(r);
-    reg_life_temporal<2>(r);
-    reg_life_temporal<4>(r);
-    reg_life_temporal<8>(r);
     reg_life_direct<1>(r);
     reg_life_direct<2>(r);
     reg_life_direct<4>(r);

@@ -679,6 +679,39 @@ def test_every_tile_of_the_life_streams(ls, border, rows_per_item, lanes):
             st.close()
 
 
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("tile", [None, (4, 16), (8, 32), (16, 64)])
+def test_life_runs_of_several_launches(ls, border, tile):
+    """Runs whose launches fuse more generations than asked for, and (a tile prescribed) exactly as many, under both fusing
+    mappings: boards lower than a tile, of exactly its rows, of one and of a few rows more, whose last tile then begins
+    within the one before; boards narrower than a word; rows that end in a word's first, last and middle cell."""
+    mappings = [(("temporal", 2, 16, 4), (4, 64)), (("temporal", 1, 16, 3), (1, 64)), (("temporal", 4, 16, 2), (16, 64))]
+    if border != "clamp":
+        mappings.append((("stream", 16, 8, 8), (4, 64)))
+    for blocking, wg in mappings:
+        lanes, per_item = (tile[1], tile[0]) if tile else (16, 4)
+        held = wg[0] * wg[1] // lanes * per_item
+        for rows, cols in [(1, 5), (held - 1, 31), (held, 33), (held + 1, 65), (2 * held - 7, 32 * (lanes - 2) + 1)]:
+            if rows < 1 or rows * cols > 300000:
+                continue
+            for iters in (blocking[3] + 1, 41):
+                w = custom(wl.LIFE, rows, cols, (1, 1, 1, 1), border, pad=1.0, seed=rows + cols, iters=iters)
+                st = ls.Stencil.from_workload(w)
+                set_mapping(st, blocking)
+                if tile:
+                    st.set_option(ls.OPT_LIFE_TILE, (tile[0] << 16) | tile[1])
+                g = w.grid()
+                tin = torch.from_numpy(g).cuda()
+                tout = torch.full_like(tin, 9)
+                try:
+                    st.run(tin, tout, iters, wg)
+                except ls.StencilError:                # a prescribed tile without a row beside its rim
+                    assert blocking[0] == "stream" and tile and held <= 2 * blocking[3]
+                else:
+                    np.testing.assert_array_equal(tout.cpu().numpy(), oracle.apply_workload(w, g))
+                st.close()
+
+
 @pytest.mark.parametrize("border", ["wrap", "constant"])
 def test_register_streaming_life_bit_exact(ls, border):
     """Generations kept in registers: matrices wider than one tile, ragged ones, ones smaller than a
