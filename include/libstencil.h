@@ -146,7 +146,7 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            the tile plus a border region STENCIL_OPT_TEMPORAL_DEPTH cells deep in local
  *            memory and advances it by that many applications before writing it back, so a
  *            stencil_run of `iters` applications takes at most ceil(iters / depth) launches
- *            (a run of more than one may be made by a kernel that fuses more: see LIFE below).
+ *            (a run of more than one may be made by a kernel that fuses more: see below).
  *            Available for HEAT and WEIGHTED_SUM with region 1/1/1/1 (cells_cols = 4) and
  *            for LIFE (cells_cols = 16); cells_rows in {1,2,4,8}.
  *   cells_rows x cells_cols: block of adjacent cells one work-item computes (register
@@ -162,7 +162,10 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            HEAT and WEIGHTED_SUM with region 1/1/1/1, WRAP and CONSTANT borders: temporal
  *            blocking, the last three rows of every time level stay in registers,
  *            STENCIL_OPT_TEMPORAL_DEPTH applications per launch (up to
- *            STENCIL_MAX_STREAM_DEPTH; one rim lane per side up to 4, two beyond);
+ *            STENCIL_MAX_STREAM_DEPTH; one rim lane per side up to 4, two beyond).  A run of more
+ *            applications than one launch makes, under this mapping or STENCIL_STAGING_TEMPORAL with a
+ *            workgroup of whole wavefronts, is made on tiles in registers, up to 16 applications per launch
+ *            in workgroups of the library's choice, where that is faster (not at a depth of 1);
  *            SINCOS with region N1 S5 E3 W0 and WEIGHTED_SUM (F32), any border mode: one
  *            application per launch, each input row is loaded and pre-processed once and folded
  *            into the N+S+1 output rows it belongs to.  WEIGHTED_SUM regions 2/2/2/2 .. 5/5/5/5

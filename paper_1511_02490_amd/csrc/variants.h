@@ -23,6 +23,11 @@
 
 #include "scenario.h"
 
+// Runs of several launches on tiles in registers (variants_register_tiles.hip): the applications a launch of a run of so
+// many makes, or 0 where the mapping's own kernel makes the run, and the launcher.
+int register_tile_per_launch(const stencil *s, int iters, int wg_rows, int wg_cols);
+RunLaunchFn register_tile_launcher(int kernel, int border);
+
 // Local memory a workgroup may allocate: the device's own figure once a GPU has been used, the
 // header's constant before that (defined in libstencil.hip).
 int64_t stencil_local_memory_limit();
@@ -611,6 +616,8 @@ void reg_temporal_one(std::vector<Variant> &r) {
     v.fuses = true;
     v.launch = &launch_temporal<Op, B, CR, STENCIL_MAX_WG_SIZE>;
     v.kernel_of = &kernel_temporal<Op, B, STENCIL_MAX_WG_SIZE>;
+    v.per_launch = &register_tile_per_launch;
+    v.launch_run = register_tile_launcher(KID, B);
     r.push_back(v);
 }
 
@@ -635,6 +642,8 @@ void reg_stream_one(std::vector<Variant> &r) {
     v.fuses = true;
     v.launch = &launch_stream<Op, B>;
     v.kernel_of = &kernel_stream<Op, B>;
+    v.per_launch = &register_tile_per_launch;
+    v.launch_run = register_tile_launcher(KID, B);
     r.push_back(v);
 }
 

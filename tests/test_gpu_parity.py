@@ -562,6 +562,29 @@ def test_register_streaming_temporal_kernel_bit_exact(ls, border):
         ls.Stencil.from_workload(clamp).set_mapping("stream", 32, 4)
 
 
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+def test_runs_on_tiles_in_registers(ls, border):
+    """Runs of several launches of heat and of the 3x3 sum under both fusing mappings: matrices smaller than a tile either
+    way, of exactly a tile's rows or columns (64 and 128 of either) and one more, of several tiles whose last one begins within
+    the one before, two and four rows per work-item in one and in several tiles per compute unit, odd and even numbers of
+    applications per launch, rows that start at any address; and the bits of the mapping's own kernel (a workgroup that is no whole wavefronts keeps it)."""
+    shapes = [(1, 1), (2, 131), (40, 3), (64, 128), (65, 129), (128, 64), (127, 257), (129, 63), (200, 341), (515, 130), (96, 1501),
+              (1025, 1999), (2200, 2103)]
+    for rows, cols in shapes:
+        for iters, depth in [(5, 4), (9, 2), (29, 4)]:
+            if rows * cols > 1000000 and iters != 29:
+                continue
+            h = wl.config(3, rows=rows, cols=cols, iters=iters)
+            h.border, h.pad = border, 30.0
+            w = custom(wl.WEIGHTED_SUM, rows, cols, (1, 1, 1, 1), border, pad=0.25, seed=rows + cols, iters=iters)
+            check(ls, h, (4, 64), blocking=("temporal", 2, 4, depth), offset=cols % 3)
+            got = check(ls, w, (4, 64), blocking=("temporal", 2, 4, depth), offset=rows % 3)
+            own = gpu_apply(ls, w, w.grid(), (5, 13), blocking=("temporal", 2, 4, depth))
+            np.testing.assert_array_equal(got, own)
+            if border != "clamp":
+                check(ls, h, (4, 64), blocking=("stream", 38, 4, depth))
+
+
 def test_sweeps_over_a_rotation_of_matrix_pairs(ls):
     """stencil_set_sweep_rotation: a sample is `iters` independent applications on the pairs in turn; every
     pair's output is the single application of its own input, the sweep's own out argument is not written,
