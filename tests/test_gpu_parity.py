@@ -765,6 +765,24 @@ def test_register_streaming_life_bit_exact(ls, border):
         ls.Stencil.from_workload(clamp).set_mapping("stream", 32, 16)
 
 
+@pytest.mark.parametrize("wg,blocking", [((5, 7), (2, 4)), ((1, 100), (2, 4)), ((3, 64), (1, 4)),
+                                         ((32, 32), (4, 4)), ((32, 32), (8, 4))])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_tiles_staged_without_registers(ls, wg, blocking, offset):
+    """Staging straight into local memory: workgroups that end in part of a wavefront, rows that start at any element, and
+    tiles of 72 and 141 KiB, whose addresses need more than 16 bits."""
+    rows, cols, halo = 3 * wg[0] * blocking[0] + 5, 3 * wg[1] * blocking[1] + 7, (2, 2, 2, 2)
+    check(ls, custom(wl.WEIGHTED_SUM, rows, cols, halo, "clamp"), wg, blocking=blocking, offset=offset)
+    rng = np.random.default_rng(3)
+    table = rng.integers(-64, 65, size=(6, 6)).astype(np.float32)
+    wi = wl.Workload("i32", rows, cols, "i32", (3, 2, 4, 1), "wrap", 3.0, wl.WEIGHTED_SUM, 1, 6, "pow2", weights=table)
+    if blocking[0] <= 4:
+        check(ls, wi, wg, blocking=blocking, offset=offset)
+        wd = wl.Workload("f64", rows, cols, "f64", halo, "constant", 0.5, wl.WEIGHTED_SUM, 1, 5, "pow2",
+                         weights=rng.random((5, 5), dtype=np.float32))
+        check(ls, wd, wg, blocking=(max(2, blocking[0]), 2), offset=offset)
+
+
 def test_temporal_blocking_not_offered_for_other_regions(ls):
     st = ls.Stencil.from_workload(wl.config(1))                    # 5x5 region
     with pytest.raises(ls.StencilError):
