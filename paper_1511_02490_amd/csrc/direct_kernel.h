@@ -122,7 +122,7 @@ __global__ __launch_bounds__(MAXT) void direct_kernel(const TileArgs<Op, Halo> a
         for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(st[cr][cc], a.scalar0);
         T *dst = a.out + (size_t)r * cols + c0;
         if (c0 + CC <= cols) {
-            store_out_vec(dst, res, a.nt_store != 0);
+            store_out_vec(dst, res, a.store == Store::kNonTemporal);
         } else {
 #pragma unroll
             for (int cc = 0; cc < CC; ++cc)
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(MAXT) void life_direct_kernel(const TileArgs<OpLife
         life_rule(o, win[cr], win[cr + 1], win[cr + 2]);
         uint8_t *dst = a.out + (size_t)r * cols + c0;
         if (c0 + CC <= cols) {
-            store_word4(dst, make_uint4(o[0], o[1], o[2], o[3]), a.nt_store != 0);
+            store_word4(dst, make_uint4(o[0], o[1], o[2], o[3]), a.store == Store::kNonTemporal);
         } else {
 #pragma unroll
             for (int k = 0; k < CC; ++k)

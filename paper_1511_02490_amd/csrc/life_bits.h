@@ -260,7 +260,7 @@ __global__ __launch_bounds__(MAXT) void life_temporal_kernel(const TileArgs<OpLi
         const uint4 o = unpack_cells16(next(up, mid, dn, r) >> half);
         uint8_t *out = a.out + (size_t)r * cols + c;
         if (c + CC <= cols) {
-            store_word4(out, o, a.nt_store != 0);
+            store_word4(out, o, a.store);
         } else {
             store_first_cells(out, o, cols - c);
         }

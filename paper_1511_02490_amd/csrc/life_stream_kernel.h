@@ -37,7 +37,7 @@ struct LifeStreamArgs {
     int tiles_c, n_tiles;
     int group_shift;             // log2 of the lanes that hold a row of the tile
     int pad;                     // 0 or 1
-    int nt_store;
+    Store store;
 };
 
 template <int B, int RPT, bool IN_BITS, bool OUT_BITS>
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(life_stream_max_threads(RPT)) void life_stream_kern
             for (int half = 0; half < 2; ++half) {
                 const uint4 o = unpack_cells16(x[i] >> (16 * half));
                 if (col + 16 * half + 16 <= cols) {
-                    store_word4(out + 16 * half, o, a.nt_store != 0);
+                    store_word4(out + 16 * half, o, a.store);
                 } else if (col + 16 * half < cols) {
                     store_first_cells(out + 16 * half, o, cols - (col + 16 * half));
                 }

@@ -226,7 +226,7 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
                         for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(sum[cc], a.scalar0);
                         if (FAST) {
                             char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
-                            store_out_vec<NT>(reinterpret_cast<T *>(rowp + out_off), res);
+                            store_out_vec<NT ? Store::kNonTemporal : Store::kPlain>(reinterpret_cast<T *>(rowp + out_off), res);
                         } else {
                             T *out = a.out + (size_t)gr * cols + gc0;
 #pragma unroll

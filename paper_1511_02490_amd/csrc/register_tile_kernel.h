@@ -172,7 +172,7 @@ __global__ __launch_bounds__(kRegisterTileMaxThreads) void register_tile_kernel(
             if (r < begin_r || r >= end_r) continue;
             float *out = a.out + (size_t)r * cols + gc0;
             if (gc0 >= begin_c && gc0 + CC <= end_c) {
-                store_out_vec(out, x[i], a.nt_store != 0);
+                store_out_vec(out, x[i], a.store);
             } else {
 #pragma unroll
                 for (int j = 0; j < CC; ++j)

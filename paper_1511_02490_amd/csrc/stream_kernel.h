@@ -31,10 +31,10 @@ __host__ __device__ constexpr int stream_cols(int depth) { return (kStreamLanes 
 // columns then lie either all inside the matrix or all outside it, every input row is one vector
 // load at a per-lane column plus a wavefront-uniform row address, issued without a branch three
 // steps ahead, and the time loop is straight-line code.  Otherwise elements are loaded one by one.
-// NT: output vectors are stored non-temporally (element-by-element stores are plain either way).
+// S: how output vectors are stored (element-by-element stores are plain in any case).
 // (A branch at the store, in an unrolled march: 148 instead of 133 registers for eight heat steps under WRAP, one wavefront
 // per SIMD fewer at depths 5 and 7; 400 steps on 4096^2, 8 per launch, 1915 instead of 1873 us.)
-template <class Op, int B, int DEPTH, bool FAST, bool NT>
+template <class Op, int B, int DEPTH, bool FAST, Store S>
 __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>> &a, const int H) {
     using T = typename Op::T;
     static_assert(B == kWrap || B == kConstant, "wrap and constant borders only");
@@ -167,7 +167,7 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
                     // gr = r0 + t - 2*DEPTH runs over this segment's rows
                     if (FAST) {
                         char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
-                        store_out_vec<NT>(reinterpret_cast<T *>(rowp + out_off), res);
+                        store_out_vec<S>(reinterpret_cast<T *>(rowp + out_off), res);
                     } else {
                         T *out = a.out + (size_t)gr * cols + gc0;
 #pragma unroll
@@ -182,7 +182,14 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
 
 template <class Op, int B, int DEPTH, bool FAST, bool NT, int MAXT>
 __global__ __launch_bounds__(MAXT) void stream_kernel(const TileArgs<Op, HaloC<1, 1, 1, 1>> a, const int H) {
-    stream_body<Op, B, DEPTH, FAST, NT>(a, H);
+    stream_body<Op, B, DEPTH, FAST, NT ? Store::kNonTemporal : Store::kPlain>(a, H);
+}
+// ... and written through, over rows of whole vectors, from kStreamThroughDepth applications per launch on (heat, WRAP, a launch
+// of eight on 4096^2, plain / through: 37.0 / 35.6 us; of two 22.6 / 23.2; of one 22.0 / 22.6).
+constexpr int kStreamThroughDepth = 4;
+template <class Op, int B, int DEPTH, int MAXT>
+__global__ __launch_bounds__(MAXT) void stream_through_kernel(const TileArgs<Op, HaloC<1, 1, 1, 1>> a, const int H) {
+    stream_body<Op, B, DEPTH, true, Store::kThrough>(a, H);
 }
 
 }  // namespace sk

@@ -139,7 +139,7 @@ __device__ __forceinline__ void temporal_application(const TileArgs<Op, HaloC<1,
                 if (!LAST) {
                     store_vec(dst + at, res);
                 } else if (!EDGE || it.gc + CC <= cols) {
-                    store_out_vec(out, res, a.nt_store != 0);
+                    store_out_vec(out, res, a.store);
                 } else {
 #pragma unroll
                     for (int cc = 0; cc < CC; ++cc)

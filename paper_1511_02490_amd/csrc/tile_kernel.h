@@ -50,6 +50,9 @@ struct WeightStore<Op, Halo, false> {
     }
 };
 
+// How vectors of output cells are stored (store_word4).
+enum class Store : int { kPlain, kNonTemporal, kThrough };
+
 template <class Op, class Halo>
 struct TileArgs {
     const typename Op::T *in;
@@ -61,7 +64,7 @@ struct TileArgs {
     int pitch;       // LDS tile pitch, in staged elements
     int plane;       // elements per LDS plane (tile rows x pitch)
     unsigned stage_magic;   // for the division by the items of a staged row: see row_of_item
-    int nt_store;    // vector stores of output cells are non-temporal
+    Store store;     // how vectors of output cells are stored
     typename Op::T pad;
     float scalar0;
     Halo halo;
@@ -123,12 +126,22 @@ __device__ __forceinline__ void load_global(E (&dst)[CNT], const E *src) {
 // Stores of output cells are optionally non-temporal: they are not read again by the launch that
 // writes them, and on matrices beyond the caches keeping them out of the way of the input pays
 // (measured on a plain copy: +20 % on 256 MiB, nothing on 64 MiB).
-template <bool NT>
+// Or they are written through (kThrough), by the kernels that make several applications per launch: what plain stores leave
+// dirty in the eight L2 caches, 4 MiB each, is written back when the kernel ends, with nothing beside it; written through it
+// is on its way while the rest computes, and stays in the cache for the next launch.  (Plain / through: four Life
+// generations on 4096^2 11.4 / 9.5 us; a launch of four heat steps there in local memory 33.5 / 33.1.  Small outputs
+// pay for it at the end of the last workgroups: a launch of two heat steps on 1024^2 9.4 / 10.0.  store_of in variants.h draws the line.
+// The tiles of single applications gain 4 % on 4096^2 and more, but the third kind of store costs them 1 % on all smaller
+// matrices.)  The two wait states keep what follows off the stored registers: the compiler counts them only after its own
+// stores.  Nothing reads the output in the same launch.
+template <Store S>
 __device__ __forceinline__ void store_word4(void *dst, uint4 v) {
     any_word4 t;
     t.x = v.x, t.y = v.y, t.z = v.z, t.w = v.w;
-    if constexpr (NT)
+    if constexpr (S == Store::kNonTemporal)
         __builtin_nontemporal_store(t, reinterpret_cast<any_word4 *>(dst));
+    else if constexpr (S == Store::kThrough)
+        asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(dst), "v"(t));
     else
         *reinterpret_cast<any_word4 *>(dst) = t;
 }
@@ -140,11 +153,17 @@ __device__ __forceinline__ void store_word4(void *dst, uint4 v) {
 __device__ __forceinline__ void store_word4(void *dst, uint4 v, bool nt) {
     if (nt) {
         asm volatile("");
-        store_word4<true>(dst, v);
+        store_word4<Store::kNonTemporal>(dst, v);
         asm volatile("");
     } else {
-        store_word4<false>(dst, v);
+        store_word4<Store::kPlain>(dst, v);
     }
+}
+__device__ __forceinline__ void store_word4(void *dst, uint4 v, Store how) {
+    if (how == Store::kThrough)
+        store_word4<Store::kThrough>(dst, v);
+    else
+        store_word4(dst, v, how == Store::kNonTemporal);
 }
 template <class E, int CNT, class Store>
 __device__ __forceinline__ void store_words_of(E *dst, const E (&src)[CNT], Store store) {
@@ -155,13 +174,13 @@ __device__ __forceinline__ void store_words_of(E *dst, const E (&src)[CNT], Stor
 #pragma unroll
     for (int k = 0; k < NV; ++k) store(reinterpret_cast<unsigned char *>(dst) + 16 * k, tmp[k]);
 }
-template <class E, int CNT>
-__device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT], bool nt) {
-    store_words_of(dst, src, [&](void *p, uint4 v) { store_word4(p, v, nt); });
+template <class E, int CNT, class How>
+__device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT], How how) {
+    store_words_of(dst, src, [&](void *p, uint4 v) { store_word4(p, v, how); });
 }
-template <bool NT, class E, int CNT>
+template <Store S, class E, int CNT>
 __device__ __forceinline__ void store_out_vec(E *dst, const E (&src)[CNT]) {
-    store_words_of(dst, src, [](void *p, uint4 v) { store_word4<NT>(p, v); });
+    store_words_of(dst, src, [](void *p, uint4 v) { store_word4<S>(p, v); });
 }
 
 // What a cell keeps while one row of its region goes by (operators that fold a row at a time).
@@ -751,7 +770,7 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
         O *dst = a.out + (size_t)r * cols + c0 + lc0;
         if constexpr (CC > 1) {
             if (c0 + lc0 + CC <= cols) {
-                store_out_vec(dst, res, a.nt_store != 0);
+                store_out_vec(dst, res, a.store == Store::kNonTemporal);
                 continue;
             }
         }

@@ -89,6 +89,14 @@ TileGeom tile_geom(const stencil *s, const Variant &v, int wr, int wc) {
     return g;
 }
 
+// How a launch stores its output where the handle does not ask for non-temporal stores: written through from half of what the
+// device's L2 caches hold on (Store::kThrough has both sides).
+constexpr size_t kThroughBytes = (size_t)16 << 20;
+sk::Store store_of(const stencil *s) {
+    if (s->nt_store) return sk::Store::kNonTemporal;
+    return s->out_bytes() >= kThroughBytes ? sk::Store::kThrough : sk::Store::kPlain;
+}
+
 // Kernel arguments and grid for one launch; `blocks` is the grid size.
 template <class Op, class Halo, int CR, int CC>
 sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, void *out, int wr, int wc,
@@ -119,7 +127,7 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
         const unsigned items = std::max(1u, (unsigned)(a.pitch / CC));
         a.stage_magic = sk::row_magic(items);
     }
-    a.nt_store = s->nt_store;
+    a.store = store_of(s);
     a.pad = (T)s->pad;
     a.scalar0 = s->scalar0;
     if constexpr (Halo::kStatic) {
@@ -194,6 +202,20 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
     blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
     const dim3 grid(blocks), block(wc, wr);
     const bool whole = s->cols % 4 == 0;      // rows of whole vectors, or the element-by-element body
+    if (whole && a.store == sk::Store::kThrough) {
+        static_assert(sk::kStreamThroughDepth == 4 && sk::kStreamMaxDepth == 8, "a case each");
+#define THROUGH_LAUNCH(D)                                                                                      \
+    hipLaunchKernelGGL((&sk::stream_through_kernel<Op, B, D, kMaxT>), grid, block, 0, stream, a, CR);          \
+    return hipGetLastError()
+        switch (depth) {
+        case 4: THROUGH_LAUNCH(4);
+        case 5: THROUGH_LAUNCH(5);
+        case 6: THROUGH_LAUNCH(6);
+        case 7: THROUGH_LAUNCH(7);
+        case 8: THROUGH_LAUNCH(8);
+        }
+#undef THROUGH_LAUNCH
+    }
 #define STREAM_LAUNCH(D)                                                                                       \
     hipLaunchKernelGGL(!whole        ? (&sk::stream_kernel<Op, B, D, false, false, kMaxT>)                     \
                        : s->nt_store ? (&sk::stream_kernel<Op, B, D, true, true, kMaxT>)                       \
@@ -313,7 +335,7 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     a.tiles_c = t.tiles_c;
     a.n_tiles = t.tiles_r * t.tiles_c;
     a.pad = s->pad != 0.0;
-    a.nt_store = s->nt_store;
+    a.store = store_of(s);
     const dim3 grid((unsigned)a.n_tiles), block(wc, wr);
     const unsigned lds = sk::life_stream_lds(wr * wc);
     switch (t.rows_per_item) {
