@@ -67,6 +67,17 @@ struct HaloTaps : HaloD {
     static constexpr Fold kFold = Fold::taps;
 };
 
+// ... or a compile-time one folded by the run-time regions' scheme, row by row: the unrolled fold of a wide region is scheduled
+// into too many registers (which tiles: by_rows in variants.h).
+template <int N_, int S_, int E_, int W_>
+struct HaloRows : HaloC<N_, S_, E_, W_> {
+    static constexpr Fold kFold = Fold::columns;
+};
+template <class Halo>
+struct folds_by_rows { static constexpr bool value = !Halo::kStatic; };
+template <int N, int S, int E, int W>
+struct folds_by_rows<HaloRows<N, S, E, W>> { static constexpr bool value = true; };
+
 // ---- weighted sum ("gaussian" of Table 2): fp32 fma chain ---------------------------------
 struct OpWeightedSum {
     static constexpr bool kRowFold = false;

@@ -14,6 +14,23 @@
 
 namespace sk {
 
+// Scalar loads of up to four words each of a table in constant memory.  (Nothing writes a table while a kernel reads it,
+// which the constant address space says; scalar loads want no more than 4-byte alignment.)
+template <class W, int CNT>
+__device__ __forceinline__ void load_scalars(W (&dst)[CNT], const __attribute__((address_space(4))) W *p) {
+    typedef W four __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll
+    for (int i = 0; i < CNT; i += 4) {
+        if (i + 4 <= CNT) {
+            const four t = *(const __attribute__((address_space(4))) four *)(p + i);
+            dst[i] = t.x, dst[i + 1] = t.y, dst[i + 2] = t.z, dst[i + 3] = t.w;
+        } else {
+#pragma unroll
+            for (int j = i; j < CNT; ++j) dst[j] = p[j];
+        }
+    }
+}
+
 template <class Op, class Halo, bool Static = Halo::kStatic>
 struct WeightStore;
 // Compile-time region: the weight table travels in the kernel arguments (scalar registers).
@@ -23,6 +40,9 @@ struct WeightStore<Op, Halo, true> {
     using W = typename weight_type_of<Op>::type;
     W v[kCount];
     __device__ __forceinline__ W operator[](int k) const { return Op::kWeights ? v[k] : W(0); }
+    // Entries k .. k + CNT - 1, k the same in all lanes, from the kernel's arguments, which lie in constant memory.
+    template <int CNT>
+    __device__ __forceinline__ void load(W (&dst)[CNT], unsigned k) const;
 };
 // Run-time region: table in device memory (uniform index -> scalar loads).
 template <class Op, class Halo>
@@ -31,22 +51,10 @@ struct WeightStore<Op, Halo, false> {
     using W = typename std::conditional<sizeof(Wt) == 4, Wt, float>::type;
     const W *v;
     __device__ __forceinline__ W operator[](int k) const { return Op::kWeights ? v[k] : W(0); }
-    // Entries k .. k + CNT - 1, k the same in all lanes, as scalar loads of up to four.  (Nothing writes a table while a
-    // kernel reads it, which the constant address space says; scalar loads want no more than 4-byte alignment.)
+    // Entries k .. k + CNT - 1, k the same in all lanes.
     template <int CNT>
     __device__ __forceinline__ void load(W (&dst)[CNT], unsigned k) const {
-        typedef W four __attribute__((ext_vector_type(4), aligned(4)));
-        const __attribute__((address_space(4))) W *p = (const __attribute__((address_space(4))) W *)(v + k);
-#pragma unroll
-        for (int i = 0; i < CNT; i += 4) {
-            if (i + 4 <= CNT) {
-                const four t = *(const __attribute__((address_space(4))) four *)(p + i);
-                dst[i] = t.x, dst[i + 1] = t.y, dst[i + 2] = t.z, dst[i + 3] = t.w;
-            } else {
-#pragma unroll
-                for (int j = i; j < CNT; ++j) dst[j] = p[j];
-            }
-        }
+        load_scalars(dst, (const __attribute__((address_space(4))) W *)(v + k));
     }
 };
 
@@ -70,6 +78,14 @@ struct TileArgs {
     Halo halo;
     WeightStore<Op, Halo> w;
 };
+
+// (TileArgs is the kernels' first argument.  Through the member itself every entry would be a load with an address of its own.)
+template <class Op, class Halo>
+template <int CNT>
+__device__ __forceinline__ void WeightStore<Op, Halo, true>::load(W (&dst)[CNT], unsigned k) const {
+    const auto *args = (const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr();
+    load_scalars(dst, (const __attribute__((address_space(4))) W *)(args + __builtin_offsetof(TileArgs<Op, Halo>, w)) + k);
+}
 
 // item / d, the items of a staged row, by a multiply: floor((item + 1) floor((2^32 - 1) / d) / 2^32), exact where
 // (item + 1) d <= 2^32.  (The usual ceil(2^32 / d) needs no addition and 33 bits for d = 1: a workgroup one work-item wide
@@ -631,7 +647,7 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
     const int r0 = tile_r * th, c0 = tile_c * tw;
     // columns staged west of the tile: under a run-time region exactly the region's (the fold wants the region's
     // west edge at a vector's start), else whole vectors
-    const int hwa = Halo::kStatic ? staged_halo<CC>(hw) : hw;
+    const int hwa = folds_by_rows<Halo>::value ? hw : staged_halo<CC>(hw);
     const int pitch = a.pitch;
     const int rows = a.rows, cols = a.cols;
     // the whole tile height is staged, also where the last tile hangs over the matrix edge (those
@@ -657,7 +673,7 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
 #pragma unroll
         for (int cc = 0; cc < CC; ++cc) Op::init(st[cr][cc]);
 
-    if constexpr (Halo::kStatic) {
+    if constexpr (!folds_by_rows<Halo>::value) {
         constexpr int N = Halo::N, S = Halo::S, E = Halo::E, W = Halo::W;
         constexpr int HWA = staged_halo<CC>(W);
         constexpr int VL = CC == 1 ? 1 : (16 / (int)sizeof(L) < 1 ? 1 : 16 / (int)sizeof(L));
@@ -710,6 +726,10 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
                 fold_taps<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
             } else if constexpr (Halo::kFold == Fold::blocks) {
                 fold_blocks<Op, Halo, CR, CC>(st, a, window, hn, hw, wrows, wcols);
+            } else if constexpr (Halo::kStatic) {
+                int n_rows = wrows;              // (a loop of two rows: unrolled further, rows are read ahead into more registers)
+                asm("" : "+s"(n_rows));
+                fold_columns<Op, Halo, CR, CC, Halo::E + Halo::W + 1>(st, a, window, hn, hw, n_rows);
             } else {
                 static_assert(kCompiledColumns == 9, "a case each");
                 switch (wcols) {

@@ -117,8 +117,8 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
     a.n_tiles = g.tiles_r * g.tiles_c;
     a.pitch = g.pitch;
     a.plane = g.plane;
-    if (!Halo::kStatic && !Halo::kMasked) {
-        // the tile kernel stages a run-time region from its west edge (never more than the geometry allows for)
+    if (sk::folds_by_rows<Halo>::value && !Halo::kMasked) {
+        // the tile kernel stages a region that it folds by rows from its west edge (never more than the geometry allows for)
         a.pitch = sk::round_up(s->hw + g.tw + s->he, CC);
         a.plane = (g.th + s->hn + s->hs) * a.pitch;
     }
@@ -477,12 +477,29 @@ sk::Fold region_fold(const stencil *s) {
     return rows * cols <= kFewTaps ? sk::Fold::taps : sk::Fold::columns;
 }
 
+// Which compile-time regions the tile folds row by row: the Gaussians of radius 3 and 4 with two and four rows of cells, whose
+// unrolled folds are bound by the wavefronts their registers leave (7x7, 2 x 4 cells: 81 registers against 48; 9x9, 4 x 4:
+// scratch memory).  (Unrolled / by rows, us: 7x7 on 8192^2 148 / 119, on 3001 x 4099 32.3 / 26.2, four rows of cells there 33.5 /
+// 30.1; 9x9 on 8192^2 170 / 162, four rows 218 / 158.  5x5 on 3001 x 4099 22.4 / 22.9, on 2048^2 10.15 / 10.45: unrolled.)
+template <class Op, class Halo, int CR, int CC>
+constexpr bool by_rows() {
+    return std::is_same<Op, sk::OpWeightedSum>::value && Halo::kStatic && Halo::N + Halo::S >= 6 && Halo::E + Halo::W >= 6 && CC > 1 &&
+           (CR == 2 || CR == 4);
+}
+// A workgroup of one row of work-items stages up to five rows for each that it computes, from the region's west edge, which
+// starts no vector in memory: unrolled, where that fits the registers (7x7 on 3001 x 4099, 1 x 64 work-items, 40.1 / 41.8 us).
+template <class Halo, int CR>
+constexpr bool unrolled_for_one_row() { return Halo::kStatic && sk::folds_by_rows<Halo>::value && (CR == 2 || Halo::N + Halo::S < 8); }
+
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
     if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1) {
         const sk::Fold fold = region_fold<Op, CR>(s);
         if (fold == sk::Fold::blocks) return launch_tile<Op, B, sk::HaloBlocks, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
         if (fold == sk::Fold::taps) return launch_tile<Op, B, sk::HaloTaps, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
+    }
+    if constexpr (unrolled_for_one_row<Halo, CR>()) {
+        if (wr == 1) return launch_tile<Op, B, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
     }
     unsigned blocks;
     size_t lds;
@@ -590,8 +607,9 @@ void reg_one(std::vector<Variant> &r) {
     constexpr int kMaxT = variant_max_threads<Op, CR, CC>();
     v.max_threads = kMaxT;
     v.staged_bytes = (int)sizeof(typename Op::L) * Op::kPlanes;
-    v.launch = &launch_tile<Op, B, Halo, CR, CC, kMaxT>;
-    v.kernel_of = &kernel_tile<Op, B, Halo, CR, CC, kMaxT>;
+    using Folded = typename std::conditional<by_rows<Op, Halo, CR, CC>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
+    v.launch = &launch_tile<Op, B, Folded, CR, CC, kMaxT>;
+    v.kernel_of = &kernel_tile<Op, B, Folded, CR, CC, kMaxT>;
     r.push_back(v);
 }
 

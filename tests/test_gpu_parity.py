@@ -783,6 +783,19 @@ def test_tiles_staged_without_registers(ls, wg, blocking, offset):
         check(ls, wd, wg, blocking=(max(2, blocking[0]), 2), offset=offset)
 
 
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("radius", [3, 4])
+@pytest.mark.parametrize("cells_rows", [2, 4])
+def test_wide_gaussians_folded_by_rows(ls, border, radius, cells_rows):
+    """Compile-time regions in the run-time fold's scheme: edges and remainders of tiles, matrices smaller than a tile, and
+    workgroups of one row of work-items, which keep the unrolled fold."""
+    for rows, cols in [(3 * 8 * cells_rows + 3, 301), (8 * cells_rows, 128), (7, 5), (61, 133)]:
+        w = custom(wl.WEIGHTED_SUM, rows, cols, (radius,) * 4, border, pad=0.25, seed=radius)
+        for wg in [(8, 32), (1, 64), (3, 5)]:
+            got = check(ls, w, wg, blocking=(cells_rows, 4), offset=1)
+            np.testing.assert_array_equal(got, check(ls, w, wg, blocking=(1, 1)))        # the same fold: the same bits
+
+
 def test_temporal_blocking_not_offered_for_other_regions(ls):
     st = ls.Stencil.from_workload(wl.config(1))                    # 5x5 region
     with pytest.raises(ls.StencilError):
