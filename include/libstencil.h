@@ -172,7 +172,10 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            have kernels of their own; any other region with N, S <= 5 and E, W <= 4 runs a
  *            kernel compiled for its number of columns E+W+1 and for at most 5 (N, S <= 2) or 11
  *            rows, which hands row neighbours through local memory (a few KiB per workgroup,
- *            never a reason for refusal).  Larger regions: not available (the local-memory
+ *            never a reason for refusal).  Where a tile of 2 x 4 cells and 8 x 32 work-items in local memory
+ *            is faster - every sum but run-time regions of 72 cells and more, SINCOS below 2^25 cells, rows
+ *            that are no multiple of 4 cells - the application is made by that; cells_rows and the
+ *            workgroup then change nothing.  Larger regions: not available (the local-memory
  *            tile is as fast there: its fold is bound by arithmetic).
  *            LIFE, WRAP and CONSTANT borders: one bit per cell, cells_cols in {4,8,16}; up to
  *            STENCIL_MAX_STREAM_DEPTH generations per launch, and between the launches of a run

@@ -32,6 +32,7 @@ __host__ __device__ constexpr int march_vectors(int W, int E) { return 64 - marc
 // NT: output vectors are stored non-temporally (element-by-element stores are plain either way).
 template <class Op, int B, class Halo, bool FAST, bool NT>
 __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const int H) {
+    static_assert(FAST, "rows of whole vectors");
     using T = typename Op::T;
     using L = typename Op::L;
     static_assert(Halo::kStatic, "compile-time border regions only");
@@ -66,11 +67,6 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
     const bool edge_wave = __any(outside) != 0;     // the same for the whole wavefront
     const unsigned in_off = (unsigned)vcol * (unsigned)sizeof(T);    // byte offsets inside a row
     const unsigned out_off = (unsigned)gc0 * (unsigned)sizeof(T);
-    // otherwise: the lane's columns after border resolution (-1: padding)
-    int col[CC];
-#pragma unroll
-    for (int j = 0; j < CC; ++j) col[j] = resolve<B>(gc0 + j, cols);
-    const bool wanted = gc0 < cols + E;             // beyond that nobody reads this lane's cells
 
     // A segment needs kSteps input rows; the march makes whole rounds of R steps (what the steps
     // past kSteps compute is never stored) and the fast body issues exactly one load per step,
@@ -82,36 +78,24 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
     auto load_row = [&](int t, T (&v)[CC]) {
         const int tt = t < kSteps ? t : kSteps - 1;
         const int gr = resolve<B>(r0 - N + tt, rows);   // the same for the whole wavefront
-        if (FAST) {
-            // scalar row address + 32-bit lane offset; a padding row is fixed up later
-            const char *rowp = reinterpret_cast<const char *>(a.in + (size_t)(gr < 0 ? 0 : gr) * cols);
-            load_global(v, reinterpret_cast<const T *>(rowp + in_off));
-        } else {
-#pragma unroll
-            for (int j = 0; j < CC; ++j)
-                v[j] = (gr >= 0 && wanted && col[j] >= 0) ? a.in[(size_t)gr * cols + col[j]] : a.pad;
-        }
+        // scalar row address + 32-bit lane offset; a padding row is fixed up later
+        const char *rowp = reinterpret_cast<const char *>(a.in + (size_t)(gr < 0 ? 0 : gr) * cols);
+        load_global(v, reinterpret_cast<const T *>(rowp + in_off));
     };
     // what the border mode substitutes in a row that has arrived
     auto fix_row = [&](int t, T (&v)[CC]) {
         const bool row_outside = B == kConstant && (unsigned)(r0 - N + t) >= (unsigned)rows;
-        if (FAST) {
-            if (B == kConstant) {
-                if (row_outside || edge_wave) {
+        if (B == kConstant) {
+            if (row_outside || edge_wave) {
 #pragma unroll
-                    for (int j = 0; j < CC; ++j) v[j] = (row_outside || outside) ? a.pad : v[j];
-                }
-            } else if (B == kClamp) {
-                if (edge_wave) {
-                    const T rep = gc0 < 0 ? v[0] : v[CC - 1];
-#pragma unroll
-                    for (int j = 0; j < CC; ++j) v[j] = outside ? rep : v[j];
-                }
+                for (int j = 0; j < CC; ++j) v[j] = (row_outside || outside) ? a.pad : v[j];
             }
-        } else {
+        } else if (B == kClamp) {
+            if (edge_wave) {
+                const T rep = gc0 < 0 ? v[0] : v[CC - 1];
 #pragma unroll
-            for (int j = 0; j < CC; ++j)
-                if (row_outside || col[j] < 0 || !wanted) v[j] = a.pad;
+                for (int j = 0; j < CC; ++j) v[j] = outside ? rep : v[j];
+            }
         }
     };
 
@@ -216,15 +200,8 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
                             T res[CC];
 #pragma unroll
                             for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(st[slot][cc], a.scalar0);
-                            if (FAST) {
-                                char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
-                                store_out_vec<NT ? Store::kNonTemporal : Store::kPlain>(reinterpret_cast<T *>(rowp + out_off), res);
-                            } else {
-                                T *out = a.out + (size_t)gr * cols + gc0;
-#pragma unroll
-                                for (int cc = 0; cc < CC; ++cc)
-                                    if (gc0 + cc < cols) out[cc] = res[cc];
-                            }
+                            char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
+                            store_out_vec<NT ? Store::kNonTemporal : Store::kPlain>(reinterpret_cast<T *>(rowp + out_off), res);
                         }
                     }
                 }

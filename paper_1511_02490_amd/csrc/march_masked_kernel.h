@@ -38,6 +38,7 @@ struct HaloM {
 
 template <class Op, int B, class Halo, int WC, bool FAST, bool NT, int MAXT>
 __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, const int H) {
+    static_assert(FAST, "rows of whole vectors");
     using T = typename Op::T;
     using L = typename Op::L;
     static_assert(!Op::kRowFold && Op::kPlanes == 1, "functions that fold tap by tap");
@@ -102,10 +103,6 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
     const bool edge_wave = __any(outside) != 0;
     const unsigned in_off = (unsigned)vcol * (unsigned)sizeof(T);
     const unsigned out_off = (unsigned)gc0 * (unsigned)sizeof(T);
-    int col[CC];
-#pragma unroll
-    for (int j = 0; j < CC; ++j) col[j] = resolve<B>(gc0 + j, cols);
-    const bool wanted = gc0 < cols + e;
 
     // input row r0 - n + t arrives at step t
     const int kSteps = H + r - 1;
@@ -113,34 +110,22 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
     auto load_row = [&](int t, T (&v)[CC]) {
         const int tt = t < kSteps ? t : kSteps - 1;
         const int gr = resolve<B>(r0 - n + tt, rows);
-        if (FAST) {
-            const char *rowp = reinterpret_cast<const char *>(a.in + (size_t)(gr < 0 ? 0 : gr) * cols);
-            load_global(v, reinterpret_cast<const T *>(rowp + in_off));
-        } else {
-#pragma unroll
-            for (int j = 0; j < CC; ++j)
-                v[j] = (gr >= 0 && wanted && col[j] >= 0) ? a.in[(size_t)gr * cols + col[j]] : a.pad;
-        }
+        const char *rowp = reinterpret_cast<const char *>(a.in + (size_t)(gr < 0 ? 0 : gr) * cols);
+        load_global(v, reinterpret_cast<const T *>(rowp + in_off));
     };
     auto fix_row = [&](int t, T (&v)[CC]) {
         const bool row_outside = B == kConstant && (unsigned)(r0 - n + t) >= (unsigned)rows;
-        if (FAST) {
-            if (B == kConstant) {
-                if (row_outside || edge_wave) {
+        if (B == kConstant) {
+            if (row_outside || edge_wave) {
 #pragma unroll
-                    for (int j = 0; j < CC; ++j) v[j] = (row_outside || outside) ? a.pad : v[j];
-                }
-            } else if (B == kClamp) {
-                if (edge_wave) {
-                    const T rep = gc0 < 0 ? v[0] : v[CC - 1];
-#pragma unroll
-                    for (int j = 0; j < CC; ++j) v[j] = outside ? rep : v[j];
-                }
+                for (int j = 0; j < CC; ++j) v[j] = (row_outside || outside) ? a.pad : v[j];
             }
-        } else {
+        } else if (B == kClamp) {
+            if (edge_wave) {
+                const T rep = gc0 < 0 ? v[0] : v[CC - 1];
 #pragma unroll
-            for (int j = 0; j < CC; ++j)
-                if (row_outside || col[j] < 0 || !wanted) v[j] = a.pad;
+                for (int j = 0; j < CC; ++j) v[j] = outside ? rep : v[j];
+            }
         }
     };
     // what one lane wrote to local memory, the others of its wavefront may read after this
@@ -224,15 +209,8 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
                         T res[CC];
 #pragma unroll
                         for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(sum[cc], a.scalar0);
-                        if (FAST) {
-                            char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
-                            store_out_vec<NT ? Store::kNonTemporal : Store::kPlain>(reinterpret_cast<T *>(rowp + out_off), res);
-                        } else {
-                            T *out = a.out + (size_t)gr * cols + gc0;
-#pragma unroll
-                            for (int cc = 0; cc < CC; ++cc)
-                                if (gc0 + cc < cols) out[cc] = res[cc];
-                        }
+                        char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
+                        store_out_vec<NT ? Store::kNonTemporal : Store::kPlain>(reinterpret_cast<T *>(rowp + out_off), res);
                     }
                 }
             }

@@ -28,6 +28,9 @@
 int register_tile_per_launch(const stencil *s, int iters, int wg_rows, int wg_cols);
 RunLaunchFn register_tile_launcher(int kernel, int border);
 
+// The launcher of the fp32 sums' tile with 2 x 4 cells (variants_weighted_sum_tiles.hip): 5x5, or a run-time region.
+LaunchFn weighted_sum_tile(int border, bool five_by_five);
+
 // Local memory a workgroup may allocate: the device's own figure once a GPU has been used, the
 // header's constant before that (defined in libstencil.hip).
 int64_t stencil_local_memory_limit();
@@ -384,57 +387,6 @@ hipError_t launch_threshold(const stencil *s, const void *in, void *out, int wr,
     return hipGetLastError();
 }
 
-// One application, marched down the matrix in registers (march_kernel.h).
-template <class Op, int B, class Halo>
-hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
-    constexpr int kMaxT = 256;
-    unsigned blocks;
-    size_t lds;
-    auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
-    // a tile is a wavefront's segment; workgroups only group wavefronts
-    const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
-    blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
-    a.xcd_chunk = 0;
-    if (s->xcd_remap && blocks >= 64) {
-        a.xcd_chunk = (int)((blocks + 7) / 8);
-        blocks = (unsigned)a.xcd_chunk * 8u;
-    }
-    // rows of whole vectors, with either kind of store, or the element-by-element body
-    hipLaunchKernelGGL(s->cols % 4 != 0 ? (&sk::march_kernel<Op, B, Halo, false, false, kMaxT>)
-                       : s->nt_store    ? (&sk::march_kernel<Op, B, Halo, true, true, kMaxT>)
-                                        : (&sk::march_kernel<Op, B, Halo, true, false, kMaxT>),
-                       dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
-    return hipGetLastError();
-}
-
-// The same for any region within the kernel's largest one (march_masked_kernel.h): the kernel compiled for the
-// region's number of columns.
-template <class Op, int B, class Halo, int WC = 1>
-hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
-    constexpr int kMaxT = 256;
-    if constexpr (WC > Halo::E + Halo::W + 1) {
-        return hipErrorInvalidValue;
-    } else {
-        if (s->he + s->hw + 1 != WC) return launch_march_masked<Op, B, Halo, WC + 1>(s, in, out, wr, wc, 0, stream);
-        if (s->hn > Halo::N || s->hs > Halo::S || s->he > Halo::E || s->hw > Halo::W) return hipErrorInvalidValue;
-        unsigned blocks;
-        size_t lds;
-        auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
-        const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
-        blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
-        a.xcd_chunk = 0;
-        if (s->xcd_remap && blocks >= 64) {
-            a.xcd_chunk = (int)((blocks + 7) / 8);
-            blocks = (unsigned)a.xcd_chunk * 8u;
-        }
-        hipLaunchKernelGGL(s->cols % 4 != 0 ? (&sk::march_masked_kernel<Op, B, Halo, WC, false, false, kMaxT>)
-                           : s->nt_store    ? (&sk::march_masked_kernel<Op, B, Halo, WC, true, true, kMaxT>)
-                                            : (&sk::march_masked_kernel<Op, B, Halo, WC, true, false, kMaxT>),
-                           dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
-        return hipGetLastError();
-    }
-}
-
 template <int B, int CR, int MAXT>
 hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int wr, int wc, int depth,
                                 hipStream_t stream) {
@@ -489,7 +441,7 @@ constexpr bool by_rows() {
 // A workgroup of one row of work-items stages up to five rows for each that it computes, from the region's west edge, which
 // starts no vector in memory: unrolled, where that fits the registers (7x7 on 3001 x 4099, 1 x 64 work-items, 40.1 / 41.8 us).
 template <class Halo, int CR>
-constexpr bool unrolled_for_one_row() { return Halo::kStatic && sk::folds_by_rows<Halo>::value && (CR == 2 || Halo::N + Halo::S < 8); }
+constexpr bool unrolled_for_one_row() { return Halo::kStatic && sk::folds_by_rows<Halo>::value && Halo::N + Halo::S <= (CR == 2 ? 8 : 6); }
 
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
@@ -510,6 +462,80 @@ hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int 
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a);
     return hipGetLastError();
+}
+
+// Single applications under the streaming mapping: whether the march makes them, or a tile of 2 x 4 cells and 8 x 32 work-items
+// (a march's workgroup only groups wavefronts, and its segment height has no meaning for a tile).  The march keeps sin/cos on
+// matrices that no cache holds, where it takes the sine and cosine of every cell once (8192^2 119 us, tile 128; 3000 x 4100
+// 28.6 / 24.9), and run-time regions of 72 taps and more there, where it is as fast (4 S4 E4 W3 152 / 151, N5 S5 E4 W3 on 6144^2
+// 97 / 101, N3 S4 E4 W4 on 8192^2 165 / 152), both with rows of whole vectors: it moves ragged ones element by element.
+// Everywhere else the tile has more wavefronts in flight (us, march / tile: N1 S5 E3 W0 on 8192^2 122 / 97, 6001 x 7003
+// 135 / 73, 2048^2 13.1 / 10.0; one cell on 8192^2 116 / 87; 5x5 there 116 / 92, 7x7 125 / 120, 9x9 209 / 163, 11x11 377 / 348).
+constexpr int64_t kMarchCells = (int64_t)1 << 25;
+bool march_pays(const stencil *s) {
+    if (s->cols % 4 != 0 || s->rows * s->cols < kMarchCells) return false;
+    if (s->kernel == STENCIL_SINCOS) return true;
+    const bool compiled = s->hn == s->hs && s->hn == s->he && s->hn == s->hw;
+    return !compiled && (s->hn + s->hs + 1) * (s->he + s->hw + 1) >= 72;
+}
+constexpr int kStreamTileRows = 8, kStreamTileCols = 32;
+
+// One application, marched down the matrix in registers (march_kernel.h).
+template <class Op, int B, class Halo>
+hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
+    constexpr int kMaxT = 256;
+    if (!march_pays(s)) {
+        if constexpr (Halo::N == 2) {
+            return weighted_sum_tile(B, true)(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
+        } else {
+            using Folded = typename std::conditional<by_rows<Op, Halo, 2, 4>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
+            return launch_tile<Op, B, Folded, 2, 4, STENCIL_MAX_WG_SIZE>(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
+        }
+    }
+    unsigned blocks;
+    size_t lds;
+    auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
+    // a tile is a wavefront's segment; workgroups only group wavefronts
+    const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
+    blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
+    a.xcd_chunk = 0;
+    if (s->xcd_remap && blocks >= 64) {
+        a.xcd_chunk = (int)((blocks + 7) / 8);
+        blocks = (unsigned)a.xcd_chunk * 8u;
+    }
+    // with either kind of store
+    hipLaunchKernelGGL(s->nt_store ? (&sk::march_kernel<Op, B, Halo, true, true, kMaxT>)
+                                   : (&sk::march_kernel<Op, B, Halo, true, false, kMaxT>),
+                       dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
+    return hipGetLastError();
+}
+
+// The same for any region within the kernel's largest one (march_masked_kernel.h): the kernel compiled for the
+// region's number of columns.
+template <class Op, int B, class Halo, int WC = 1>
+hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
+    constexpr int kMaxT = 256;
+    if constexpr (WC > Halo::E + Halo::W + 1) {
+        return hipErrorInvalidValue;
+    } else {
+        if (!march_pays(s)) return weighted_sum_tile(B, false)(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
+        if (s->he + s->hw + 1 != WC) return launch_march_masked<Op, B, Halo, WC + 1>(s, in, out, wr, wc, 0, stream);
+        if (s->hn > Halo::N || s->hs > Halo::S || s->he > Halo::E || s->hw > Halo::W) return hipErrorInvalidValue;
+        unsigned blocks;
+        size_t lds;
+        auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
+        const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
+        blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
+        a.xcd_chunk = 0;
+        if (s->xcd_remap && blocks >= 64) {
+            a.xcd_chunk = (int)((blocks + 7) / 8);
+            blocks = (unsigned)a.xcd_chunk * 8u;
+        }
+        hipLaunchKernelGGL(s->nt_store ? (&sk::march_masked_kernel<Op, B, Halo, WC, true, true, kMaxT>)
+                                       : (&sk::march_masked_kernel<Op, B, Halo, WC, true, false, kMaxT>),
+                           dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
+        return hipGetLastError();
+    }
 }
 
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>

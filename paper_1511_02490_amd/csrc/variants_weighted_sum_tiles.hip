@@ -39,3 +39,13 @@ void register_weighted_sum_tiles(std::vector<Variant> &r) {
     reg_borders<sk::OpWeightedSumU8, STENCIL_WEIGHTED_SUM_U8, sk::HaloD, 1, 16>(r);
     reg_borders<sk::OpWeightedSumU8, STENCIL_WEIGHTED_SUM_U8, sk::HaloD, 2, 16>(r);
 }
+
+LaunchFn weighted_sum_tile(int border, bool five_by_five) {
+    using Op = sk::OpWeightedSum;
+    using Five = sk::HaloC<2, 2, 2, 2>;
+    switch (border) {
+    case STENCIL_CLAMP: return five_by_five ? &launch_tile<Op, sk::kClamp, Five, 2, 4, STENCIL_MAX_WG_SIZE> : &launch_tile<Op, sk::kClamp, sk::HaloD, 2, 4, STENCIL_MAX_WG_SIZE>;
+    case STENCIL_WRAP: return five_by_five ? &launch_tile<Op, sk::kWrap, Five, 2, 4, STENCIL_MAX_WG_SIZE> : &launch_tile<Op, sk::kWrap, sk::HaloD, 2, 4, STENCIL_MAX_WG_SIZE>;
+    default: return five_by_five ? &launch_tile<Op, sk::kConstant, Five, 2, 4, STENCIL_MAX_WG_SIZE> : &launch_tile<Op, sk::kConstant, sk::HaloD, 2, 4, STENCIL_MAX_WG_SIZE>;
+    }
+}

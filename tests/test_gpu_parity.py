@@ -796,6 +796,30 @@ def test_wide_gaussians_folded_by_rows(ls, border, radius, cells_rows):
             np.testing.assert_array_equal(got, check(ls, w, wg, blocking=(1, 1)))        # the same fold: the same bits
 
 
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("kernel,halo", [(wl.WEIGHTED_SUM, (4, 4, 4, 3)), (wl.WEIGHTED_SUM, (5, 4, 3, 4)), (wl.WEIGHTED_SUM, (5, 5, 3, 3)),
+                                         (wl.WEIGHTED_SUM, (1, 5, 3, 0)), (wl.WEIGHTED_SUM, (5, 5, 5, 5)), (wl.SINCOS, (1, 5, 3, 0))])
+def test_single_applications_of_the_streaming_mapping(ls, kernel, halo, border):
+    """On both sides of the line between the march and the tile (2^25 cells, rows of whole vectors) the output has the bits
+    of one cell per work-item, which is compared with the oracle on small matrices."""
+    for rows, cols in [(4097, 8192), (4094, 8192), (4100, 8191), (61, 133), (7, 12)]:
+        w = custom(kernel, rows, cols, halo, border, pad=0.25, seed=rows)
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(rows)
+        tin = torch.rand((rows, cols), generator=gen, device="cuda")
+        outs = []
+        for mapping, wg, nt in [(("local", 1, 1), (8, 32), 0), (("stream", 37, 4), (4, 64), 0), (("stream", 16, 4), (1, 64), 1)]:
+            st = ls.Stencil.from_workload(w)
+            st.set_mapping(*mapping)
+            st.set_option(ls.OPT_NT_STORE, nt)
+            outs.append(st.run(tin, torch.full_like(tin, 7.0), 1, wg))
+            torch.cuda.synchronize()
+            st.close()
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (rows, cols)
+        if rows < 100:
+            check(ls, w, (4, 64), blocking=("stream", 37, 4))
+
+
 def test_temporal_blocking_not_offered_for_other_regions(ls):
     st = ls.Stencil.from_workload(wl.config(1))                    # 5x5 region
     with pytest.raises(ls.StencilError):
