@@ -103,6 +103,13 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
+# What every call of run looks up, once: the smallest calls take as long as the host takes to make them.
+try:
+    import torch as _torch
+    _TORCH_TYPES = {key: t for keys, t in ((("f32", F32), _torch.float32), (("u8", U8), _torch.uint8), (("i32", I32), _torch.int32),
+                                           (("f64", F64), _torch.float64)) for key in keys}
+except ImportError:
+    _torch, _TORCH_TYPES = None, {}
 EXPORTS = ("stencil_create", "stencil_destroy", "stencil_set_kernel", "stencil_set_border_value",
            "stencil_set_mapping", "stencil_get_mapping", "stencil_stream_segment_rows", "stencil_set_sweep_rotation", "stencil_output_dtype", "stencil_set_option",
            "stencil_max_wg_size", "stencil_tile_bytes", "stencil_is_legal", "stencil_enumerate_wg", "stencil_run",
@@ -313,16 +320,13 @@ class Stencil:
     @staticmethod
     def _stream_ptr(stream):
         if stream is None:
-            import torch
-            stream = torch.cuda.current_stream()
-        return ctypes.c_void_p(getattr(stream, "cuda_stream", stream))
+            return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())      # of the current device, as a number
+        return getattr(stream, "cuda_stream", stream)
 
     def _check_tensors(self, tin, tout):
-        import torch
-        types = {"f32": torch.float32, F32: torch.float32, "u8": torch.uint8, U8: torch.uint8,
-                 "i32": torch.int32, I32: torch.int32, "f64": torch.float64, F64: torch.float64}
-        for t, want in ((tin, types[self.dtype]), (tout, types[self.output_dtype()])):
-            if not t.is_cuda or not t.is_contiguous() or t.dtype != want or t.numel() != self.rows * self.cols:
+        cells = self.rows * self.cols
+        for t, want in ((tin, _TORCH_TYPES[self.dtype]), (tout, _TORCH_TYPES[self.output_dtype()])):
+            if not t.is_cuda or not t.is_contiguous() or t.dtype != want or t.numel() != cells:
                 raise ValueError("tensors must be contiguous CUDA %s of %d x %d" % (want, self.rows, self.cols))
 
     def output_dtype(self) -> int:
@@ -331,15 +335,15 @@ class Stencil:
 
     def run(self, tin, tout, iters: int = 1, wg: Tuple[int, int] = (0, 0), stream=None):
         self._check_tensors(tin, tout)
-        _check(_lib.stencil_run(self._h, ctypes.c_void_p(tin.data_ptr()), ctypes.c_void_p(tout.data_ptr()),
-                                int(iters), int(wg[0]), int(wg[1]), self._stream_ptr(stream)))
+        _check(_lib.stencil_run(self._h, tin.data_ptr(), tout.data_ptr(), int(iters), int(wg[0]), int(wg[1]),
+                                self._stream_ptr(stream)))
         return tout
 
     def run_static(self, tin, tout, iters: int = 1, wg: Tuple[int, int] = (0, 0), stream=None):
         """stencil_run out of the library's fixed device buffer (allocates nothing)."""
         self._check_tensors(tin, tout)
-        _check(_lib.stencil_run_static(self._h, ctypes.c_void_p(tin.data_ptr()), ctypes.c_void_p(tout.data_ptr()),
-                                       int(iters), int(wg[0]), int(wg[1]), self._stream_ptr(stream)))
+        _check(_lib.stencil_run_static(self._h, tin.data_ptr(), tout.data_ptr(), int(iters), int(wg[0]), int(wg[1]),
+                                       self._stream_ptr(stream)))
         return tout
 
     def sweep(self, tin, tout, sizes: Sequence[Tuple[int, int]], iters: int = 1,
