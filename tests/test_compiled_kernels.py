@@ -116,3 +116,16 @@ def test_folds_of_few_taps_keep_their_wavefronts(kernels):
         assert len(found) == 3
         for name, (_, _, vgprs) in found.items():
             assert vgprs <= limit, (name, vgprs)
+
+
+def memory_loads(instructions):
+    """Loads from global memory into vector registers."""
+    return sum(1 for i in instructions if i.startswith("global_load") and not i.startswith("global_load_lds"))
+
+
+def test_weights_of_run_time_regions_are_scalar_loads(kernels):
+    """The tap-by-tap tiles load into vector registers what the tiles that fold in blocks do: the cells they stage."""
+    taps, blocks = kernels.instructions("^tile_kernel<.*HaloTaps"), kernels.instructions("^tile_kernel<.*HaloBlocks")
+    assert len(taps) >= 45
+    for name, instructions in taps.items():
+        assert memory_loads(instructions) == memory_loads(blocks[name.replace("HaloTaps", "HaloBlocks")]), name
