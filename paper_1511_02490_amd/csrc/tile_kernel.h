@@ -661,10 +661,13 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
     // Under a run-time region, eight rows of cells per work-item: nine items and more per work-item, and no gain from
     // finding their addresses sooner (2048 x 4096 floats, 1 x 7 taps, resolved / not: 16.2 / 17.7 us; 7 x 4 taps 21.2 / 22.4).
     constexpr bool kInside = Halo::kStatic || CR < 8 || NP > 1;
-    __builtin_amdgcn_s_setprio(3);
+    // (Not where single elements are staged: with scalar weights, WeightStore, it gained 1 % there and cost up to 9; and before
+    // the fold it made the weights vector loads: 25 taps on 3280 x 4064 doubles, one cell per work-item, 393 us, without 240;
+    // 49 on 2145 x 2816 floats, two cells, 62 and 47.)
+    if constexpr (CC > 1) __builtin_amdgcn_s_setprio(3);
     stage_tile<Op, B, CC, kInside>(tile, a.plane, pitch, a.in, rows, cols, r0 - hn, c0 - hwa, TH, cols + he, a.pad,
                                    a.stage_magic, ty * wc + tx, wr * wc);
-    __builtin_amdgcn_s_setprio(0);
+    if constexpr (CC > 1) __builtin_amdgcn_s_setprio(0);
     __syncthreads();
 
     // ---- fold the customising function over the border region ----------------------------

@@ -129,3 +129,13 @@ def test_weights_of_run_time_regions_are_scalar_loads(kernels):
     assert len(taps) >= 45
     for name, instructions in taps.items():
         assert memory_loads(instructions) == memory_loads(blocks[name.replace("HaloTaps", "HaloBlocks")]), name
+
+
+def test_tiles_of_single_cells_stage_at_ordinary_priority(kernels):
+    """... and, with nothing before the fold that could write to memory, read the weights by scalar loads: the one vector
+    load is the staging's."""
+    code = kernels.instructions(r"^tile_kernel<.*, 1, \d+>$")
+    assert len(code) >= 60
+    for name, instructions in code.items():
+        assert not any(i.startswith("s_setprio") for i in instructions), name
+        assert memory_loads(instructions) == 1, name
