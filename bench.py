@@ -255,15 +255,16 @@ def strong_configs(w):
     return LARGE_HEAT_CONFIGS if w.name.startswith("H") else STRONG_CONFIGS[w.kernel]
 
 
-def kernel_label(w, mapping, size, depth, nt, remap=1):
-    """Name under which a kernel's rocprofv3 counters are kept in profiles/traffic.json."""
-    family = {"local": "tile", "direct": "direct", "temporal": "temporal", "stream": "stream"}[mapping[0]]
-    if mapping[0] == "stream" and depth == 0:
-        family = "march"            # register streaming, one application per launch
-    return "%s: %s_kernel<%s> %dx%d cells/work-item, wg %dx%d" % (
-        w.name.split()[0], family, w.kernel, mapping[1], mapping[2], size[0], size[1]) + (
-        ", %d applications/launch" % depth if depth > 1 else "") + (", non-temporal stores" if nt else "") + (
-        "" if remap else ", plain workgroup numbering")
+def kernel_label(w, mapping, info, nt, remap=1):
+    """Name under which a kernel's rocprofv3 counters are kept in profiles/traffic.json: the kernel that runs
+    (Stencil.describe_run), which need not be the mapping's own, its cells per work-item and its workgroup."""
+    kernel = info["kernel"].split()[0]
+    cells = (2, 4) if mapping[0] == "stream" and kernel == "tile_kernel" else mapping[1:3]
+    return "%s: %s<%s>%s, wg %dx%d" % (
+        w.name.split()[0], kernel, w.kernel,
+        "" if kernel in ("register_tile_kernel", "life_stream_kernel") else " %dx%d cells/work-item" % tuple(cells), *info["wg"]) + (
+        ", %d applications/launch" % info["applications"] if info["applications"] > 1 else "") + (
+        ", non-temporal stores" if nt else "") + ("" if remap else ", plain workgroup numbering")
 
 
 def recorded_counters(label):
@@ -278,7 +279,7 @@ def recorded_counters(label):
     except (OSError, ValueError):
         return None
     rec = table.get(label)
-    if rec is None and ("stream_kernel" in label or "march_kernel" in label):
+    if rec is None and any(k in label for k in (" stream_kernel<", " stream_through_kernel<", " march_kernel<", " march_masked_kernel<")):
         # in the streaming kernels a wavefront's accesses do not depend on how wavefronts are grouped
         # into workgroups: a record taken with another workgroup size of the same mapping serves
         strip = lambda k: re.sub(r", wg \d+x\d+", "", k)
@@ -479,23 +480,26 @@ class Bench:
         else:
             apply_mapping(st, mapping)
             st.set_option(self.ls.OPT_NT_STORE, nt)
-        depth = mapping[3] if len(mapping) > 3 and mapping[3] else 1
-        self.rotation()
+        # what a sample's launches are (with a rotation of pairs: single applications)
+        chain = self.burst if len(self.rotation()) == 1 else 1
+        info = st.describe_run(chain, size)
+        depth = info["applications"]
+        per_launch = chain / info["launches"]            # on average: the last launch makes what is left
         self.precondition(size)
         k_res = st.sweep(self.tin, self.tout, [size], iters=self.burst, fixed=(0, 0), reps=max(a.reps, 30))
-        launches = -(-self.burst // depth)
+        launches = info["launches"] * (self.burst // chain)
         kernel_ms = same_ms = k_res.mean_ms[0] / launches
         if len(self.pairs) > 1:
             kernel_ms = self.timed_kernel(size, max(a.reps, 30))
             same_ms = self.timed_kernel(size, max(a.reps, 30), one_pair=True)
         achieved = self.alg_bytes / (kernel_ms * 1e-3) / 1e9
-        label = kernel_label(w, mapping, size, depth if len(mapping) > 3 and mapping[3] else 0, nt, remap)
+        label = kernel_label(w, mapping, info, nt, remap)
         rec = recorded_counters(label)
         out = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                "frac": achieved / HBM_PEAK_GBS, "traffic": rec["traffic_bytes_per_launch"] if rec else None,
                "kernel": label, "kernel_ms": kernel_ms, "algorithmic_bytes_per_launch": self.alg_bytes,
                "applications_per_launch": depth, "nt_store": nt,
-               "gcells_s": self.cells * depth / (kernel_ms * 1e-3) / 1e9,
+               "gcells_s": self.cells * per_launch / (kernel_ms * 1e-3) / 1e9,
                "matrix_pairs_in_rotation": len(self.pairs)}
         if len(self.pairs) > 1:
             # the same launches on one matrix pair, part of whose input the last-level cache still holds
@@ -505,7 +509,7 @@ class Bench:
         # the arithmetic views: algorithmic fp32 operations against the published vector peak ...
         flops = flops_per_cell_update(w)
         if flops:
-            tflops = flops * self.cells * depth / (kernel_ms * 1e-3) / 1e12
+            tflops = flops * self.cells * per_launch / (kernel_ms * 1e-3) / 1e12
             out["alu"] = {"bound": "alu", "achieved": tflops, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                           "frac": tflops / FP32_VECTOR_PEAK_TFLOPS, "flops_per_cell_update": flops}
         # ... and vector instructions issued (rocprofv3 SQ_INSTS_VALU, 64 lanes each; an instruction of
@@ -515,8 +519,8 @@ class Bench:
             rate = slots / (kernel_ms * 1e-3)
             out["valu_issue"] = {"bound": "alu", "achieved": rate / 1e12, "peak": VALU_LANE_ISSUE_PEAK / 1e12,
                                  "unit": "T lane-instructions/s", "frac": rate / VALU_LANE_ISSUE_PEAK,
-                                 "valu_insts_per_cell_update": rec["valu_insts_per_launch"] * 64.0 / (self.cells * depth),
-                                 "issue_slots_per_cell_update": slots / (self.cells * depth),
+                                 "valu_insts_per_cell_update": rec["valu_insts_per_launch"] * 64.0 / (self.cells * per_launch),
+                                 "issue_slots_per_cell_update": slots / (self.cells * per_launch),
                                  "valu_busy_frac_in_profile": rec.get("valu_busy_frac")}
         return out
 
@@ -557,13 +561,14 @@ def sub_record(ls, torch, wl, name, args):
     c1 = configs[min(single, key=lambda k: mean[k])] if single else None
 
     nt = configure(c)
+    info = b.st.describe_run(w.iters, c[4])
     steps = {"C1": 200, "C2": 200, "C3": 10, "C4": 3, "C5": 30, "H8192": 50, "H16384": 20, "W8192": 30, "G5": 30, "G7": 30, "D5": 50, "I5": 50}[name]
     ms_per_step, value = b.timed_steps(c[4], steps, max(1, steps // 10))
     out = {"workload": w.name, "metric": "Gcells/s", "value": value, "unit": "Gcells/s", "ms_per_step": ms_per_step,
            "steps": steps, "dtype": w.dtype,
            "config": {"rows": w.rows, "cols": w.cols, "iters": w.iters, "mapping": mapping_name(as_mapping(c)),
                       "wg": list(c[4]), "xcd_remap": flags(c)[0], "nt_store": nt,
-                      "applications_per_launch": max(1, c[3]), "configurations_swept": len(configs),
+                      "applications_per_launch": info["applications"], "kernel": info["kernel"], "configurations_swept": len(configs),
                       "matrix_pairs_in_rotation": len(b.pairs)}}
     if c1 is not None:
         nt1 = configure(c1)
@@ -800,6 +805,7 @@ def main():
         st.set_option(ls.OPT_NT_STORE, nt_store)
     else:
         nt_store = b.choose_stores_for_steps(blocking, wg)
+    timed_run = st.describe_run(w.iters, wg)
     ms_per_step, value = b.timed_steps(wg, steps, warmup)
 
     # `roofline` prices the best kernel that makes ONE application per launch: that is the
@@ -832,7 +838,7 @@ def main():
         "config": {"workload": w.name, "rows": w.rows, "cols": w.cols, "iters": w.iters,
                    "halo_nsew": list(w.halo), "border": w.border, "best_wg": list(wg),
                    "staging": blocking[0], "cells_per_work_item": list(blocking[1:3]),
-                   "applications_per_launch": blocking[3] if len(blocking) > 3 else 1,
+                   "applications_per_launch": timed_run["applications"],
                    "nt_store": nt_store, "sweep_burst": burst, "sweep_reps": args.reps,
                    "preconditioning_seconds": PRECONDITION_SECONDS, "matrix_pairs_in_rotation": n_pairs},
         "roofline": roofline,

@@ -262,6 +262,21 @@ int64_t stencil_tile_bytes(const stencil_t *st, int wg_rows, int wg_cols);
  * STENCIL_E_REFUSED with the runtime's text, the sweeps record the size as refused and go on). */
 int stencil_is_legal(const stencil_t *st, int wg_rows, int wg_cols);
 
+/* What stencil_run(st, ..., iters, wg_rows, wg_cols, ...) starts.  Under STENCIL_STAGING_STREAM and
+ * STENCIL_STAGING_TEMPORAL the library may take another kernel than the mapping's own, in a workgroup of its own
+ * choice, or fuse more applications than asked for (stencil_set_mapping says where); stencil_max_wg_size,
+ * stencil_tile_bytes and stencil_is_legal speak of the mapping's own kernel, this of the one that runs.
+ * No GPU call.  STENCIL_E_REFUSED as for stencil_run. */
+typedef struct stencil_launch_info {
+    char kernel[48];          /* its name without parameters ("tile_kernel by rows": folded row by row) */
+    int launches;             /* that the run takes */
+    int applications;         /* per launch (the last makes what is left) */
+    int wg_rows, wg_cols;     /* the workgroup */
+    int64_t workgroups;       /* of the first launch */
+    int64_t local_bytes;      /* local memory per workgroup */
+} stencil_launch_info_t;
+int stencil_describe_run(const stencil_t *st, int iters, int wg_rows, int wg_cols, stencil_launch_info_t *info);
+
 /* Section 5's enumeration.  Writes up to `cap` pairs to rows[]/cols[] (may be NULL when
  * cap = 0) in row-major order of (w_r, w_c) and returns the total number of pairs with
  * w_r*w_c <= max_threads (or a negative status). */
@@ -332,7 +347,9 @@ int stencil_set_sweep_rotation(stencil_t *st, const void *const *ins, void *cons
  * best_index = argmin of the mean over legal sizes (Eq. 3; ties: fewer work-items, then
  * smaller w_r), -1 if none.  speedup_over_fixed = mean(fixed) / mean(best) (Section 7's
  * speedup metric; the fixed size is timed additionally if it is not in the list; NaN if it
- * is refused); pass fixed_rows = 0 to skip.  Synchronous: returns after the last sample.
+ * is refused); pass fixed_rows = 0 to skip.  Sizes that come to the same launches (stencil_describe_run: the
+ * same kernel, workgroup and applications per launch, whatever was asked for) are timed once and share the
+ * figures, so that of them the best is the smallest.  Synchronous: returns after the last sample.
  * Remembers the best size for stencil_run(0, 0). */
 int stencil_sweep_wg(stencil_t *st, const void *in, void *out, int iters,
                      const int *wg_rows_list, const int *wg_cols_list, int n,

@@ -280,6 +280,21 @@ int launch_failure(hipError_t e, int wr, int wc) {
     }
 }
 
+// Applications per launch of a run, and whether it is made by the variant's kernel for runs of several launches.
+struct RunPlan {
+    int per;
+    bool run;
+    int launches(int iters) const { return (iters + per - 1) / per; }
+};
+RunPlan run_plan(const stencil *s, const Variant *v, int iters, int wr, int wc) {
+    const int per = v->fuses ? s->temporal_depth : 1;
+    const int run_per = v->per_launch && iters > per ? v->per_launch(s, iters, wr, wc) : 0;
+    return {run_per > 0 ? run_per : per, run_per > 0};
+}
+LaunchPlan launch_plan(const stencil *s, const Variant *v, const RunPlan &p, int iters, int wr, int wc) {
+    return (p.run ? v->plan_run : v->plan)(s, wr, wc, std::min(p.per, std::max(1, iters)));
+}
+
 // `iters` out-of-place applications ending in `out`, never writing `in`.
 int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *pingpong, int iters, int wr, int wc,
                 hipStream_t stream) {
@@ -291,14 +306,12 @@ int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *p
     }
     // `per` applications per launch; the launches alternate between `out` and the scratch
     // matrix so that the last one lands in `out`
-    int per = v->fuses ? s->temporal_depth : 1;
-    const int run_per = v->per_launch && iters > per ? v->per_launch(s, iters, wr, wc) : 0;
-    if (run_per > 0) per = run_per;
-    const int launches = (iters + per - 1) / per;
+    const RunPlan plan = run_plan(s, v, iters, wr, wc);
+    const int per = plan.per, launches = plan.launches(iters);
     // (or, of Life, between two matrices of packed bits, which the scratch matrix holds both of unless its rows are
     // shorter than two words are in bytes)
     const size_t packed_bytes = (size_t)s->rows * (size_t)life_words(s) * 4;
-    const bool packed = run_per > 0 && s->kernel == STENCIL_LIFE && launches > 1 && 2 * packed_bytes <= s->bytes();
+    const bool packed = plan.run && s->kernel == STENCIL_LIFE && launches > 1 && 2 * packed_bytes <= s->bytes();
     void *const halves[2] = {pingpong, static_cast<char *>(pingpong) + (packed ? packed_bytes : 0)};
     const void *src = in;
     void *dst = packed ? halves[0] : (launches % 2 == 1) ? out : pingpong;
@@ -308,8 +321,8 @@ int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *p
         if (packed && last) dst = out;
         const bool injected = s->fail_rows == -1 || (s->fail_rows == wr && s->fail_cols == wc);
         hipError_t e = injected ? hipErrorLaunchOutOfResources
-                       : run_per > 0 ? v->launch_run(s, src, packed && src != in, dst, packed && !last, wr, wc, now, stream)
-                                     : v->launch(s, src, dst, wr, wc, now, stream);
+                       : plan.run ? v->launch_run(s, src, packed && src != in, dst, packed && !last, wr, wc, now, stream)
+                                  : v->launch(s, src, dst, wr, wc, now, stream);
         if (e != hipSuccess) return launch_failure(e, wr, wc);
         done += now;
         src = dst;
@@ -673,6 +686,25 @@ int stencil_is_legal(const stencil_t *s, int wg_rows, int wg_cols) {
     return check_legal(s, find_variant(s), wg_rows, wg_cols) == STENCIL_OK ? 1 : 0;
 }
 
+int stencil_describe_run(const stencil_t *s, int iters, int wg_rows, int wg_cols, stencil_launch_info_t *info) {
+    if (!s || !info) return fail(STENCIL_E_INVALID, "NULL argument");
+    if (iters < 1) return fail(STENCIL_E_INVALID, "iters must be >= 1");
+    const Variant *v = find_variant(s);
+    int rc = check_legal(s, v, wg_rows, wg_cols);
+    if (rc != STENCIL_OK) return rc;
+    const RunPlan plan = run_plan(s, v, iters, wg_rows, wg_cols);
+    const LaunchPlan l = launch_plan(s, v, plan, iters, wg_rows, wg_cols);
+    std::snprintf(info->kernel, sizeof(info->kernel), "%s", l.kernel);
+    info->launches = plan.launches(iters);
+    info->applications = std::min(plan.per, iters);
+    info->wg_rows = l.wg_rows;
+    info->wg_cols = l.wg_cols;
+    info->workgroups = l.blocks;
+    info->local_bytes = l.lds_bytes;
+    g_err[0] = '\0';
+    return STENCIL_OK;
+}
+
 int stencil_enumerate_wg(int mode, int max_threads, int *rows, int *cols, int cap) {
     if (max_threads < 1 || cap < 0 || (cap > 0 && (!rows || !cols)))
         return fail(STENCIL_E_INVALID, "bad arguments to stencil_enumerate_wg");
@@ -814,6 +846,15 @@ int stencil_sweep_wg(stencil_t *s, const void *in, void *out, int iters, const i
 
     std::vector<double> means((size_t)n + 1, nan);
     std::vector<int> stat((size_t)n + 1, STENCIL_E_REFUSED);
+    // the launches of each size timed so far, and whether it was only probed: sizes that come to the same launches
+    // (a mapping's tile or run kernel takes a workgroup of its own) are timed once and share the figures
+    struct Timed {
+        LaunchPlan launch{};
+        int per = 0;
+        bool probed = false;
+    };
+    std::vector<Timed> timed((size_t)n + 1);
+    const int chain = s->rotation.empty() ? iters : 1;
 
     // times one size into slot k; returns STENCIL_OK also when the size is refused
     // probe_only: one warm-up and two samples instead of three warm-ups and `reps` samples
@@ -831,6 +872,24 @@ int stencil_sweep_wg(stencil_t *s, const void *in, void *out, int iters, const i
             return STENCIL_OK;
         };
         if (check_legal(s, v, wr, wc) != STENCIL_OK) return refused();
+        const RunPlan plan = run_plan(s, v, chain, wr, wc);
+        const LaunchPlan launch = launch_plan(s, v, plan, chain, wr, wc);
+        for (int j = 0; j < n && s->fail_rows == 0; ++j) {
+            const LaunchPlan &l = timed[j].launch;
+            if (j == k || stat[j] != STENCIL_OK || timed[j].per != plan.per || timed[j].probed != probe_only ||
+                l.kernel != launch.kernel || l.wg_rows != launch.wg_rows || l.wg_cols != launch.wg_cols ||
+                l.blocks != launch.blocks || l.lds_bytes != launch.lds_bytes)
+                continue;
+            means[k] = means[j];
+            stat[k] = STENCIL_OK;
+            timed[k] = timed[j];
+            if (k < n) {
+                if (min_ms) min_ms[k] = min_ms[j];
+                if (median_ms) median_ms[k] = median_ms[j];
+                if (stddev_ms) stddev_ms[k] = stddev_ms[j];
+            }
+            return STENCIL_OK;
+        }
         // samples [from, to) into the event pairs, then wait for them and read the times
         auto take = [&](int from, int to) -> int {
             for (int i = from; i < to; ++i) {
@@ -870,6 +929,7 @@ int stencil_sweep_wg(stencil_t *s, const void *in, void *out, int iters, const i
         samples.resize((size_t)reps);
         means[k] = st.mean;
         stat[k] = STENCIL_OK;
+        timed[k] = {launch, plan.per, probe_only};
 
         if (k < n) {
             if (min_ms) min_ms[k] = st.min;

@@ -20,6 +20,14 @@ using LaunchFn = hipError_t (*)(const stencil *, const void *, void *, int, int,
 using RunLaunchFn = hipError_t (*)(const stencil *, const void *in, bool in_bits, void *out, bool out_bits, int wg_rows,
                                    int wg_cols, int fused, hipStream_t);
 
+// What a launch starts: the launchers cut their grids from the same functions (stencil_describe_run).
+struct LaunchPlan {
+    const char *kernel;        // without its parameters
+    int wg_rows, wg_cols;
+    int64_t blocks;
+    int64_t lds_bytes;         // dynamic local memory of a workgroup
+};
+
 struct Variant {
     int staging;          // STENCIL_STAGING_LOCAL, _DIRECT, _TEMPORAL or _STREAM
     int kernel, border;
@@ -34,6 +42,9 @@ struct Variant {
     // (0: the run is made by `launch`), and its launcher
     int (*per_launch)(const stencil *, int iters, int wg_rows, int wg_cols) = nullptr;
     RunLaunchFn launch_run = nullptr;
+    // what `launch` and `launch_run` start for so many applications
+    LaunchPlan (*plan)(const stencil *, int wg_rows, int wg_cols, int fused) = nullptr;
+    LaunchPlan (*plan_run)(const stencil *, int wg_rows, int wg_cols, int fused) = nullptr;
     // the compiled kernel a launch of this scenario would start (what hipFuncGetAttributes is asked about)
     const void *(*kernel_of)(const stencil *) = nullptr;
 };

@@ -27,9 +27,11 @@
 // many makes, or 0 where the mapping's own kernel makes the run, and the launcher.
 int register_tile_per_launch(const stencil *s, int iters, int wg_rows, int wg_cols);
 RunLaunchFn register_tile_launcher(int kernel, int border);
+LaunchPlan register_tile_plan(const stencil *s, int wg_rows, int wg_cols, int fused);
 
-// The launcher of the fp32 sums' tile with 2 x 4 cells (variants_weighted_sum_tiles.hip): 5x5, or a run-time region.
+// The launcher of the fp32 sums' tile with 2 x 4 cells (variants_weighted_sum_tiles.hip): 5x5, or a run-time region.  And its kernel.
 LaunchFn weighted_sum_tile(int border, bool five_by_five);
+const void *weighted_sum_tile_kernel(const stencil *s, bool five_by_five);
 
 // Local memory a workgroup may allocate: the device's own figure once a GPU has been used, the
 // header's constant before that (defined in libstencil.hip).
@@ -100,6 +102,12 @@ sk::Store store_of(const stencil *s) {
     return s->out_bytes() >= kThroughBytes ? sk::Store::kThrough : sk::Store::kPlain;
 }
 
+// Blocks of a launch of so many tiles: the workgroups numbered for the eight XCDs, `chunk` to each, or (0) as they come.
+int64_t numbered_blocks(const stencil *s, int64_t tiles, int *chunk) {
+    *chunk = s->xcd_remap && tiles >= 64 ? (int)((tiles + 7) / 8) : 0;
+    return *chunk ? (int64_t)*chunk * 8 : tiles;
+}
+
 // Kernel arguments and grid for one launch; `blocks` is the grid size.
 template <class Op, class Halo, int CR, int CC>
 sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, void *out, int wr, int wc,
@@ -145,14 +153,39 @@ sk::TileArgs<Op, Halo> make_args(const stencil *s, int staging, const void *in, 
         a.halo.w_ = s->hw;
         a.w.v = static_cast<decltype(a.w.v)>(s->table_in_use);
     }
-    *blocks = (unsigned)a.n_tiles;
-    a.xcd_chunk = 0;
-    if (s->xcd_remap && a.n_tiles >= 64) {
-        a.xcd_chunk = (a.n_tiles + 7) / 8;
-        *blocks = (unsigned)a.xcd_chunk * 8u;
-    }
+    *blocks = (unsigned)numbered_blocks(s, a.n_tiles, &a.xcd_chunk);
     *lds_bytes = (size_t)g.lds_bytes;
     return a;
+}
+
+// ... and what such a launch starts.
+LaunchPlan plan_tiles(const stencil *s, const char *kernel, int staging, int cr, int cc, int staged_bytes, int wr, int wc) {
+    Variant v{};
+    v.staging = staging;
+    v.cr = cr;
+    v.cc = cc;
+    v.staged_bytes = staged_bytes;
+    const TileGeom g = tile_geom(s, v, wr, wc);
+    int chunk;
+    return {kernel, wr, wc, numbered_blocks(s, (int64_t)g.tiles_r * g.tiles_c, &chunk), g.lds_bytes};
+}
+template <class Op, class Halo, int CR, int CC>
+LaunchPlan plan_tile(const stencil *s, int wr, int wc, int) {
+    const char *kernel = sk::folds_by_rows<Halo>::value && Halo::kStatic ? "tile_kernel by rows" : "tile_kernel";
+    return plan_tiles(s, kernel, STENCIL_STAGING_LOCAL, CR, CC, (int)sizeof(typename Op::L) * Op::kPlanes, wr, wc);
+}
+template <class Op, int CR, int CC>
+LaunchPlan plan_direct(const stencil *s, int wr, int wc, int) {
+    return plan_tiles(s, std::is_same<Op, sk::OpLife>::value ? "life_direct_kernel" : "direct_kernel", STENCIL_STAGING_DIRECT, CR, CC, 0, wr, wc);
+}
+template <int CR>
+LaunchPlan plan_temporal(const stencil *s, int wr, int wc, int) {
+    return plan_tiles(s, "temporal_kernel", STENCIL_STAGING_TEMPORAL, CR, 4, 4, wr, wc);
+}
+// Marches: a wavefront to a segment, workgroups only group wavefronts (blocks before numbering).
+LaunchPlan plan_segments(const stencil *s, const char *kernel, int strip_cols, int wr, int wc) {
+    const int64_t segments = (s->rows + s->cr - 1) / s->cr * ((s->cols + strip_cols - 1) / strip_cols), waves = wr * wc / 64;
+    return {kernel, wr, wc, (segments + waves - 1) / waves, 0};
 }
 
 // Tiles above 64 KiB need the kernel's dynamic local-memory limit raised, once per kernel and
@@ -186,6 +219,14 @@ hipError_t launch_temporal(const stencil *s, const void *in, void *out, int wr, 
     return hipGetLastError();
 }
 
+// Which launches of a march of several applications have their output written through.
+bool stream_goes_through(const stencil *s, int depth) {
+    return s->cols % 4 == 0 && depth >= sk::kStreamThroughDepth && store_of(s) == sk::Store::kThrough;
+}
+LaunchPlan plan_stream(const stencil *s, int wr, int wc, int depth) {
+    return plan_segments(s, stream_goes_through(s, depth) ? "stream_through_kernel" : "stream_kernel", sk::stream_cols(depth), wr, wc);
+}
+
 template <class Op, int B>
 hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, int wc, int depth, hipStream_t stream) {
     using Halo = sk::HaloC<1, 1, 1, 1>;
@@ -205,7 +246,7 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
     blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
     const dim3 grid(blocks), block(wc, wr);
     const bool whole = s->cols % 4 == 0;      // rows of whole vectors, or the element-by-element body
-    if (whole && a.store == sk::Store::kThrough) {
+    if (stream_goes_through(s, depth)) {
         static_assert(sk::kStreamThroughDepth == 4 && sk::kStreamMaxDepth == 8, "a case each");
 #define THROUGH_LAUNCH(D)                                                                                      \
     hipLaunchKernelGGL((&sk::stream_through_kernel<Op, B, D, kMaxT>), grid, block, 0, stream, a, CR);          \
@@ -349,6 +390,10 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     }
     return hipGetLastError();
 }
+LaunchPlan plan_life_stream(const stencil *s, int wr, int wc, int depth) {
+    const LifeTile t = life_tile(s, wr * wc, depth, true);
+    return {"life_stream_kernel", wr, wc, (int64_t)t.tiles_r * t.tiles_c, sk::life_stream_lds(wr * wc)};
+}
 template <int B>
 hipError_t launch_life_stream(const stencil *s, const void *in, void *out, int wr, int wc, int depth, hipStream_t stream) {
     if (depth < 1 || depth > STENCIL_MAX_STREAM_DEPTH) return hipErrorInvalidValue;
@@ -377,14 +422,14 @@ hipError_t launch_threshold(const stencil *s, const void *in, void *out, int wr,
     a.tiles_c = (a.cols + tw - 1) / tw;
     a.n_tiles = ((a.rows + th - 1) / th) * a.tiles_c;
     a.level = s->scalar0;
-    unsigned blocks = (unsigned)a.n_tiles;
-    a.xcd_chunk = 0;
-    if (s->xcd_remap && a.n_tiles >= 64) {
-        a.xcd_chunk = (a.n_tiles + 7) / 8;
-        blocks = (unsigned)a.xcd_chunk * 8u;
-    }
+    const unsigned blocks = (unsigned)numbered_blocks(s, a.n_tiles, &a.xcd_chunk);
     hipLaunchKernelGGL((sk::threshold_kernel<CR, CC, STENCIL_MAX_WG_SIZE>), dim3(blocks), dim3(wc, wr), 0, stream, a);
     return hipGetLastError();
+}
+
+template <int CR, int CC>
+LaunchPlan plan_threshold(const stencil *s, int wr, int wc, int) {
+    return plan_tiles(s, "threshold_kernel", STENCIL_STAGING_DIRECT, CR, CC, 0, wr, wc);
 }
 
 template <int B, int CR, int MAXT>
@@ -403,6 +448,13 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
     lds = 4 * (2 * (size_t)a.plane + 2);         // + one spare word at each end
     hipLaunchKernelGGL((sk::life_temporal_kernel<B, CR, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a, depth);
     return hipGetLastError();
+}
+template <int CR>
+LaunchPlan plan_life_temporal(const stencil *s, int wr, int wc, int) {
+    LaunchPlan p = plan_tiles(s, "life_temporal_kernel", STENCIL_STAGING_TEMPORAL, CR, 16, 1, wr, wc);
+    const int64_t words = (wc * 16 + 2 * 16 + 31) / 32;
+    p.lds_bytes = 4 * (2 * (wr * CR + 2 * s->temporal_depth) * words + 2);
+    return p;
 }
 
 // Which fold of the tile kernel serves a run-time region (work-items of several columns of cells).
@@ -464,6 +516,15 @@ hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int 
     return hipGetLastError();
 }
 
+// ... and what it starts.  (The run-time folds are one kernel as far as a plan goes.)
+template <class Op, class Halo, int CR, int CC>
+LaunchPlan plan_launch_tile(const stencil *s, int wr, int wc, int) {
+    if constexpr (unrolled_for_one_row<Halo, CR>()) {
+        if (wr == 1) return plan_tile<Op, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC>(s, wr, wc, 1);
+    }
+    return plan_tile<Op, Halo, CR, CC>(s, wr, wc, 1);
+}
+
 // Single applications under the streaming mapping: whether the march makes them, or a tile of 2 x 4 cells and 8 x 32 work-items
 // (a march's workgroup only groups wavefronts, and its segment height has no meaning for a tile).  The march keeps sin/cos on
 // matrices that no cache holds, where it takes the sine and cosine of every cell once (8192^2 119 us, tile 128; 3000 x 4100
@@ -480,6 +541,10 @@ bool march_pays(const stencil *s) {
 }
 constexpr int kStreamTileRows = 8, kStreamTileCols = 32;
 
+// The region as that tile folds it.
+template <class Op, class Halo>
+using StreamTileHalo = typename std::conditional<by_rows<Op, Halo, 2, 4>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
+
 // One application, marched down the matrix in registers (march_kernel.h).
 template <class Op, int B, class Halo>
 hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
@@ -488,8 +553,7 @@ hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int
         if constexpr (Halo::N == 2) {
             return weighted_sum_tile(B, true)(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
         } else {
-            using Folded = typename std::conditional<by_rows<Op, Halo, 2, 4>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
-            return launch_tile<Op, B, Folded, 2, 4, STENCIL_MAX_WG_SIZE>(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
+            return launch_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
         }
     }
     unsigned blocks;
@@ -497,17 +561,24 @@ hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int
     auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
     // a tile is a wavefront's segment; workgroups only group wavefronts
     const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
-    blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
-    a.xcd_chunk = 0;
-    if (s->xcd_remap && blocks >= 64) {
-        a.xcd_chunk = (int)((blocks + 7) / 8);
-        blocks = (unsigned)a.xcd_chunk * 8u;
-    }
+    blocks = (unsigned)numbered_blocks(s, ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block, &a.xcd_chunk);
     // with either kind of store
     hipLaunchKernelGGL(s->nt_store ? (&sk::march_kernel<Op, B, Halo, true, true, kMaxT>)
                                    : (&sk::march_kernel<Op, B, Halo, true, false, kMaxT>),
                        dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
     return hipGetLastError();
+}
+
+template <class Op, class Halo>
+LaunchPlan plan_march(const stencil *s, int wr, int wc, int) {
+    if (!march_pays(s)) {
+        if constexpr (Halo::kMasked) return plan_tile<Op, sk::HaloD, 2, 4>(s, kStreamTileRows, kStreamTileCols, 1);
+        else return plan_launch_tile<Op, StreamTileHalo<Op, Halo>, 2, 4>(s, kStreamTileRows, kStreamTileCols, 1);
+    }
+    LaunchPlan p = plan_segments(s, Halo::kMasked ? "march_masked_kernel" : "march_kernel", sk::march_vectors(s->hw, s->he) * 4, wr, wc);
+    int chunk;
+    p.blocks = numbered_blocks(s, p.blocks, &chunk);
+    return p;
 }
 
 // The same for any region within the kernel's largest one (march_masked_kernel.h): the kernel compiled for the
@@ -525,12 +596,7 @@ hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int 
         size_t lds;
         auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
         const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
-        blocks = ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block;
-        a.xcd_chunk = 0;
-        if (s->xcd_remap && blocks >= 64) {
-            a.xcd_chunk = (int)((blocks + 7) / 8);
-            blocks = (unsigned)a.xcd_chunk * 8u;
-        }
+        blocks = (unsigned)numbered_blocks(s, ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block, &a.xcd_chunk);
         hipLaunchKernelGGL(s->nt_store ? (&sk::march_masked_kernel<Op, B, Halo, WC, true, true, kMaxT>)
                                        : (&sk::march_masked_kernel<Op, B, Halo, WC, true, false, kMaxT>),
                            dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
@@ -579,9 +645,16 @@ const void *kernel_life_temporal(const stencil *) { return reinterpret_cast<cons
 template <int CR, int CC>
 const void *kernel_threshold(const stencil *) { return reinterpret_cast<const void *>(&sk::threshold_kernel<CR, CC, STENCIL_MAX_WG_SIZE>); }
 template <class Op, int B, class Halo>
-const void *kernel_march(const stencil *) { return reinterpret_cast<const void *>(&sk::march_kernel<Op, B, Halo, true, false, 256>); }
+const void *kernel_march(const stencil *s) {
+    if (!march_pays(s)) {
+        if constexpr (Halo::N == 2) return weighted_sum_tile_kernel(s, true);
+        else return kernel_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s);
+    }
+    return reinterpret_cast<const void *>(&sk::march_kernel<Op, B, Halo, true, false, 256>);
+}
 template <class Op, int B, class Halo, int WC = 1>
 const void *kernel_march_masked(const stencil *s) {
+    if (!march_pays(s)) return weighted_sum_tile_kernel(s, false);
     if constexpr (WC > Halo::E + Halo::W + 1)
         return nullptr;
     else if (s->he + s->hw + 1 != WC)
@@ -635,6 +708,7 @@ void reg_one(std::vector<Variant> &r) {
     v.staged_bytes = (int)sizeof(typename Op::L) * Op::kPlanes;
     using Folded = typename std::conditional<by_rows<Op, Halo, CR, CC>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
     v.launch = &launch_tile<Op, B, Folded, CR, CC, kMaxT>;
+    v.plan = &plan_launch_tile<Op, Folded, CR, CC>;
     v.kernel_of = &kernel_tile<Op, B, Folded, CR, CC, kMaxT>;
     r.push_back(v);
 }
@@ -651,6 +725,7 @@ void reg_direct_one(std::vector<Variant> &r) {
     v.max_threads = STENCIL_MAX_WG_SIZE;
     v.staged_bytes = 0;
     v.launch = &launch_direct<Op, B, Halo, CR, CC, STENCIL_MAX_WG_SIZE>;
+    v.plan = &plan_direct<Op, CR, CC>;
     v.kernel_of = &kernel_direct<Op, B, Halo, CR, CC, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);
 }
@@ -681,9 +756,11 @@ void reg_temporal_one(std::vector<Variant> &r) {
     v.staged_bytes = 4;
     v.fuses = true;
     v.launch = &launch_temporal<Op, B, CR, STENCIL_MAX_WG_SIZE>;
+    v.plan = &plan_temporal<CR>;
     v.kernel_of = &kernel_temporal<Op, B, STENCIL_MAX_WG_SIZE>;
     v.per_launch = &register_tile_per_launch;
     v.launch_run = register_tile_launcher(KID, B);
+    v.plan_run = &register_tile_plan;
     r.push_back(v);
 }
 
@@ -707,9 +784,11 @@ void reg_stream_one(std::vector<Variant> &r) {
     v.staged_bytes = 0;
     v.fuses = true;
     v.launch = &launch_stream<Op, B>;
+    v.plan = &plan_stream;
     v.kernel_of = &kernel_stream<Op, B>;
     v.per_launch = &register_tile_per_launch;
     v.launch_run = register_tile_launcher(KID, B);
+    v.plan_run = &register_tile_plan;
     r.push_back(v);
 }
 
@@ -732,8 +811,10 @@ void reg_life_stream_one(std::vector<Variant> &r) {
     v.staged_bytes = 0;
     v.fuses = true;
     v.launch = &launch_life_stream<B>;
+    v.plan = &plan_life_stream;
     v.per_launch = &life_per_launch;
     v.launch_run = &launch_life_stream_run<B>;
+    v.plan_run = &plan_life_stream;
     v.kernel_of = &kernel_life_stream<B>;
     r.push_back(v);
 }
@@ -756,6 +837,7 @@ void reg_threshold_one(std::vector<Variant> &r) {
     v.max_threads = STENCIL_MAX_WG_SIZE;
     v.staged_bytes = 0;
     v.launch = &launch_threshold<CR, CC>;
+    v.plan = &plan_threshold<CR, CC>;
     v.kernel_of = &kernel_threshold<CR, CC>;
     r.push_back(v);
 }
@@ -783,6 +865,7 @@ void reg_march_one(std::vector<Variant> &r) {
     v.staged_bytes = 0;
     v.fuses = false;
     v.launch = &launch_march<Op, B, Halo>;
+    v.plan = &plan_march<Op, Halo>;
     v.kernel_of = &kernel_march<Op, B, Halo>;
     r.push_back(v);
 }
@@ -811,6 +894,7 @@ void reg_march_masked_one(std::vector<Variant> &r) {
     v.staged_bytes = 0;
     v.fuses = false;
     v.launch = &launch_march_masked<Op, B, Halo>;
+    v.plan = &plan_march<Op, Halo>;
     v.kernel_of = &kernel_march_masked<Op, B, Halo>;
     r.push_back(v);
 }
@@ -834,9 +918,11 @@ void reg_life_temporal_one(std::vector<Variant> &r) {
     v.max_threads = STENCIL_MAX_WG_SIZE;
     v.staged_bytes = 1;
     v.fuses = true;
+    v.plan = &plan_life_temporal<CR>;
     v.launch = &launch_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;
     v.per_launch = &life_per_launch;
     v.launch_run = &launch_life_stream_run<B>;
+    v.plan_run = &plan_life_stream;
     v.kernel_of = &kernel_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);
 }
@@ -859,6 +945,7 @@ void reg_life_direct_one(std::vector<Variant> &r) {
     v.cc = 16;
     v.max_threads = STENCIL_MAX_WG_SIZE;
     v.staged_bytes = 0;
+    v.plan = &plan_direct<sk::OpLife, CR, 16>;
     v.launch = &launch_life_direct<B, CR, STENCIL_MAX_WG_SIZE>;
     v.kernel_of = &kernel_life_direct<B, CR, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);

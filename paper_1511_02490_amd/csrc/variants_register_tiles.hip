@@ -119,6 +119,11 @@ int register_tile_per_launch(const stencil *s, int iters, int wr, int wc) {
     return best;
 }
 
+LaunchPlan register_tile_plan(const stencil *s, int, int, int depth) {
+    const RegisterTile t = register_tile(s, depth);
+    return {"register_tile_kernel", 1, t.threads, (int64_t)t.tiles_r * t.tiles_c, sk::register_tile_lds(t.threads)};
+}
+
 RunLaunchFn register_tile_launcher(int kernel, int border) {
     return kernel == STENCIL_HEAT ? launcher_of<sk::OpHeat>(border) : launcher_of<sk::OpWeightedSum>(border);
 }

@@ -49,3 +49,13 @@ LaunchFn weighted_sum_tile(int border, bool five_by_five) {
     default: return five_by_five ? &launch_tile<Op, sk::kConstant, Five, 2, 4, STENCIL_MAX_WG_SIZE> : &launch_tile<Op, sk::kConstant, sk::HaloD, 2, 4, STENCIL_MAX_WG_SIZE>;
     }
 }
+
+const void *weighted_sum_tile_kernel(const stencil *s, bool five_by_five) {
+    using Op = sk::OpWeightedSum;
+    using Five = sk::HaloC<2, 2, 2, 2>;
+    switch (s->border) {
+    case STENCIL_CLAMP: return five_by_five ? kernel_tile<Op, sk::kClamp, Five, 2, 4, STENCIL_MAX_WG_SIZE>(s) : kernel_tile<Op, sk::kClamp, sk::HaloD, 2, 4, STENCIL_MAX_WG_SIZE>(s);
+    case STENCIL_WRAP: return five_by_five ? kernel_tile<Op, sk::kWrap, Five, 2, 4, STENCIL_MAX_WG_SIZE>(s) : kernel_tile<Op, sk::kWrap, sk::HaloD, 2, 4, STENCIL_MAX_WG_SIZE>(s);
+    default: return five_by_five ? kernel_tile<Op, sk::kConstant, Five, 2, 4, STENCIL_MAX_WG_SIZE>(s) : kernel_tile<Op, sk::kConstant, sk::HaloD, 2, 4, STENCIL_MAX_WG_SIZE>(s);
+    }
+}

@@ -41,6 +41,12 @@ class Refused(StencilError):
     """The workgroup size is not legal for the scenario (Section 3.1's refused parameter)."""
 
 
+class _LaunchInfo(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_char * 48), ("launches", ctypes.c_int), ("applications", ctypes.c_int),
+                ("wg_rows", ctypes.c_int), ("wg_cols", ctypes.c_int), ("workgroups", ctypes.c_int64),
+                ("local_bytes", ctypes.c_int64)]
+
+
 def _load() -> ctypes.CDLL:
     if not os.path.exists(LIB_PATH):
         raise ImportError(
@@ -69,6 +75,7 @@ def _load() -> ctypes.CDLL:
         "stencil_max_wg_size": (c_int, [vp]),
         "stencil_tile_bytes": (c_i64, [vp, c_int, c_int]),
         "stencil_is_legal": (c_int, [vp, c_int, c_int]),
+        "stencil_describe_run": (c_int, [vp, c_int, c_int, c_int, ctypes.POINTER(_LaunchInfo)]),
         "stencil_enumerate_wg": (c_int, [c_int, c_int, ip, ip, c_int]),
         "stencil_run": (c_int, [vp, vp, vp, c_int, c_int, c_int, vp]),
         "stencil_run_static": (c_int, [vp, vp, vp, c_int, c_int, c_int, vp]),
@@ -112,7 +119,7 @@ except ImportError:
     _torch, _TORCH_TYPES = None, {}
 EXPORTS = ("stencil_create", "stencil_destroy", "stencil_set_kernel", "stencil_set_border_value",
            "stencil_set_mapping", "stencil_get_mapping", "stencil_stream_segment_rows", "stencil_set_sweep_rotation", "stencil_output_dtype", "stencil_set_option",
-           "stencil_max_wg_size", "stencil_tile_bytes", "stencil_is_legal", "stencil_enumerate_wg", "stencil_run",
+           "stencil_max_wg_size", "stencil_tile_bytes", "stencil_is_legal", "stencil_describe_run", "stencil_enumerate_wg", "stencil_run",
            "stencil_run_static",
            "stencil_sweep_wg", "stencil_sweep_configs", "stencil_device_copy", "stencil_time_copy",
            "stencil_sweep_reduce", "stencil_baseline_wg", "stencil_features", "stencil_predictor_create",
@@ -310,6 +317,13 @@ class Stencil:
 
     def is_legal(self, wg_rows: int, wg_cols: int) -> bool:
         return bool(_lib.stencil_is_legal(self._h, int(wg_rows), int(wg_cols)))
+
+    def describe_run(self, iters: int, wg: Tuple[int, int]) -> dict:
+        """What run(..., iters, wg) starts: kernel, launches, applications (per launch), wg, workgroups, local_bytes."""
+        info = _LaunchInfo()
+        _check(_lib.stencil_describe_run(self._h, int(iters), int(wg[0]), int(wg[1]), ctypes.byref(info)))
+        return {"kernel": info.kernel.decode(), "launches": info.launches, "applications": info.applications,
+                "wg": (info.wg_rows, info.wg_cols), "workgroups": info.workgroups, "local_bytes": info.local_bytes}
 
     def features(self) -> List[float]:
         f = (ctypes.c_double * N_FEATURES)()

@@ -20,6 +20,7 @@ import glob
 import hashlib
 import json
 import os
+import re
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -36,23 +37,29 @@ PMC_PASSES = {
 N_SIMD = 256 * 4            # SIMD units of an MI355X
 N_SHADER_ENGINES = 32       # SQ_BUSY_CYCLES is summed over them
 
-# source files that shape each kernel family's device code and launches
+# source files that shape each kernel's device code and launches
 _COMMON = ["stencil_ops.h", "tile_kernel.h", "variants.h"]
 FAMILY_SOURCES = {
-    "tile": _COMMON,
-    "direct": _COMMON + ["direct_kernel.h"],
-    "temporal": _COMMON + ["temporal_kernel.h", "life_bits.h"],
-    "stream": _COMMON + ["stream_kernel.h", "life_stream_kernel.h", "life_bits.h"],
-    "march": _COMMON + ["march_kernel.h", "march_masked_kernel.h"],
+    "tile_kernel": _COMMON,
+    "direct_kernel": _COMMON + ["direct_kernel.h"],
+    "life_direct_kernel": _COMMON + ["direct_kernel.h"],
+    "temporal_kernel": _COMMON + ["temporal_kernel.h"],
+    "life_temporal_kernel": _COMMON + ["temporal_kernel.h", "life_bits.h"],
+    "register_tile_kernel": _COMMON + ["temporal_kernel.h", "register_tile_kernel.h", "variants_register_tiles.hip"],
+    "stream_kernel": _COMMON + ["stream_kernel.h"],
+    "stream_through_kernel": _COMMON + ["stream_kernel.h"],
+    "life_stream_kernel": _COMMON + ["temporal_kernel.h", "life_stream_kernel.h", "life_bits.h"],
+    "march_kernel": _COMMON + ["march_kernel.h"],
+    "march_masked_kernel": _COMMON + ["march_kernel.h", "march_masked_kernel.h"],
 }
 
 
 def family_of(label: str) -> str:
-    """Kernel family of a label like 'C5: march_kernel<sincos> 134x4 cells/work-item, wg 32x8'."""
-    for fam in FAMILY_SOURCES:
-        if fam + "_kernel<" in label:
-            return fam
-    raise ValueError("no kernel family in %r" % label)
+    """Kernel of a label like 'C5: march_kernel<sincos> 134x4 cells/work-item, wg 32x8'."""
+    m = re.match(r"[^:]*: (\w+)<", label)
+    if not m or m.group(1) not in FAMILY_SOURCES:
+        raise ValueError("no kernel in %r" % label)
+    return m.group(1)
 
 
 def kernel_source_hash(family: str) -> str:

@@ -1287,6 +1287,27 @@ def test_pretrained_predictor_picks_a_good_size(ls, tmp_path):
         st.close()
 
 
+@pytest.mark.parametrize("cutoff", [0, 150])
+def test_sweep_times_sizes_that_come_to_the_same_launches_once(ls, cutoff):
+    """Runs of heat on tiles in registers take a workgroup of their own: of the sizes that lead there the figures are shared
+    and the smallest is best; a size that is no whole wavefronts keeps the mapping's kernel and has its own."""
+    w = wl.config(3, rows=700, cols=900, iters=24)
+    st = ls.Stencil.from_workload(w)
+    st.set_mapping("temporal", 2, 4)
+    st.set_option(ls.OPT_TEMPORAL_DEPTH, 4)
+    st.set_option(ls.OPT_SWEEP_CUTOFF, cutoff)
+    tin = torch.from_numpy(w.grid()).cuda()
+    res = st.sweep(tin, torch.empty_like(tin), [(16, 64), (5, 13), (4, 64), (3, 64)], iters=24, fixed=(8, 32), reps=5)
+    assert [st.describe_run(24, wg)["kernel"] for wg in [(16, 64), (5, 13), (8, 32)]] == [
+        "register_tile_kernel", "temporal_kernel", "register_tile_kernel"]
+    for figures in (res.mean_ms, res.min_ms, res.median_ms, res.stddev_ms):
+        assert figures[0] == figures[2] == figures[3] != figures[1]
+    assert res.best == (3, 64) and st.default_wg() == (3, 64)
+    if cutoff == 0:
+        assert res.speedup_over_fixed == 1.0
+    st.close()
+
+
 def test_sweep_with_adaptive_sampling_finds_the_same_best(ls):
     import time
     w = wl.config(3, rows=1024, cols=1024)

@@ -654,3 +654,48 @@ def test_bench_line_is_short_and_keeps_the_contracts_fields():
                 "vs_baseline", "dtype", "data", "config", "roofline", "cpu_baseline"):
         assert key in rec, key
     assert set(rec["other_workloads"]) == set(bench.WORKLOADS) and rec["other_workloads"]["W8192"]["value"] == 712.346
+
+
+def describe(rows, cols, kernel, halo, border, mapping, iters, wg, depth=0, dtype="f32", nt=0):
+    st = ls.Stencil(rows, cols, dtype, halo, border)
+    n, s, e, w = halo
+    if kernel in ("weighted_sum", "sincos"):
+        st.set_kernel(kernel, np.ones((n + s + 1, e + w + 1), np.float32))
+    else:
+        st.set_kernel(kernel, scalars=(0.2,) if kernel == "heat" else ())
+    st.set_mapping(*mapping)
+    if depth:
+        st.set_option(ls.OPT_TEMPORAL_DEPTH, depth)
+    st.set_option(ls.OPT_NT_STORE, nt)
+    info = st.describe_run(iters, wg)
+    st.close()
+    return info
+
+
+def test_describe_run_names_the_kernel_that_runs():
+    one = (1, 1, 1, 1)
+    # the mapping's own kernel, in the caller's workgroup
+    assert describe(100, 100, "weighted_sum", (2, 2, 2, 2), "clamp", ("local", 2, 4), 1, (4, 16)) == {
+        "kernel": "tile_kernel", "launches": 1, "applications": 1, "wg": (4, 16), "workgroups": 26, "local_bytes": 12 * 72 * 4}
+    assert describe(100, 128, "heat", one, "wrap", ("direct", 2, 4), 3, (4, 16))["kernel"] == "direct_kernel"
+    assert describe(100, 128, "heat", one, "wrap", ("stream", 20, 4), 4, (2, 64), depth=4) == {
+        "kernel": "stream_kernel", "launches": 1, "applications": 4, "wg": (2, 64), "workgroups": 3, "local_bytes": 0}
+    assert describe(2048, 2052, "heat", one, "wrap", ("stream", 20, 4), 4, (1, 64), depth=4)["kernel"] == "stream_through_kernel"
+    assert describe(2048, 2052, "heat", one, "wrap", ("stream", 20, 4), 4, (1, 64), depth=4, nt=1)["kernel"] == "stream_kernel"
+    assert describe(2048, 2052, "heat", one, "wrap", ("stream", 20, 4), 3, (1, 64), depth=3)["kernel"] == "stream_kernel"
+    assert describe(8192, 8192, "sincos", (1, 5, 3, 0), "clamp", ("stream", 64, 4), 1, (4, 64))["kernel"] == "march_kernel"
+    assert describe(8192, 8192, "weighted_sum", (5, 4, 4, 3), "clamp", ("stream", 64, 4), 1, (4, 64))["kernel"] == "march_masked_kernel"
+    # a tile in the place of a march
+    tile = describe(1000, 1001, "sincos", (1, 5, 3, 0), "clamp", ("stream", 64, 4), 1, (1, 64))
+    assert (tile["kernel"], tile["wg"], tile["local_bytes"]) == ("tile_kernel", (8, 32), (16 + 6) * (128 + 4) * 8)
+    assert describe(8192, 8192, "weighted_sum", (3, 3, 3, 3), "clamp", ("stream", 64, 4), 1, (1, 64))["kernel"] == "tile_kernel by rows"
+    # runs of several launches in registers
+    run = describe(1025, 1999, "heat", one, "clamp", ("temporal", 2, 4), 100, (32, 32), depth=4)
+    assert run["kernel"] == "register_tile_kernel" and run["launches"] == -(-100 // run["applications"]) < 25
+    assert describe(1025, 1999, "heat", one, "clamp", ("temporal", 2, 4), 100, (5, 13), depth=4)["launches"] == 25
+    assert describe(1025, 1999, "heat", one, "clamp", ("temporal", 2, 4), 3, (32, 32), depth=4)["kernel"] == "temporal_kernel"
+    life = describe(1001, 1503, "life", one, "clamp", ("temporal", 2, 16), 50, (64, 8), depth=4, dtype="u8")
+    assert life["kernel"] == "life_stream_kernel" and 4 < life["applications"] <= 32 and life["wg"] == (64, 8)
+    assert describe(1001, 1503, "life", one, "clamp", ("temporal", 2, 16), 4, (64, 8), depth=4, dtype="u8")["kernel"] == "life_temporal_kernel"
+    with pytest.raises(ls.Refused):
+        describe(100, 128, "heat", one, "wrap", ("stream", 20, 4), 4, (5, 13), depth=4)
