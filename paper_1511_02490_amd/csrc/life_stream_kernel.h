@@ -50,22 +50,23 @@ __global__ __launch_bounds__(life_stream_max_threads(RPT)) void life_stream_kern
     const int held = groups * RPT, step = held - 2 * depth;            // rows of the tile; the rows from one tile to the next
     // the first row it holds, and the rows it writes
     int top, begin, end;
+    // (differences from `rows`: what lies beyond the last tile may be beyond the largest int)
     if (B == kWrap) {
         top = tile_r * step - depth;
         begin = tile_r * step;
-        end = min(rows, begin + step);
+        end = begin + min(step, rows - begin);
     } else {
         top = max(0, min(tile_r * step, rows - held));
         begin = tile_r == 0 ? 0 : tile_r * step + depth;
-        end = tile_r * step + held >= rows ? rows : (tile_r + 1) * step + depth;
+        end = tile_r * step >= rows - held ? rows : (tile_r + 1) * step + depth;
     }
-    const int row0 = top + (tid >> a.group_shift) * RPT;
+    const int below_top = (tid >> a.group_shift) * RPT, row0 = (int)((unsigned)top + (unsigned)below_top);
     const uint32_t pad = a.pad ? ~0u : 0u;
     const uint32_t inside = inside_bits(col, cols);
 
     // the matrix rows it loads: under WRAP row0's and, going round, those after it; else any where there is none
     int gr[RPT];
-    gr[0] = B == kWrap ? resolve<kWrap>(row0, rows) : min(row0, rows - 1);
+    gr[0] = B == kWrap ? resolve<kWrap>((top > INT32_MAX - held ? top - rows : top) + below_top, rows) : min(row0, rows - 1);
 #pragma unroll
     for (int i = 1; i < RPT; ++i) {
         if (B == kWrap)

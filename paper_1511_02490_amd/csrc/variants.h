@@ -102,6 +102,9 @@ sk::Store store_of(const stencil *s) {
     return s->out_bytes() >= kThroughBytes ? sk::Store::kThrough : sk::Store::kPlain;
 }
 
+// A launch has at most so many work-items; more are turned down.
+constexpr int64_t kMaxGridItems = ((int64_t)1 << 32) - 1;
+
 // Blocks of a launch of so many tiles: the workgroups numbered for the eight XCDs, `chunk` to each, or (0) as they come.
 int64_t numbered_blocks(const stencil *s, int64_t tiles, int *chunk) {
     *chunk = s->xcd_remap && tiles >= 64 ? (int)((tiles + 7) / 8) : 0;
@@ -315,6 +318,7 @@ LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
             if (s->life_rows ? rpt != s->life_rows || 1 << shift != s->life_lanes : few_rows && rpt > 4 && best.tiles_r > 0) continue;
             const int steps = (rows - 1) / step + 1;
             const int tiles = s->border == STENCIL_WRAP ? steps : rows <= held ? 1 : (rows - held - 1) / step + 2;
+            if ((int64_t)strips * tiles * threads > kMaxGridItems) continue;
             double cost;
             if (as_asked) {
                 cost = std::max(1.0, (double)strips * steps * wave_count / simds) * (rpt + 2) *
@@ -338,11 +342,12 @@ LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
 
 // Generations per launch of a run that takes several launches: a launch costs as much as some ten generations do
 // (kLifeLaunchUs), but every generation fused repeats two more rows of every tile.  At least the number asked for, as far as
-// it divides the run into the same launches, and exactly that where the tile is prescribed or nothing is to be fused.  0: the workgroup is no
-// whole wavefronts, or too small for a tile.
+// it divides the run into the same launches, and exactly that where the tile is prescribed or nothing is to be fused.  0, the run
+// stays with its mapping's kernel: the workgroup is no whole wavefronts, or too small for a tile; or the matrix is so thin that
+// its tiles have more work-items than a launch, or that a tile's last columns are beyond the largest int.
 int life_per_launch(const stencil *s, int iters, int wr, int wc) {
     const int threads = wr * wc;
-    if (threads % 64 != 0) return 0;
+    if (threads % 64 != 0 || s->cols > INT32_MAX - 64 * 32) return 0;
     if (s->life_rows != 0 || s->temporal_depth == 1)
         return s->staging == STENCIL_STAGING_STREAM || life_tile(s, threads, s->temporal_depth, false).tiles_r > 0 ? s->temporal_depth : 0;
     int best = s->temporal_depth, launches_before = 0;
@@ -353,7 +358,7 @@ int life_per_launch(const stencil *s, int iters, int wr, int wc) {
         launches_before = launches;
         const int per = (iters + launches - 1) / launches;
         const LifeTile t = life_tile(s, threads, per, false);
-        if (t.tiles_r == 0) break;
+        if (t.tiles_r == 0) break;           // (nor has any with more generations one)
         const double us = launches * (kLifeLaunchUs + per * t.rows_worth * kLifeRowUs);
         if (best_us == 0.0 || us < best_us) {
             best_us = us;
@@ -539,7 +544,15 @@ bool march_pays(const stencil *s) {
     const bool compiled = s->hn == s->hs && s->hn == s->he && s->hn == s->hw;
     return !compiled && (s->hn + s->hs + 1) * (s->he + s->hw + 1) >= 72;
 }
-constexpr int kStreamTileRows = 8, kStreamTileCols = 32;
+// Its workgroup: 8 x 32 work-items, and 256 x 1 where a matrix is so thin that those would be more than a launch has (from
+// 2^28 rows on).
+struct StreamTile {
+    int rows, cols;
+};
+StreamTile stream_tile(const stencil *s) {
+    const int64_t tiles = ((s->rows + 15) / 16) * ((s->cols + 127) / 128);
+    return (tiles + 8) * 256 > kMaxGridItems ? StreamTile{256, 1} : StreamTile{8, 32};
+}
 
 // The region as that tile folds it.
 template <class Op, class Halo>
@@ -550,10 +563,11 @@ template <class Op, int B, class Halo>
 hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
     constexpr int kMaxT = 256;
     if (!march_pays(s)) {
+        const StreamTile t = stream_tile(s);
         if constexpr (Halo::N == 2) {
-            return weighted_sum_tile(B, true)(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
+            return weighted_sum_tile(B, true)(s, in, out, t.rows, t.cols, 1, stream);
         } else {
-            return launch_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
+            return launch_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s, in, out, t.rows, t.cols, 1, stream);
         }
     }
     unsigned blocks;
@@ -572,8 +586,9 @@ hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int
 template <class Op, class Halo>
 LaunchPlan plan_march(const stencil *s, int wr, int wc, int) {
     if (!march_pays(s)) {
-        if constexpr (Halo::kMasked) return plan_tile<Op, sk::HaloD, 2, 4>(s, kStreamTileRows, kStreamTileCols, 1);
-        else return plan_launch_tile<Op, StreamTileHalo<Op, Halo>, 2, 4>(s, kStreamTileRows, kStreamTileCols, 1);
+        const StreamTile t = stream_tile(s);
+        if constexpr (Halo::kMasked) return plan_tile<Op, sk::HaloD, 2, 4>(s, t.rows, t.cols, 1);
+        else return plan_launch_tile<Op, StreamTileHalo<Op, Halo>, 2, 4>(s, t.rows, t.cols, 1);
     }
     LaunchPlan p = plan_segments(s, Halo::kMasked ? "march_masked_kernel" : "march_kernel", sk::march_vectors(s->hw, s->he) * 4, wr, wc);
     int chunk;
@@ -589,7 +604,10 @@ hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int 
     if constexpr (WC > Halo::E + Halo::W + 1) {
         return hipErrorInvalidValue;
     } else {
-        if (!march_pays(s)) return weighted_sum_tile(B, false)(s, in, out, kStreamTileRows, kStreamTileCols, 1, stream);
+        if (!march_pays(s)) {
+            const StreamTile t = stream_tile(s);
+            return weighted_sum_tile(B, false)(s, in, out, t.rows, t.cols, 1, stream);
+        }
         if (s->he + s->hw + 1 != WC) return launch_march_masked<Op, B, Halo, WC + 1>(s, in, out, wr, wc, 0, stream);
         if (s->hn > Halo::N || s->hs > Halo::S || s->he > Halo::E || s->hw > Halo::W) return hipErrorInvalidValue;
         unsigned blocks;

@@ -38,6 +38,9 @@ RegisterTile register_tile(const stencil *s, int depth) {
                 const bool small = !wrap && (rows < held_r || cols < held_c);
                 if (step_r <= 0 || (small && rpt > 2)) continue;
                 const int tiles = wrap ? (rows - 1) / step_r + 1 : rows <= held_r ? 1 : (rows - held_r - 1) / step_r + 2;
+                // (a matrix so thin that a launch cannot have the tiles' work-items, or that its last tile ends beyond the
+                // largest int)
+                if ((int64_t)strips * tiles * threads > kMaxGridItems || rows > INT32_MAX - held_r || cols > INT32_MAX - held_c) continue;
                 const double simd_rows = (double)(((int64_t)strips * tiles + units - 1) / units) * (threads / 256) * rpt;
                 const double us = kLaunchUs + kCellUs * 1e-6 * rows * cols +
                                   depth * (row_us * (shift == 4 ? 1.04 : 1.0) * simd_rows + kWaitUs + kOwnRowUs * rpt);
@@ -52,6 +55,7 @@ hipError_t launch_register_tile(const stencil *s, const void *in, bool, void *ou
                                 hipStream_t stream) {
     if (depth < 1 || depth > sk::kRegisterTileMaxDepth) return hipErrorInvalidValue;
     const RegisterTile t = register_tile(s, depth);
+    if (t.threads == 0) return hipErrorInvalidValue;
     unsigned blocks;
     size_t unused;
     auto a = make_args<Op, sk::HaloC<1, 1, 1, 1>, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &unused);
@@ -101,13 +105,15 @@ int register_tile_per_launch(const stencil *s, int iters, int wr, int wc) {
         if (launches == launches_before) continue;
         launches_before = launches;
         const int per = (iters + launches - 1) / launches;
-        const double us = launches * register_tile(s, per).us;
+        const RegisterTile t = register_tile(s, per);
+        if (t.threads == 0) break;           // (nor has any with more applications one)
+        const double us = launches * t.us;
         if (best == 0 || us < best_us) {
             best_us = us;
             best = per;
         }
     }
-    if (s->staging == STENCIL_STAGING_STREAM) {
+    if (best > 0 && s->staging == STENCIL_STAGING_STREAM) {
         const int strip_cols = sk::stream_cols(asked);
         const int64_t waves = (s->cols + strip_cols - 1) / strip_cols * ((s->rows + s->cr - 1) / s->cr), simds = 4 * stencil_compute_units();
         const double rows = (double)((waves + simds - 1) / simds) * (s->cr + 2 * asked);

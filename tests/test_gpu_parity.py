@@ -585,6 +585,33 @@ def test_runs_on_tiles_in_registers(ls, border):
                 check(ls, h, (4, 64), blocking=("stream", 38, 4, depth))
 
 
+@pytest.mark.parametrize("kernel,cols,mapping,depth,wg,iters", [
+    (wl.LIFE, 1, ("stream", 64, 8), 8, (4, 64), 21), (wl.LIFE, 1, ("temporal", 8, 16), 4, (64, 1), 9),
+    (wl.HEAT, 1, ("temporal", 8, 4), 4, (16, 4), 9), (wl.WEIGHTED_SUM, 4, ("stream", 64, 4), 0, (4, 64), 1)])
+def test_matrices_as_long_as_a_handle_takes(ls, kernel, cols, mapping, depth, wg, iters):
+    """Rows up to just below 2^31: both ends of the matrix agree with the oracle on the rows around the seam of the torus."""
+    rows, ends = (2 ** 31 - 70) // cols, 4096
+    halo = (2, 2, 2, 2) if kernel == wl.WEIGHTED_SUM else (1, 1, 1, 1)
+    w = custom(kernel, 2 * ends, cols, halo, "wrap", seed=7, iters=iters)
+    seam = w.grid()                                        # the last rows, then the first
+    tin = torch.zeros((rows, cols), device="cuda", dtype=torch.uint8 if kernel == wl.LIFE else torch.float32)
+    tin[-ends:], tin[:ends] = torch.from_numpy(seam[:ends]).cuda(), torch.from_numpy(seam[ends:]).cuda()
+    st = ls.Stencil(rows, cols, "u8" if kernel == wl.LIFE else "f32", halo, "wrap")
+    st.set_kernel(kernel, w.weights, scalars=w.scalars)
+    st.set_mapping(*mapping)
+    if depth:
+        st.set_option(ls.OPT_TEMPORAL_DEPTH, depth)
+    tout = st.run(tin, torch.full_like(tin, 1), iters, wg)
+    got = torch.cat([tout[-ends:], tout[:ends]]).cpu().numpy()
+    st.close()
+    keep = slice(2 * iters + 2, 2 * ends - 2 * iters - 2)  # what the slice's own ends do not reach
+    want = oracle.apply_workload(w, seam)
+    if kernel == wl.WEIGHTED_SUM:
+        assert rel_err(got[keep], want[keep]) <= REL_1
+    else:
+        np.testing.assert_array_equal(got[keep], want[keep])
+
+
 def test_sweeps_over_a_rotation_of_matrix_pairs(ls):
     """stencil_set_sweep_rotation: a sample is `iters` independent applications on the pairs in turn; every
     pair's output is the single application of its own input, the sweep's own out argument is not written,

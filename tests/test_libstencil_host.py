@@ -699,3 +699,31 @@ def test_describe_run_names_the_kernel_that_runs():
     assert describe(1001, 1503, "life", one, "clamp", ("temporal", 2, 16), 4, (64, 8), depth=4, dtype="u8")["kernel"] == "life_temporal_kernel"
     with pytest.raises(ls.Refused):
         describe(100, 128, "heat", one, "wrap", ("stream", 20, 4), 4, (5, 13), depth=4)
+
+
+@pytest.mark.parametrize("rows,cols", [(2 ** 31 - 1, 1), (2 ** 31 - 70, 1), (2 ** 29 - 1, 4), (2 ** 28 - 1, 8), (1, 2 ** 31 - 1), (8, 2 ** 28 - 1)])
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+def test_thin_matrices_stay_within_a_launch(rows, cols, border):
+    """Matrices as long as a handle takes: no kernel in the place of a mapping's own may need more work-items than a launch
+    has, or tiles whose last row or column is beyond the largest int."""
+    one = (1, 1, 1, 1)
+    for kernel in ("heat", "weighted_sum", "life"):
+        u8 = kernel == "life"
+        mappings = [("temporal", 8, 16 if u8 else 4, 4)] + ([] if border == "clamp" or cols * (1 if u8 else 4) >= 2 ** 32 else [
+                ("stream", 4096, 8 if u8 else 4, 8)])
+        for *mapping, depth in mappings:
+            for wg in [(4, 64), (1, 64), (64, 4)] + ([(16, 32), (8, 64)] if mapping[0] == "temporal" else []):
+                for iters in (depth + 1, 60):
+                    info = describe(rows, cols, kernel, one, border, mapping, iters, wg, depth, "u8" if u8 else "f32")
+                    own = describe(rows, cols, kernel, one, border, mapping, depth, wg, depth, "u8" if u8 else "f32")
+                    items = lambda i: i["workgroups"] * i["wg"][0] * i["wg"][1]
+                    assert items(info) < 2 ** 32 or info["kernel"] == own["kernel"], (kernel, mapping, wg, info, own)
+                    if info["kernel"] == "register_tile_kernel":         # its tiles hold up to 256 rows and columns
+                        assert rows + 256 < 2 ** 31 and cols + 256 < 2 ** 31
+                    if info["kernel"] == "life_stream_kernel" and mapping[0] == "temporal":
+                        assert cols + 2048 < 2 ** 31
+    for kernel, halo in [("weighted_sum", (2, 2, 2, 2)), ("weighted_sum", (5, 5, 5, 5)), ("weighted_sum", (0, 3, 1, 2)), ("sincos", (1, 5, 3, 0))]:
+        if cols * 4 >= 2 ** 32:
+            continue                             # rows of 4 GiB: not on the mapping
+        info = describe(rows, cols, kernel, halo, border, ("stream", 4096, 4), 1, (4, 64))
+        assert info["workgroups"] * info["wg"][0] * info["wg"][1] < 2 ** 32 and info["local_bytes"] <= 65536, info
