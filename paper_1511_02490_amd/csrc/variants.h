@@ -495,10 +495,21 @@ constexpr bool by_rows() {
     return std::is_same<Op, sk::OpWeightedSum>::value && Halo::kStatic && Halo::N + Halo::S >= 6 && Halo::E + Halo::W >= 6 && CC > 1 &&
            (CR == 2 || CR == 4);
 }
-// A workgroup of one row of work-items stages up to five rows for each that it computes, from the region's west edge, which
-// starts no vector in memory: unrolled, where that fits the registers (7x7 on 3001 x 4099, 1 x 64 work-items, 40.1 / 41.8 us).
-template <class Halo, int CR>
-constexpr bool unrolled_for_one_row() { return Halo::kStatic && sk::folds_by_rows<Halo>::value && Halo::N + Halo::S <= (CR == 2 ? 8 : 6); }
+// ... and where it unrolls them after all.  A workgroup of one row of work-items stages up to five rows for each that it computes,
+// from the region's west edge, which starts no vector in memory: unrolled, where that fits the registers (7x7 on 3001 x 4099,
+// 1 x 64 work-items, 40.1 / 41.8 us).  And where hardly a SIMD has a second wavefront, registers cost nothing and the rows' round
+// trips to local memory are all there is (unrolled / by rows, us: 7x7 on 118 x 42, 16 x 8 work-items, 5.1 / 5.5; four rows on
+// 512 x 960, 8 x 8, 6.9 / 8.4; 9x9 on 160 x 950, 18 x 14, 5.4 / 6.4; four rows on 336 x 869, 4 x 64, 9.7 / 11.4; two to four
+// wavefronts per SIMD, 9x9 on 752 x 1296, 8 x 32: 10.4 / 8.6).
+template <class Halo>
+constexpr bool may_unroll() { return Halo::kStatic && sk::folds_by_rows<Halo>::value && Halo::N + Halo::S <= 8; }
+template <class Halo, int CR, int CC>
+bool unrolls(const stencil *s, int wr, int wc) {
+    if (wr == 1 && Halo::N + Halo::S <= (CR == 2 ? 8 : 6)) return true;
+    const int64_t tiles = ((s->rows + wr * CR - 1) / (wr * CR)) * ((s->cols + wc * CC - 1) / (wc * CC));
+    const int units = stencil_compute_units();
+    return (tiles + units - 1) / units * ((wr * wc + 63) / 64) <= 6;
+}
 
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
@@ -507,8 +518,9 @@ hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int 
         if (fold == sk::Fold::blocks) return launch_tile<Op, B, sk::HaloBlocks, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
         if (fold == sk::Fold::taps) return launch_tile<Op, B, sk::HaloTaps, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
     }
-    if constexpr (unrolled_for_one_row<Halo, CR>()) {
-        if (wr == 1) return launch_tile<Op, B, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
+    if constexpr (may_unroll<Halo>()) {
+        if (unrolls<Halo, CR, CC>(s, wr, wc))
+            return launch_tile<Op, B, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
     }
     unsigned blocks;
     size_t lds;
@@ -524,8 +536,8 @@ hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int 
 // ... and what it starts.  (The run-time folds are one kernel as far as a plan goes.)
 template <class Op, class Halo, int CR, int CC>
 LaunchPlan plan_launch_tile(const stencil *s, int wr, int wc, int) {
-    if constexpr (unrolled_for_one_row<Halo, CR>()) {
-        if (wr == 1) return plan_tile<Op, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC>(s, wr, wc, 1);
+    if constexpr (may_unroll<Halo>()) {
+        if (unrolls<Halo, CR, CC>(s, wr, wc)) return plan_tile<Op, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC>(s, wr, wc, 1);
     }
     return plan_tile<Op, Halo, CR, CC>(s, wr, wc, 1);
 }

@@ -816,7 +816,8 @@ def test_tiles_staged_without_registers(ls, wg, blocking, offset):
 def test_wide_gaussians_folded_by_rows(ls, border, radius, cells_rows):
     """Compile-time regions in the run-time fold's scheme: edges and remainders of tiles, matrices smaller than a tile, and
     workgroups of one row of work-items, which keep the unrolled fold."""
-    for rows, cols in [(3 * 8 * cells_rows + 3, 301), (8 * cells_rows, 128), (7, 5), (61, 133)]:
+    # (the last one has several wavefronts per SIMD: folded by rows in every workgroup but the first's of one row)
+    for rows, cols in [(3 * 8 * cells_rows + 3, 301), (8 * cells_rows, 128), (7, 5), (61, 133), (8 * cells_rows * 33 + 3, 1030)]:
         w = custom(wl.WEIGHTED_SUM, rows, cols, (radius,) * 4, border, pad=0.25, seed=radius)
         for wg in [(8, 32), (1, 64), (3, 5)]:
             got = check(ls, w, wg, blocking=(cells_rows, 4), offset=1)

@@ -727,3 +727,15 @@ def test_thin_matrices_stay_within_a_launch(rows, cols, border):
             continue                             # rows of 4 GiB: not on the mapping
         info = describe(rows, cols, kernel, halo, border, ("stream", 4096, 4), 1, (4, 64))
         assert info["workgroups"] * info["wg"][0] * info["wg"][1] < 2 ** 32 and info["local_bytes"] <= 65536, info
+
+
+def test_wide_gaussians_are_folded_by_rows_where_simds_have_several_wavefronts():
+    for radius in (3, 4):
+        for cells_rows in (2, 4):
+            kernel = lambda rows, cols, wg: describe(rows, cols, "weighted_sum", (radius,) * 4, "clamp", ("local", cells_rows, 4), 1, wg)["kernel"]
+            assert kernel(160, 950, (8, 32)) == "tile_kernel"                    # a workgroup per compute unit
+            assert kernel(8 * cells_rows * 256, 128, (8, 32)) == "tile_kernel"
+            assert kernel(8 * cells_rows * 256 + 1, 128, (8, 32)) == "tile_kernel by rows"
+            assert kernel(8 * cells_rows * 1536, 32, (8, 8)) == "tile_kernel"    # six workgroups of a wavefront
+            assert kernel(8 * cells_rows * 1536 + 1, 32, (8, 8)) == "tile_kernel by rows"
+            assert kernel(48, 48, (32, 32)) == "tile_kernel by rows"             # sixteen wavefronts in one compute unit
