@@ -543,18 +543,29 @@ LaunchPlan plan_launch_tile(const stencil *s, int wr, int wc, int) {
 }
 
 // Single applications under the streaming mapping: whether the march makes them, or a tile of 2 x 4 cells and 8 x 32 work-items
-// (a march's workgroup only groups wavefronts, and its segment height has no meaning for a tile).  The march keeps sin/cos on
-// matrices that no cache holds, where it takes the sine and cosine of every cell once (8192^2 119 us, tile 128; 3000 x 4100
-// 28.6 / 24.9), and run-time regions of 72 taps and more there, where it is as fast (4 S4 E4 W3 152 / 151, N5 S5 E4 W3 on 6144^2
-// 97 / 101, N3 S4 E4 W4 on 8192^2 165 / 152), both with rows of whole vectors: it moves ragged ones element by element.
-// Everywhere else the tile has more wavefronts in flight (us, march / tile: N1 S5 E3 W0 on 8192^2 122 / 97, 6001 x 7003
-// 135 / 73, 2048^2 13.1 / 10.0; one cell on 8192^2 116 / 87; 5x5 there 116 / 92, 7x7 125 / 120, 9x9 209 / 163, 11x11 377 / 348).
-constexpr int64_t kMarchCells = (int64_t)1 << 25;
+// (a march's workgroup only groups wavefronts, and its segment height has no meaning for a tile).  On rows of whole vectors -
+// ragged ones it would move element by element - and with segments that suit it the march is ahead (us, march / tile, matrices
+// fresh from memory and then in the caches):
+// - under regions of up to five rows, of a few columns and up to 30 cells, on matrices up to 2^24 cells, which the caches hold
+//   with their output: 5x5 on 1024^2 5.3 / 6.7 and 5.1 / 5.0, on 2048^2 9.7 / 11.8 and 7.6 / 8.3, on 4096^2 30.4 / 31.2 and
+//   22.3 / 22.2; N1 S2 E1 W2 on 2048^2 9.7 / 11.0 and 7.1 / 7.5; 3 x 10 on 1500 x 2000 8.5 / 10.7 and 8.5 / 7.6.
+//   Beyond that size, or with more cells, the tile is: 5x5 on 8192^2 110 / 95 and 81 / 74, 5 x 9 on 2048^2 13.1 / 13.2 and
+//   11.5 / 10.1; and regions of one column fold as fast there at any size (S1 on 2048^2 8.3 / 7.3 and 5.5 / 5.5).
+// - with the sine and cosine of every cell, taken once, from 2^24 cells on: 4096^2 34.5 / 37.2 and 28.7 / 31.6, 5000^2 47.9 / 51.3
+//   and 39.8 / 46.5, 8192^2 117 / 131; 2800^2 20.0 / 18.7 and 18.2 / 16.3.
+// - under run-time regions of 72 cells and more on matrices that no cache holds, where it is as fast: N5 S4 E4 W3 on 8192^2 170 /
+//   170, N4 S4 E3 W4 158 / 160, N3 S4 E4 W4 165 / 152.
+// Under taller regions the tile is: N1 S5 E3 W0 on 2048^2 12.1 / 12.5 and 10.9 / 9.1, on 8192^2 111 / 101; 7x7 there 127 / 125, 9x9
+// 192 / 170, 11x11 372 / 240.
+constexpr int64_t kCachedCells = (int64_t)1 << 24, kMarchCells = (int64_t)1 << 25;
 bool march_pays(const stencil *s) {
-    if (s->cols % 4 != 0 || s->rows * s->cols < kMarchCells) return false;
-    if (s->kernel == STENCIL_SINCOS) return true;
+    if (s->cols % 4 != 0) return false;
+    const int64_t cells = s->rows * s->cols;
+    if (s->kernel == STENCIL_SINCOS) return cells >= kCachedCells;
+    const int taps = (s->hn + s->hs + 1) * (s->he + s->hw + 1);
+    if (s->hn <= 2 && s->hs <= 2) return s->he + s->hw >= 1 && taps <= 30 && cells <= kCachedCells;
     const bool compiled = s->hn == s->hs && s->hn == s->he && s->hn == s->hw;
-    return !compiled && (s->hn + s->hs + 1) * (s->he + s->hw + 1) >= 72;
+    return !compiled && taps >= 72 && cells >= kMarchCells;
 }
 // Its workgroup: 8 x 32 work-items, and 256 x 1 where a matrix is so thin that those would be more than a launch has (from
 // 2^28 rows on).
