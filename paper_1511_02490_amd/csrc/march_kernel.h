@@ -25,14 +25,11 @@ namespace sk {
 __host__ __device__ constexpr int march_rim(int h) { return (h + 3) / 4; }
 __host__ __device__ constexpr int march_vectors(int W, int E) { return 64 - march_rim(W) - march_rim(E); }
 
-// FAST: rows are whole vectors (cols % 4 == 0).  A lane's four
-// columns then lie either all inside the matrix or all outside it, every row is one vector load
-// at a per-lane column plus a wavefront-uniform row address, and what the border mode asks for
-// beyond that is a per-lane fix-up of the loaded vector.  Otherwise elements are loaded one by one.
-// NT: output vectors are stored non-temporally (element-by-element stores are plain either way).
-template <class Op, int B, class Halo, bool FAST, bool NT>
+// Rows are whole vectors (cols % 4 == 0): a lane's four columns lie either all inside the matrix or all outside it, every row
+// is one vector load at a per-lane column plus a wavefront-uniform row address, and what the border mode asks for beyond that
+// is a per-lane fix-up of the loaded vector.  NT: output vectors are stored non-temporally.
+template <class Op, int B, class Halo, bool NT>
 __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const int H) {
-    static_assert(FAST, "rows of whole vectors");
     using T = typename Op::T;
     using L = typename Op::L;
     static_assert(Halo::kStatic, "compile-time border regions only");
@@ -60,7 +57,7 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
     const int gc0 = strip * kCols - kRimW * CC + lane * CC;    // first of this lane's four columns
     const bool writes = lane >= kRimW && lane < kRimW + march_vectors(W, E) && gc0 < cols;
 
-    // FAST: the column the lane's vector load starts at, and its fix-up
+    // the column the lane's vector load starts at, and its fix-up
     const bool outside = (unsigned)gc0 >= (unsigned)cols;
     int vcol = gc0;
     if (outside) vcol = B == kWrap ? resolve<B>(gc0, cols) : (gc0 < 0 ? 0 : cols - CC);
@@ -210,9 +207,9 @@ __device__ __forceinline__ void march_body(const TileArgs<Op, Halo> &a, const in
     }
 }
 
-template <class Op, int B, class Halo, bool FAST, bool NT, int MAXT>
+template <class Op, int B, class Halo, bool NT, int MAXT>
 __global__ __launch_bounds__(MAXT) void march_kernel(const TileArgs<Op, Halo> a, const int H) {
-    march_body<Op, B, Halo, FAST, NT>(a, H);
+    march_body<Op, B, Halo, NT>(a, H);
 }
 
 }  // namespace sk

@@ -36,9 +36,8 @@ struct HaloM {
     __host__ __device__ int w() const { return w_; }
 };
 
-template <class Op, int B, class Halo, int WC, bool FAST, bool NT, int MAXT>
+template <class Op, int B, class Halo, int WC, bool NT, int MAXT>
 __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, const int H) {
-    static_assert(FAST, "rows of whole vectors");
     using T = typename Op::T;
     using L = typename Op::L;
     static_assert(!Op::kRowFold && Op::kPlanes == 1, "functions that fold tap by tap");
@@ -218,9 +217,9 @@ __device__ __forceinline__ void march_masked_body(const TileArgs<Op, Halo> &a, c
     }
 }
 
-template <class Op, int B, class Halo, int WC, bool FAST, bool NT, int MAXT>
+template <class Op, int B, class Halo, int WC, bool NT, int MAXT>
 __global__ __launch_bounds__(MAXT) void march_masked_kernel(const TileArgs<Op, Halo> a, const int H) {
-    march_masked_body<Op, B, Halo, WC, FAST, NT, MAXT>(a, H);
+    march_masked_body<Op, B, Halo, WC, NT, MAXT>(a, H);
 }
 
 }  // namespace sk

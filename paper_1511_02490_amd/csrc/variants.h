@@ -581,29 +581,37 @@ StreamTile stream_tile(const stencil *s) {
 template <class Op, class Halo>
 using StreamTileHalo = typename std::conditional<by_rows<Op, Halo, 2, 4>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
 
+// The marches that the rule can choose (and so the compiled ones): of the compile-time regions sin/cos and 5x5 ...
+template <class Op, class Halo>
+constexpr bool marched() { return std::is_same<Op, sk::OpSinCos>::value || Halo::N == 2; }
+// ... of the run-time ones, by the kernel's largest region, two to nine columns of up to five rows and seven to nine of more.
+template <class Halo>
+constexpr bool marched_columns(int columns) { return Halo::N == 2 ? columns >= 2 : columns * (Halo::N + Halo::S + 1) >= 72; }
+
 // One application, marched down the matrix in registers (march_kernel.h).
 template <class Op, int B, class Halo>
 hipError_t launch_march(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
     constexpr int kMaxT = 256;
-    if (!march_pays(s)) {
-        const StreamTile t = stream_tile(s);
-        if constexpr (Halo::N == 2) {
-            return weighted_sum_tile(B, true)(s, in, out, t.rows, t.cols, 1, stream);
-        } else {
-            return launch_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s, in, out, t.rows, t.cols, 1, stream);
+    if constexpr (marched<Op, Halo>()) {
+        if (march_pays(s)) {
+            unsigned blocks;
+            size_t lds;
+            auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
+            // a tile is a wavefront's segment; workgroups only group wavefronts
+            const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
+            blocks = (unsigned)numbered_blocks(s, ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block, &a.xcd_chunk);
+            // with either kind of store
+            hipLaunchKernelGGL(s->nt_store ? (&sk::march_kernel<Op, B, Halo, true, kMaxT>)
+                                           : (&sk::march_kernel<Op, B, Halo, false, kMaxT>),
+                               dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
+            return hipGetLastError();
         }
     }
-    unsigned blocks;
-    size_t lds;
-    auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
-    // a tile is a wavefront's segment; workgroups only group wavefronts
-    const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
-    blocks = (unsigned)numbered_blocks(s, ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block, &a.xcd_chunk);
-    // with either kind of store
-    hipLaunchKernelGGL(s->nt_store ? (&sk::march_kernel<Op, B, Halo, true, true, kMaxT>)
-                                   : (&sk::march_kernel<Op, B, Halo, true, false, kMaxT>),
-                       dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
-    return hipGetLastError();
+    const StreamTile t = stream_tile(s);
+    if constexpr (Halo::N == 2)
+        return weighted_sum_tile(B, true)(s, in, out, t.rows, t.cols, 1, stream);
+    else
+        return launch_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s, in, out, t.rows, t.cols, 1, stream);
 }
 
 template <class Op, class Halo>
@@ -633,15 +641,19 @@ hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int 
         }
         if (s->he + s->hw + 1 != WC) return launch_march_masked<Op, B, Halo, WC + 1>(s, in, out, wr, wc, 0, stream);
         if (s->hn > Halo::N || s->hs > Halo::S || s->he > Halo::E || s->hw > Halo::W) return hipErrorInvalidValue;
-        unsigned blocks;
-        size_t lds;
-        auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
-        const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
-        blocks = (unsigned)numbered_blocks(s, ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block, &a.xcd_chunk);
-        hipLaunchKernelGGL(s->nt_store ? (&sk::march_masked_kernel<Op, B, Halo, WC, true, true, kMaxT>)
-                                       : (&sk::march_masked_kernel<Op, B, Halo, WC, true, false, kMaxT>),
-                           dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
-        return hipGetLastError();
+        if constexpr (!marched_columns<Halo>(WC)) {
+            return hipErrorInvalidValue;
+        } else {
+            unsigned blocks;
+            size_t lds;
+            auto a = make_args<Op, Halo, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &lds);
+            const unsigned waves_per_block = (unsigned)(wr * wc) / 64u;
+            blocks = (unsigned)numbered_blocks(s, ((unsigned)a.n_tiles + waves_per_block - 1) / waves_per_block, &a.xcd_chunk);
+            hipLaunchKernelGGL(s->nt_store ? (&sk::march_masked_kernel<Op, B, Halo, WC, true, kMaxT>)
+                                           : (&sk::march_masked_kernel<Op, B, Halo, WC, false, kMaxT>),
+                               dim3(blocks), dim3(wc, wr), 0, stream, a, s->cr);
+            return hipGetLastError();
+        }
     }
 }
 
@@ -687,11 +699,11 @@ template <int CR, int CC>
 const void *kernel_threshold(const stencil *) { return reinterpret_cast<const void *>(&sk::threshold_kernel<CR, CC, STENCIL_MAX_WG_SIZE>); }
 template <class Op, int B, class Halo>
 const void *kernel_march(const stencil *s) {
-    if (!march_pays(s)) {
-        if constexpr (Halo::N == 2) return weighted_sum_tile_kernel(s, true);
-        else return kernel_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s);
+    if constexpr (marched<Op, Halo>()) {
+        if (march_pays(s)) return reinterpret_cast<const void *>(&sk::march_kernel<Op, B, Halo, false, 256>);
     }
-    return reinterpret_cast<const void *>(&sk::march_kernel<Op, B, Halo, true, false, 256>);
+    if constexpr (Halo::N == 2) return weighted_sum_tile_kernel(s, true);
+    else return kernel_tile<Op, B, StreamTileHalo<Op, Halo>, 2, 4, STENCIL_MAX_WG_SIZE>(s);
 }
 template <class Op, int B, class Halo, int WC = 1>
 const void *kernel_march_masked(const stencil *s) {
@@ -700,8 +712,10 @@ const void *kernel_march_masked(const stencil *s) {
         return nullptr;
     else if (s->he + s->hw + 1 != WC)
         return kernel_march_masked<Op, B, Halo, WC + 1>(s);
+    else if constexpr (marched_columns<Halo>(WC))
+        return reinterpret_cast<const void *>(&sk::march_masked_kernel<Op, B, Halo, WC, false, 256>);
     else
-        return reinterpret_cast<const void *>(&sk::march_masked_kernel<Op, B, Halo, WC, true, false, 256>);
+        return nullptr;
 }
 template <class Op, int B>
 const void *kernel_stream(const stencil *s) {

@@ -68,12 +68,19 @@ def vector_stores(instructions):
 
 
 def test_marching_kernels_store_as_they_were_compiled_to(kernels):
-    """The marches over rows of whole vectors exist once for plain and once for non-temporal stores."""
-    code = kernels.instructions(r"^(stream_kernel|march_kernel|march_masked_kernel)<.*, true, (true|false), 256>$")
-    assert len(code) >= 2 * (2 * 2 * 8 + 3 * 5 + 3 * 2 * 9)
+    """The marches over rows of whole vectors exist once for plain and once for non-temporal stores, those of four to eight
+    applications for written-through ones too; and of the marches of one application those that the rule can choose:
+    sin/cos, 5x5, two to nine columns of up to five rows and seven to nine of up to eleven."""
+    code = kernels.instructions(r"^(stream_kernel<.*, true, (true|false), 256>|march_kernel<.*>|march_masked_kernel<.*>)$")
+    assert len(code) == 2 * (2 * 2 * 8 + 3 * 2 + 3 * (8 + 3))
     for name, instructions in code.items():
         plain, nt = vector_stores(instructions)
-        assert (plain, nt > 0) == (0, True) if ", true, true, 256>" in name else (plain > 0, nt) == (True, 0), (name, plain, nt)
+        assert (plain, nt > 0) == (0, True) if name.endswith(", true, 256>") else (plain > 0, nt) == (True, 0), (name, plain, nt)
+    through = kernels.instructions(r"^stream_through_kernel<")
+    assert len(through) == 2 * 2 * 5
+    for name, instructions in through.items():
+        stores = [i for i in instructions if i.startswith("global_store_dwordx4")]
+        assert stores and all(i.endswith(" sc1") for i in stores), name
 
 
 def test_kernels_that_choose_at_run_time_keep_both_kinds_of_store(kernels):
