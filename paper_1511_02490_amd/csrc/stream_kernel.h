@@ -27,6 +27,20 @@ constexpr int kStreamMaxDepth = 8;
 __host__ __device__ constexpr int stream_rim(int depth) { return (depth + 3) / 4; }
 __host__ __device__ constexpr int stream_cols(int depth) { return (kStreamLanes - 2 * stream_rim(depth)) * 4; }
 
+// A vector at a byte offset in a row of so many bytes, written through the L2 cache (Store::kThrough): by the row's own buffer
+// descriptor, which is scalar, so that a lane keeps its offset as for the other kinds of store.  (With a 64-bit address per lane,
+// in a statement that the compiler cannot move, a heat march took 8 to 18 registers more and at 5, 7 and 8 applications per
+// launch a wavefront per SIMD: constant border, 8 per launch, up to 7 % slower than with plain stores, now as fast or faster.)
+template <class E>
+__device__ __forceinline__ void store_through(char *row, unsigned row_bytes, unsigned offset, const E (&src)[4]) {
+    static_assert(sizeof(src) == 16, "one 16-byte vector");
+    typedef uint32_t word4 __attribute__((ext_vector_type(4)));
+    word4 v;
+    __builtin_memcpy(&v, src, sizeof(v));
+    constexpr int kRaw32 = 0x00020000, kSc1 = 16;      // the descriptor's data format; the store's cache policy
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(row, 0, (int)row_bytes, kRaw32), (int)offset, 0, kSc1);
+}
+
 // FAST: rows are whole vectors (cols % 4 == 0).  A lane's four
 // columns then lie either all inside the matrix or all outside it, every input row is one vector
 // load at a per-lane column plus a wavefront-uniform row address, issued without a branch three
@@ -167,7 +181,10 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
                     // gr = r0 + t - 2*DEPTH runs over this segment's rows
                     if (FAST) {
                         char *rowp = reinterpret_cast<char *>(a.out + (size_t)gr * cols);
-                        store_out_vec<S>(reinterpret_cast<T *>(rowp + out_off), res);
+                        if constexpr (S == Store::kThrough)
+                            store_through(rowp, (unsigned)cols * (unsigned)sizeof(T), out_off, res);
+                        else
+                            store_out_vec<S>(reinterpret_cast<T *>(rowp + out_off), res);
                     } else {
                         T *out = a.out + (size_t)gr * cols + gc0;
 #pragma unroll
@@ -184,7 +201,7 @@ template <class Op, int B, int DEPTH, bool FAST, bool NT, int MAXT>
 __global__ __launch_bounds__(MAXT) void stream_kernel(const TileArgs<Op, HaloC<1, 1, 1, 1>> a, const int H) {
     stream_body<Op, B, DEPTH, FAST, NT ? Store::kNonTemporal : Store::kPlain>(a, H);
 }
-// ... and written through, over rows of whole vectors, from kStreamThroughDepth applications per launch on (heat, WRAP, a launch
+// ... and written through (store_through), over rows of whole vectors, from kStreamThroughDepth applications per launch on (heat, WRAP, a launch
 // of eight on 4096^2, plain / through: 37.0 / 35.6 us; of two 22.6 / 23.2; of one 22.0 / 22.6).
 constexpr int kStreamThroughDepth = 4;
 template <class Op, int B, int DEPTH, int MAXT>

@@ -79,8 +79,8 @@ def test_marching_kernels_store_as_they_were_compiled_to(kernels):
     through = kernels.instructions(r"^stream_through_kernel<")
     assert len(through) == 2 * 2 * 5
     for name, instructions in through.items():
-        stores = [i for i in instructions if i.startswith("global_store_dwordx4")]
-        assert stores and all(i.endswith(" sc1") for i in stores), name
+        stores = [i for i in instructions if re.match("(global|buffer)_store", i)]
+        assert stores and all(i.startswith("buffer_store_dwordx4") and i.endswith(" offen sc1") for i in stores), name
 
 
 def test_kernels_that_choose_at_run_time_keep_both_kinds_of_store(kernels):
@@ -100,7 +100,9 @@ def test_kernels_that_choose_at_run_time_keep_both_kinds_of_store(kernels):
 def test_heat_marches_keep_their_wavefronts(kernels):
     """A SIMD's 512 vector registers hold this many wavefronts of a heat march of so many steps per launch."""
     for border, depth, waves in [(1, 5, 5), (1, 7, 4), (2, 5, 5), (2, 7, 4), (1, 8, 3), (2, 8, 4)]:
-        for name, (_, _, vgprs) in kernels.matching(r"^stream_kernel<OpHeat, %d, %d, true, " % (border, depth)).items():
+        found = kernels.matching(r"^(stream_kernel<OpHeat, %d, %d, true, |stream_through_kernel<OpHeat, %d, %d, )" % (border, depth, border, depth))
+        assert len(found) == 3                   # plain, non-temporal and written-through stores
+        for name, (_, _, vgprs) in found.items():
             assert 512 // ((vgprs + 7) // 8 * 8) >= waves, (name, vgprs)
 
 
