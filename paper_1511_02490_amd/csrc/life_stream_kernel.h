@@ -197,6 +197,30 @@ __global__ __launch_bounds__(life_stream_max_threads(RPT)) void life_stream_kern
         generations(std::false_type{}, std::false_type{});
 
     const int lane = tid & (G - 1);
+    if (!OUT_BITS && a.store == Store::kThrough) {
+        // Adjacent lanes store adjacent 16 bytes: a row in two pieces, each lane one half of another lane's cells.  (By two stores
+        // of a lane's own 32 cells each instruction writes every other 16 bytes of a line, which a cache puts together, but written
+        // through the halves go to memory one by one: boards of 16 MiB and more, from bytes to bytes, 1.3 to 1.6 times as long.)
+        const int shift = 16 * (lane & 1);
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int r = row0 + i;
+            if (r < begin || r >= end) continue;                         // (the same for a group of lanes)
+#pragma unroll
+            for (int piece = 0; piece < 2; ++piece) {
+                const int from = (lane >> 1) + piece * (G >> 1);         // the lane of the group whose cells they are
+                const uint32_t cells = (uint32_t)__builtin_amdgcn_ds_bpermute(((tid - lane + from) & 63) << 2, (int)x[i]) >> shift;
+                const int at = (word - lane + from) * 32 + shift;
+                if (from == 0 || from == G - 1 || at >= cols) continue;
+                uint8_t *out = static_cast<uint8_t *>(a.out) + (unsigned)(r * cols + at);
+                if (at + 16 <= cols)
+                    store_word4<Store::kThrough>(out, unpack_cells16(cells));
+                else
+                    store_first_cells(out, unpack_cells16(cells), cols - at);
+            }
+        }
+        return;
+    }
     if (lane == 0 || lane == G - 1 || word >= a.words) return;
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
@@ -210,7 +234,7 @@ __global__ __launch_bounds__(life_stream_max_threads(RPT)) void life_stream_kern
             for (int half = 0; half < 2; ++half) {
                 const uint4 o = unpack_cells16(x[i] >> (16 * half));
                 if (col + 16 * half + 16 <= cols) {
-                    store_word4(out + 16 * half, o, a.store);
+                    store_word4(out + 16 * half, o, a.store == Store::kNonTemporal);
                 } else if (col + 16 * half < cols) {
                     store_first_cells(out + 16 * half, o, cols - (col + 16 * half));
                 }

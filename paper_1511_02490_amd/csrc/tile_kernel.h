@@ -149,9 +149,10 @@ __device__ __forceinline__ void load_global(E (&dst)[CNT], const E *src) {
 // Or they are written through (kThrough), by the kernels that make several applications per launch: what plain stores leave
 // dirty in the eight L2 caches, 4 MiB each, is written back when the kernel ends, with nothing beside it; written through it
 // is on its way while the rest computes, and stays in the cache for the next launch.  (Plain / through: four Life
-// generations on 4096^2 11.4 / 9.5 us; a launch of four heat steps there in local memory 33.5 / 33.1.  Small outputs
-// pay for it at the end of the last workgroups: a launch of two heat steps on 1024^2 9.4 / 10.0.  store_of in variants.h draws the line.
-// The tiles of single applications gain 4 % on 4096^2 and more, but the third kind of store costs them 1 % on all smaller
+// generations on 4096^2 in local memory 11.4 / 9.5 us; a launch of four heat steps there 33.5 / 33.1.  Small outputs
+// pay for it at the end of the last workgroups: a launch of two heat steps on 1024^2 9.4 / 10.0.  And what a store leaves of a
+// cache line is written to memory by itself.  Each launcher in variants.h and variants_register_tiles.hip draws its line.)
+// (The tiles of single applications gain 4 % on 4096^2 and more, but the third kind of store costs them 1 % on all smaller
 // matrices.)  The two wait states keep what follows off the stored registers: the compiler counts them only after its own
 // stores.  Nothing reads the output in the same launch.
 template <Store S>

@@ -94,12 +94,20 @@ TileGeom tile_geom(const stencil *s, const Variant &v, int wr, int wc) {
     return g;
 }
 
-// How a launch stores its output where the handle does not ask for non-temporal stores: written through from half of what the
-// device's L2 caches hold on (Store::kThrough has both sides).
+// How a launch stores its output: as the handle says, but the kernels that make several applications per launch may write it
+// through where non-temporal stores are not asked for (Store::kThrough), from half of what the device's L2 caches hold on.
 constexpr size_t kThroughBytes = (size_t)16 << 20;
-sk::Store store_of(const stencil *s) {
-    if (s->nt_store) return sk::Store::kNonTemporal;
-    return s->out_bytes() >= kThroughBytes ? sk::Store::kThrough : sk::Store::kPlain;
+sk::Store store_of(const stencil *s) { return s->nt_store ? sk::Store::kNonTemporal : sk::Store::kPlain; }
+// The temporal kernels and Life in registers (to bytes): up to twice that, where a matrix that was used before is still in the
+// last-level cache; life_temporal_kernel from three generations on (its rows of a byte per cell hardly ever start at a cache line,
+// and the pieces of lines that meet are written to memory one by one).  Written through / plain, geometric means over 2 to 85 drawn
+// launches, matrices used before and fresh ones: temporal_kernel, 16 to 32 MiB 0.89 to 0.94 and 1.00 to 1.02, 32 to 64 MiB 0.98 to
+// 1.00 and 1.02 to 1.06, more 1.01 to 1.03 and 1.02 to 1.07; life_temporal_kernel, 16 to 32 MiB, three and four generations 0.90 and
+// 1.02, one and two 0.94 and 1.11; life_stream_kernel, 16 to 32 MiB 0.89 and 1.01 (its last launch of a run 0.87 to 0.99 and 0.96
+// to 1.00), 32 to 64 MiB 1.01 and 1.01.
+sk::Store fused_store(const stencil *s, bool may) {
+    const bool through = may && s->out_bytes() >= kThroughBytes && s->out_bytes() < 2 * kThroughBytes;
+    return s->nt_store || !through ? store_of(s) : sk::Store::kThrough;
 }
 
 // A launch has at most so many work-items; more are turned down.
@@ -212,7 +220,8 @@ hipError_t launch_temporal(const stencil *s, const void *in, void *out, int wr, 
     using Halo = sk::HaloC<1, 1, 1, 1>;
     unsigned blocks;
     size_t lds;
-    const auto a = make_args<Op, Halo, CR, 4>(s, STENCIL_STAGING_TEMPORAL, in, out, wr, wc, &blocks, &lds);
+    auto a = make_args<Op, Halo, CR, 4>(s, STENCIL_STAGING_TEMPORAL, in, out, wr, wc, &blocks, &lds);
+    a.store = fused_store(s, true);
     const bool whole_waves = wr * wc % 64 == 0;
     const auto kernel = whole_waves ? &sk::temporal_kernel<Op, B, true, MAXT> : &sk::temporal_kernel<Op, B, false, MAXT>;
     static thread_local int raised_on[2] = {-1, -1};
@@ -224,7 +233,7 @@ hipError_t launch_temporal(const stencil *s, const void *in, void *out, int wr, 
 
 // Which launches of a march of several applications have their output written through.
 bool stream_goes_through(const stencil *s, int depth) {
-    return s->cols % 4 == 0 && depth >= sk::kStreamThroughDepth && store_of(s) == sk::Store::kThrough;
+    return s->cols % 4 == 0 && depth >= sk::kStreamThroughDepth && !s->nt_store && s->out_bytes() >= kThroughBytes;
 }
 LaunchPlan plan_stream(const stencil *s, int wr, int wc, int depth) {
     return plan_segments(s, stream_goes_through(s, depth) ? "stream_through_kernel" : "stream_kernel", sk::stream_cols(depth), wr, wc);
@@ -384,7 +393,7 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     a.tiles_c = t.tiles_c;
     a.n_tiles = t.tiles_r * t.tiles_c;
     a.pad = s->pad != 0.0;
-    a.store = store_of(s);
+    a.store = fused_store(s, true);
     const dim3 grid((unsigned)a.n_tiles), block(wc, wr);
     const unsigned lds = sk::life_stream_lds(wr * wc);
     switch (t.rows_per_item) {
@@ -444,6 +453,7 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
     size_t lds;
     auto a = make_args<sk::OpLife, sk::HaloC<1, 1, 1, 1>, CR, 16>(s, STENCIL_STAGING_TEMPORAL, in, out, wr, wc,
                                                                   &blocks, &lds);
+    a.store = fused_store(s, depth >= 3);
     // The kernel keeps the tile as bits, rows of whole words.  (Which sizes are legal still follows from
     // the tile counted in bytes: tile_geom.)
     const unsigned words = (unsigned)(a.pitch + 31) / 32;

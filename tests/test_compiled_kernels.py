@@ -97,6 +97,16 @@ def test_kernels_that_choose_at_run_time_keep_both_kinds_of_store(kernels):
     assert checked > 60
 
 
+def test_life_streams_write_whole_lines_through(kernels):
+    """Bytes that are written through are handed to the lane whose neighbours store the bytes beside them."""
+    code = kernels.instructions(r"^life_stream_kernel<.*, false>$")
+    assert len(code) == 3 * 4 * 2
+    for name, instructions in code.items():
+        moves = sum(i.startswith("ds_bpermute_b32") for i in instructions)
+        through = sum(i.startswith("global_store_dwordx4") and " sc1" in i for i in instructions)
+        assert through == moves > 0, (name, through, moves)
+
+
 def test_heat_marches_keep_their_wavefronts(kernels):
     """A SIMD's 512 vector registers hold this many wavefronts of a heat march of so many steps per launch."""
     for border, depth, waves in [(1, 5, 5), (1, 7, 4), (2, 5, 5), (2, 7, 4), (1, 8, 3), (2, 8, 4)]:
