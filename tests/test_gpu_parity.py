@@ -529,9 +529,9 @@ def test_temporal_items_of_whole_and_ragged_workgroups(ls, border, wg):
 
 @pytest.mark.parametrize("border", ["wrap", "constant"])
 def test_register_streaming_temporal_kernel_bit_exact(ls, border):
-    """Time levels kept in registers, row neighbours from adjacent lanes; every wavefront owns a
-    strip of 248 (240 beyond depth 4) columns: matrices wider than one strip, ragged ones, and ones
-    smaller than a strip."""
+    """Runs under the streaming mapping, made by the march (time levels kept in registers, row neighbours from adjacent
+    lanes; every wavefront owns a strip of 248, beyond depth 4 of 240 columns) or, of several launches, by the tiles in
+    registers that take its place on matrices of this size: wider than one strip, ragged, smaller than a strip."""
     for rows, cols, iters in [(70, 600, 9), (37, 250, 5), (130, 83, 6), (64, 256, 8), (5, 3, 7), (1, 1, 4),
                               (40, 244, 17), (33, 484, 11)]:
         w = wl.config(3, rows=rows, cols=cols, iters=iters)
@@ -543,7 +543,7 @@ def test_register_streaming_temporal_kernel_bit_exact(ls, border):
     check(ls, w, (1, 64), blocking=("stream", 32, 4, 4))
     check(ls, w, (2, 64), blocking=("stream", 16, 4, 3), offset=1)          # rows of whole vectors, at no multiple of 16 bytes
     w = custom(wl.WEIGHTED_SUM, 90, 301, (1, 1, 1, 1), border, pad=0.4, seed=23, iters=7)
-    check(ls, w, (2, 64), blocking=("stream", 16, 4, 3), offset=1)          # ragged rows: element by element
+    check(ls, w, (2, 64), blocking=("stream", 16, 4, 3), offset=1)          # ragged rows
     st = ls.Stencil.from_workload(wl.config(3, rows=64, cols=64))
     st.set_mapping("stream", 32, 4)
     assert st.max_wg_size() == 256 and st.tile_bytes(1, 64) == 0
@@ -645,16 +645,15 @@ def test_sweeps_over_a_rotation_of_matrix_pairs(ls):
 
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
 def test_register_marching_single_application_kernels(ls, border):
-    """One application marched down the matrix in registers (sin/cos stencil N1 S5 E3 W0 and the
-    5x5 to 11x11 weighted sums, the last with row neighbours two lanes away): matrices wider than
-    one strip (252 / 248 / 240 columns), ragged ones, ones smaller
-    than a strip or than the region, unaligned rows, segment heights that do and do not divide
-    the rows, and the output bits of the local-memory mapping."""
+    """One application under the streaming mapping, at the sizes of this test marched down the matrix in registers where the
+    region has up to five rows, two columns and more and up to 30 cells and rows are whole vectors, and made by a tile of 2x4
+    cells elsewhere (the other marches: test_marches_at_any_address, test_c5_full_size_every_cell): matrices wider than
+    one strip (252 / 248 / 240 columns), ragged ones, ones smaller than a strip or than the region, unaligned rows, segment
+    heights that do and do not divide the rows, and the output bits of the local-memory mapping."""
     shapes = [(70, 600), (37, 252), (41, 256), (130, 83), (64, 1024), (5, 3), (1, 1), (9, 508)]
     for kernel, halo in [(wl.SINCOS, (1, 5, 3, 0)), (wl.WEIGHTED_SUM, (2, 2, 2, 2)), (wl.WEIGHTED_SUM, (3, 3, 3, 3)),
                          (wl.WEIGHTED_SUM, (4, 4, 4, 4)), (wl.WEIGHTED_SUM, (5, 5, 5, 5)),
-                         # regions without a variant of their own: the kernels compiled for a largest region (5 or
-                         # 11 rows) and the region's number of columns
+                         # regions given at run time
                          (wl.WEIGHTED_SUM, (1, 5, 3, 0)), (wl.WEIGHTED_SUM, (2, 1, 2, 2)), (wl.WEIGHTED_SUM, (0, 0, 0, 0)),
                          (wl.WEIGHTED_SUM, (4, 0, 0, 3)), (wl.WEIGHTED_SUM, (0, 5, 4, 0)), (wl.WEIGHTED_SUM, (5, 5, 4, 4)),
                          (wl.WEIGHTED_SUM, (0, 0, 4, 4)), (wl.WEIGHTED_SUM, (2, 2, 1, 0)), (wl.WEIGHTED_SUM, (0, 3, 0, 1)),
@@ -670,7 +669,7 @@ def test_register_marching_single_application_kernels(ls, border):
         w = custom(kernel, 50, 300, halo, border, pad=0.3, seed=77)
         check(ls, w, (1, 64), blocking=("stream", 16, 4), offset=1)            # rows of whole vectors, at no multiple of 16 bytes
         check(ls, custom(kernel, 50, 301, halo, border, pad=0.3, seed=78), (1, 64), blocking=("stream", 16, 4),
-              offset=1)                                                          # ragged rows: element by element
+              offset=1)                                                          # ragged rows
         big = w.grid() * np.float32(300.0)                                       # beyond the small-argument range
         big[3, 5], big[20, 299] = 1.0e6, -3.0e7
         # sums of sines and cosines of large arguments pass near zero: absolute error here
@@ -846,6 +845,73 @@ def test_single_applications_of_the_streaming_mapping(ls, kernel, halo, border):
         assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (rows, cols)
         if rows < 100:
             check(ls, w, (4, 64), blocking=("stream", 37, 4))
+
+
+@pytest.mark.parametrize("border", ["wrap", "constant"])
+@pytest.mark.parametrize("kernel", [wl.HEAT, wl.WEIGHTED_SUM])
+def test_single_launches_of_the_fusing_march(ls, kernel, border):
+    """Runs that one launch makes stay with the march whatever the size: every number of applications it is compiled for, rows of
+    whole vectors and ragged ones at any address, fewer applications than the handle's depth."""
+    for rows, cols in [(70, 600), (37, 250), (130, 83), (40, 244), (5, 3)]:
+        for depth in range(1, 9):
+            for iters in {depth, max(1, depth - 1)}:
+                w = custom(kernel, rows, cols, (1, 1, 1, 1), border, pad=0.4, seed=rows + depth, iters=iters)
+                st = ls.Stencil.from_workload(w)
+                set_mapping(st, ("stream", 16, 4, depth))
+                assert st.describe_run(iters, (2, 64))["kernel"] == "stream_kernel"
+                st.close()
+                check(ls, w, (2, 64), blocking=("stream", 16, 4, depth), offset=depth % 2)
+
+
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+def test_outputs_written_through(ls, border):
+    """Launches of several applications with outputs of 16 MiB and a little more, which are written through the L2 caches: the
+    march at every depth that does it, the temporal kernels, the register tiles, Life from and to bytes and bits; rows of whole
+    vectors and ragged ones, at any address."""
+    cases = [(kernel, 2049, 2051, ("temporal", 2, 4, 3), (8, 32), iters, name)
+             for kernel in (wl.HEAT, wl.WEIGHTED_SUM) for iters, name in ((3, "temporal_kernel"), (7, "register_tile_kernel"))]
+    cases += [(wl.LIFE, 4099, 4101, ("temporal", 2, 16, 4), (16, 32), 4, "life_temporal_kernel"),
+              (wl.LIFE, 4099, 4101, ("temporal", 2, 16, 4), (16, 32), 21, "life_stream_kernel")]
+    if border != "clamp":
+        cases += [(kernel, 2049, 2052, ("stream", 38, 4, depth), (2, 64), depth, "stream_through_kernel")
+                  for kernel in (wl.HEAT, wl.WEIGHTED_SUM) for depth in (4, 5, 6, 7, 8)]
+        cases += [(wl.LIFE, 4099, 4101, ("stream", 16, 8, 8), (4, 64), iters, "life_stream_kernel") for iters in (8, 40)]
+    for kernel, rows, cols, blocking, wg, iters, name in cases:
+        w = custom(kernel, rows, cols, (1, 1, 1, 1), border, pad=1.0, seed=iters, iters=iters)
+        st = ls.Stencil.from_workload(w)
+        set_mapping(st, blocking)
+        assert st.describe_run(iters, wg)["kernel"] == name, blocking
+        st.close()
+        check(ls, w, wg, blocking=blocking, offset=iters % 2)
+
+
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("kernel,halo,rows,cols", [
+    (wl.WEIGHTED_SUM, (3, 4, 4, 4), 4098, 8192), (wl.WEIGHTED_SUM, (5, 5, 4, 4), 4098, 8196), (wl.WEIGHTED_SUM, (5, 4, 3, 4), 4098, 8192),
+    (wl.WEIGHTED_SUM, (5, 5, 3, 3), 4098, 8192), (wl.SINCOS, (1, 5, 3, 0), 2050, 8196), (wl.WEIGHTED_SUM, (2, 2, 2, 2), 1030, 2052),
+    (wl.WEIGHTED_SUM, (1, 1, 4, 4), 1030, 2052), (wl.WEIGHTED_SUM, (2, 0, 0, 1), 517, 1028)])
+def test_marches_at_any_address(ls, kernel, halo, rows, cols, border):
+    """The marches of one application, each with seven to nine columns of eight rows and more, sin/cos and regions of up to five
+    rows among them: rows that start at a multiple of 16 bytes and at none, both kinds of store, the bits of one cell per
+    work-item (compared with the oracle on small matrices by other tests)."""
+    w = custom(kernel, rows, cols, halo, border, pad=0.25, seed=rows)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows)
+    for offset in (0, 1):
+        tin = torch.rand(rows * cols + offset, generator=gen, device="cuda")[offset:]
+        outs = []
+        for mapping, wg, nt in [(("local", 1, 1), (8, 32), 0), (("stream", 37, 4), (4, 64), 0), (("stream", 16, 4), (1, 64), 1)]:
+            st = ls.Stencil.from_workload(w)
+            st.set_mapping(*mapping)
+            st.set_option(ls.OPT_NT_STORE, nt)
+            assert mapping[0] == "local" or "march" in st.describe_run(1, wg)["kernel"]
+            out = torch.full((rows * cols + offset + 1,), 7.0, device="cuda")
+            st.run(tin, out[offset:-1], 1, wg)
+            torch.cuda.synchronize()
+            assert float(out[-1]) == 7.0 and (offset == 0 or float(out[0]) == 7.0)
+            outs.append(out)
+            st.close()
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), offset
 
 
 def test_temporal_blocking_not_offered_for_other_regions(ls):
@@ -1433,7 +1499,7 @@ def test_c5_full_size_every_cell(ls):
 def test_weighted_sums_on_8192_squared_every_cell(ls):
     """The weighted sums bench.py times on 8192^2 - the 28-tap sum with a border region given at run time, the
     7x7 Gaussian - in its launch configurations: every cell against the oracle's whole-matrix result, and the
-    marching kernels bit for bit against the local-memory tile."""
+    streaming mapping bit for bit against a tile with other cells per work-item."""
     import bench
     for name, marches in (("W8192", [(133, (4, 64)), (89, (1, 64))]), ("G7", [(69, (4, 64)), (46, (4, 64))])):
         w = bench.named_workload(wl, name)
