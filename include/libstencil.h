@@ -175,9 +175,10 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            never a reason for refusal).  Where a tile of 2 x 4 cells and 8 x 32 work-items in local memory
  *            is faster, the application is made by that, and cells_rows and the workgroup change nothing:
  *            everywhere but, on rows of a multiple of 4 cells, sums over up to five rows (N, S <= 2), two
- *            columns and more and up to 30 cells on matrices up to 2^24 cells, SINCOS from 2^24 cells on, and
- *            run-time regions of 72 cells and more from 2^25 cells on (stencil_describe_run).  Larger
- *            regions: not available (the local-memory tile is as fast there: its fold is bound by arithmetic).
+ *            columns and more and up to 30 cells in segments of up to six rows (up to six wavefronts per SIMD),
+ *            SINCOS from 2^24 cells on, and run-time regions of 72 cells and more from 2^25 cells on
+ *            (stencil_describe_run).  Larger regions: not available (the local-memory tile is as fast
+ *            there: its fold is bound by arithmetic).
  *            LIFE, WRAP and CONSTANT borders: one bit per cell, cells_cols in {4,8,16}; up to
  *            STENCIL_MAX_STREAM_DEPTH generations per launch, and between the launches of a run
  *            the matrix stays in bits.  A run of more generations than one launch makes is dealt to

@@ -556,24 +556,30 @@ LaunchPlan plan_launch_tile(const stencil *s, int wr, int wc, int) {
 // (a march's workgroup only groups wavefronts, and its segment height has no meaning for a tile).  On rows of whole vectors -
 // ragged ones it would move element by element - and with segments that suit it the march is ahead (us, march / tile, matrices
 // fresh from memory and then in the caches):
-// - under regions of up to five rows, of a few columns and up to 30 cells, on matrices up to 2^24 cells, which the caches hold
-//   with their output: 5x5 on 1024^2 5.3 / 6.7 and 5.1 / 5.0, on 2048^2 9.7 / 11.8 and 7.6 / 8.3, on 4096^2 30.4 / 31.2 and
-//   22.3 / 22.2; N1 S2 E1 W2 on 2048^2 9.7 / 11.0 and 7.1 / 7.5; 3 x 10 on 1500 x 2000 8.5 / 10.7 and 8.5 / 7.6.
-//   Beyond that size, or with more cells, the tile is: 5x5 on 8192^2 110 / 95 and 81 / 74, 5 x 9 on 2048^2 13.1 / 13.2 and
-//   11.5 / 10.1; and regions of one column fold as fast there at any size (S1 on 2048^2 8.3 / 7.3 and 5.5 / 5.5).
+// - under regions of up to five rows, two columns and more and up to 30 cells, in segments of up to six rows, up to six wavefronts per
+//   SIMD (march / tile, geometric means over 6 to 240 drawn matrices of 2^10 to 2^24 cells, in the caches and fresh: one row 0.84 and
+//   0.74, two and three 0.94 and 0.85, four to six 0.97 and 0.93; with ten wavefronts and more 1.06 to 1.40 and 1.15 to 1.42.  5x5 on
+//   1024^2 5.1 / 5.0 and 5.3 / 6.7 us, on 2048^2 7.6 / 8.3 and 9.7 / 11.8).  A taller segment is a chain of as many rows, which fewer
+//   wavefronts cover: seven to twelve rows 1.25 to 1.39 and 1.04 to 1.28 below a wavefront per SIMD, 0.95 to 1.07 and 1.00 to 1.10 with
+//   more; 13 to 24 1.03 to 1.86 and 0.99 to 1.78; 25 and more up to 6.8.  Nor does it pay with more cells (5 x 9 on 2048^2 11.5 / 10.1
+//   and 13.1 / 13.2) or in one column (S1 there 5.5 / 5.5 and 8.3 / 7.3).
 // - with the sine and cosine of every cell, taken once, from 2^24 cells on: 4096^2 34.5 / 37.2 and 28.7 / 31.6, 5000^2 47.9 / 51.3
 //   and 39.8 / 46.5, 8192^2 117 / 131; 2800^2 20.0 / 18.7 and 18.2 / 16.3.
 // - under run-time regions of 72 cells and more on matrices that no cache holds, where it is as fast: N5 S4 E4 W3 on 8192^2 170 /
 //   170, N4 S4 E3 W4 158 / 160, N3 S4 E4 W4 165 / 152.
 // Under taller regions the tile is: N1 S5 E3 W0 on 2048^2 12.1 / 12.5 and 10.9 / 9.1, on 8192^2 111 / 101; 7x7 there 127 / 125, 9x9
 // 192 / 170, 11x11 372 / 240.
-constexpr int64_t kCachedCells = (int64_t)1 << 24, kMarchCells = (int64_t)1 << 25;
+constexpr int64_t kSinCosMarchCells = (int64_t)1 << 24, kMarchCells = (int64_t)1 << 25;
 bool march_pays(const stencil *s) {
     if (s->cols % 4 != 0) return false;
     const int64_t cells = s->rows * s->cols;
-    if (s->kernel == STENCIL_SINCOS) return cells >= kCachedCells;
+    if (s->kernel == STENCIL_SINCOS) return cells >= kSinCosMarchCells;
     const int taps = (s->hn + s->hs + 1) * (s->he + s->hw + 1);
-    if (s->hn <= 2 && s->hs <= 2) return s->he + s->hw >= 1 && taps <= 30 && cells <= kCachedCells;
+    if (s->hn <= 2 && s->hs <= 2) {
+        const int strip_cols = sk::march_vectors(s->hw, s->he) * 4;
+        const int64_t waves = (s->cols + strip_cols - 1) / strip_cols * ((s->rows + s->cr - 1) / s->cr);
+        return s->he + s->hw >= 1 && taps <= 30 && s->cr <= 6 && waves <= 6 * 4 * (int64_t)stencil_compute_units();
+    }
     const bool compiled = s->hn == s->hs && s->hn == s->he && s->hn == s->hw;
     return !compiled && taps >= 72 && cells >= kMarchCells;
 }

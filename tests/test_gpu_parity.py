@@ -646,8 +646,8 @@ def test_sweeps_over_a_rotation_of_matrix_pairs(ls):
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
 def test_register_marching_single_application_kernels(ls, border):
     """One application under the streaming mapping, at the sizes of this test marched down the matrix in registers where the
-    region has up to five rows, two columns and more and up to 30 cells and rows are whole vectors, and made by a tile of 2x4
-    cells elsewhere (the other marches: test_marches_at_any_address, test_c5_full_size_every_cell): matrices wider than
+    region has up to five rows, two columns and more and up to 30 cells, in segments of up to six rows, and rows are whole
+    vectors, and made by a tile of 2x4 cells elsewhere (the other marches: test_marches_at_any_address, test_c5_full_size_every_cell): matrices wider than
     one strip (252 / 248 / 240 columns), ragged ones, ones smaller than a strip or than the region, unaligned rows, segment
     heights that do and do not divide the rows, and the output bits of the local-memory mapping."""
     shapes = [(70, 600), (37, 252), (41, 256), (130, 83), (64, 1024), (5, 3), (1, 1), (9, 508)]
@@ -661,12 +661,13 @@ def test_register_marching_single_application_kernels(ls, border):
         for rows, cols in shapes + [(23, 241), (12, 484)]:
             w = custom(kernel, rows, cols, halo, border, pad=0.3, seed=rows + cols)
             ref = None
-            for h, wg in [(64, (1, 64)), (8, (2, 64)), (1, (4, 64)), (29, (8, 8)), (4096, (2, 32))]:
+            for h, wg in [(64, (1, 64)), (8, (2, 64)), (1, (4, 64)), (5, (1, 64)), (6, (16, 16)), (29, (8, 8)), (4096, (2, 32))]:
                 got = check(ls, w, wg, blocking=("stream", h, 4))
                 if ref is None:
                     ref = gpu_apply(ls, w, w.grid(), (8, 8), blocking=(2, 4))
                 np.testing.assert_array_equal(got, ref)
         w = custom(kernel, 50, 300, halo, border, pad=0.3, seed=77)
+        check(ls, w, (1, 64), blocking=("stream", 5, 4), offset=1)
         check(ls, w, (1, 64), blocking=("stream", 16, 4), offset=1)            # rows of whole vectors, at no multiple of 16 bytes
         check(ls, custom(kernel, 50, 301, halo, border, pad=0.3, seed=78), (1, 64), blocking=("stream", 16, 4),
               offset=1)                                                          # ragged rows
@@ -900,7 +901,8 @@ def test_marches_at_any_address(ls, kernel, halo, rows, cols, border):
     for offset in (0, 1):
         tin = torch.rand(rows * cols + offset, generator=gen, device="cuda")[offset:]
         outs = []
-        for mapping, wg, nt in [(("local", 1, 1), (8, 32), 0), (("stream", 37, 4), (4, 64), 0), (("stream", 16, 4), (1, 64), 1)]:
+        tall, low = (6, 3) if max(halo[:2]) <= 2 else (37, 16)
+        for mapping, wg, nt in [(("local", 1, 1), (8, 32), 0), (("stream", tall, 4), (4, 64), 0), (("stream", low, 4), (1, 64), 1)]:
             st = ls.Stencil.from_workload(w)
             st.set_mapping(*mapping)
             st.set_option(ls.OPT_NT_STORE, nt)

@@ -741,14 +741,16 @@ def test_wide_gaussians_are_folded_by_rows_where_simds_have_several_wavefronts()
             assert kernel(48, 48, (32, 32)) == "tile_kernel by rows"             # sixteen wavefronts in one compute unit
 
 
-@pytest.mark.parametrize("kernel,halo,rows,cols,marched", [
-    ("weighted_sum", (2, 2, 2, 2), 2048, 2048, True), ("weighted_sum", (2, 2, 2, 2), 4096, 4096, True),
-    ("weighted_sum", (2, 2, 2, 2), 4097, 4096, False), ("weighted_sum", (2, 2, 2, 2), 2048, 2047, False),
-    ("weighted_sum", (1, 2, 1, 2), 512, 512, True), ("weighted_sum", (2, 2, 2, 3), 1500, 2000, True),
-    ("weighted_sum", (2, 2, 4, 4), 1500, 2000, False), ("weighted_sum", (2, 2, 0, 0), 1500, 2000, False),
-    ("weighted_sum", (3, 1, 1, 1), 1500, 2000, False), ("weighted_sum", (3, 3, 3, 3), 2048, 2048, False),
-    ("weighted_sum", (4, 4, 3, 4), 8192, 8192, True), ("weighted_sum", (4, 4, 4, 4), 8192, 8192, False),
-    ("sincos", (1, 5, 3, 0), 4096, 4096, True), ("sincos", (1, 5, 3, 0), 4096, 4092, False)])
-def test_single_applications_are_marched_where_it_is_faster(kernel, halo, rows, cols, marched):
-    info = describe(rows, cols, kernel, halo, "clamp", ("stream", 16, 4), 1, (1, 64))
+@pytest.mark.parametrize("kernel,halo,rows,cols,height,marched", [
+    ("weighted_sum", (2, 2, 2, 2), 2048, 2048, 5, True), ("weighted_sum", (2, 2, 2, 2), 2048, 2048, 6, True),
+    ("weighted_sum", (2, 2, 2, 2), 2048, 2048, 7, False), ("weighted_sum", (2, 2, 2, 2), 16, 48, 64, False),
+    ("weighted_sum", (2, 2, 2, 2), 1536, 992, 1, True), ("weighted_sum", (2, 2, 2, 2), 1537, 992, 1, False),   # six wavefronts per SIMD
+    ("weighted_sum", (2, 2, 2, 2), 4096, 4096, 5, False), ("weighted_sum", (2, 2, 2, 2), 2048, 2047, 5, False),
+    ("weighted_sum", (1, 2, 1, 2), 512, 512, 4, True), ("weighted_sum", (2, 2, 2, 3), 1500, 2000, 5, True),
+    ("weighted_sum", (2, 2, 4, 4), 1500, 2000, 5, False), ("weighted_sum", (2, 2, 0, 0), 1500, 2000, 5, False),
+    ("weighted_sum", (3, 1, 1, 1), 1500, 2000, 5, False), ("weighted_sum", (3, 3, 3, 3), 2048, 2048, 5, False),
+    ("weighted_sum", (4, 4, 3, 4), 8192, 8192, 16, True), ("weighted_sum", (4, 4, 4, 4), 8192, 8192, 16, False),
+    ("sincos", (1, 5, 3, 0), 4096, 4096, 16, True), ("sincos", (1, 5, 3, 0), 4096, 4092, 16, False)])
+def test_single_applications_are_marched_where_it_is_faster(kernel, halo, rows, cols, height, marched):
+    info = describe(rows, cols, kernel, halo, "clamp", ("stream", height, 4), 1, (1, 64))
     assert ("march" in info["kernel"], info["wg"]) == ((True, (1, 64)) if marched else (False, (8, 32)))
