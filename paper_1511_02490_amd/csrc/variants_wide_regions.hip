@@ -1,5 +1,5 @@
 // Variants: weighted sums with the wider symmetric border regions (Table 2's gaussian goes up to 10) as compile-time
-// regions: 7x7 and 9x9 under every mapping, 11x11 marched.
+// regions: 7x7 and 9x9 under every mapping, 11x11 under the streaming one (by tiles: march_pays in variants.h).
 #include "variants.h"
 
 void register_wide_regions(std::vector<Variant> &r) {
