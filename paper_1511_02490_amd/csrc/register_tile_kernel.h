@@ -9,8 +9,8 @@
 // computes within k cells of the tile's rim is stale after k applications: `depth` rows above and below and as many cells,
 // in whole vectors, left and right are not written.  Bound by vector-ALU issue (24 instructions per vector and application of
 // heat, 22 % to 45 % of them for rim cells) where every SIMD has several wavefronts, by the barrier and the launch where it
-// has one.  (100 heat steps, us before / now: 1025 x 1999, CLAMP, 4 per launch in local memory 280 / 125; 1001 x 1503, WRAP, 8
-// per launch marched element by element 362 / 117; 64^2, WRAP, 2 per launch 285 / 43.)
+// has one.  (100 heat steps, us before / now: 1025 x 1999, CLAMP, 4 per launch in local memory 280 / 108; 1001 x 1503, WRAP, 8
+// per launch marched element by element 362 / 106; 64^2, WRAP, 2 per launch 285 / 43.)
 //
 // Borders.  WRAP: a periodic copy evolves like its original.  CLAMP and CONSTANT: the first tile of a row or column of tiles
 // begins with the matrix and the last one ends with it, wherever that puts its vectors, so that no cell of a tile lies
@@ -101,12 +101,15 @@ __global__ __launch_bounds__(kRegisterTileMaxThreads) void register_tile_kernel(
             for (int i = 0; i < RPT; ++i) pad_outside(x[i], i);
         }
 
-        auto row_of = [&](const float (&v)[CC]) {
+        struct Ends { float w, e; };
+        auto ends_of = [&](const float (&v)[CC]) {
+            return Ends{__uint_as_float(from_lane_below(__float_as_uint(v[CC - 1]))), __uint_as_float(from_lane_above(__float_as_uint(v[0])))};
+        };
+        auto row_of = [&](const float (&v)[CC], const Ends &ends) {
             QuadRow r;
 #pragma unroll
             for (int j = 0; j < CC; ++j) r.v[j] = v[j];
-            r.w = __uint_as_float(from_lane_below(__float_as_uint(v[CC - 1])));
-            r.e = __uint_as_float(from_lane_above(__float_as_uint(v[0])));
+            r.w = ends.w, r.e = ends.e;
             if (SMALL && B == kClamp) {
                 clamp_columns(r, gc0, cols);
             } else if (kEdge) {
@@ -126,8 +129,18 @@ __global__ __launch_bounds__(kRegisterTileMaxThreads) void register_tile_kernel(
                     temporal_quad<Op>(y[i], up, mid, dn, a.w, a.scalar0);
                 if (B == kConstant && SMALL) pad_outside(y[i], i);
             };
+            // All rows' cross-lane moves together, nothing between them.  Two wavefronts of a SIMD issue vector instructions in
+            // the same cycles; after a cross-lane move they take turns instead, until a scalar instruction parts them (a
+            // microbenchmark's additions: 2.1 cycles each with two wavefronts, 4.1 with a move among 24 of them), and after many
+            // moves in a row for no longer.  As parts of the additions all over the rows: 100 clamped heat steps on 1025 x 1999
+            // 118 us, now 108; 96 on 3072^2 262 and 223.  (An s_nop behind the moves: 111.)
+            Ends ends[RPT];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 1; i < RPT - 1; ++i) apply(i, row_of(x[i - 1]), row_of(x[i]), row_of(x[i + 1]));
+            for (int i = 0; i < RPT; ++i) ends[i] = ends_of(x[i]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 1; i < RPT - 1; ++i) apply(i, row_of(x[i - 1], ends[i - 1]), row_of(x[i], ends[i]), row_of(x[i + 1], ends[i + 1]));
             __syncthreads();
             float above[CC], below[CC];
             load_vec(above, last_rows + buffer + above_at);
@@ -139,8 +152,8 @@ __global__ __launch_bounds__(kRegisterTileMaxThreads) void register_tile_kernel(
                     below[j] = no_below ? (B == kClamp ? x[RPT - 1][j] : a.pad) : below[j];
                 }
             }
-            apply(0, row_of(above), row_of(x[0]), row_of(x[1]));
-            apply(RPT - 1, row_of(x[RPT - 2]), row_of(x[RPT - 1]), row_of(below));
+            apply(0, row_of(above, ends_of(above)), row_of(x[0], ends[0]), row_of(x[1], ends[1]));
+            apply(RPT - 1, row_of(x[RPT - 2], ends[RPT - 2]), row_of(x[RPT - 1], ends[RPT - 1]), row_of(below, ends_of(below)));
         };
         float y[RPT][CC];
         auto move_back = [&] {

@@ -8,13 +8,16 @@ namespace {
 
 // A launch's tile and workgroup, cut by what a run of launches like it is estimated to take (us; from some 900 runs of 96 and
 // 100 heat steps on 256^2 to 4096^2 cells, workgroups of 256, 512 and 1024, 4 to 16 steps per launch, each tile below and ones of eight rows: 11 %
-// off on average, and the tile taken 1.4 % slower than the best one).  A launch, its loads and its stores: kLaunchUs and
-// kCellUs a million cells.  An application: kRowUs for every row that a SIMD of the fullest compute unit goes through (half
-// as much again for a 3x3 sum), kWaitUs for the barrier and what hangs on it, kOwnRowUs for every row of a work-item.
-// (Eight rows per work-item were as fast as four on the largest matrices, 425 / 428 us for 96 steps on 4096^2, and slower on
-// all others.)
-constexpr double kLaunchUs = 3.1, kCellUs = 0.8, kWaitUs = 0.25, kOwnRowUs = 0.023, kRowUs = 0.0312;
-double op_weight(const stencil *s) { return s->kernel == STENCIL_HEAT ? 1.0 : 1.5; }
+// off on average, and the tile taken 1.4 % slower than the best one; row_us taken again since from nine runs of 96 steps on 8 to 17
+// million cells, which it gives within 7 %).  A launch, its loads and its stores: kLaunchUs and kCellUs a million cells.  An
+// application: row_us for every row that a SIMD of the fullest compute unit goes through, kWaitUs for the barrier and what hangs on
+// it, kOwnRowUs for every row of a work-item.
+// (Eight rows per work-item leave room for one workgroup of 1024 on a compute unit, nothing beside its loads and stores: 96
+// steps on 4096^2 549 us, by four rows 385.)
+constexpr double kLaunchUs = 3.1, kCellUs = 0.8, kWaitUs = 0.25, kOwnRowUs = 0.023;
+// heat 0.024 (0.0312 before the tile's cross-lane moves went together), a 3x3 sum 0.0468: by 0.037 its runs take too few of the
+// launches that overlap (96 on 3000^2 461 us, 399 by this)
+double row_us(const stencil *s) { return s->kernel == STENCIL_HEAT ? 0.024 : 0.0468; }
 
 struct RegisterTile {
     int threads = 0, rows_per_item = 0, group_shift = 0;
@@ -24,7 +27,6 @@ struct RegisterTile {
     double us = 0.0;                 // of one launch
 };
 RegisterTile register_tile(const stencil *s, int depth) {
-    const double row_us = kRowUs * op_weight(s);
     const int units = stencil_compute_units(), rows = (int)s->rows, cols = (int)s->cols, rim = sk::register_tile_rim(depth);
     const bool wrap = s->border == STENCIL_WRAP;
     RegisterTile best;
@@ -43,7 +45,7 @@ RegisterTile register_tile(const stencil *s, int depth) {
                 if ((int64_t)strips * tiles * threads > kMaxGridItems || rows > INT32_MAX - held_r || cols > INT32_MAX - held_c) continue;
                 const double simd_rows = (double)(((int64_t)strips * tiles + units - 1) / units) * (threads / 256) * rpt;
                 const double us = kLaunchUs + kCellUs * 1e-6 * rows * cols +
-                                  depth * (row_us * (shift == 4 ? 1.04 : 1.0) * simd_rows + kWaitUs + kOwnRowUs * rpt);
+                                  depth * (row_us(s) * (shift == 4 ? 1.04 : 1.0) * simd_rows + kWaitUs + kOwnRowUs * rpt);
                 if (best.threads == 0 || us < best.us) best = {threads, rpt, shift, tiles, strips, small, simd_rows, us};
             }
     }
@@ -88,13 +90,17 @@ RunLaunchFn launcher_of(int border) {
 
 }  // namespace
 
+// What the marching kernel takes for a row and an application of a SIMD's wavefronts, us (runs of eight per launch on 4096^2 and
+// 2048 x 8192): heat 0.037 under WRAP, 0.042 where padded cells are set back, a 3x3 sum 0.06.
+static double march_row_us(const stencil *s) { return s->kernel != STENCIL_HEAT ? 0.06 : s->border == STENCIL_WRAP ? 0.037 : 0.042; }
+
 // Applications per launch of a run that takes several launches: at least the number asked for, as far as it divides the run
 // into the same launches.  0, the run stays with its mapping's kernel: nothing is to be fused; the workgroup is no whole
 // wavefronts; or the marching kernel is faster, which fills the device on matrices of ten million cells and more.  Its time:
-// every SIMD marches its wavefronts one after the other, 0.04 us a row and application, half as much again element by element,
+// every SIMD marches its wavefronts one after the other, march_row_us a row and application, half as much again element by element,
 // unless a launch of few applications takes longer to move the matrix, 1.3 us a million cells
-// (us a run of 96 heat steps, 8 per launch there, register tiles / march: 2048^2 175 / 285, 3072^2 277 / 296, 4096 x 3072
-// 365 / 391, 4096^2 447 / 444, 8192 x 2048 473 / 440; 3001 x 3003 289 / 421, 4001 x 4003 439 / 624).
+// (us a run of 96 heat steps, 8 per launch there, register tiles / march: 2048 x 4096 214 / 247, 3072^2 223 / 254, 4096 x 3072
+// 292 / 337, 4096^2 385 / 418, CONSTANT 393 / 472; 4001 x 4003 368 / 560).
 int register_tile_per_launch(const stencil *s, int iters, int wr, int wc) {
     const int asked = s->temporal_depth;
     if (wr * wc % 64 != 0 || asked == 1) return 0;
@@ -118,7 +124,7 @@ int register_tile_per_launch(const stencil *s, int iters, int wr, int wc) {
         const int64_t waves = (s->cols + strip_cols - 1) / strip_cols * ((s->rows + s->cr - 1) / s->cr), simds = 4 * stencil_compute_units();
         const double rows = (double)((waves + simds - 1) / simds) * (s->cr + 2 * asked);
         const double moved_us = 1.3e-6 * (double)s->rows * (double)s->cols;
-        const double marched_us = asked * rows * 0.04 * op_weight(s) * (s->cols % 4 != 0 ? 1.5 : 1.0);
+        const double marched_us = asked * rows * march_row_us(s) * (s->cols % 4 != 0 ? 1.5 : 1.0);
         const double march_us = (double)iters / asked * (kLaunchUs + std::max(moved_us, marched_us));
         if (march_us <= best_us) return 0;
     }
