@@ -54,6 +54,9 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
     static_assert(B == kWrap || B == kConstant, "wrap and constant borders only");
     static_assert(DEPTH >= 1 && DEPTH <= kStreamMaxDepth, "a rim lane covers four applications");
     static_assert(Op::kPlanes == 1 && sizeof(T) == 4, "fp32, one value per cell");
+    // only a cell's own row has neighbours in other lanes, nothing parts the levels of a step, and the moves of several are worth
+    // their registers (97 instead of 95 at five levels, a wavefront per SIMD; five levels 338 / 332 us for 56 steps on 4096^2)
+    constexpr bool kCross = std::is_same<Op, OpHeat>::value && B == kWrap && DEPTH >= 6;
     constexpr int CC = 4;
     constexpr int R = 3;                            // rows of a level kept
     constexpr int PF = 6;                           // input rows in flight = steps per round (a multiple of R)
@@ -146,6 +149,21 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
             for (int j = 0; j < CC; ++j) lv[0][u][j] = pf[v][j];
             pad_outside(r0 - DEPTH + t, lv[0][u]);
             load_row(t + PF, pf[v]);
+            // The cross-lane moves of all levels together: the row in the middle of each is there since the step before.  (A
+            // cross-lane move costs a SIMD's wavefronts the cycles in which two of them issue, many in a row no more than one:
+            // register_tile_kernel.h.  As part of each level's additions a launch of eight heat steps on 4096^2, WRAP, took
+            // 35.6 us, now 32.5: 18.7 k vector instructions per SIMD, at the 1.85 GHz that this load leaves of the clock.
+            // CONSTANT, where a branch after every level parts them, gains nothing.)
+            T sides[DEPTH][2];
+            if constexpr (kCross) {
+#pragma unroll
+                for (int k = 0; k < DEPTH; ++k) {
+                    const T(&mid)[CC] = lv[k][(u + 2) % R];
+                    sides[k][0] = __uint_as_float(from_lane_below(__float_as_uint(mid[CC - 1])));
+                    sides[k][1] = __uint_as_float(from_lane_above(__float_as_uint(mid[0])));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
 #pragma unroll
             for (int k = 1; k <= DEPTH; ++k) {
                 // level k's first row that anything depends on is r0 - DEPTH + k, due at step 2k:
@@ -161,8 +179,8 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
 #pragma unroll
                 for (int dr = -1; dr <= 1; ++dr) {
                     const T(&q)[CC] = dr < 0 ? up : (dr == 0 ? mid : dn);
-                    const T row[6] = {__uint_as_float(from_lane_below(__float_as_uint(q[3]))), q[0], q[1], q[2],
-                                      q[3], __uint_as_float(from_lane_above(__float_as_uint(q[0])))};
+                    const T row[6] = {kCross ? sides[k - 1][0] : __uint_as_float(from_lane_below(__float_as_uint(q[3]))), q[0], q[1], q[2],
+                                      q[3], kCross ? sides[k - 1][1] : __uint_as_float(from_lane_above(__float_as_uint(q[0])))};
 #pragma unroll
                     for (int cc = 0; cc < CC; ++cc)
                         fold_row<Op>(
