@@ -122,7 +122,10 @@ __global__ __launch_bounds__(MAXT) void direct_kernel(const TileArgs<Op, Halo> a
         for (int cc = 0; cc < CC; ++cc) res[cc] = Op::finish(st[cr][cc], a.scalar0);
         T *dst = a.out + (size_t)r * cols + c0;
         if (c0 + CC <= cols) {
-            store_out_vec(dst, res, a.store == Store::kNonTemporal);
+            if constexpr (goes_through<Op>::value)
+                store_out_vec<Store::kThrough>(dst, res);
+            else
+                store_out_vec(dst, res, a.store == Store::kNonTemporal);
         } else {
 #pragma unroll
             for (int cc = 0; cc < CC; ++cc)

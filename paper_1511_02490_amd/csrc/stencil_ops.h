@@ -195,6 +195,15 @@ struct out_type_of { using type = typename Op::T; };
 template <class Op>
 struct out_type_of<Op, decltype(void(sizeof(typename Op::O)))> { using type = typename Op::O; };
 
+// A customising function whose kernel writes its output vectors through (store_word4 in tile_kernel.h), whatever the handle says:
+// kernels of their own, since a third kind of store, chosen in the kernel, costs the others 1 %.
+template <class Op>
+struct WrittenThrough : Op {};
+template <class Op>
+struct goes_through { static constexpr bool value = false; };
+template <class Op>
+struct goes_through<WrittenThrough<Op>> { static constexpr bool value = true; };
+
 // Packed bytes, each below 0x80: 0x01 in every byte of the result whose byte of x is zero.
 // (Adding 0x7f carries into a byte's top bit exactly when the byte is not zero, and never beyond.)
 __device__ __forceinline__ uint32_t zero_bytes(uint32_t x) {

@@ -152,8 +152,7 @@ __device__ __forceinline__ void load_global(E (&dst)[CNT], const E *src) {
 // generations on 4096^2 in local memory 11.4 / 9.5 us; a launch of four heat steps there 33.5 / 33.1.  Small outputs
 // pay for it at the end of the last workgroups: a launch of two heat steps on 1024^2 9.4 / 10.0.  And what a store leaves of a
 // cache line is written to memory by itself.  Each launcher in variants.h and variants_register_tiles.hip draws its line.)
-// (The tiles of single applications gain 4 % on 4096^2 and more, but the third kind of store costs them 1 % on all smaller
-// matrices.)  The two wait states keep what follows off the stored registers: the compiler counts them only after its own
+// (The tiles of single applications: WrittenThrough, and tile_goes_through in variants.h.)  The two wait states keep what follows off the stored registers: the compiler counts them only after its own
 // stores.  Nothing reads the output in the same launch.
 template <Store S>
 __device__ __forceinline__ void store_word4(void *dst, uint4 v) {
@@ -798,7 +797,10 @@ __global__ __launch_bounds__(MAXT) void tile_kernel(const TileArgs<Op, Halo> a) 
         O *dst = a.out + (size_t)r * cols + c0 + lc0;
         if constexpr (CC > 1) {
             if (c0 + lc0 + CC <= cols) {
-                store_out_vec(dst, res, a.store == Store::kNonTemporal);
+                if constexpr (goes_through<Op>::value)
+                    store_out_vec<Store::kThrough>(dst, res);
+                else
+                    store_out_vec(dst, res, a.store == Store::kNonTemporal);
                 continue;
             }
         }

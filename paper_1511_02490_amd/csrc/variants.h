@@ -110,6 +110,26 @@ sk::Store fused_store(const stencil *s, bool may) {
     return s->nt_store || !through ? store_of(s) : sk::Store::kThrough;
 }
 
+// Tiles and direct kernels of a single application, two rows of one vector per work-item, where non-temporal stores are not
+// asked for, write their output through: what plain stores leave in the L2 caches is written back when the launch ends, with
+// nothing beside it.  From 6 MiB of output on, and where its rows are not whole cache lines of 128 bytes up to 32 MiB.  Written
+// through / plain, 3x3, 5x5 and run-time regions of floats on matrices in turn: 1024^2 0.97 to 1.02, 1400 x 1404 0.90 to 0.94,
+// 1400 x 1401 0.95 to 1.00, 2048^2 0.83 to 0.89 (5x5 10.7 -> 9.2 us), 2000 x 2001 0.86 to 0.93, 2900 x 2912 0.92 to 0.96, 2900 x 2908
+// 0.94 to 0.99, 2900 x 2901 0.99 to 1.05, 4096^2 0.97 to 1.01, 4000 x 4012 1.06 to 1.10, 4000 x 4001 1.09 to 1.12, 8192^2 0.97 to
+// 0.99.  5x5 doubles on 1000^2 5.9 -> 5.4 us, on 2048^2 13.6 -> 12.8; integers there 12.8 -> 10.9; sin/cos there 12.9 -> 11.5; the
+// edge detector's stages on 4096^2, three of which this serves, 88.7 -> 85.2; ten applications in turn on 2048^2 90.3 -> 87.3.
+template <class Op, int CR, int CC>
+constexpr bool may_go_through() {
+    using O = typename sk::out_type_of<Op>::type;
+    return !sk::goes_through<Op>::value && CR == 2 && CC * sizeof(O) == 16 &&
+           (Op::kWeights || std::is_same<Op, sk::OpSobel>::value || std::is_same<Op, sk::OpNms>::value);
+}
+bool tile_goes_through(const stencil *s) {
+    const size_t bytes = s->out_bytes();
+    const bool lines = (size_t)s->cols * s->out_elem() % 128 == 0;
+    return !s->nt_store && bytes >= (size_t)6 << 20 && (lines || bytes <= (size_t)32 << 20);
+}
+
 // A launch has at most so many work-items; more are turned down.
 constexpr int64_t kMaxGridItems = ((int64_t)1 << 32) - 1;
 
@@ -522,6 +542,19 @@ bool unrolls(const stencil *s, int wr, int wc) {
 }
 
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
+hipError_t start_tile(const stencil *s, const void *in, void *out, int wr, int wc, hipStream_t stream) {
+    unsigned blocks;
+    size_t lds;
+    const auto a = make_args<Op, Halo, CR, CC>(s, STENCIL_STAGING_LOCAL, in, out, wr, wc, &blocks, &lds);
+    static thread_local int raised_on = -1;
+    hipError_t e = allow_large_tiles(reinterpret_cast<const void *>(&sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>),
+                                     lds, &raised_on);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a);
+    return hipGetLastError();
+}
+
+template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
     if constexpr (std::is_same<Halo, sk::HaloD>::value && CC > 1) {
         const sk::Fold fold = region_fold<Op, CR>(s);
@@ -532,15 +565,10 @@ hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int 
         if (unrolls<Halo, CR, CC>(s, wr, wc))
             return launch_tile<Op, B, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
     }
-    unsigned blocks;
-    size_t lds;
-    const auto a = make_args<Op, Halo, CR, CC>(s, STENCIL_STAGING_LOCAL, in, out, wr, wc, &blocks, &lds);
-    static thread_local int raised_on = -1;
-    hipError_t e = allow_large_tiles(reinterpret_cast<const void *>(&sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>),
-                                     lds, &raised_on);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sk::tile_kernel<Op, B, Halo, CR, CC, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a);
-    return hipGetLastError();
+    if constexpr (may_go_through<Op, CR, CC>()) {
+        if (tile_goes_through(s)) return start_tile<sk::WrittenThrough<Op>, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, stream);
+    }
+    return start_tile<Op, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, stream);
 }
 
 // ... and what it starts.  (The run-time folds are one kernel as far as a plan goes.)
@@ -675,6 +703,9 @@ hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int 
 
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_direct(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
+    if constexpr (may_go_through<Op, CR, CC>()) {
+        if (tile_goes_through(s)) return launch_direct<sk::WrittenThrough<Op>, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
+    }
     unsigned blocks;
     size_t lds;
     const auto a = make_args<Op, Halo, CR, CC>(s, STENCIL_STAGING_DIRECT, in, out, wr, wc, &blocks, &lds);

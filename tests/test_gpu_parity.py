@@ -1210,6 +1210,41 @@ def test_runs_on_a_side_stream(ls):
     assert rel_err(tout.cpu().numpy(), oracle.apply_workload(w, g)) <= REL_1
 
 
+@pytest.mark.parametrize("rows,cols", [(1229, 1280), (1228, 1280), (1100, 1431), (2046, 4099), (2047, 4099), (2049, 4128)])
+def test_single_applications_written_through(ls, rows, cols):
+    """Outputs from 6 MiB on (ragged rows: up to 32 MiB) are written through by kernels of their own: the bits are those of the
+    kernels that non-temporal stores keep, in every cell, and cells behind the output stay as they were."""
+    gen = np.random.default_rng(rows * 10000 + cols)
+    types = {"f32": torch.float32, "u8": torch.uint8, "i32": torch.int32, "f64": torch.float64}
+    for kernel, dtype, halo, border, mapping in [
+            ("weighted_sum", "f32", (1, 1, 1, 1), "clamp", ("local", 2, 4)), ("weighted_sum", "f32", (2, 2, 2, 2), "wrap", ("local", 2, 4)),
+            ("weighted_sum", "f32", (3, 3, 3, 3), "constant", ("local", 2, 4)), ("weighted_sum", "f32", (1, 0, 3, 2), "clamp", ("local", 2, 4)),
+            ("weighted_sum", "f32", (2, 2, 2, 2), "clamp", ("direct", 2, 4)), ("weighted_sum", "u8", (2, 2, 2, 2), "clamp", ("local", 2, 4)),
+            ("weighted_sum", "i32", (3, 2, 4, 1), "wrap", ("local", 2, 4)), ("weighted_sum", "f64", (2, 2, 2, 2), "constant", ("local", 2, 2)),
+            ("sincos", "f32", (1, 5, 3, 0), "constant", ("local", 2, 4)), ("sobel", "f32", (1, 1, 1, 1), "wrap", ("direct", 2, 4)),
+            ("nms", "f32", (1, 1, 1, 1), "clamp", ("direct", 2, 4))]:
+        n, s, e, w = halo
+        shape = (n + s + 1, e + w + 1)
+        grid = gen.integers(0, 200, size=(rows, cols)) if dtype in ("u8", "i32") else gen.random((rows, cols))
+        tin = torch.from_numpy(grid).to(types[dtype]).cuda()
+        st = ls.Stencil(rows, cols, dtype, halo, border)
+        if kernel in ("weighted_sum", "sincos"):
+            st.set_kernel(kernel, gen.integers(-9, 10, size=shape).astype(np.float32) if dtype == "i32" else gen.random(shape, dtype=np.float32))
+        else:
+            st.set_kernel(kernel)
+        st.set_mapping(*mapping)
+        outs = []
+        for nt in (0, 1):
+            st.set_option(ls.OPT_NT_STORE, nt)
+            buf = torch.full((rows * cols + 64,), 77, dtype=types[{1: "f32"}.get(tin.element_size(), dtype)], device="cuda")
+            st.run(tin, buf[:rows * cols], 1, (8, 32))
+            torch.cuda.synchronize()
+            assert bool((buf[rows * cols:] == 77).all())
+            outs.append(buf)
+        assert torch.equal(outs[0], outs[1]), (kernel, dtype, halo, border, mapping)
+        st.close()
+
+
 def test_iterated_run_inside_a_hip_graph(ls):
     """An iterated stencil_run is only kernel launches once its scratch matrix exists, so it can
     be captured into a HIP graph; every replay must reproduce the eager result."""
