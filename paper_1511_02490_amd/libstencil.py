@@ -244,6 +244,7 @@ class Stencil:
         bm = _BORDERS[border] if isinstance(border, str) else int(border)
         _check(_lib.stencil_create(ctypes.byref(self._h), int(rows), int(cols), dt, n, s, e, w, bm))
         self.rows, self.cols, self.dtype, self.halo = int(rows), int(cols), dtype, (n, s, e, w)
+        self._tensor_types()
         if pad:
             self.set_border_value(pad)
 
@@ -279,6 +280,7 @@ class Stencil:
             wbuf = (ctypes.c_float * nw)(*flat.tolist())
         sc = (ctypes.c_float * max(1, len(scalars)))(*[float(x) for x in scalars])
         _check(_lib.stencil_set_kernel(self._h, kid, wbuf, nw, sc, len(scalars)))
+        self._tensor_types()
 
     def set_border_value(self, v: float):
         _check(_lib.stencil_set_border_value(self._h, float(v)))
@@ -337,11 +339,18 @@ class Stencil:
             return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())      # of the current device, as a number
         return getattr(stream, "cuda_stream", stream)
 
+    def _tensor_types(self):
+        # what _check_tensors compares with; the output's type follows from the kernel
+        self._types = _TORCH_TYPES.get(self.dtype), _TORCH_TYPES.get(self.output_dtype())
+
     def _check_tensors(self, tin, tout):
         cells = self.rows * self.cols
-        for t, want in ((tin, _TORCH_TYPES[self.dtype]), (tout, _TORCH_TYPES[self.output_dtype()])):
-            if not t.is_cuda or not t.is_contiguous() or t.dtype != want or t.numel() != cells:
-                raise ValueError("tensors must be contiguous CUDA %s of %d x %d" % (want, self.rows, self.cols))
+        want_in, want_out = self._types
+        # (one expression: a loop over the two tensors that asks the library for the output's type takes 0.77 us, this 0.46,
+        # of the 4.3 of a small call)
+        if not (tin.dtype is want_in and tout.dtype is want_out and tin.is_cuda and tout.is_cuda and tin.numel() == cells and
+                tout.numel() == cells and tin.is_contiguous() and tout.is_contiguous()):
+            raise ValueError("tensors must be contiguous CUDA %s (in) and %s (out) of %d x %d" % (want_in, want_out, self.rows, self.cols))
 
     def output_dtype(self) -> int:
         """Element type of the output matrix (the input's, except bytes for the threshold stencil)."""
