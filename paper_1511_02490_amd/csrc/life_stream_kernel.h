@@ -19,7 +19,7 @@
 // launches, so that both are small together (life_tile and life_per_launch in variants.h).
 // (100 generations of 4096 x 4096, WRAP: 282 us by marching packed bytes down the matrix, 121 on bits with 8 to a
 // launch, 77 with 20 or 25.  50 generations of 1001 x 1503, CLAMP: 83 us by life_temporal_kernel, 4 to a launch from
-// bytes to bytes, 24 here with 17.)
+// bytes to bytes, 23 here with 17.)
 #pragma once
 #include "life_bits.h"
 

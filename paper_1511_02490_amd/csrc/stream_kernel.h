@@ -152,7 +152,7 @@ __device__ __forceinline__ void stream_body(const TileArgs<Op, HaloC<1, 1, 1, 1>
             // The cross-lane moves of all levels together: the row in the middle of each is there since the step before.  (A
             // cross-lane move costs a SIMD's wavefronts the cycles in which two of them issue, many in a row no more than one:
             // register_tile_kernel.h.  As part of each level's additions a launch of eight heat steps on 4096^2, WRAP, took
-            // 35.6 us, now 32.5: 18.7 k vector instructions per SIMD, at the 1.85 GHz that this load leaves of the clock.
+            // 36.9 us, now 34.9: 18.7 k vector instructions per SIMD, at the 1.85 GHz that this load leaves of the clock.
             // CONSTANT, where a branch after every level parts them, gains nothing.)
             T sides[DEPTH][2];
             if constexpr (kCross) {
