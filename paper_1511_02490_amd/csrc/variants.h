@@ -369,6 +369,19 @@ LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
     return best;
 }
 
+// The work-items of a launch that makes more generations than the handle asks for, whose tile is the library's: 512, or 1024 of four
+// rows where those would have eight and more and the border's cells are looked after; the workgroup's own where the tile is
+// prescribed or the matrix has none for these.  (us a run, 256 / 512 / 1024 work-items: 100 generations, WRAP, 4096^2 77.3 / 65.5 /
+// 67.0, 2048^2 51.0 / 42.2 / 48.9; CLAMP, 4096^2 86.7 / 81.5 / 69.7, 8192 x 2048 88.4 / 81.3 / 69.7, 50 of 1001 x 1503 23.7 / 22.7 /
+// 28.1; 60 padded ones of 3000 x 5000 54.9 / 45.6 / 43.8; 200 of 512^2 68.4 / 67.8 / 86.9.  More wavefronts share a tile's rim and
+// its barrier; 128, 384 and 768 are slower than the better of 512 and 1024 by 2 % and more in all but three of ten.)
+int life_run_threads(const stencil *s, int threads, int depth) {
+    if (s->life_rows != 0 || depth <= s->temporal_depth) return threads;
+    const LifeTile t = life_tile(s, 512, depth, false);
+    if (t.tiles_r == 0) return threads;
+    return s->border != STENCIL_WRAP && t.rows_per_item >= 8 && life_tile(s, 1024, depth, false).tiles_r > 0 ? 1024 : 512;
+}
+
 // Generations per launch of a run that takes several launches: a launch costs as much as some ten generations do
 // (kLifeLaunchUs), but every generation fused repeats two more rows of every tile.  At least the number asked for, as far as
 // it divides the run into the same launches, and exactly that where the tile is prescribed or nothing is to be fused.  0, the run
@@ -386,7 +399,7 @@ int life_per_launch(const stencil *s, int iters, int wr, int wc) {
         if (launches == launches_before) continue;
         launches_before = launches;
         const int per = (iters + launches - 1) / launches;
-        const LifeTile t = life_tile(s, threads, per, false);
+        const LifeTile t = life_tile(s, life_run_threads(s, threads, per), per, false);
         if (t.tiles_r == 0) break;           // (nor has any with more generations one)
         const double us = launches * (kLifeLaunchUs + per * t.rows_worth * kLifeRowUs);
         if (best_us == 0.0 || us < best_us) {
@@ -407,15 +420,16 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     a.rows = (int)s->rows;
     a.cols = (int)s->cols;
     a.words = (int)life_words(s);
-    const LifeTile t = life_tile(s, wr * wc, depth, !IN_BITS);
+    const int threads = life_run_threads(s, wr * wc, depth);
+    const LifeTile t = life_tile(s, threads, depth, !IN_BITS);
     if (t.tiles_r == 0) return hipErrorInvalidValue;
     a.group_shift = t.group_shift;
     a.tiles_c = t.tiles_c;
     a.n_tiles = t.tiles_r * t.tiles_c;
     a.pad = s->pad != 0.0;
     a.store = fused_store(s, true);
-    const dim3 grid((unsigned)a.n_tiles), block(wc, wr);
-    const unsigned lds = sk::life_stream_lds(wr * wc);
+    const dim3 grid((unsigned)a.n_tiles), block((unsigned)threads);
+    const unsigned lds = sk::life_stream_lds(threads);
     switch (t.rows_per_item) {
     case 2: hipLaunchKernelGGL((sk::life_stream_kernel<B, 2, IN_BITS, OUT_BITS>), grid, block, lds, stream, a, depth); break;
     case 4: hipLaunchKernelGGL((sk::life_stream_kernel<B, 4, IN_BITS, OUT_BITS>), grid, block, lds, stream, a, depth); break;
@@ -425,8 +439,10 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     return hipGetLastError();
 }
 LaunchPlan plan_life_stream(const stencil *s, int wr, int wc, int depth) {
-    const LifeTile t = life_tile(s, wr * wc, depth, true);
-    return {"life_stream_kernel", wr, wc, (int64_t)t.tiles_r * t.tiles_c, sk::life_stream_lds(wr * wc)};
+    const int threads = life_run_threads(s, wr * wc, depth);
+    const LifeTile t = life_tile(s, threads, depth, true);
+    if (threads != wr * wc) wr = threads / 64, wc = 64;
+    return {"life_stream_kernel", wr, wc, (int64_t)t.tiles_r * t.tiles_c, sk::life_stream_lds(threads)};
 }
 template <int B>
 hipError_t launch_life_stream(const stencil *s, const void *in, void *out, int wr, int wc, int depth, hipStream_t stream) {

@@ -701,6 +701,19 @@ def test_describe_run_names_the_kernel_that_runs():
         describe(100, 128, "heat", one, "wrap", ("stream", 20, 4), 4, (5, 13), depth=4)
 
 
+@pytest.mark.parametrize("border,rows,cols,items", [("wrap", 4096, 4096, 512), ("clamp", 4096, 4096, 1024), ("constant", 3000, 5000, 1024),
+                                                     ("clamp", 1001, 1503, 512), ("wrap", 16, 600, 512)])
+def test_life_runs_take_workgroups_of_their_own(border, rows, cols, items):
+    """Launches of more generations than asked for have the library's workgroup; those of as many the caller's."""
+    one, mapping = (1, 1, 1, 1), ("temporal", 2, 16)
+    run = describe(rows, cols, "life", one, border, mapping, 100, (4, 64), depth=4, dtype="u8")
+    assert run["kernel"] == "life_stream_kernel" and run["applications"] > 4
+    assert run["wg"][0] * run["wg"][1] == items and run["local_bytes"] == 16 * items
+    if border == "wrap":
+        own = describe(rows, cols, "life", one, border, ("stream", 16, 8), 4, (4, 64), depth=4, dtype="u8")
+        assert own["wg"] == (4, 64) and own["local_bytes"] == 16 * 256
+
+
 @pytest.mark.parametrize("rows,cols", [(2 ** 31 - 1, 1), (2 ** 31 - 70, 1), (2 ** 29 - 1, 4), (2 ** 28 - 1, 8), (1, 2 ** 31 - 1), (8, 2 ** 28 - 1)])
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
 def test_thin_matrices_stay_within_a_launch(rows, cols, border):
