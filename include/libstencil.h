@@ -279,6 +279,13 @@ typedef struct stencil_launch_info {
 } stencil_launch_info_t;
 int stencil_describe_run(const stencil_t *st, int iters, int wg_rows, int wg_cols, stencil_launch_info_t *info);
 
+/* The same of one launch of that run, 0 for the first (`applications`: those it makes), and in *store how it writes its
+ * output if that is at `out`: its 16-byte stores of output cells (narrower ones are plain).  A testing aid: the kernels of
+ * either kind of store go by one name.  STENCIL_E_INVALID if the run has no such launch. */
+enum stencil_store { STENCIL_STORE_PLAIN = 0, STENCIL_STORE_NON_TEMPORAL = 1, STENCIL_STORE_THROUGH = 2 };
+int stencil_describe_launch(const stencil_t *st, int iters, int wg_rows, int wg_cols, int launch, const void *out,
+                            stencil_launch_info_t *info, int *store);
+
 /* Section 5's enumeration.  Writes up to `cap` pairs to rows[]/cols[] (may be NULL when
  * cap = 0) in row-major order of (w_r, w_c) and returns the total number of pairs with
  * w_r*w_c <= max_threads (or a negative status). */

@@ -295,6 +295,13 @@ LaunchPlan launch_plan(const stencil *s, const Variant *v, const RunPlan &p, int
     return (p.run ? v->plan_run : v->plan)(s, wr, wc, std::min(p.per, std::max(1, iters)));
 }
 
+// Whether the launches of a run hand each other matrices of packed bits, two of which the scratch matrix holds unless its rows
+// are shorter than two words are in bytes.
+size_t packed_matrix_bytes(const stencil *s) { return (size_t)s->rows * (size_t)life_words(s) * 4; }
+bool packs(const stencil *s, const RunPlan &p, int iters) {
+    return p.run && s->kernel == STENCIL_LIFE && p.launches(iters) > 1 && 2 * packed_matrix_bytes(s) <= s->bytes();
+}
+
 // `iters` out-of-place applications ending in `out`, never writing `in`.
 int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *pingpong, int iters, int wr, int wc,
                 hipStream_t stream) {
@@ -308,11 +315,9 @@ int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *p
     // matrix so that the last one lands in `out`
     const RunPlan plan = run_plan(s, v, iters, wr, wc);
     const int per = plan.per, launches = plan.launches(iters);
-    // (or, of Life, between two matrices of packed bits, which the scratch matrix holds both of unless its rows are
-    // shorter than two words are in bytes)
-    const size_t packed_bytes = (size_t)s->rows * (size_t)life_words(s) * 4;
-    const bool packed = plan.run && s->kernel == STENCIL_LIFE && launches > 1 && 2 * packed_bytes <= s->bytes();
-    void *const halves[2] = {pingpong, static_cast<char *>(pingpong) + (packed ? packed_bytes : 0)};
+    // (or, of Life, between two matrices of packed bits)
+    const bool packed = packs(s, plan, iters);
+    void *const halves[2] = {pingpong, static_cast<char *>(pingpong) + (packed ? packed_matrix_bytes(s) : 0)};
     const void *src = in;
     void *dst = packed ? halves[0] : (launches % 2 == 1) ? out : pingpong;
     for (int done = 0; done < iters;) {
@@ -337,6 +342,16 @@ int validate_buffers(const stencil *s, const void *in, const void *out) {
     if (a < b + m && b < a + n) return fail(STENCIL_E_INVALID, "in and out overlap");
     if (a % s->elem() || b % s->out_elem()) return fail(STENCIL_E_INVALID, "in/out are not element-aligned");
     return STENCIL_OK;
+}
+
+void describe_launch(const LaunchPlan &l, int launches, int applications, stencil_launch_info_t *info) {
+    std::snprintf(info->kernel, sizeof(info->kernel), "%s", l.kernel);
+    info->launches = launches;
+    info->applications = applications;
+    info->wg_rows = l.wg_rows;
+    info->wg_cols = l.wg_cols;
+    info->workgroups = l.blocks;
+    info->local_bytes = l.lds_bytes;
 }
 
 // f(s) (Section 3.2): dataset, kernel and device features.
@@ -693,14 +708,29 @@ int stencil_describe_run(const stencil_t *s, int iters, int wg_rows, int wg_cols
     int rc = check_legal(s, v, wg_rows, wg_cols);
     if (rc != STENCIL_OK) return rc;
     const RunPlan plan = run_plan(s, v, iters, wg_rows, wg_cols);
-    const LaunchPlan l = launch_plan(s, v, plan, iters, wg_rows, wg_cols);
-    std::snprintf(info->kernel, sizeof(info->kernel), "%s", l.kernel);
-    info->launches = plan.launches(iters);
-    info->applications = std::min(plan.per, iters);
-    info->wg_rows = l.wg_rows;
-    info->wg_cols = l.wg_cols;
-    info->workgroups = l.blocks;
-    info->local_bytes = l.lds_bytes;
+    describe_launch(launch_plan(s, v, plan, iters, wg_rows, wg_cols), plan.launches(iters), std::min(plan.per, iters), info);
+    g_err[0] = '\0';
+    return STENCIL_OK;
+}
+
+int stencil_describe_launch(const stencil_t *s, int iters, int wg_rows, int wg_cols, int launch, const void *out,
+                            stencil_launch_info_t *info, int *store) {
+    if (!s || !info || !store) return fail(STENCIL_E_INVALID, "NULL argument");
+    if (iters < 1) return fail(STENCIL_E_INVALID, "iters must be >= 1");
+    const Variant *v = find_variant(s);
+    int rc = check_legal(s, v, wg_rows, wg_cols);
+    if (rc != STENCIL_OK) return rc;
+    const RunPlan plan = run_plan(s, v, iters, wg_rows, wg_cols);
+    const int launches = plan.launches(iters);
+    if (launch < 0 || launch >= launches) return fail(STENCIL_E_INVALID, "the run takes %d launches", launches);
+    const bool last = launch == launches - 1;
+    const int now = last ? iters - launch * plan.per : plan.per;
+    const LaunchPlan l = launch_plan(s, v, plan, now, wg_rows, wg_cols);
+    describe_launch(l, launches, now, info);
+    const auto stores = plan.run ? v->stores_run : v->stores;
+    *store = !last && packs(s, plan, iters) ? STENCIL_STORE_PLAIN
+             : stores                       ? stores(s, out, l.wg_rows, l.wg_cols, now)
+                                            : (int)store_of(s);
     g_err[0] = '\0';
     return STENCIL_OK;
 }

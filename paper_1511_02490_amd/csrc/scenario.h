@@ -45,6 +45,9 @@ struct Variant {
     // what `launch` and `launch_run` start for so many applications
     LaunchPlan (*plan)(const stencil *, int wg_rows, int wg_cols, int fused) = nullptr;
     LaunchPlan (*plan_run)(const stencil *, int wg_rows, int wg_cols, int fused) = nullptr;
+    // ... and how it stores whole vectors of an output at `out` (enum stencil_store; none: as the handle says)
+    int (*stores)(const stencil *, const void *out, int wg_rows, int wg_cols, int fused) = nullptr;
+    int (*stores_run)(const stencil *, const void *out, int wg_rows, int wg_cols, int fused) = nullptr;
     // the compiled kernel a launch of this scenario would start (what hipFuncGetAttributes is asked about)
     const void *(*kernel_of)(const stencil *) = nullptr;
 };

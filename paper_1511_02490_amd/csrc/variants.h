@@ -28,6 +28,7 @@
 int register_tile_per_launch(const stencil *s, int iters, int wg_rows, int wg_cols);
 RunLaunchFn register_tile_launcher(int kernel, int border);
 LaunchPlan register_tile_plan(const stencil *s, int wg_rows, int wg_cols, int fused);
+int register_tile_stores(const stencil *s, const void *out, int wg_rows, int wg_cols, int fused);
 
 // The launcher of the fp32 sums' tile with 2 x 4 cells (variants_weighted_sum_tiles.hip): 5x5, or a run-time region.  And its kernel.
 LaunchFn weighted_sum_tile(int border, bool five_by_five);
@@ -98,6 +99,8 @@ TileGeom tile_geom(const stencil *s, const Variant &v, int wr, int wc) {
 // through where non-temporal stores are not asked for (Store::kThrough), from half of what the device's L2 caches hold on.
 constexpr size_t kThroughBytes = (size_t)16 << 20;
 sk::Store store_of(const stencil *s) { return s->nt_store ? sk::Store::kNonTemporal : sk::Store::kPlain; }
+static_assert((int)sk::Store::kPlain == STENCIL_STORE_PLAIN && (int)sk::Store::kNonTemporal == STENCIL_STORE_NON_TEMPORAL &&
+              (int)sk::Store::kThrough == STENCIL_STORE_THROUGH, "one numbering");
 // The temporal kernels and Life in registers (to bytes): up to twice that, where a matrix that was used before is still in the
 // last-level cache; life_temporal_kernel from three generations on (its rows of a byte per cell hardly ever start at a cache line,
 // and the pieces of lines that meet are written to memory one by one).  Written through / plain, geometric means over 2 to 85 drawn
@@ -128,6 +131,13 @@ bool tile_goes_through(const stencil *s) {
     const size_t bytes = s->out_bytes();
     const bool lines = (size_t)s->cols * s->out_elem() % 128 == 0;
     return !s->nt_store && bytes >= (size_t)6 << 20 && (lines || bytes <= (size_t)32 << 20);
+}
+template <class Op, int CR, int CC>
+int stores_tile(const stencil *s, const void *, int, int, int) {
+    if constexpr (may_go_through<Op, CR, CC>()) {
+        if (tile_goes_through(s)) return STENCIL_STORE_THROUGH;
+    }
+    return (int)store_of(s);
 }
 
 // A launch has at most so many work-items; more are turned down.
@@ -234,6 +244,7 @@ hipError_t allow_large_tiles(const void *kernel, size_t lds, int *raised_on) {
     return hipSuccess;
 }
 
+int stores_temporal(const stencil *s, const void *, int, int, int) { return (int)fused_store(s, true); }
 template <class Op, int B, int CR, int MAXT>
 hipError_t launch_temporal(const stencil *s, const void *in, void *out, int wr, int wc, int depth,
                            hipStream_t stream) {
@@ -257,6 +268,10 @@ bool stream_goes_through(const stencil *s, int depth) {
 }
 LaunchPlan plan_stream(const stencil *s, int wr, int wc, int depth) {
     return plan_segments(s, stream_goes_through(s, depth) ? "stream_through_kernel" : "stream_kernel", sk::stream_cols(depth), wr, wc);
+}
+
+int stores_stream(const stencil *s, const void *, int, int, int depth) {
+    return stream_goes_through(s, depth) ? STENCIL_STORE_THROUGH : (int)store_of(s);
 }
 
 template <class Op, int B>
@@ -444,6 +459,7 @@ LaunchPlan plan_life_stream(const stencil *s, int wr, int wc, int depth) {
     if (threads != wr * wc) wr = threads / 64, wc = 64;
     return {"life_stream_kernel", wr, wc, (int64_t)t.tiles_r * t.tiles_c, sk::life_stream_lds(threads)};
 }
+int stores_life_stream(const stencil *s, const void *, int, int, int) { return (int)fused_store(s, true); }
 template <int B>
 hipError_t launch_life_stream(const stencil *s, const void *in, void *out, int wr, int wc, int depth, hipStream_t stream) {
     if (depth < 1 || depth > STENCIL_MAX_STREAM_DEPTH) return hipErrorInvalidValue;
@@ -500,6 +516,7 @@ hipError_t launch_life_temporal(const stencil *s, const void *in, void *out, int
     hipLaunchKernelGGL((sk::life_temporal_kernel<B, CR, MAXT>), dim3(blocks), dim3(wc, wr), lds, stream, a, depth);
     return hipGetLastError();
 }
+int stores_life_temporal(const stencil *s, const void *, int, int, int depth) { return (int)fused_store(s, depth >= 3); }
 template <int CR>
 LaunchPlan plan_life_temporal(const stencil *s, int wr, int wc, int) {
     LaunchPlan p = plan_tiles(s, "life_temporal_kernel", STENCIL_STAGING_TEMPORAL, CR, 16, 1, wr, wc);
@@ -687,6 +704,13 @@ LaunchPlan plan_march(const stencil *s, int wr, int wc, int) {
     return p;
 }
 
+template <class Op>
+int stores_march(const stencil *s, const void *out, int, int, int) {
+    if (march_pays(s)) return (int)store_of(s);
+    const StreamTile t = stream_tile(s);
+    return stores_tile<Op, 2, 4>(s, out, t.rows, t.cols, 1);
+}
+
 // The same for any region within the kernel's largest one (march_masked_kernel.h): the kernel compiled for the
 // region's number of columns.
 template <class Op, int B, class Halo, int WC = 1>
@@ -827,6 +851,7 @@ void reg_one(std::vector<Variant> &r) {
     using Folded = typename std::conditional<by_rows<Op, Halo, CR, CC>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
     v.launch = &launch_tile<Op, B, Folded, CR, CC, kMaxT>;
     v.plan = &plan_launch_tile<Op, Folded, CR, CC>;
+    v.stores = &stores_tile<Op, CR, CC>;
     v.kernel_of = &kernel_tile<Op, B, Folded, CR, CC, kMaxT>;
     r.push_back(v);
 }
@@ -844,6 +869,7 @@ void reg_direct_one(std::vector<Variant> &r) {
     v.staged_bytes = 0;
     v.launch = &launch_direct<Op, B, Halo, CR, CC, STENCIL_MAX_WG_SIZE>;
     v.plan = &plan_direct<Op, CR, CC>;
+    v.stores = &stores_tile<Op, CR, CC>;
     v.kernel_of = &kernel_direct<Op, B, Halo, CR, CC, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);
 }
@@ -875,10 +901,12 @@ void reg_temporal_one(std::vector<Variant> &r) {
     v.fuses = true;
     v.launch = &launch_temporal<Op, B, CR, STENCIL_MAX_WG_SIZE>;
     v.plan = &plan_temporal<CR>;
+    v.stores = &stores_temporal;
     v.kernel_of = &kernel_temporal<Op, B, STENCIL_MAX_WG_SIZE>;
     v.per_launch = &register_tile_per_launch;
     v.launch_run = register_tile_launcher(KID, B);
     v.plan_run = &register_tile_plan;
+    v.stores_run = &register_tile_stores;
     r.push_back(v);
 }
 
@@ -903,10 +931,12 @@ void reg_stream_one(std::vector<Variant> &r) {
     v.fuses = true;
     v.launch = &launch_stream<Op, B>;
     v.plan = &plan_stream;
+    v.stores = &stores_stream;
     v.kernel_of = &kernel_stream<Op, B>;
     v.per_launch = &register_tile_per_launch;
     v.launch_run = register_tile_launcher(KID, B);
     v.plan_run = &register_tile_plan;
+    v.stores_run = &register_tile_stores;
     r.push_back(v);
 }
 
@@ -930,9 +960,11 @@ void reg_life_stream_one(std::vector<Variant> &r) {
     v.fuses = true;
     v.launch = &launch_life_stream<B>;
     v.plan = &plan_life_stream;
+    v.stores = &stores_life_stream;
     v.per_launch = &life_per_launch;
     v.launch_run = &launch_life_stream_run<B>;
     v.plan_run = &plan_life_stream;
+    v.stores_run = &stores_life_stream;
     v.kernel_of = &kernel_life_stream<B>;
     r.push_back(v);
 }
@@ -984,6 +1016,7 @@ void reg_march_one(std::vector<Variant> &r) {
     v.fuses = false;
     v.launch = &launch_march<Op, B, Halo>;
     v.plan = &plan_march<Op, Halo>;
+    v.stores = &stores_march<Op>;
     v.kernel_of = &kernel_march<Op, B, Halo>;
     r.push_back(v);
 }
@@ -1013,6 +1046,7 @@ void reg_march_masked_one(std::vector<Variant> &r) {
     v.fuses = false;
     v.launch = &launch_march_masked<Op, B, Halo>;
     v.plan = &plan_march<Op, Halo>;
+    v.stores = &stores_march<Op>;
     v.kernel_of = &kernel_march_masked<Op, B, Halo>;
     r.push_back(v);
 }
@@ -1037,10 +1071,12 @@ void reg_life_temporal_one(std::vector<Variant> &r) {
     v.staged_bytes = 1;
     v.fuses = true;
     v.plan = &plan_life_temporal<CR>;
+    v.stores = &stores_life_temporal;
     v.launch = &launch_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;
     v.per_launch = &life_per_launch;
     v.launch_run = &launch_life_stream_run<B>;
     v.plan_run = &plan_life_stream;
+    v.stores_run = &stores_life_stream;
     v.kernel_of = &kernel_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);
 }

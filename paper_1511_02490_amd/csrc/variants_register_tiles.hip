@@ -63,7 +63,7 @@ hipError_t launch_register_tile(const stencil *s, const void *in, bool, void *ou
     auto a = make_args<Op, sk::HaloC<1, 1, 1, 1>, 0, 4>(s, STENCIL_STAGING_STREAM, in, out, wr, wc, &blocks, &unused);
     a.tiles_c = t.tiles_c;
     // (here at every size: 1001 x 1503 1.21 -> 1.09 us a step, 512^2 0.57 -> 0.55, two steps a launch asked for)
-    if (!s->nt_store) a.store = sk::Store::kThrough;
+    a.store = (sk::Store)register_tile_stores(s, out, wr, wc, depth);
     a.n_tiles = t.tiles_r * t.tiles_c;
     const dim3 grid((unsigned)a.n_tiles), block((unsigned)t.threads);
     const unsigned lds = sk::register_tile_lds(t.threads);
@@ -135,6 +135,8 @@ LaunchPlan register_tile_plan(const stencil *s, int, int, int depth) {
     const RegisterTile t = register_tile(s, depth);
     return {"register_tile_kernel", 1, t.threads, (int64_t)t.tiles_r * t.tiles_c, sk::register_tile_lds(t.threads)};
 }
+
+int register_tile_stores(const stencil *s, const void *, int, int, int) { return s->nt_store ? STENCIL_STORE_NON_TEMPORAL : STENCIL_STORE_THROUGH; }
 
 RunLaunchFn register_tile_launcher(int kernel, int border) {
     return kernel == STENCIL_HEAT ? launcher_of<sk::OpHeat>(border) : launcher_of<sk::OpWeightedSum>(border);

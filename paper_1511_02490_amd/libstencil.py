@@ -20,6 +20,7 @@ WEIGHTED_SUM, LIFE, HEAT, SINCOS, SOBEL, NMS, THRESHOLD = 0, 1, 2, 3, 4, 5, 6
 ENUM_POW2, ENUM_EVEN = 0, 1
 STAGING_LOCAL, STAGING_DIRECT, STAGING_TEMPORAL, STAGING_STREAM = 0, 1, 2, 3
 OPT_XCD_REMAP, OPT_TEMPORAL_DEPTH, OPT_SWEEP_CUTOFF, OPT_NT_STORE, OPT_FAIL_LAUNCH, OPT_LIFE_TILE = 0, 1, 2, 3, 4, 5
+STORE_PLAIN, STORE_NON_TEMPORAL, STORE_THROUGH = 0, 1, 2
 _STAGINGS = {"local": STAGING_LOCAL, "direct": STAGING_DIRECT, "temporal": STAGING_TEMPORAL,
              "stream": STAGING_STREAM}
 N_FEATURES = 16
@@ -76,6 +77,7 @@ def _load() -> ctypes.CDLL:
         "stencil_tile_bytes": (c_i64, [vp, c_int, c_int]),
         "stencil_is_legal": (c_int, [vp, c_int, c_int]),
         "stencil_describe_run": (c_int, [vp, c_int, c_int, c_int, ctypes.POINTER(_LaunchInfo)]),
+        "stencil_describe_launch": (c_int, [vp, c_int, c_int, c_int, c_int, vp, ctypes.POINTER(_LaunchInfo), ip]),
         "stencil_enumerate_wg": (c_int, [c_int, c_int, ip, ip, c_int]),
         "stencil_run": (c_int, [vp, vp, vp, c_int, c_int, c_int, vp]),
         "stencil_run_static": (c_int, [vp, vp, vp, c_int, c_int, c_int, vp]),
@@ -119,7 +121,7 @@ except ImportError:
     _torch, _TORCH_TYPES = None, {}
 EXPORTS = ("stencil_create", "stencil_destroy", "stencil_set_kernel", "stencil_set_border_value",
            "stencil_set_mapping", "stencil_get_mapping", "stencil_stream_segment_rows", "stencil_set_sweep_rotation", "stencil_output_dtype", "stencil_set_option",
-           "stencil_max_wg_size", "stencil_tile_bytes", "stencil_is_legal", "stencil_describe_run", "stencil_enumerate_wg", "stencil_run",
+           "stencil_max_wg_size", "stencil_tile_bytes", "stencil_is_legal", "stencil_describe_run", "stencil_describe_launch", "stencil_enumerate_wg", "stencil_run",
            "stencil_run_static",
            "stencil_sweep_wg", "stencil_sweep_configs", "stencil_device_copy", "stencil_time_copy",
            "stencil_sweep_reduce", "stencil_baseline_wg", "stencil_features", "stencil_predictor_create",
@@ -324,6 +326,17 @@ class Stencil:
         """What run(..., iters, wg) starts: kernel, launches, applications (per launch), wg, workgroups, local_bytes."""
         info = _LaunchInfo()
         _check(_lib.stencil_describe_run(self._h, int(iters), int(wg[0]), int(wg[1]), ctypes.byref(info)))
+        return self._launch_fields(info)
+
+    def describe_launch(self, iters: int, wg: Tuple[int, int], launch: int = 0, out: int = 0) -> dict:
+        """The same of one launch of the run, and "store": how it writes an output at address `out` (STORE_*)."""
+        info, store = _LaunchInfo(), ctypes.c_int()
+        _check(_lib.stencil_describe_launch(self._h, int(iters), int(wg[0]), int(wg[1]), int(launch), int(out), ctypes.byref(info),
+                                            ctypes.byref(store)))
+        return dict(self._launch_fields(info), store=store.value)
+
+    @staticmethod
+    def _launch_fields(info) -> dict:
         return {"kernel": info.kernel.decode(), "launches": info.launches, "applications": info.applications,
                 "wg": (info.wg_rows, info.wg_cols), "workgroups": info.workgroups, "local_bytes": info.local_bytes}
 

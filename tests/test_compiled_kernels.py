@@ -97,6 +97,17 @@ def test_kernels_that_choose_at_run_time_keep_both_kinds_of_store(kernels):
     assert checked > 60
 
 
+def test_written_through_tiles_write_vectors_through(kernels):
+    """Every tile and direct kernel that is there once more to write its output through does so with all its 16-byte stores."""
+    code = kernels.instructions(r"^(tile|direct)_kernel<WrittenThrough<")
+    assert len(code) >= 120
+    plain = kernels.matching(r"^(tile|direct)_kernel<(?!WrittenThrough)")
+    for name, instructions in code.items():
+        vectors = [i for i in instructions if re.match("(global|flat|buffer)_store_dwordx4", i)]
+        assert vectors and all(i.startswith("global_store_dwordx4") and i.endswith(" sc1") for i in vectors), name
+        assert re.sub(r"WrittenThrough<(\w+) ?>", r"\1", name) in plain, name
+
+
 def test_life_streams_write_whole_lines_through(kernels):
     """Bytes that are written through are handed to the lane whose neighbours store the bytes beside them."""
     code = kernels.instructions(r"^life_stream_kernel<.*, false>$")

@@ -1245,6 +1245,32 @@ def test_single_applications_written_through(ls, rows, cols):
         st.close()
 
 
+WRITTEN_THROUGH = [(wl.WEIGHTED_SUM, "f32", (1, 1, 1, 1), ("local", 2, 4)), (wl.WEIGHTED_SUM, "f32", (2, 2, 2, 2), ("local", 2, 4)),
+                   (wl.WEIGHTED_SUM, "f32", (4, 4, 4, 4), ("local", 2, 4)), (wl.WEIGHTED_SUM, "f32", (1, 0, 3, 2), ("local", 2, 4)),
+                   (wl.WEIGHTED_SUM, "f32", (3, 3, 3, 3), ("direct", 2, 4)), (wl.WEIGHTED_SUM, "u8", (2, 2, 2, 2), ("local", 2, 4)),
+                   (wl.WEIGHTED_SUM, "i32", (3, 2, 4, 1), ("local", 2, 4)), (wl.WEIGHTED_SUM, "f64", (2, 2, 2, 2), ("local", 2, 2)),
+                   (wl.SINCOS, "f32", (1, 5, 3, 0), ("local", 2, 4)), (wl.SOBEL, "f32", (1, 1, 1, 1), ("direct", 2, 4)),
+                   (wl.NMS, "f32", (1, 1, 1, 1), ("local", 2, 4))]
+
+
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("kernel,dtype,halo,blocking", WRITTEN_THROUGH)
+def test_written_through_kernels_against_the_oracle(ls, kernel, dtype, halo, blocking, border):
+    """The smallest output that is written through, by the kernel that the library says does it, and one row less, which is not:
+    against the oracle, whole and ragged tiles below and right."""
+    for rows in (1229, 1228):
+        cols = 1280 if dtype != "f64" else 640
+        w = custom(kernel, rows, cols, halo, border, pad=0.0 if dtype in ("u8", "i32") else 0.25, seed=rows)
+        w.dtype = dtype
+        if dtype == "i32":
+            w.weights = np.rint(w.weights * 1000).astype(np.float32)
+        st = ls.Stencil.from_workload(w)
+        st.set_mapping(*blocking)
+        assert st.describe_launch(1, (8, 32))["store"] == (ls.STORE_THROUGH if rows == 1229 else ls.STORE_PLAIN)
+        st.close()
+        check(ls, w, (8, 32), blocking=blocking)
+
+
 def test_iterated_run_inside_a_hip_graph(ls):
     """An iterated stencil_run is only kernel launches once its scratch matrix exists, so it can
     be captured into a HIP graph; every replay must reproduce the eager result."""

@@ -701,6 +701,58 @@ def test_describe_run_names_the_kernel_that_runs():
         describe(100, 128, "heat", one, "wrap", ("stream", 20, 4), 4, (5, 13), depth=4)
 
 
+def describe_launches(rows, cols, kernel, halo, border, mapping, iters, wg, depth=0, dtype="f32", nt=0, out=0):
+    """describe_launch of every launch of the run."""
+    st = ls.Stencil(rows, cols, dtype, halo, border)
+    n, s, e, w = halo
+    if kernel in ("weighted_sum", "sincos"):
+        st.set_kernel(kernel, np.ones((n + s + 1, e + w + 1), np.float32))
+    else:
+        st.set_kernel(kernel, scalars=(0.2,) if kernel in ("heat", "threshold") else ())
+    st.set_mapping(*mapping)
+    if depth:
+        st.set_option(ls.OPT_TEMPORAL_DEPTH, depth)
+    st.set_option(ls.OPT_NT_STORE, nt)
+    launches = [st.describe_launch(iters, wg, k, out) for k in range(st.describe_run(iters, wg)["launches"])]
+    for k in (-1, len(launches)):
+        with pytest.raises(ls.StencilError):
+            st.describe_launch(iters, wg, k, out)
+    run = dict(st.describe_run(iters, wg), store=launches[0]["store"])
+    st.close()
+    assert launches[0] == run and sum(l["applications"] for l in launches) == iters
+    return launches
+
+
+def test_describe_launch_says_how_the_output_is_stored():
+    one, five, plain, through = (1, 1, 1, 1), (2, 2, 2, 2), ls.STORE_PLAIN, ls.STORE_THROUGH
+    stores = lambda *a, **k: [l["store"] for l in describe_launches(*a, **k)]
+    # single applications: from 6 MiB on, ragged rows up to 32 MiB, two rows of one vector per work-item
+    for kernel, halo, dtype, mapping in [("weighted_sum", five, "f32", ("local", 2, 4)), ("weighted_sum", (1, 0, 3, 2), "f32", ("local", 2, 4)),
+                                         ("weighted_sum", five, "f32", ("direct", 2, 4)), ("weighted_sum", five, "u8", ("local", 2, 4)),
+                                         ("weighted_sum", five, "i32", ("local", 2, 4)), ("sincos", (1, 5, 3, 0), "f32", ("local", 2, 4)),
+                                         ("sobel", one, "f32", ("direct", 2, 4)), ("nms", one, "f32", ("local", 2, 4))]:
+        for rows, cols, nt, how in [(1229, 1280, 0, through), (1228, 1280, 0, plain), (2046, 4099, 0, through), (2047, 4099, 0, plain),
+                                    (4096, 4096, 0, through), (4096, 4096, 1, ls.STORE_NON_TEMPORAL)]:
+            assert stores(rows, cols, kernel, halo, "wrap", mapping, 1, (8, 32), dtype=dtype, nt=nt) == [how], (kernel, mapping, rows, cols)
+    assert stores(2048, 1024, "weighted_sum", five, "clamp", ("local", 2, 2), 3, (8, 32), dtype="f64") == [through] * 3
+    assert stores(8192, 8192, "weighted_sum", (3, 3, 3, 3), "clamp", ("stream", 64, 4), 1, (1, 64)) == [through]     # a tile
+    assert stores(8192, 8192, "sincos", (1, 5, 3, 0), "clamp", ("stream", 64, 4), 1, (1, 64)) == [plain]             # a march
+    for kernel, mapping, dtype in [("weighted_sum", ("local", 4, 4), "f32"), ("weighted_sum", ("local", 1, 4), "f32"), ("heat", ("local", 2, 4), "f32"),
+                                   ("heat", ("direct", 2, 4), "f32"), ("life", ("local", 2, 16), "u8"), ("life", ("direct", 2, 16), "u8")]:
+        assert stores(4096, 4096, kernel, one, "wrap", mapping, 1, (8, 32), dtype=dtype) == [plain]
+    # several applications per launch
+    assert stores(1025, 1999, "heat", one, "clamp", ("temporal", 2, 4), 9, (32, 32), depth=4) == [through]     # a tile in registers
+    assert stores(2048, 2048, "heat", one, "clamp", ("temporal", 2, 4), 4, (32, 32), depth=4) == [through]
+    assert stores(2047, 2048, "heat", one, "clamp", ("temporal", 2, 4), 4, (32, 32), depth=4) == [plain]
+    assert stores(2048, 2052, "heat", one, "wrap", ("stream", 20, 4), 4, (1, 64), depth=4) == [through]
+    assert stores(2048, 2052, "heat", one, "wrap", ("stream", 20, 4), 3, (1, 64), depth=3) == [plain]
+    # Life between launches in bits: those are plain
+    assert stores(4096, 4096, "life", one, "clamp", ("temporal", 2, 16), 100, (4, 64), depth=4, dtype="u8") == [plain] * 3 + [through]
+    assert stores(4096, 8192, "life", one, "clamp", ("temporal", 2, 16), 3, (4, 64), depth=4, dtype="u8") == [plain]
+    assert stores(4096, 8184, "life", one, "clamp", ("temporal", 2, 16), 3, (4, 64), depth=4, dtype="u8") == [through]
+    assert stores(4096, 8184, "life", one, "clamp", ("temporal", 2, 16), 2, (4, 64), depth=4, dtype="u8") == [plain]
+
+
 @pytest.mark.parametrize("border,rows,cols,items", [("wrap", 4096, 4096, 512), ("clamp", 4096, 4096, 1024), ("constant", 3000, 5000, 1024),
                                                      ("clamp", 1001, 1503, 512), ("wrap", 16, 600, 512)])
 def test_life_runs_take_workgroups_of_their_own(border, rows, cols, items):
