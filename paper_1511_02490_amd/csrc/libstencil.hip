@@ -280,19 +280,22 @@ int launch_failure(hipError_t e, int wr, int wc) {
     }
 }
 
-// Applications per launch of a run, and whether it is made by the variant's kernel for runs of several launches.
+// Applications per launch of a run, whether it is made by the variant's kernel for runs of several launches, and what the
+// launchers are given for a workgroup.
 struct RunPlan {
     int per;
     bool run;
+    int wg_rows, wg_cols;
     int launches(int iters) const { return (iters + per - 1) / per; }
 };
 RunPlan run_plan(const stencil *s, const Variant *v, int iters, int wr, int wc) {
     const int per = v->fuses ? s->temporal_depth : 1;
     const int run_per = v->per_launch && iters > per ? v->per_launch(s, iters, wr, wc) : 0;
-    return {run_per > 0 ? run_per : per, run_per > 0};
+    if (run_per > 0 && v->run_wg) v->run_wg(s, run_per, &wr, &wc);
+    return {run_per > 0 ? run_per : per, run_per > 0, wr, wc};
 }
-LaunchPlan launch_plan(const stencil *s, const Variant *v, const RunPlan &p, int iters, int wr, int wc) {
-    return (p.run ? v->plan_run : v->plan)(s, wr, wc, std::min(p.per, std::max(1, iters)));
+LaunchPlan launch_plan(const stencil *s, const Variant *v, const RunPlan &p, int iters) {
+    return (p.run ? v->plan_run : v->plan)(s, p.wg_rows, p.wg_cols, std::min(p.per, std::max(1, iters)));
 }
 
 // Whether the launches of a run hand each other matrices of packed bits, two of which the scratch matrix holds unless its rows
@@ -326,7 +329,7 @@ int run_checked(stencil *s, const Variant *v, const void *in, void *out, void *p
         if (packed && last) dst = out;
         const bool injected = s->fail_rows == -1 || (s->fail_rows == wr && s->fail_cols == wc);
         hipError_t e = injected ? hipErrorLaunchOutOfResources
-                       : plan.run ? v->launch_run(s, src, packed && src != in, dst, packed && !last, wr, wc, now, stream)
+                       : plan.run ? v->launch_run(s, src, packed && src != in, dst, packed && !last, plan.wg_rows, plan.wg_cols, now, stream)
                                   : v->launch(s, src, dst, wr, wc, now, stream);
         if (e != hipSuccess) return launch_failure(e, wr, wc);
         done += now;
@@ -708,7 +711,7 @@ int stencil_describe_run(const stencil_t *s, int iters, int wg_rows, int wg_cols
     int rc = check_legal(s, v, wg_rows, wg_cols);
     if (rc != STENCIL_OK) return rc;
     const RunPlan plan = run_plan(s, v, iters, wg_rows, wg_cols);
-    describe_launch(launch_plan(s, v, plan, iters, wg_rows, wg_cols), plan.launches(iters), std::min(plan.per, iters), info);
+    describe_launch(launch_plan(s, v, plan, iters), plan.launches(iters), std::min(plan.per, iters), info);
     g_err[0] = '\0';
     return STENCIL_OK;
 }
@@ -725,7 +728,7 @@ int stencil_describe_launch(const stencil_t *s, int iters, int wg_rows, int wg_c
     if (launch < 0 || launch >= launches) return fail(STENCIL_E_INVALID, "the run takes %d launches", launches);
     const bool last = launch == launches - 1;
     const int now = last ? iters - launch * plan.per : plan.per;
-    const LaunchPlan l = launch_plan(s, v, plan, now, wg_rows, wg_cols);
+    const LaunchPlan l = launch_plan(s, v, plan, now);
     describe_launch(l, launches, now, info);
     const auto stores = plan.run ? v->stores_run : v->stores;
     *store = !last && packs(s, plan, iters) ? STENCIL_STORE_PLAIN
@@ -903,7 +906,7 @@ int stencil_sweep_wg(stencil_t *s, const void *in, void *out, int iters, const i
         };
         if (check_legal(s, v, wr, wc) != STENCIL_OK) return refused();
         const RunPlan plan = run_plan(s, v, chain, wr, wc);
-        const LaunchPlan launch = launch_plan(s, v, plan, chain, wr, wc);
+        const LaunchPlan launch = launch_plan(s, v, plan, chain);
         for (int j = 0; j < n && s->fail_rows == 0; ++j) {
             const LaunchPlan &l = timed[j].launch;
             if (j == k || stat[j] != STENCIL_OK || timed[j].per != plan.per || timed[j].probed != probe_only ||

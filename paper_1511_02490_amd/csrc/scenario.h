@@ -39,8 +39,9 @@ struct Variant {
     bool fuses = false;   // a launch makes `temporal_depth` applications instead of one
     LaunchFn launch;
     // where runs of several launches have a kernel of their own: the applications it makes per launch of a run of so many
-    // (0: the run is made by `launch`), and its launcher
+    // (0: the run is made by `launch`), the workgroup of all its launches where that is not the caller's, and its launcher
     int (*per_launch)(const stencil *, int iters, int wg_rows, int wg_cols) = nullptr;
+    void (*run_wg)(const stencil *, int per, int *wg_rows, int *wg_cols) = nullptr;
     RunLaunchFn launch_run = nullptr;
     // what `launch` and `launch_run` start for so many applications
     LaunchPlan (*plan)(const stencil *, int wg_rows, int wg_cols, int fused) = nullptr;

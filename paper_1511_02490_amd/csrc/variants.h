@@ -384,7 +384,7 @@ LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
     return best;
 }
 
-// The work-items of a launch that makes more generations than the handle asks for, whose tile is the library's: 512, or 1024 of four
+// The work-items of a run whose launches make `depth` generations, more than the handle asks for, and whose tile is the library's: 512, or 1024 of four
 // rows where those would have eight and more and the border's cells are looked after; the workgroup's own where the tile is
 // prescribed or the matrix has none for these.  (us a run, 256 / 512 / 1024 work-items: 100 generations, WRAP, 4096^2 77.3 / 65.5 /
 // 67.0, 2048^2 51.0 / 42.2 / 48.9; CLAMP, 4096^2 86.7 / 81.5 / 69.7, 8192 x 2048 88.4 / 81.3 / 69.7, 50 of 1001 x 1503 23.7 / 22.7 /
@@ -435,7 +435,7 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     a.rows = (int)s->rows;
     a.cols = (int)s->cols;
     a.words = (int)life_words(s);
-    const int threads = life_run_threads(s, wr * wc, depth);
+    const int threads = wr * wc;
     const LifeTile t = life_tile(s, threads, depth, !IN_BITS);
     if (t.tiles_r == 0) return hipErrorInvalidValue;
     a.group_shift = t.group_shift;
@@ -454,10 +454,13 @@ hipError_t launch_life_stream_formats(const stencil *s, const void *in, void *ou
     return hipGetLastError();
 }
 LaunchPlan plan_life_stream(const stencil *s, int wr, int wc, int depth) {
-    const int threads = life_run_threads(s, wr * wc, depth);
-    const LifeTile t = life_tile(s, threads, depth, true);
-    if (threads != wr * wc) wr = threads / 64, wc = 64;
-    return {"life_stream_kernel", wr, wc, (int64_t)t.tiles_r * t.tiles_c, sk::life_stream_lds(threads)};
+    const LifeTile t = life_tile(s, wr * wc, depth, true);
+    return {"life_stream_kernel", wr, wc, (int64_t)t.tiles_r * t.tiles_c, sk::life_stream_lds(wr * wc)};
+}
+// (One for all launches of a run, also a last one that makes fewer generations: runs that begin alike are alike.)
+void life_run_wg(const stencil *s, int per, int *wr, int *wc) {
+    const int threads = life_run_threads(s, *wr * *wc, per);
+    if (threads != *wr * *wc) *wr = threads / 64, *wc = 64;
 }
 int stores_life_stream(const stencil *s, const void *, int, int, int) { return (int)fused_store(s, true); }
 template <int B>
@@ -963,6 +966,7 @@ void reg_life_stream_one(std::vector<Variant> &r) {
     v.stores = &stores_life_stream;
     v.per_launch = &life_per_launch;
     v.launch_run = &launch_life_stream_run<B>;
+    v.run_wg = &life_run_wg;
     v.plan_run = &plan_life_stream;
     v.stores_run = &stores_life_stream;
     v.kernel_of = &kernel_life_stream<B>;
@@ -1075,6 +1079,7 @@ void reg_life_temporal_one(std::vector<Variant> &r) {
     v.launch = &launch_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;
     v.per_launch = &life_per_launch;
     v.launch_run = &launch_life_stream_run<B>;
+    v.run_wg = &life_run_wg;
     v.plan_run = &plan_life_stream;
     v.stores_run = &stores_life_stream;
     v.kernel_of = &kernel_life_temporal<B, CR, STENCIL_MAX_WG_SIZE>;

@@ -766,6 +766,19 @@ def test_life_runs_take_workgroups_of_their_own(border, rows, cols, items):
         assert own["wg"] == (4, 64) and own["local_bytes"] == 16 * 256
 
 
+@pytest.mark.parametrize("rows,cols,border,iters,depth", [(9429, 8468, "wrap", 82, 3), (1001, 1503, "clamp", 35, 4), (3000, 5000, "constant", 81, 3),
+                                                           (300, 200, "wrap", 64, 4), (4096, 4096, "clamp", 101, 2)])
+def test_runs_that_begin_alike_are_alike(rows, cols, border, iters, depth):
+    """Sizes that a sweep takes for one run, by its first launch, have every launch in common, also a last one of a few
+    generations."""
+    runs = {}
+    for wg in [(1, 64), (2, 64), (4, 64), (8, 64), (16, 64), (64, 8)]:
+        launches = describe_launches(rows, cols, "life", (1, 1, 1, 1), border, ("temporal", 2, 16), iters, wg, depth=depth, dtype="u8")
+        assert {l["wg"] for l in launches} == {launches[0]["wg"]}
+        assert runs.setdefault(str(launches[0]), launches) == launches
+    assert len(runs) < 6
+
+
 @pytest.mark.parametrize("rows,cols", [(2 ** 31 - 1, 1), (2 ** 31 - 70, 1), (2 ** 29 - 1, 4), (2 ** 28 - 1, 8), (1, 2 ** 31 - 1), (8, 2 ** 28 - 1)])
 @pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
 def test_thin_matrices_stay_within_a_launch(rows, cols, border):
