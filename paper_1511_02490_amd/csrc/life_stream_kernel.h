@@ -16,7 +16,7 @@
 // into bits, the last one bits into bytes, and the launches between them move an eighth of the bytes.  They are
 // bound by the generations' serial chain (a row's sums, the barrier, the rule), not by memory, and by what a launch,
 // its loads and its stores cost whatever it computes: the tile is cut, and the generations of a run are dealt to
-// launches, so that both are small together (life_tile, life_run_threads and life_per_launch in variants.h).
+// launches, so that both are small together (life_tile, life_run_tile and life_per_launch in variants.h).
 // (100 generations of 4096 x 4096, WRAP: 282 us by marching packed bytes down the matrix, 121 on bits with 8 to a
 // launch, 65 with 25 in workgroups of 512.  50 generations of 1001 x 1503, CLAMP: 83 us by life_temporal_kernel, 4 to a launch from
 // bytes to bytes, 23 here with 17.)

@@ -328,32 +328,46 @@ hipError_t launch_stream(const stencil *s, const void *in, void *out, int wr, in
     return hipGetLastError();
 }
 
-// The tile of a Life launch (life_stream_kernel.h): rows per work-item and lanes per row.  A generation takes as long
-// as the wavefronts of a SIMD take for their rows and for what a generation costs whatever their number (some rows' worth);
-// narrow tiles also load and store shorter pieces of rows.  Two rules:
+// What Life runs take, us.  A launch kLifeLaunchUs and kLifeLaunchCellUs a million cells.  A generation kLifeOwnRowUs for every row of
+// a work-item, the chain from the rows it is handed to those it hands on, and kLifeWaveUs for every wavefront of a SIMD of the fullest
+// compute unit (by border and rows of a work-item, 2 to 16); with up to 256 work-items 10 % more than with 512, with 1024 under WRAP
+// 11 %, in groups of 16 lanes 1.5 %.  (From 3395 runs of three and four launches on 30^2 to 80 million cells, 5 to 31 generations per
+// launch, every tile and workgroup, and some 40 ways each to make 300 runs on up to 300 million cells: the way taken by these is 1.4 %
+// slower than the fastest on average, 5 % for one run of ten.  By a SIMD's rows alone, in workgroups of 512: 240 runs 3.0 % and 11 %; 68
+// generations of 4407 x 5557 in six launches 89 us, in three 64; 98 padded ones of 4265 x 5936 in ten 127, in five 99.)
+constexpr double kLifeLaunchUs = 3.1, kLifeLaunchCellUs = 0.065, kLifeOwnRowUs = 0.027;
+constexpr double kLifeWaveUs[3][4] = {{0.08, 0.088, 0.22, 0.31}, {0.063, 0.078, 0.117, 0.3}, {0.063, 0.097, 0.175, 0.24}};   // STENCIL_CLAMP, ...
+constexpr double kLifeLeastUs = 2 * kLifeOwnRowUs + 0.063;        // of the least generation
+double life_generation_us(const stencil *s, int64_t tiles, int threads, int rows_per_item, int group_shift) {
+    const int units = stencil_compute_units(), kind = rows_per_item == 2 ? 0 : rows_per_item == 4 ? 1 : rows_per_item == 8 ? 2 : 3;
+    const double waves = (double)(((tiles + units - 1) / units * (threads / 64) + 3) / 4);       // of a SIMD
+    return (kLifeOwnRowUs * rows_per_item + waves * kLifeWaveUs[s->border][kind]) * (group_shift == 4 ? 1.015 : 1.0) *
+           (threads <= 256 ? 1.1 : threads > 512 && s->border == STENCIL_WRAP ? 1.11 : 1.0);
+}
+
+// The tile of a Life launch (life_stream_kernel.h): rows per work-item and lanes per row.  Two rules:
 // - A launch of as many generations as the handle asks for, or fewer, is as much loading and storing as computing, and its
-//   tiles come and go: wavefronts are counted over the whole device, one at least, and narrow tiles cost up to a quarter.
+//   tiles come and go: wavefronts are counted over the whole device, one at least, and narrow tiles, which load and store
+//   shorter pieces of rows, cost up to a quarter.
 //   (us per launch of 8 generations with 256 work-items, rows per item x lanes: 4096 x 4096 4x16 9.8, 8x16 10.3, 8x32 9.8,
 //   8x64 11.2, 16x16 11.0, 16x32 10.4, 16x64 11.1; 256 x 256 4x16 4.6, 4x32 4.8, 8x32 6.2, 16x32 8.2.)  A launch that reads
 //   bytes has 32 registers per row under way: 16 rows leave room for two wavefronts per SIMD, too few to keep the memory busy
 //   (8192 x 8192, one generation: 4x32 25.5, 8x32 23.5, 16x32 27.6).  And a single generation on a matrix that is up to three
 //   wavefronts of four-row items per SIMD (the rim aside) is over before eight rows' loads are in (4096 x 4096: 8.0, 9.3, 10.7).
-// - A launch of more is a long stay of few tiles: its generations take what the SIMDs of the fullest compute unit take.
-//   (us per generation / rows by this rule, rows per item x lanes, workgroup, generations per launch: 4096 x 4096, WRAP, 8x16,
-//   256, 20 0.55 / 20; 8x16, 512, 25 0.54 / 20; 4x16, 1024, 25 0.55 / 20; 16x16, 256, 25 0.66 / 20; 1001 x 1503, CLAMP, 2x16,
-//   512, 17 0.21 / 8.  By the first rule runs of 400 generations on 2048 x 2048 take 211 us, 170 by this.)
+// - A launch of more is a long stay of few tiles: the tile whose generations take least (life_generation_us).
 struct LifeTile {
+    int threads = 0;
     int rows_per_item = 0, group_shift = 0;
     int tiles_r = 0, tiles_c = 0;
-    double rows_worth = 0.0;         // of a generation, in rows of a SIMD
+    double us = 0.0;                 // of a generation
 };
-constexpr double kLifeRowUs = 0.028, kLifeLaunchUs = 4.5;
 LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
     const bool as_asked = depth <= s->temporal_depth;
-    const int units = stencil_compute_units(), rows = (int)s->rows, words = (int)life_words(s), wave_count = threads / 64;
-    const double simds = 4.0 * units;
+    const int rows = (int)s->rows, words = (int)life_words(s), wave_count = threads / 64;
+    const double simds = 4.0 * stencil_compute_units();
     const bool few_rows = from_bytes && depth == 1 && (double)rows * words / (4 * 64) <= 3.0 * simds;
     LifeTile best;
+    double best_cost = 0.0;
     for (int shift = 4; shift <= 6; ++shift) {
         const int strips = words / ((1 << shift) - 2) + (words % ((1 << shift) - 2) != 0);
         for (int rpt = as_asked ? 4 : 2; rpt <= 16; rpt *= 2) {
@@ -363,41 +377,34 @@ LifeTile life_tile(const stencil *s, int threads, int depth, bool from_bytes) {
             const int steps = (rows - 1) / step + 1;
             const int tiles = s->border == STENCIL_WRAP ? steps : rows <= held ? 1 : (rows - held - 1) / step + 2;
             if ((int64_t)strips * tiles * threads > kMaxGridItems) continue;
-            double cost;
-            if (as_asked) {
-                cost = std::max(1.0, (double)strips * steps * wave_count / simds) * (rpt + 2) *
-                       (shift == 4 ? 1.25 : shift == 5 ? 1.05 : 1.0) * (from_bytes && rpt == 16 ? 1.3 : 1.0);
-            } else {
-                const int64_t fullest = ((int64_t)strips * tiles + units - 1) / units * wave_count;      // wavefronts
-                cost = ((double)((fullest + 3) / 4) * rpt + 4) * (shift == 4 ? 1.05 : shift == 5 ? 1.02 : 1.0) *
-                       (rpt == 16 ? 1.12 : 1.0);
-            }
-            if (best.tiles_r == 0 || cost < best.rows_worth) {
-                best.rows_per_item = rpt;
-                best.group_shift = shift;
-                best.tiles_r = tiles;
-                best.tiles_c = strips;
-                best.rows_worth = cost;
+            const double us = life_generation_us(s, (int64_t)strips * tiles, threads, rpt, shift);
+            const double cost = !as_asked ? us
+                                          : std::max(1.0, (double)strips * steps * wave_count / simds) * (rpt + 2) *
+                                                (shift == 4 ? 1.25 : shift == 5 ? 1.05 : 1.0) * (from_bytes && rpt == 16 ? 1.3 : 1.0);
+            if (best.tiles_r == 0 || cost < best_cost) {
+                best_cost = cost;
+                best = {threads, rpt, shift, tiles, strips, us};
             }
         }
     }
     return best;
 }
 
-// The work-items of a run whose launches make `depth` generations, more than the handle asks for, and whose tile is the library's: 512, or 1024 of four
-// rows where those would have eight and more and the border's cells are looked after; the workgroup's own where the tile is
-// prescribed or the matrix has none for these.  (us a run, 256 / 512 / 1024 work-items: 100 generations, WRAP, 4096^2 77.3 / 65.5 /
-// 67.0, 2048^2 51.0 / 42.2 / 48.9; CLAMP, 4096^2 86.7 / 81.5 / 69.7, 8192 x 2048 88.4 / 81.3 / 69.7, 50 of 1001 x 1503 23.7 / 22.7 /
-// 28.1; 60 padded ones of 3000 x 5000 54.9 / 45.6 / 43.8; 200 of 512^2 68.4 / 67.8 / 86.9.  More wavefronts share a tile's rim and
-// its barrier; 128, 384 and 768 are slower than the better of 512 and 1024 by 2 % and more in all but three of ten.)
-int life_run_threads(const stencil *s, int threads, int depth) {
-    if (s->life_rows != 0 || depth <= s->temporal_depth) return threads;
-    const LifeTile t = life_tile(s, 512, depth, false);
-    if (t.tiles_r == 0) return threads;
-    return s->border != STENCIL_WRAP && t.rows_per_item >= 8 && life_tile(s, 1024, depth, false).tiles_r > 0 ? 1024 : 512;
+// The tile and the workgroup of a run whose launches make `depth` generations.  If that is more than the handle asks for, and the
+// tile is the library's: 256, 512 or 1024 work-items, whichever's tile takes least; the workgroup's own else, or if the matrix has no
+// tile for these.  (us a run, 256 / 512 / 1024 work-items, each by its own tile: 100 generations, WRAP, 4096^2 77.3 / 65.5 / 67.0,
+// 2048^2 51.0 / 42.2 / 48.9; CLAMP, 4096^2 86.7 / 81.5 / 69.7, 8192 x 2048 88.4 / 81.3 / 69.7; 200 of 512^2 68.4 / 67.8 / 86.9; where
+// tiles of 256 with two rows per item do, 15 padded ones of 64 x 1033 6.0 / 7.2 / 9.6, 10 of 657 x 421 5.6 / 6.5 / 8.9.)
+LifeTile life_run_tile(const stencil *s, int threads, int depth) {
+    LifeTile best;
+    for (int own = 256; own <= 1024 && s->life_rows == 0 && depth > s->temporal_depth; own *= 2) {
+        const LifeTile t = life_tile(s, own, depth, false);
+        if (t.tiles_r > 0 && (best.tiles_r == 0 || t.us < best.us)) best = t;
+    }
+    return best.tiles_r > 0 ? best : life_tile(s, threads, depth, false);
 }
 
-// Generations per launch of a run that takes several launches: a launch costs as much as some ten generations do
+// Generations per launch of a run that takes several launches: a launch costs as much as several generations do
 // (kLifeLaunchUs), but every generation fused repeats two more rows of every tile.  At least the number asked for, as far as
 // it divides the run into the same launches, and exactly that where the tile is prescribed or nothing is to be fused.  0, the run
 // stays with its mapping's kernel: the workgroup is no whole wavefronts, or too small for a tile; or the matrix is so thin that
@@ -407,22 +414,25 @@ int life_per_launch(const stencil *s, int iters, int wr, int wc) {
     if (threads % 64 != 0 || s->cols > INT32_MAX - 64 * 32) return 0;
     if (s->life_rows != 0 || s->temporal_depth == 1)
         return s->staging == STENCIL_STAGING_STREAM || life_tile(s, threads, s->temporal_depth, false).tiles_r > 0 ? s->temporal_depth : 0;
-    int best = s->temporal_depth, launches_before = 0;
+    const int most = (iters + s->temporal_depth - 1) / s->temporal_depth;
+    if (life_run_tile(s, threads, (iters + most - 1) / most).tiles_r == 0) return 0;      // (nor has any with more generations one)
+    // from the fewest launches on, so that few more are worth a look
+    const double launch_us = kLifeLaunchUs + kLifeLaunchCellUs * 1e-6 * (double)s->rows * (double)s->cols;
+    int best = 0;
     double best_us = 0.0;
-    for (int d = s->temporal_depth; d <= sk::kLifeStreamMaxDepth; ++d) {
-        const int launches = (iters + d - 1) / d;
-        if (launches == launches_before) continue;
-        launches_before = launches;
+    for (int launches = std::min(most, (iters + sk::kLifeStreamMaxDepth - 1) / sk::kLifeStreamMaxDepth); launches <= most; ++launches) {
         const int per = (iters + launches - 1) / launches;
-        const LifeTile t = life_tile(s, life_run_threads(s, threads, per), per, false);
-        if (t.tiles_r == 0) break;           // (nor has any with more generations one)
-        const double us = launches * (kLifeLaunchUs + per * t.rows_worth * kLifeRowUs);
-        if (best_us == 0.0 || us < best_us) {
+        if (best > 0 && launches * (launch_us + per * kLifeLeastUs) > best_us) break;
+        if ((iters + per - 1) / per != launches) continue;
+        const LifeTile t = life_run_tile(s, threads, per);
+        if (t.tiles_r == 0) continue;
+        const double us = launches * (launch_us + per * t.us);
+        if (best == 0 || us <= best_us) {
             best_us = us;
             best = per;
         }
     }
-    return best_us == 0.0 ? 0 : best;
+    return best;
 }
 
 // Game of Life, `depth` generations per launch in registers, from and to a matrix of bytes or of bits.
@@ -459,8 +469,8 @@ LaunchPlan plan_life_stream(const stencil *s, int wr, int wc, int depth) {
 }
 // (One for all launches of a run, also a last one that makes fewer generations: runs that begin alike are alike.)
 void life_run_wg(const stencil *s, int per, int *wr, int *wc) {
-    const int threads = life_run_threads(s, *wr * *wc, per);
-    if (threads != *wr * *wc) *wr = threads / 64, *wc = 64;
+    const LifeTile t = life_run_tile(s, *wr * *wc, per);
+    if (t.tiles_r > 0 && t.threads != *wr * *wc) *wr = t.threads / 64, *wc = 64;
 }
 int stores_life_stream(const stencil *s, const void *, int, int, int) { return (int)fused_store(s, true); }
 template <int B>

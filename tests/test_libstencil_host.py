@@ -766,6 +766,17 @@ def test_life_runs_take_workgroups_of_their_own(border, rows, cols, items):
         assert own["wg"] == (4, 64) and own["local_bytes"] == 16 * 256
 
 
+@pytest.mark.parametrize("rows,cols,border,iters,depth,launches,items", [
+    (4407, 5557, "wrap", 68, 4, 3, 512), (4265, 5936, "constant", 98, 4, 5, 512), (7340, 3316, "constant", 80, 4, 4, 512),
+    (20000, 3000, "constant", 10, 3, 1, 512), (64, 1033, "constant", 15, 3, 1, 256), (657, 421, "wrap", 10, 4, 1, 256),
+    (16384, 16384, "wrap", 20, 3, 1, 512)])
+def test_life_runs_take_the_fastest_of_ways_that_were_measured(rows, cols, border, iters, depth, launches, items):
+    """Runs that a rule made for workgroups of 256 dealt to twice the launches, or gave tiles of work-items that were slower."""
+    for wg in [(1, 64), (4, 64), (16, 64)]:
+        run = describe(rows, cols, "life", (1, 1, 1, 1), border, ("temporal", 2, 16), iters, wg, depth=depth, dtype="u8")
+        assert (run["launches"], run["wg"][0] * run["wg"][1]) == (launches, items)
+
+
 @pytest.mark.parametrize("rows,cols,border,iters,depth", [(9429, 8468, "wrap", 82, 3), (1001, 1503, "clamp", 35, 4), (3000, 5000, "constant", 81, 3),
                                                            (300, 200, "wrap", 64, 4), (4096, 4096, "clamp", 101, 2)])
 def test_runs_that_begin_alike_are_alike(rows, cols, border, iters, depth):
