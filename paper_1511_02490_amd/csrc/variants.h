@@ -115,29 +115,41 @@ sk::Store fused_store(const stencil *s, bool may) {
 
 // Tiles and direct kernels of a single application, two rows of one vector per work-item, where non-temporal stores are not
 // asked for, write their output through: what plain stores leave in the L2 caches is written back when the launch ends, with
-// nothing beside it.  From 6 MiB of output on, and where its rows are not whole cache lines of 128 bytes up to 32 MiB.  Written
-// through / plain, 3x3, 5x5 and run-time regions of floats on matrices in turn: 1024^2 0.97 to 1.02, 1400 x 1404 0.90 to 0.94,
-// 1400 x 1401 0.95 to 1.00, 2048^2 0.83 to 0.89 (5x5 10.7 -> 9.2 us), 2000 x 2001 0.86 to 0.93, 2900 x 2912 0.92 to 0.96, 2900 x 2908
-// 0.94 to 0.99, 2900 x 2901 0.99 to 1.05, 4096^2 0.97 to 1.01, 4000 x 4012 1.06 to 1.10, 4000 x 4001 1.09 to 1.12, 8192^2 0.97 to
-// 0.99.  5x5 doubles on 1000^2 5.9 -> 5.4 us, on 2048^2 13.6 -> 12.8; integers there 12.8 -> 10.9; sin/cos there 12.9 -> 11.5; the
+// nothing beside it.  From 6 MiB of output on.  But a row of a workgroup, 16 bytes for each of its work-items, that begins or ends
+// within a cache line of 128 bytes or within one of its halves leaves pieces, and those are written to memory one by one:
+// - Whole lines (by the workgroup's columns, the matrix's and the output's address) at every size.
+// - Whole halves up to 32 MiB, where the workgroup has one half a row up to 16.
+// - Else, workgroups of 14 columns and more up to 32 MiB, of nine and more up to 16, narrower ones not.
+// Written through / plain, 3x3, 5x5 and 28 run-time taps of floats, 8 x 32 work-items where not said, matrices in turn.  Whole lines:
+// 1024^2 0.97 to 1.02, 2048^2 0.83 to 0.89 (5x5 10.7 -> 9.1 us), 4096^2 0.97 to 1.01, 8192^2 0.97 to 0.99; of 32 x 8 0.85 to 0.92 up to
+// 16 MiB, 0.96 to 1.00 beyond.  Halves: rows of 2032 0.86 to 0.94, 2864 0.91 to 0.98; 64 x 4 0.92 to 0.97 up to 16 MiB (a direct kernel
+// 1.07), on 32 and 64 MiB 1.00 to 1.07; 21 x 12 0.87 to 1.01, on 64 MiB 1.00 to 1.02.  Else: 1400 x 1401 0.95 to 1.00, 2000 x 2001 0.86 to
+// 0.93, 2900 x 2908 0.94 to 0.99, 4000 x 4001 1.09 to 1.12; on 4096^2 4 bytes further on 1.06, of 25, 27, 29 and 33 columns 1.06 to 1.12;
+// 14 to 33 columns on 2048 x 4096 0.92 to 1.04; 9 to 13 on 2048^2 0.87 to 1.06, on 2048 x 4096 0.99 to 1.11; 5 and 7 0.97 to 1.12 and 1.10
+// to 1.22; 1 to 3 on 2048^2 0.92 to 1.42, on 8192^2 1.34 to 1.59; 4 in ragged rows 1.10 to 1.31.
+// 5x5 doubles on 1000^2 5.9 -> 5.4 us, on 2048^2 13.6 -> 12.8; integers there 12.8 -> 10.9; sin/cos there 12.9 -> 11.5; the
 // edge detector's stages on 4096^2, three of which this serves, 88.7 -> 85.2; ten applications in turn on 2048^2 90.3 -> 87.3.
+// Each is a kernel compiled once more, 120 of them an eighth of the library, and so only for the work-items that sums and the detector are
+// best made with; heat, Life and one, four and eight rows would gain as much (2048^2 0.86 to 0.92, 4096^2 0.96 to 1.02).  9x9 by the
+// direct kernel, which runs out of registers, gains nothing (0.98 to 1.02).
 template <class Op, int CR, int CC>
 constexpr bool may_go_through() {
     using O = typename sk::out_type_of<Op>::type;
     return !sk::goes_through<Op>::value && CR == 2 && CC * sizeof(O) == 16 &&
            (Op::kWeights || std::is_same<Op, sk::OpSobel>::value || std::is_same<Op, sk::OpNms>::value);
 }
-bool tile_goes_through(const stencil *s) {
-    const size_t bytes = s->out_bytes();
-    const bool lines = (size_t)s->cols * s->out_elem() % 128 == 0;
-    return !s->nt_store && bytes >= (size_t)6 << 20 && (lines || bytes <= (size_t)32 << 20);
+template <class Op, class Halo, int CR, int CC>
+constexpr bool direct_may_go_through() { return may_go_through<Op, CR, CC>() && Halo::N + Halo::S < 8; }
+bool tile_goes_through(const stencil *s, const void *out, int wc) {
+    const size_t bytes = s->out_bytes(), mib = (size_t)1 << 20;
+    if (s->nt_store || bytes < 6 * mib) return false;
+    const uintptr_t ends = (uintptr_t)out | (uintptr_t)s->cols * s->out_elem() | (uintptr_t)wc * 16;
+    if (ends % 128 == 0) return true;
+    return bytes <= (ends % 64 == 0 ? (wc >= 8 ? 32 : 16) : wc >= 14 ? 32 : wc >= 9 ? 16 : 0) * mib;
 }
-template <class Op, int CR, int CC>
-int stores_tile(const stencil *s, const void *, int, int, int) {
-    if constexpr (may_go_through<Op, CR, CC>()) {
-        if (tile_goes_through(s)) return STENCIL_STORE_THROUGH;
-    }
-    return (int)store_of(s);
+template <bool MAY>
+int stores_tile(const stencil *s, const void *out, int, int wc, int) {
+    return MAY && tile_goes_through(s, out, wc) ? STENCIL_STORE_THROUGH : (int)store_of(s);
 }
 
 // A launch has at most so many work-items; more are turned down.
@@ -612,7 +624,7 @@ hipError_t launch_tile(const stencil *s, const void *in, void *out, int wr, int 
             return launch_tile<Op, B, sk::HaloC<Halo::N, Halo::S, Halo::E, Halo::W>, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
     }
     if constexpr (may_go_through<Op, CR, CC>()) {
-        if (tile_goes_through(s)) return start_tile<sk::WrittenThrough<Op>, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, stream);
+        if (tile_goes_through(s, out, wc)) return start_tile<sk::WrittenThrough<Op>, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, stream);
     }
     return start_tile<Op, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, stream);
 }
@@ -721,7 +733,7 @@ template <class Op>
 int stores_march(const stencil *s, const void *out, int, int, int) {
     if (march_pays(s)) return (int)store_of(s);
     const StreamTile t = stream_tile(s);
-    return stores_tile<Op, 2, 4>(s, out, t.rows, t.cols, 1);
+    return stores_tile<may_go_through<Op, 2, 4>()>(s, out, t.rows, t.cols, 1);
 }
 
 // The same for any region within the kernel's largest one (march_masked_kernel.h): the kernel compiled for the
@@ -756,8 +768,8 @@ hipError_t launch_march_masked(const stencil *s, const void *in, void *out, int 
 
 template <class Op, int B, class Halo, int CR, int CC, int MAXT>
 hipError_t launch_direct(const stencil *s, const void *in, void *out, int wr, int wc, int, hipStream_t stream) {
-    if constexpr (may_go_through<Op, CR, CC>()) {
-        if (tile_goes_through(s)) return launch_direct<sk::WrittenThrough<Op>, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
+    if constexpr (direct_may_go_through<Op, Halo, CR, CC>()) {
+        if (tile_goes_through(s, out, wc)) return launch_direct<sk::WrittenThrough<Op>, B, Halo, CR, CC, MAXT>(s, in, out, wr, wc, 0, stream);
     }
     unsigned blocks;
     size_t lds;
@@ -864,7 +876,7 @@ void reg_one(std::vector<Variant> &r) {
     using Folded = typename std::conditional<by_rows<Op, Halo, CR, CC>(), sk::HaloRows<Halo::N, Halo::S, Halo::E, Halo::W>, Halo>::type;
     v.launch = &launch_tile<Op, B, Folded, CR, CC, kMaxT>;
     v.plan = &plan_launch_tile<Op, Folded, CR, CC>;
-    v.stores = &stores_tile<Op, CR, CC>;
+    v.stores = &stores_tile<may_go_through<Op, CR, CC>()>;
     v.kernel_of = &kernel_tile<Op, B, Folded, CR, CC, kMaxT>;
     r.push_back(v);
 }
@@ -882,7 +894,7 @@ void reg_direct_one(std::vector<Variant> &r) {
     v.staged_bytes = 0;
     v.launch = &launch_direct<Op, B, Halo, CR, CC, STENCIL_MAX_WG_SIZE>;
     v.plan = &plan_direct<Op, CR, CC>;
-    v.stores = &stores_tile<Op, CR, CC>;
+    v.stores = &stores_tile<direct_may_go_through<Op, Halo, CR, CC>()>;
     v.kernel_of = &kernel_direct<Op, B, Halo, CR, CC, STENCIL_MAX_WG_SIZE>;
     r.push_back(v);
 }

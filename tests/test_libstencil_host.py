@@ -753,6 +753,31 @@ def test_describe_launch_says_how_the_output_is_stored():
     assert stores(4096, 8184, "life", one, "clamp", ("temporal", 2, 16), 2, (4, 64), depth=4, dtype="u8") == [plain]
 
 
+def test_pieces_of_cache_lines_are_not_written_through():
+    """Whether a row of a workgroup fills whole cache lines, or whole halves, follows from its columns, the matrix's and the
+    output's address; the narrower its pieces, the smaller the output up to which they are written through."""
+    through = lambda rows, cols, wc, out=0, dtype="f32", mapping=("local", 2, 4): describe_launches(
+        rows, cols, "weighted_sum", (2, 2, 2, 2), "clamp", mapping, 1, (4, wc), dtype=dtype, out=out)[0]["store"] == ls.STORE_THROUGH
+    for mapping, dtype, cols in [(("local", 2, 4), "f32", 1), (("direct", 2, 4), "f32", 1), (("local", 2, 4), "i32", 1), (("local", 2, 2), "f64", 2)]:
+        at = lambda mib, wc, out=0, ragged=0: through(mib * 256, 1024 // cols + ragged, wc, out, dtype, mapping)
+        for wc in (8, 16, 32, 64, 200):                                      # whole lines
+            assert at(8, wc) and at(64, wc) and at(256, wc, 2 ** 40 + 128)
+        for wc in (8, 12, 20, 32):                                           # halves
+            assert at(32, wc, 64) and not at(33, wc, 64)
+        assert at(32, 12) and not at(33, 12) and at(32, 28) and not at(64, 28)
+        assert at(16, 4) and not at(17, 4) and at(16, 4, 64)
+        for wc in (14, 15, 33, 64):                                          # other pieces
+            assert at(32, wc, 8) and not at(33, wc, 8) and at(31, wc, 0, 1) and not at(33, wc, 0, 1)
+        for wc in (9, 13):
+            assert at(16, wc) and not at(17, wc) and at(15, wc, 0, 1)
+        for wc in (1, 2, 3, 5, 6, 7):
+            assert not at(8, wc) and not at(16, wc)
+        assert not at(8, 8, 8) and not at(8, 4, 8) and not at(8, 8, 0, 1)
+        assert not at(5, 32)
+    assert not through(4096, 4096, 4) and not through(4096, 4096, 1)         # the sweeps' fixed 4 x 4 on 64 MiB
+    assert ls.STORE_PLAIN == describe_launches(4096, 4096, "weighted_sum", (4, 4, 4, 4), "clamp", ("direct", 2, 4), 1, (8, 32))[0]["store"]
+
+
 @pytest.mark.parametrize("border,rows,cols,items", [("wrap", 4096, 4096, 512), ("clamp", 4096, 4096, 1024), ("constant", 3000, 5000, 1024),
                                                      ("clamp", 1001, 1503, 512), ("wrap", 16, 600, 512)])
 def test_life_runs_take_workgroups_of_their_own(border, rows, cols, items):
