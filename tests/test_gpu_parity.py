@@ -762,6 +762,43 @@ def test_life_runs_of_several_launches(ls, border, tile):
                 st.close()
 
 
+def rows_where_tiles_are_added(ls, cols, border, iters, rows, count):
+    """The first `count` heights from `rows` on at which the first launch of the run needs more tiles, or others."""
+    found, before = [], None
+    while len(found) < count:
+        st = ls.Stencil.from_workload(custom(wl.LIFE, rows, cols, (1, 1, 1, 1), border, iters=iters))
+        set_mapping(st, ("temporal", 2, 16, 4))
+        run = st.describe_run(iters, (4, 64))
+        st.close()
+        tiles = run["wg"], run["workgroups"], run["launches"]
+        if before is not None and tiles != before:
+            found.append((rows, run["wg"][0] * run["wg"][1]))
+        before, rows = tiles, rows + 1
+    return found
+
+
+@pytest.mark.parametrize("border", ["clamp", "wrap", "constant"])
+@pytest.mark.parametrize("iters,items", [(5, 256), (9, 256), (17, 512), (41, 512)])
+def test_life_runs_at_the_edges_of_their_tiles(ls, border, iters, items):
+    """Boards of exactly the rows of a launch's tiles, whatever workgroup the library takes for them, one row less and one more,
+    in one launch (bytes in and out) and in two."""
+    for rows, found in rows_where_tiles_are_added(ls, 33, border, iters, 1, 3):
+        assert found == items
+        for near in (rows - 1, rows, rows + 1):
+            for cols in (33, 64, 5):
+                check(ls, custom(wl.LIFE, near, cols, (1, 1, 1, 1), border, pad=1.0, seed=near + cols, iters=iters), (4, 64),
+                      blocking=("temporal", 2, 16, 4))
+
+
+@pytest.mark.parametrize("border", ["clamp", "constant"])
+def test_life_runs_of_large_workgroups_at_the_edges_of_their_tiles(ls, border):
+    """The same where workgroups of 1024 are taken: boards of some 10 million cells, two launches."""
+    ((rows, items),) = rows_where_tiles_are_added(ls, 2501, border, 41, 4400, 1)
+    assert items == 1024
+    for near in (rows - 1, rows):
+        check(ls, custom(wl.LIFE, near, 2501, (1, 1, 1, 1), border, pad=1.0, seed=near, iters=41), (4, 64), blocking=("temporal", 2, 16, 4))
+
+
 @pytest.mark.parametrize("border", ["wrap", "constant"])
 def test_register_streaming_life_bit_exact(ls, border):
     """Generations kept in registers: matrices wider than one tile, ragged ones, ones smaller than a
