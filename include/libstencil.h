@@ -185,9 +185,11 @@ int stencil_set_border_value(stencil_t *st, double value);
  *            fewer launches where that is faster (up to 32 generations in one, unless the depth is 1 or
  *            the tile is prescribed); under STENCIL_STAGING_TEMPORAL, where the workgroup is whole
  *            wavefronts, such a run is made by the same kernel.  The library cuts the tile from the
- *            matrix, the depth and the workgroup's number of wavefronts (STENCIL_OPT_LIFE_TILE
- *            overrules it); cells_rows and cells_cols do not change it.
- *            The workgroup only groups wavefronts: w_r*w_c must be a multiple of 64 (other
+ *            matrix, the generations of a launch and the workgroup's number of wavefronts, and a run whose
+ *            launches make more generations than the depth has workgroups of its own choice (256, 512 or
+ *            1024 work-items, stencil_describe_run) whatever is given; STENCIL_OPT_LIFE_TILE overrules
+ *            both.  cells_rows and cells_cols change neither.
+ *            The workgroup that is given only groups wavefronts: w_r*w_c must be a multiple of 64 (other
  *            sizes are refused) and at most 256.  Not available for a matrix whose rows are 4 GiB
  *            or longer (cells within a row are addressed by 32-bit byte offsets).
  * Output values never depend on the mapping.  Heavily blocked variants have a lower per-kernel
@@ -232,7 +234,8 @@ int stencil_stream_segment_rows(const stencil_t *st, int wavefronts_per_simd, in
  * non-temporal stores (the output is not read again by the launch that writes it); narrower
  * stores (a ragged row's last cells, one cell per work-item, the threshold stencil) stay plain.  Same
  * results, different cache behaviour: it pays on matrices beyond the caches and costs where
- * the next application would have found its input in a cache.
+ * the next application would have found its input in a cache.  With 0 the library stores as is faster: into
+ * the L2 caches, or from 6 MiB of output on through them (stencil_describe_launch says which).
  * STENCIL_OPT_FAIL_LAUNCH (default 0 = off) is a testing aid for the handling of refused parameters
  * that only show when a launch fails (Section 3.1): with value (w_r << 16) | w_c every launch with
  * that workgroup size - with -1 every launch - is not made and reports the runtime's

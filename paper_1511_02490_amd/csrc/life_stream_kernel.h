@@ -19,7 +19,7 @@
 // launches, so that both are small together (life_tile, life_run_tile and life_per_launch in variants.h).
 // (100 generations of 4096 x 4096, WRAP: 282 us by marching packed bytes down the matrix, 121 on bits with 8 to a
 // launch, 65 with 25 in workgroups of 512.  50 generations of 1001 x 1503, CLAMP: 83 us by life_temporal_kernel, 4 to a launch from
-// bytes to bytes, 23 here with 17.)
+// bytes to bytes, 23 here with 25.)
 #pragma once
 #include "life_bits.h"
 
@@ -169,8 +169,8 @@ __global__ __launch_bounds__(life_stream_max_threads(RPT)) void life_stream_kern
             last_rows[buffer + tid] = x[RPT - 1];
             LifeBits h[RPT];
             // (All rows' cross-lane moves together: after one the wavefronts of a SIMD take turns for a while where two would issue
-            // at once, and after many in a row for no longer.  30 clamped generations of 1000^2 15.3 -> 13.1 us, 50 of
-            // 1001 x 1503 24.5 -> 22.8, 100 of 2048^2 52.8 -> 51.3; of 4096^2, whose SIMDs have many wavefronts, 77.3 and 77.4.)
+            // at once, and after many in a row for no longer.  In workgroups of 256, 30 clamped generations of 1000^2 15.3 -> 13.1
+            // us, 50 of 1001 x 1503 24.5 -> 22.8, 100 of 2048^2 52.8 -> 51.3; of 4096^2, by eight rows per item, 77.3 and 77.4.)
             Beside b[RPT];
 #pragma unroll
             for (int i = 0; i < RPT; ++i) b[i] = beside(x[i]);

@@ -146,14 +146,14 @@ __device__ __forceinline__ void load_global(E (&dst)[CNT], const E *src) {
 // Stores of output cells are optionally non-temporal: they are not read again by the launch that
 // writes them, and on matrices beyond the caches keeping them out of the way of the input pays
 // (measured on a plain copy: +20 % on 256 MiB, nothing on 64 MiB).
-// Or they are written through (kThrough), by the kernels that make several applications per launch: what plain stores leave
-// dirty in the eight L2 caches, 4 MiB each, is written back when the kernel ends, with nothing beside it; written through it
+// Or they are written through (kThrough), by the kernels that make several applications per launch and by tiles and direct kernels
+// of their own (WrittenThrough): what plain stores leave dirty in the eight L2 caches, 4 MiB each, is written back when the kernel ends, with nothing beside it; written through it
 // is on its way while the rest computes, and stays in the cache for the next launch.  (Plain / through: four Life
 // generations on 4096^2 in local memory 11.4 / 9.5 us; a launch of four heat steps there 33.5 / 33.1.  Small outputs
 // pay for it at the end of the last workgroups: a launch of two heat steps on 1024^2 9.4 / 10.0.  And what a store leaves of a
-// cache line is written to memory by itself.  Each launcher in variants.h and variants_register_tiles.hip draws its line.)
-// (The tiles of single applications: WrittenThrough, and tile_goes_through in variants.h.)  The two wait states keep what follows off the stored registers: the compiler counts them only after its own
-// stores.  Nothing reads the output in the same launch.
+// cache line is written to memory by itself.  Each launcher in variants.h and variants_register_tiles.hip draws its line; for single
+// applications tile_goes_through.)  The two wait states keep what follows off the stored registers: the compiler counts them only
+// after its own stores.  Nothing reads the output in the same launch.
 template <Store S>
 __device__ __forceinline__ void store_word4(void *dst, uint4 v) {
     any_word4 t;

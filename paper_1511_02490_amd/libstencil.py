@@ -359,8 +359,8 @@ class Stencil:
     def _check_tensors(self, tin, tout):
         cells = self.rows * self.cols
         want_in, want_out = self._types
-        # (one expression: a loop over the two tensors that asks the library for the output's type takes 0.77 us, this 0.46,
-        # of the 4.3 of a small call)
+        # (one expression: a loop over the two tensors that asks the library for the output's type takes 0.79 us, this 0.48; a 3x3
+        # blur of 256^2, one call after the other, 5.25 -> 5.0)
         if not (tin.dtype is want_in and tout.dtype is want_out and tin.is_cuda and tout.is_cuda and tin.numel() == cells and
                 tout.numel() == cells and tin.is_contiguous() and tout.is_contiguous()):
             raise ValueError("tensors must be contiguous CUDA %s (in) and %s (out) of %d x %d" % (want_in, want_out, self.rows, self.cols))
